@@ -648,11 +648,16 @@ static hi_status prefill_impl(hi_ctx* c, int32_t layer, int32_t kv_head, int32_t
   const bool run = !(c->flags & HI_FLAG_SKIP_KERNELS);
   const bool timed = (c->flags & HI_FLAG_TIME_KERNELS) != 0;
   PrefillSegment diag{k_new_dev, v_new_dev, chunk_len, 1};
+  const bool from_ring = unit_kind(c, layer, kv_head) == 0;
+  // the state images of a unit may also take the room of the decode partials behind the carry: decode units run on the
+  // same stream, and their partials do not outlive them
+  const PrefillLaunch unit = prefill_unit_shape(G, chunk_len, nh, pf_variant(c), past_len, from_ring ? rows_of(c, nh) : 0,
+                                                c->plan.ws_writeback_offset);
   auto launch = [&](const PrefillSegment& seg, const PrefillSegment& own, int first, int last) -> hi_status {
     TimedSpan sp;
     if (timed) HI_TRY(span_begin(c, 0, &sp));
     HI_TRY(launch_prefill(c->sc, q_dev, G, chunk_len, seg, own, first, last, c->ws, out_dev, c->prob.out_fp32,
-                          pf_variant(c), nh, c->plan.ws_partials_offset));
+                          pf_variant(c), unit, nh, c->plan.ws_writeback_offset));
     if (timed) HI_TRY(span_end(c, sp));
     c->stats.n_prefill_kernels += 1;
     return HI_OK;
@@ -662,7 +667,7 @@ static hi_status prefill_impl(hi_ctx* c, int32_t layer, int32_t kv_head, int32_t
   // kernel must fit the carry, the encoded rows the write-back buffer.
   if (!unit_streaming(c, layer, kv_head)) {
     const PrefillLaunch shape = prefill_launch_shape(G, chunk_len, nh, pf_variant(c), 1, 1);
-    if (shape.carry_bytes > c->plan.ws_partials_offset) {
+    if (shape.carry_bytes > c->plan.ws_partials_offset || unit.carry_bytes > c->plan.ws_writeback_offset) {
       set_last_error("prefill: the workspace holds %lld bytes of attention state, %lld needed",
                      (long long)c->plan.ws_partials_offset, (long long)shape.carry_bytes);
       return HI_ERR_UNSUPPORTED;
@@ -717,8 +722,7 @@ static hi_status prefill_impl(hi_ctx* c, int32_t layer, int32_t kv_head, int32_t
   // a jump inside the past segment): a launch costs a round trip of the softmax state through HBM, a ring to fill
   // and a tail to drain, about 30 us, which is 7 % of a launch over one 16 384-row slice of two heads.  Two slots are
   // half the ring, so the copies of the next pair still run under the kernel of this one.
-  const PrefillLaunch shape = prefill_launch_shape(G, chunk_len, nh, pf_variant(c), 1, 1);
-  const bool pairs = shape.deep && !(pf_variant(c) & 16) && c->n_slots >= 4 && st / 64 < kPrefillWideMinTiles &&
+  const bool pairs = unit.deep && !(pf_variant(c) & 16) && c->n_slots >= 4 && st / 64 < kPrefillWideMinTiles &&
                      !(c->flags & HI_FLAG_PREFILL_SINGLE_SLICES);
   for (int64_t i = 0; i < ns;) {
     HI_TRY(top_up(c, cur, next));          // guarantees slice i has been fetched

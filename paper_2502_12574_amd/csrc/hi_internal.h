@@ -52,6 +52,8 @@ struct PrefillLaunch {
   int nbk;             // blocks of positions per head (8-wave kernel)
   int merge;           // a merge launch follows
   int64_t carry_bytes; // state images the launches of this unit address in the carry
+  int img_row;         // state images of one grid row (a head, a quad of query heads)
+  int xcd;             // the workgroups of a grid row are numbered so that neighbours share an XCD (pf_wg_index)
 };
 inline PrefillLaunch prefill_launch_shape(int G, int64_t chunk_len, int n_heads, int variant, int last, int has_own) {
   PrefillLaunch p;
@@ -59,7 +61,8 @@ inline PrefillLaunch prefill_launch_shape(int G, int64_t chunk_len, int n_heads,
   p.split = prefill_split(G, chunk_len, n_heads);
   p.nbk = (int)ceil_div(chunk_len, 2 * strip);
   p.deep = base == 3 || (base == 0 && (int64_t)p.nbk * gy * n_heads * p.split >= kPrefillDeepMinWorkgroups);
-  p.paired = p.merge = 0;
+  p.paired = p.merge = p.xcd = 0;
+  p.img_row = 2 * p.nbk * p.split;
   if (p.deep) {
     // tiles the workgroups of the deepest block sweep beyond the average (the causal triangle), which pairing removes
     const int64_t saved = (int64_t)(2 * strip / 64) * (p.nbk - 1) / (2 * p.split);
@@ -72,6 +75,97 @@ inline PrefillLaunch prefill_launch_shape(int G, int64_t chunk_len, int n_heads,
   }
   return p;
 }
+
+// The split and the pairing of one unit, chosen for what the unit sweeps: `past` cached rows in launches of up to
+// `slice` of them (0: one launch), then the chunk's own rows.  capacity: bytes the state images may take (the plan's
+// carry holds what prefill_launch_shape asks for; the decode partials behind it are idle while a prefill unit runs).
+// The result is that of the unit's last launch; prefill_launch_of gives the others.
+//
+// The candidate with the least time by this model wins, in microseconds, fitted to sweeps of split and pairing over 17
+// shapes (1 to 32 heads, chunks of 30 to 4096 rows, 0 to 100 thousand cached rows; it picks a split within 6 % of the best
+// one in all of them).  A workgroup of the 8-wave kernel, one per compute unit: 10 to start, load and store its state;
+// 1.9 per tile for its first 14 tiles (ring fill, masked and alignment tiles), then 1.1 per tile while at most 190 run and
+// up to 1.45 on a full chip (power).  A paired launch makes two passes (12 more).  The merge: 5 + 0.035 per image.  The
+// 4-wave kernel: 4 + 1.3 per tile with one workgroup per compute unit, 1.9 with two.
+// What it replaces sized the split by the chunk alone, in powers of two up to 8: 30 rows of 8 heads behind 100 thousand
+// ran on 16 workgroups of the 4-wave kernel (1952 us with the append, now 120), 77 rows on 128 (302 -> 178), 600 rows
+// behind 3000 in two rounds of workgroups (92 -> 70), 2400 rows behind 5000 likewise (333 -> 277).
+constexpr int kPrefillUnitMaxSplit = 64;
+constexpr int kPrefillCus = 256;
+inline PrefillLaunch prefill_launch_of(PrefillLaunch unit, int last, int has_own) {
+  if (unit.deep && !(last && has_own)) unit.paired = 0;
+  if (unit.paired) unit.xcd = 0;           // pairs are numbered range by range already
+  if (!last) unit.merge = 0;
+  return unit;
+}
+inline PrefillLaunch prefill_unit_shape(int G, int64_t C, int n_heads, int variant, int64_t past, int64_t slice,
+                                        int64_t capacity) {
+  PrefillLaunch best = prefill_launch_shape(G, C, n_heads, variant, 1, 1);
+  const int strip = prefill_strip(G), rows = prefill_grid_y(G) * n_heads, base = variant & 3;
+  // 2048 rows in all: the 4-wave kernel where the chunk alone would pick it - it sums a row's keys in one order whether they
+  // come from HBM or slice by slice, so offloaded and resident results of short contexts agree bit for bit
+  if (base == 1 || (base == 0 && !best.deep && past + C <= 2048)) return best;
+  const int64_t launches = past > 0 && slice > 0 ? ceil_div(past, slice) : 1;
+  const double tiles_past = (double)ceil_div(past, 64) / (double)launches;       // of one launch
+  const int64_t own = ceil_div(C, 64), m = 2 * strip / 64, image = (int64_t)kPdLanes * kCarryFloatsPerLane * 4;
+  const double deepest = (double)(own < best.nbk * m ? own : best.nbk * m), average = 0.5 * (deepest + (double)m);
+  auto workgroup = [](double tiles, int64_t running) {
+    const double tile = running > 194 ? 1.45 * (double)running / kPrefillCus : 1.1;
+    return 10.0 + (tiles < 14.0 ? tiles * 1.9 : 14.0 * 1.9 + (tiles - 14.0) * tile);
+  };
+  // wgs workgroups of `first` tiles in the first round (the deepest), `others` in the rounds after it
+  auto rounds = [&](int64_t wgs, double first, double others) {
+    const int64_t full = wgs / kPrefillCus, rest = wgs % kPrefillCus;
+    if (full == 0) return workgroup(first, rest);
+    return workgroup(first, kPrefillCus) + (double)(full - 1) * workgroup(others, kPrefillCus) + (rest ? workgroup(others, rest) : 0.0);
+  };
+  auto cost = [&](int split, int paired) {
+    const int64_t wgs = (int64_t)best.nbk * rows * split;
+    auto range = [&](double tiles) { return (double)(int64_t)(tiles / split + 0.999); };
+    double us = (double)(launches - 1) * rounds(wgs, range(tiles_past), range(tiles_past));
+    if (paired) us += rounds(wgs, range(tiles_past + average), range(tiles_past + average)) + 12.0 * (double)ceil_div(wgs, kPrefillCus);
+    else us += rounds(wgs, range(tiles_past + deepest), range(tiles_past + average));
+    if (split > 1 || paired) us += 5.0 + (double)wgs * 0.035;
+    return us;
+  };
+  double best_us = 1e30;
+  if (best.deep) {
+    best_us = 0.97 * cost(best.split, best.paired);          // a clear gain, or stay with the default
+  }
+  if (base != 3 && !(best.deep && (variant & (4 | 8 | 16 | 64 | 128)))) {       // (those flags name forms of the 8-wave kernel)
+    const int64_t wgs = ceil_div(C, strip) * rows;
+    const double us = (double)launches * ((double)ceil_div(wgs, 2 * kPrefillCus) *
+                                          (4.0 + (tiles_past + (double)own) * (wgs > kPrefillCus ? 1.9 : 1.3)));
+    if (us < best_us) {
+      best_us = us;
+      best.deep = best.paired = best.merge = 0;
+      best.split = 1;
+      best.carry_bytes = wgs * kWgThreads * kCarryFloatsPerLane * 4;
+    }
+  }
+  const int64_t fewest = past > 0 ? (past < slice || slice <= 0 ? past : slice) / 64 : own;   // tiles of a full launch
+  for (int split = 1; split <= kPrefillUnitMaxSplit; ++split) {
+    if (split > 1 && split > fewest) break;
+    for (int paired = 0; paired < 2; ++paired) {
+      if (paired && (best.nbk < 2 || (variant & 8))) continue;
+      if (!paired && best.nbk >= 2 && (variant & 4)) continue;
+      const int64_t images = (int64_t)(paired ? 2 : 1) * best.nbk * split;
+      if (images * rows * image > capacity) continue;
+      const double us = cost(split, paired);
+      if (us >= best_us) continue;
+      best_us = us;
+      best.deep = 1; best.split = split; best.paired = paired;
+      best.merge = split > 1 || paired;
+      best.img_row = (int)images;
+      best.carry_bytes = images * rows * image;
+    }
+  }
+  // neighbours in the numbering read the same K/V rows: let them share an XCD's L2 when one round of workgroups holds all
+  best.xcd = best.deep && best.split > 1 && best.nbk * best.split % 8 == 0 &&
+             (int64_t)best.nbk * rows * best.split <= kPrefillCus;
+  return best;
+}
+
 // the largest carry any launch of chunks up to C rows over groups of up to n_heads heads can address, whatever the
 // kernel variant (both kernels' image counts are step functions of the chunk length with steps at multiples of strip)
 inline int64_t prefill_carry_bound(int G, int64_t C, int n_heads) {
@@ -128,14 +222,14 @@ struct PrefillSegment {
 
 // One launch of the prefill kernel over up to two KV segments.  first: start from an empty softmax state
 // instead of loading the carry; last: normalise and write `out` instead of storing the carry.
-// variant: as at prefill_launch_shape (+ 32: the queries are pre-scaled, see softmax_scale_log2); every launch of one
-// unit must use the same variant (the carry layouts differ).
-// carry_bytes: size of the carry buffer (checked against what the launch will use; -1: not checked).
+// variant: as at prefill_launch_shape (+ 32: the queries are pre-scaled, see softmax_scale_log2); shape: the unit's, from
+// prefill_unit_shape; every launch of one unit must use the same variant and shape (the carry layouts differ).
+// carry_bytes: size of the carry buffer (checked against what the launch will use).
 // n_heads > 1: one launch over a group of KV heads; q is [n_heads][G][chunk_len][128], out likewise, the causal
 // segment's rows [n_heads][chunk_len][128], the other segment's heads head_stride bytes apart.
 hi_status launch_prefill(void* stream, const void* q, int G, int chunk_len, const PrefillSegment& a,
                          const PrefillSegment& b, int first, int last, void* carry, void* out, int out_fp32,
-                         int variant, int n_heads = 1, int64_t carry_bytes = -1);
+                         int variant, const PrefillLaunch& unit, int n_heads, int64_t carry_bytes);
 
 // The factor between a query-key dot product and the base-2 exponent of its softmax weight: log2(e) / sqrt(128) for
 // the q of Eq. 3, 1 for queries that already carry that factor (hi_problem.q_prescaled).

@@ -49,6 +49,8 @@ struct PrefillArgs {
   int64_t a_head_stride;  // bytes between the heads' rows in the past segment
   int paired;             // 8-wave kernel: deep and shallow blocks of the causal triangle share their tiles
   int nbk;                // 8-wave kernel: blocks of positions per head
+  int img_row;            // 8-wave kernel: state images per grid row
+  int xcd;                // 8-wave kernel: see pf_wg_index
   int a_jump_tile;        // the past segment's tiles from this one on lie a_jump_bytes further on (0: one piece)
   int64_t a_jump_bytes;
 };
@@ -625,16 +627,17 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel_deep(PrefillArgs a) {
   sh.split = a.split; sh.paired = a.paired; sh.carried = !a.first;
   constexpr int kLanes = kPdWaves * 64;
   constexpr int kImageFloats = kCarryFloatsPerLane * kLanes;
-  float* const images = a.carry + (int64_t)blockIdx.y * pf_images_per_row(a.nbk, a.split) * kImageFloats + threadIdx.x;
+  float* const images = a.carry + (int64_t)blockIdx.y * a.img_row * kImageFloats + threadIdx.x;
   // the pass that holds past tiles goes first, so that the workgroups of a range walk the past rows in step
+  const int wg = pf_wg_index(blockIdx.x, gridDim.x, a.xcd);
   int first_which = 0;
   {
-    const PfPass d = pf_pass(sh, blockIdx.x, 0, a.last), sw = pf_pass(sh, blockIdx.x, 1, a.last);
+    const PfPass d = pf_pass(sh, wg, 0, a.last), sw = pf_pass(sh, wg, 1, a.last);
     if (sw.run && sw.a1 > sw.a0 && !(d.run && d.a1 > d.a0)) first_which = 1;
   }
 #pragma nounroll
   for (int pi = 0; pi < 2; ++pi) {
-    const PfPass ps = pf_pass(sh, blockIdx.x, first_which ^ pi, a.last);
+    const PfPass ps = pf_pass(sh, wg, first_which ^ pi, a.last);
     if (ps.init) {                 // a range without tiles in the first launch of a unit: an empty state
       float* im = images + (int64_t)ps.store * kImageFloats;
 #pragma unroll
@@ -1219,15 +1222,16 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel_deep16(PrefillArgs a) {
   sh.split = a.split; sh.paired = a.paired; sh.carried = !a.first;
   constexpr int kLanes = kPdWaves * 64;
   constexpr int kImageFloats = kCarryFloatsPerLane * kLanes;
-  float* const images = a.carry + (int64_t)blockIdx.y * pf_images_per_row(a.nbk, a.split) * kImageFloats + threadIdx.x;
+  float* const images = a.carry + (int64_t)blockIdx.y * a.img_row * kImageFloats + threadIdx.x;
+  const int wg = pf_wg_index(blockIdx.x, gridDim.x, a.xcd);
   int first_which = 0;
   {
-    const PfPass d = pf_pass(sh, blockIdx.x, 0, a.last), sw = pf_pass(sh, blockIdx.x, 1, a.last);
+    const PfPass d = pf_pass(sh, wg, 0, a.last), sw = pf_pass(sh, wg, 1, a.last);
     if (sw.run && sw.a1 > sw.a0 && !(d.run && d.a1 > d.a0)) first_which = 1;
   }
 #pragma nounroll
   for (int pi = 0; pi < 2; ++pi) {
-    const PfPass ps = pf_pass(sh, blockIdx.x, first_which ^ pi, a.last);
+    const PfPass ps = pf_pass(sh, wg, first_which ^ pi, a.last);
     if (ps.init) {
       float* im = images + (int64_t)ps.store * kImageFloats;
 #pragma unroll
@@ -1493,8 +1497,9 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel_deep16(PrefillArgs a) {
   }
 }
 
-// Merge of the states of prefill_kernel_deep16 (its own image layout): grid (blocks, grid rows, 4): quarter z combines
-// dim blocks 2 z and 2 z + 1 of both query rows of the lane.
+// Merge of the states of prefill_kernel_deep16 (its own image layout): grid (blocks, grid rows, 8): z is one dim block
+// of both query rows of the lane.  Bound by the read of the images (139 KB each, up to 64 per block): 8 dim blocks per
+// image and four images in flight per lane, because the grid is small exactly where a block has many images.
 __global__ __launch_bounds__(512) void prefill_merge16_kernel(PrefillArgs a) {
   const int lane = lane_id();
   const int wave = wave_id();
@@ -1503,9 +1508,10 @@ __global__ __launch_bounds__(512) void prefill_merge16_kernel(PrefillArgs a) {
   const int gl = a.G < 4 ? a.G : 4;
   const int strip = 32 * (kPdWaves / gl);
   const int bx = blockIdx.x;
-  const int zq = blockIdx.z;
+  const int db = blockIdx.z;
   const int g = pf_select_head(a) * 4 + (wave % gl);
   const int i0 = bx * strip + 32 * (wave / gl);
+  if (i0 >= a.C) return;                    // rows past the chunk's end
   constexpr int kLanes = kPdWaves * 64;
   constexpr int kImageFloats = kCarryFloatsPerLane * kLanes;
   PfShape sh;
@@ -1516,36 +1522,35 @@ __global__ __launch_bounds__(512) void prefill_merge16_kernel(PrefillArgs a) {
   int n_e, n_x;
   pf_block_images(sh, bx, n_e, n_x);
   if (n_e + n_x == 1 && a.split == 1) return;
-  const float* images = a.carry + (int64_t)blockIdx.y * pf_images_per_row(a.nbk, a.split) * kImageFloats + threadIdx.x;
+  const float* images = a.carry + (int64_t)blockIdx.y * a.img_row * kImageFloats + threadIdx.x;
   auto image_of = [&](int i) { return images + (int64_t)(i < n_e ? pf_image_e(sh, bx, i) : pf_image_x(sh, bx, i - n_e)) * kImageFloats; };
   float m[2] = {kNegBig, kNegBig};
-  for (int i = 0; i < n_e + n_x; ++i) {
+  const int n = n_e + n_x;
+#pragma unroll 4
+  for (int i = 0; i < n; ++i) {
     const float* im = image_of(i);
     m[0] = fmaxf(m[0], im[64 * kLanes]);
     m[1] = fmaxf(m[1], im[65 * kLanes]);
   }
-  f32x4 o[2][2];      // [dim block 2 zq + d][qb]
+  f32x4 o[2];
 #pragma unroll
-  for (int d = 0; d < 2; ++d)
-#pragma unroll
-    for (int qb = 0; qb < 2; ++qb) o[d][qb] = (f32x4){0.f, 0.f, 0.f, 0.f};
+  for (int qb = 0; qb < 2; ++qb) o[qb] = (f32x4){0.f, 0.f, 0.f, 0.f};
   float l[2] = {0.f, 0.f};
-  for (int i = 0; i < n_e + n_x; ++i) {
+#pragma unroll 4
+  for (int i = 0; i < n; ++i) {
     const float* im = image_of(i);
 #pragma unroll
     for (int qb = 0; qb < 2; ++qb) {
       const float w = fast_exp2((im[(64 + qb) * kLanes] - m[qb]) * a.c);
       l[qb] += w * im[(66 + qb) * kLanes];
 #pragma unroll
-      for (int d = 0; d < 2; ++d)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) o[d][qb][r] += w * im[(((2 * zq + d) * 2 + qb) * 4 + r) * kLanes];
+      for (int r = 0; r < 4; ++r) o[qb][r] += w * im[((db * 2 + qb) * 4 + r) * kLanes];
     }
   }
 #pragma unroll
   for (int qb = 0; qb < 2; ++qb) {
-    const f32x4 rows[2] = {o[0][qb], o[1][qb]};
-    pf16_write_row<2>(a.out, a.out_fp32, a.C, g, i0 + 16 * qb + c16, g16, 2 * zq, rows, l[qb]);
+    const f32x4 rows[1] = {o[qb]};
+    pf16_write_row<1>(a.out, a.out_fp32, a.C, g, i0 + 16 * qb + c16, g16, db, rows, l[qb]);
   }
 }
 
@@ -1598,7 +1603,7 @@ __global__ __launch_bounds__(512) void prefill_merge_kernel(PrefillArgs a) {
   int n_e, n_x;
   pf_block_images(sh, bx, n_e, n_x);
   if (n_e + n_x == 1 && a.split == 1) return;
-  const float* images = a.carry + (int64_t)blockIdx.y * pf_images_per_row(a.nbk, a.split) * kImageFloats + threadIdx.x;
+  const float* images = a.carry + (int64_t)blockIdx.y * a.img_row * kImageFloats + threadIdx.x;
   auto image_of = [&](int i) { return images + (int64_t)(i < n_e ? pf_image_e(sh, bx, i) : pf_image_x(sh, bx, i - n_e)) * kImageFloats; };
   float m = kNegBig;
   for (int i = 0; i < n_e + n_x; ++i) m = fmaxf(m, image_of(i)[64 * kLanes]);
@@ -1855,7 +1860,7 @@ __global__ __launch_bounds__(256) void stream_store_update_kernel(const char* __
 
 hi_status launch_prefill(void* stream, const void* q, int G, int chunk_len, const PrefillSegment& sa,
                          const PrefillSegment& sb, int first, int last, void* carry, void* out, int out_fp32,
-                         int variant, int n_heads, int64_t carry_bytes) {
+                         int variant, const PrefillLaunch& unit, int n_heads, int64_t carry_bytes) {
   if (n_heads < 1 || (variant & 3) == 2) { set_last_error("prefill launch: head group or variant"); return HI_ERR_UNSUPPORTED; }
   if (chunk_len < 1 || !(G == 1 || G == 2 || G == 4 || G == 8)) { set_last_error("prefill launch: bad shape"); return HI_ERR_ARG; }
   if (sa.causal || (sb.n > 0 && !sb.causal)) { set_last_error("prefill launch: segment order"); return HI_ERR_ARG; }
@@ -1879,15 +1884,17 @@ hi_status launch_prefill(void* stream, const void* q, int G, int chunk_len, cons
     return HI_ERR_ARG;
   }
   a.a_head_stride = sa.head_stride;
-  const PrefillLaunch pl = prefill_launch_shape(G, chunk_len, n_heads, variant, last, sb.n > 0);
+  const PrefillLaunch pl = prefill_launch_of(unit, last, sb.n > 0);
   if (sa.n >= (1LL << 31) || sb.n >= (1LL << 31)) { set_last_error("prefill launch: more than 2^31 rows"); return HI_ERR_RANGE; }
-  if (carry_bytes >= 0 && pl.carry_bytes > carry_bytes) {     // the carry must hold every state image of the launch
+  if (pl.carry_bytes > carry_bytes) {     // the carry must hold every state image of the launch
     set_last_error("prefill launch: carry of %lld bytes needed, %lld provided", (long long)pl.carry_bytes, (long long)carry_bytes);
     return HI_ERR_ARG;
   }
   a.split = pl.split;
   a.paired = pl.paired;
   a.nbk = pl.nbk;
+  a.img_row = pl.img_row;
+  a.xcd = pl.xcd;
   if (sa.jump_rows != 0 && !(pl.deep && (variant & 16) == 0)) {
     set_last_error("prefill launch: this kernel takes its past segment in one piece");
     return HI_ERR_UNSUPPORTED;
@@ -1914,10 +1921,10 @@ hi_status launch_prefill(void* stream, const void* q, int G, int chunk_len, cons
     if (attr_err != hipSuccess) { set_last_error("hipFuncSetAttribute: %s", hipGetErrorString(attr_err)); return HI_ERR_HIP; }
     dim3 grid((unsigned)(pl.nbk * pl.split), (unsigned)(gy * n_heads));
     const bool mfma32 = (variant & 16) != 0;        // the 32x32x16 form of the kernel (its state images differ)
-    // the 4-wave, 64-rows-per-wavefront form of the 16x16x32 kernel: for launches long enough to pay for its slow
-    // straight-line tiles (it gains about 3 % per steady-state tile and loses about 20 tiles' worth at the ends)
+    // the 4-wave, 64-rows-per-wavefront form of the 16x16x32 kernel: for workgroups that sweep enough tiles to pay for its
+    // slow straight-line ones (it gains about 3 % per steady-state tile and loses about 20 tiles' worth at the ends)
     const bool wide = !mfma32 && ((variant & 128) != 0 ||
-                                  ((variant & 64) == 0 && (sa.n + sb.n) / kPfTileRows >= kPrefillWideMinTiles));
+                                  ((variant & 64) == 0 && (sa.n + sb.n) / kPfTileRows >= (int64_t)kPrefillWideMinTiles * pl.split));
     if (mfma32) hipLaunchKernelGGL(prefill_kernel_deep, grid, dim3(kPdWaves * 64), kPdLdsBytes, (hipStream_t)stream, a);
     else if (wide && q_prescaled) hipLaunchKernelGGL(prefill_kernel_wide<true>, grid, dim3(kPwWaves * 64), kPdLdsBytes, (hipStream_t)stream, a);
     else if (wide) hipLaunchKernelGGL(prefill_kernel_wide<false>, grid, dim3(kPwWaves * 64), kPdLdsBytes, (hipStream_t)stream, a);
@@ -1927,7 +1934,7 @@ hi_status launch_prefill(void* stream, const void* q, int G, int chunk_len, cons
       hipError_t e1 = hipGetLastError();
       if (e1 != hipSuccess) { set_last_error("prefill launch: %s", hipGetErrorString(e1)); return HI_ERR_HIP; }
       if (mfma32) hipLaunchKernelGGL(prefill_merge_kernel, dim3((unsigned)pl.nbk, grid.y, 4), dim3(kPdWaves * 64), 0, (hipStream_t)stream, a);
-      else hipLaunchKernelGGL(prefill_merge16_kernel, dim3((unsigned)pl.nbk, grid.y, 4), dim3(kPdWaves * 64), 0, (hipStream_t)stream, a);
+      else hipLaunchKernelGGL(prefill_merge16_kernel, dim3((unsigned)pl.nbk, grid.y, 8), dim3(kPdWaves * 64), 0, (hipStream_t)stream, a);
     }
   } else {
     dim3 grid((unsigned)ceil_div(chunk_len, strip), (unsigned)(gy * n_heads));

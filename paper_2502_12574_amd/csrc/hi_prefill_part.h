@@ -52,8 +52,13 @@ HI_HD int pf_images_per_row(int nbk, int split) { return 2 * nbk * split; }
 HI_HD int pf_image_e(const PfShape& s, int b, int j) { return j * s.nbk + b; }
 HI_HD int pf_image_x(const PfShape& s, int b, int j) { return s.nbk * s.split + b * s.split + j; }
 
-// boundary k of the nr equal ranges a sequence of L tiles is cut into (nr is a power of two; L * nr < 2^32)
-HI_HD int pf_cut(int L, int k, int nr) { return (int)(((uint32_t)L * (uint32_t)k) >> __builtin_ctz((unsigned)nr)); }
+// boundary k of the nr equal ranges a sequence of L tiles is cut into (L * nr < 2^32)
+HI_HD int pf_cut(int L, int k, int nr) { return (int)((uint32_t)L * (uint32_t)k / (uint32_t)nr); }
+
+// Workgroup number of grid position x in a grid row of n workgroups.  xcd: the hardware deals workgroups to the 8 XCDs
+// in turn; position x takes number (x % 8) (n / 8) + x / 8, so that an XCD's workgroups have consecutive numbers - those
+// of one range of K/V rows, which its L2 then fetches once (n is a multiple of 8).
+HI_HD int pf_wg_index(int x, int n, int xcd) { return xcd ? (x & 7) * (n >> 3) + (x >> 3) : x; }
 
 HI_HD int pf_own_tiles(const PfShape& s, int b) {
   const int o = (b + 1) * s.m;
@@ -74,6 +79,15 @@ HI_HD void pf_contributors(const PfShape& s, int deep, int shallow, int nr, int 
   const int Td = s.ta + pf_own_tiles(s, deep);
   const int L = Td + (shallow >= 0 ? s.ta + pf_own_tiles(s, shallow) : 0);
   before = total = 0;
+  if (L >= nr) {
+    // no range is empty: the ranges that start before Td hold deep tiles, those that end after it shallow ones
+    const uint32_t u = (uint32_t)nr, l = (uint32_t)L, td = (uint32_t)Td;
+    const int kd = (int)((td * u + l - 1) / l);              // first k with cut(k) >= Td
+    const int ks = (int)(((td + 1) * u + l - 1) / l) - 1;    // first k with cut(k + 1) > Td
+    if (is_shallow) { total = nr - ks; before = k > ks ? k - ks : 0; }
+    else { total = kd < nr ? kd : nr; before = k < total ? k : total; }
+    return;
+  }
   for (int kk = 0; kk < nr; ++kk) {
     const int x0 = pf_cut(L, kk, nr), x1 = pf_cut(L, kk + 1, nr);
     const bool hit = x1 > x0 && (is_shallow ? x1 > Td : x0 < Td);
