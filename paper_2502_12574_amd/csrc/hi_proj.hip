@@ -395,6 +395,199 @@ __global__ __launch_bounds__(256, 1) void proj_gemm_kernel(ProjArgs p) {
   }
 }
 
+// ---- chunks too short to fill the chip with 256 x 256 tiles: the same contraction in 128 x 128 tiles, one per workgroup.
+// 600 tokens of Llama-3-8B are 72 (Q/K/V) and 48 (output) of the large tiles on 256 compute units, 240 and 160 of these.
+// A wavefront owns 64 x 64 (2 x 2 blocks of the 32x32x16 MFMA; its A rows are 32 wa .. +31 and 64 + 32 wa .. +31, so that
+// rotary pairs still meet in one lane).  Per 16 contraction elements it reads 4 KB of operands for 4 MFMAs: the tile is
+// bound by the LDS read rate.  One workgroup per compute unit has to cover the latency of its loads itself: four stages of
+// 32 KB, loads three steps (of 64 elements) ahead, operand reads two sub-steps ahead.  The order of every sum is the large
+// tile's, so the results are the same bits.  Measured (hidden size 4096, 32 + 16 heads, weights of 6 layers in turn;
+// large tile -> small): Q/K/V with its table at 64 / 600 / 1000 / 2000 tokens 90 -> 33, 97 -> 40, 102 -> 69, 110 -> 108 us,
+// output 74 -> 24, 77 -> 28, 78 -> 35, 80 -> 66 us.
+constexpr int kPsTile = 128;
+constexpr int kPsOperandBytes = kPsTile * kPjRowBytes;    // 16 KiB
+constexpr int kPsStageBytes = 2 * kPsOperandBytes;
+constexpr int kPsStages = 4;
+constexpr int kPsLdsBytes = kPsStages * kPsStageBytes;    // 128 KiB
+
+template <int MODE>
+__global__ __launch_bounds__(256, 1) void proj_gemm_small_kernel(ProjArgs p) {
+  extern __shared__ __attribute__((aligned(1024))) char lds_dyn[];
+  const uint32_t lds_base = (uint32_t)(uintptr_t)(lds_char*)lds_dyn;
+  const int lane = lane_id();
+  const int wave = wave_id();
+  const int l = lane & 31, hl = lane >> 5;
+  const int wa = wave & 1, wb = wave >> 1;
+
+  // XCD x (= blockIdx % 8) owns tiles [x * per, (x + 1) * per) of the ordered list: a compact block of the tile grid
+  const int total = p.a_tiles * p.b_tiles;
+  const int per = (total + 7) >> 3;
+  const int slot = (int)(blockIdx.x >> 3), tile = (int)(blockIdx.x & 7) * per + slot;
+  if (slot >= per || tile >= total) return;
+  int ta, tb;
+  pj_tile_of(p, tile, ta, tb);
+
+  // tile traffic: this wavefront's 4 load instructions per operand and step cover rows 32 w + 8 u + lane / 8
+  uint32_t ga_off[4], gb_off[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int row = 32 * wave + 8 * u + (lane >> 3);
+    const int chunk = (lane & 7) ^ (4 * (u & 1) + (lane >> 4));      // = (lane & 7) ^ ((row >> 1) & 7)
+    int ra = ta * kPsTile + row, rb = tb * kPsTile + row;
+    ra = ra < p.a_rows ? ra : p.a_rows - 1;
+    rb = rb < p.b_rows ? rb : p.b_rows - 1;
+    ga_off[u] = (uint32_t)ra * p.a_stride + (chunk << 4);
+    gb_off[u] = (uint32_t)rb * p.b_stride + (chunk << 4);
+  }
+  auto issue_one = [&](int t, int u) __attribute__((always_inline)) {
+    const int k0 = t * kPjK;
+    const uint32_t la = lds_base + (t & (kPsStages - 1)) * kPsStageBytes + wave * 4096;
+    if (u < 4) {
+      g2lds16_s<0>(p.a + (int64_t)k0 * 2, ga_off[u], la + u * 1024);
+    } else {
+      const char* bb = MODE == kPjOut ? p.b + (int64_t)(k0 >> 7) * p.b_head_stride + (k0 & 127) * 2 : p.b + (int64_t)k0 * 2;
+      g2lds16_s<0>(bb, gb_off[u - 4], la + kPsOperandBytes + (u - 4) * 1024);
+    }
+  };
+
+  // operand reads: lane l reads row (block + l), chunk (2 kk + hl); operands 0, 1: A blocks, 2, 3: B blocks
+  uint32_t va[4], vb[4];
+  {
+    const int sw = (l >> 1) & 7;
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) {
+      const uint32_t ko = (uint32_t)(l * kPjRowBytes + (((2 * kk + hl) ^ sw) << 4));
+      va[kk] = lds_base + wa * 32 * kPjRowBytes + ko;
+      vb[kk] = lds_base + kPsOperandBytes + wb * 64 * kPjRowBytes + ko;
+    }
+  }
+  auto read_op = [&](uint32_t stage, int kk, int i) __attribute__((always_inline)) -> bf16x8 {
+    return i < 2 ? *(lds_bf16x8_p)((lds_char*)(uintptr_t)(va[kk] + stage) + i * 64 * kPjRowBytes)
+                 : *(lds_bf16x8_p)((lds_char*)(uintptr_t)(vb[kk] + stage) + (i - 2) * 32 * kPjRowBytes);
+  };
+
+  const int T = p.K / kPjK;        // at least 4 (the launcher's rule)
+#pragma unroll
+  for (int t = 0; t < kPsStages; ++t)
+#pragma unroll
+    for (int u = 0; u < 8; ++u) issue_one(t, u);
+
+  f32x16 acc[2][2];
+#pragma unroll
+  for (int ia = 0; ia < 2; ++ia)
+#pragma unroll
+    for (int ib = 0; ib < 2; ++ib)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[ia][ib][r] = 0.f;
+  bf16x8 op[4][4];
+  auto mfma4 = [&](int kk, int j) __attribute__((always_inline)) {
+    acc[j & 1][j >> 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op[kk][j & 1], op[kk][2 + (j >> 1)], acc[j & 1][j >> 1], 0, 0, 0);
+  };
+
+  wait_vmcnt<24>();          // step 0 has landed
+  __syncthreads();
+#pragma unroll
+  for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) op[kk][i] = read_op(0, kk, i);
+
+  // Step t: sub-steps 0 and 1 read the operands of 2 and 3; then this wavefront is done with the stage, the barrier
+  // publishes step t + 1, and sub-steps 2 and 3 cover the first reads of step t + 1 and the issue of step t + 4 into the
+  // stage just freed.  LEFT: steps after this one whose loads may still be in flight behind step t + 1's (8 per step).
+  auto step = [&](int t, auto left_tag, auto issue_tag) __attribute__((always_inline)) {
+    constexpr int LEFT = decltype(left_tag)::value;          // -1: this is the last step
+    constexpr bool ISSUE = decltype(issue_tag)::value;
+    const uint32_t st = (uint32_t)(t & (kPsStages - 1)) * kPsStageBytes;
+    const uint32_t sn = (uint32_t)((t + 1) & (kPsStages - 1)) * kPsStageBytes;
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        op[kk + 2][j] = read_op(st, kk + 2, j);
+        mfma4(kk, j);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    if (LEFT >= 0) {
+      wait_vmcnt<LEFT < 0 ? 0 : 8 * LEFT>();                // this wave's loads of step t + 1 have landed
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // this wave is done reading this stage
+      __syncthreads();
+      __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        if (LEFT >= 0) op[kk][j] = read_op(sn, kk, j);
+        mfma4(kk + 2, j);
+        if (ISSUE) issue_one(t + kPsStages, kk * 4 + j);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+  };
+  int t = 0;
+  for (; t + kPsStages < T; ++t) step(t, std::integral_constant<int, 2>(), std::true_type());
+  step(t, std::integral_constant<int, 2>(), std::false_type());
+  step(t + 1, std::integral_constant<int, 1>(), std::false_type());
+  step(t + 2, std::integral_constant<int, 0>(), std::false_type());
+  step(t + 3, std::integral_constant<int, -1>(), std::false_type());
+
+  // Register r of block (ia, ib): feature 64 ia + 32 wa + 8 (r / 4) + 4 hl + r % 4 of the tile, token 64 wb + 32 ib + l.
+  char* base;
+  int64_t row_bytes;
+  bool rotate = false;
+  float osc = 1.0f;
+  if (MODE == kPjQkv) {
+    const int head = ta;
+    int hh;
+    if (head < p.n_q_heads) { base = (char*)p.q_out; hh = head; osc = p.q_scale; }
+    else if (head < p.n_q_heads + p.n_kv_heads) { base = (char*)p.k_out; hh = head - p.n_q_heads; }
+    else { base = (char*)p.v_out; hh = head - p.n_q_heads - p.n_kv_heads; }
+    rotate = p.rope != nullptr && head < p.n_q_heads + p.n_kv_heads;
+    base += (int64_t)hh * p.b_rows * kRowBytes;
+    row_bytes = kRowBytes;
+  } else {
+    base = (char*)p.y + (int64_t)ta * kPsTile * 2;
+    row_bytes = p.y_stride * 2;
+  }
+#pragma unroll
+  for (int ib = 0; ib < 2; ++ib) {
+    const int m = tb * kPsTile + 64 * wb + 32 * ib + l;
+    const bool ok = m < p.b_rows;
+    float lo[16], hi[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) { lo[r] = acc[0][ib][r]; hi[r] = acc[1][ib][r]; }
+    if (MODE == kPjQkv) {
+      if (rotate) {
+        const int mt = ok ? m : p.b_rows - 1;
+#pragma unroll
+        for (int rq = 0; rq < 4; ++rq) {
+          const float4* cs = (const float4*)(p.rope + ((int64_t)(8 * wa + 2 * rq + hl) * p.b_rows + mt) * 4);
+          const float4 c01 = cs[0], c23 = cs[1];
+          const float cv[4] = {c01.x, c01.z, c23.x, c23.z}, sv[4] = {c01.y, c01.w, c23.y, c23.w};
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const float x = lo[4 * rq + e], y = hi[4 * rq + e];
+            lo[4 * rq + e] = pj_rot_lo(x, y, cv[e], sv[e]);
+            hi[4 * rq + e] = pj_rot_hi(x, y, cv[e], sv[e]);
+          }
+        }
+      }
+#pragma unroll
+      for (int r = 0; r < 16; ++r) { lo[r] *= osc; hi[r] *= osc; }
+    }
+    char* row = base + (int64_t)m * row_bytes + 32 * wa * 2;
+#pragma unroll
+    for (int rp = 0; rp < 2; ++rp) {
+      const float l8[8] = {lo[8 * rp], lo[8 * rp + 1], lo[8 * rp + 2], lo[8 * rp + 3],
+                           lo[8 * rp + 4], lo[8 * rp + 5], lo[8 * rp + 6], lo[8 * rp + 7]};
+      const float h8[8] = {hi[8 * rp], hi[8 * rp + 1], hi[8 * rp + 2], hi[8 * rp + 3],
+                           hi[8 * rp + 4], hi[8 * rp + 5], hi[8 * rp + 6], hi[8 * rp + 7]};
+      pj_store_rows_bf16(row, l8, rp, hl, ok);
+      pj_store_rows_bf16(row + 128, h8, rp, hl, ok);
+    }
+  }
+}
+
 // (cos, sin) of position (past + t) times theta^(-i / 64) for i < 64, in double precision: at a million tokens the
 // angle of the fastest pair is a million radians, beyond what fp32 can reduce
 struct RopeFreqs { double inv[64]; };
@@ -511,10 +704,11 @@ static hi_status pj_launch(void* stream, ProjArgs& p, int mode) {
   static std::once_flag attr_once;      // the projections are stateless: any host thread may get here first
   static hipError_t attr_err = hipSuccess;
   std::call_once(attr_once, [] {
-    const void* kernels[4] = {(const void*)proj_gemm_kernel<kPjQkv, true>, (const void*)proj_gemm_kernel<kPjQkv, false>,
-                              (const void*)proj_gemm_kernel<kPjOut, true>, (const void*)proj_gemm_kernel<kPjOut, false>};
-    for (int i = 0; i < 4 && attr_err == hipSuccess; ++i)
-      attr_err = hipFuncSetAttribute(kernels[i], hipFuncAttributeMaxDynamicSharedMemorySize, kPjLdsBytes);
+    const void* kernels[6] = {(const void*)proj_gemm_kernel<kPjQkv, true>, (const void*)proj_gemm_kernel<kPjQkv, false>,
+                              (const void*)proj_gemm_kernel<kPjOut, true>, (const void*)proj_gemm_kernel<kPjOut, false>,
+                              (const void*)proj_gemm_small_kernel<kPjQkv>, (const void*)proj_gemm_small_kernel<kPjOut>};
+    for (int i = 0; i < 6 && attr_err == hipSuccess; ++i)
+      attr_err = hipFuncSetAttribute(kernels[i], hipFuncAttributeMaxDynamicSharedMemorySize, i < 4 ? kPjLdsBytes : kPsLdsBytes);
   });
   if (attr_err != hipSuccess) { set_last_error("hipFuncSetAttribute: %s", hipGetErrorString(attr_err)); return HI_ERR_HIP; }
   p.a_tiles = (int)ceil_div(p.a_rows, kPjTile);
@@ -527,6 +721,24 @@ static hi_status pj_launch(void* stream, ProjArgs& p, int mode) {
   // 16-byte stores need bf16 output, whole runs of 128 features per wavefront and an aligned row pitch
   const bool wide = !p.out_fp32 && p.a_rows % 128 == 0 && (mode == kPjQkv || (p.y_stride * 2) % 16 == 0);
   const dim3 block(kPjWaves * 64);
+  // Which tile: at a contraction of 4096 a round of 256 small tiles takes 25 to 33 us; 256 large ones take 112 us, and a
+  // last round with fewer of them 78 (a few, no power limit) to 112 us.  So the small tile wins up to about 2400 tokens of
+  // a Llama-3-8B Q/K/V projection and just above 2730, where the large one starts a second round (165 against 199 us at
+  // 3000), and the large one from there on (a 16384-token chunk: 6 full rounds against 24).
+  const int64_t small_tiles = ceil_div(p.a_rows, kPsTile) * ceil_div(p.b_rows, kPsTile), rest = total % 256;
+  const int64_t small_us = 33 * ceil_div(small_tiles, 256);
+  const int64_t large_us = 112 * (total / 256) + (rest ? 78 + 34 * rest / 256 : 0);
+  if (wide && p.K >= kPsStages * kPjK && small_us < large_us) {
+    p.a_tiles = (int)ceil_div(p.a_rows, kPsTile);
+    p.b_tiles = (int)ceil_div(p.b_rows, kPsTile);
+    p.ga = p.a_tiles / 8 > 0 ? p.a_tiles / 8 : 1;
+    const dim3 sgrid((unsigned)(8 * ceil_div(small_tiles, 8)));
+    if (mode == kPjQkv) hipLaunchKernelGGL(proj_gemm_small_kernel<kPjQkv>, sgrid, block, kPsLdsBytes, (hipStream_t)stream, p);
+    else hipLaunchKernelGGL(proj_gemm_small_kernel<kPjOut>, sgrid, block, kPsLdsBytes, (hipStream_t)stream, p);
+    hipError_t es = hipGetLastError();
+    if (es != hipSuccess) { set_last_error("projection launch: %s", hipGetErrorString(es)); return HI_ERR_HIP; }
+    return HI_OK;
+  }
   if (mode == kPjQkv && wide) hipLaunchKernelGGL((proj_gemm_kernel<kPjQkv, true>), grid, block, kPjLdsBytes, (hipStream_t)stream, p);
   else if (mode == kPjQkv) hipLaunchKernelGGL((proj_gemm_kernel<kPjQkv, false>), grid, block, kPjLdsBytes, (hipStream_t)stream, p);
   else if (wide) hipLaunchKernelGGL((proj_gemm_kernel<kPjOut, true>), grid, block, kPjLdsBytes, (hipStream_t)stream, p);
