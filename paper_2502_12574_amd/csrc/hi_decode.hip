@@ -8,6 +8,7 @@
 // as the 16 columns of small MFMA tiles (S^T = K Q^T, O^T += V^T P^T), which keeps the vector ALU nearly idle;
 // the matrix unit runs at a few percent of its rate and is not the bound.
 #include <mutex>
+#include <type_traits>
 #include "hi_device.h"
 #include "hi_internal.h"
 
@@ -37,17 +38,97 @@ __device__ __forceinline__ void dec_issue_block(const char* __restrict__ k, cons
   }
 }
 
-// RAGGED: the heads of the launch have their own numbers of rows (sequences of different lengths served as more KV
-// heads); a head with fewer 16-row blocks than the grid has wavefronts leaves neutral partials.
-template <bool RAGGED>
+struct NoLens {};        // every head of the launch has the same number of rows
+template <class Lens> constexpr bool kRagged = std::is_same<Lens, DecodeLens>::value;
+
+// partials that cross workgroups inside one launch: through the point all XCDs agree on, past the L2s
+__device__ __forceinline__ void store_shared(float* p, float x) {
+  __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ float2 load_shared2(const float* p) {      // 8-byte aligned
+  const uint64_t v = __hip_atomic_load((const uint64_t*)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return make_float2(__uint_as_float((uint32_t)v), __uint_as_float((uint32_t)(v >> 32)));
+}
+
+// What decode_combine_kernel does, for all G query heads of one KV head, by the workgroup that finished its partial last.
+// Bound by the latency of its loads (the partials come from beyond the L2), so all of them are asked for at once: that is
+// why a launch has to have few partitions for it.  lds: 2 * 8 * kTailMaxParts floats.
+__device__ __forceinline__ void decode_tail(const uint16_t* q, int G, const float* part, int n_part, const DecodeTail& tl,
+                                            int64_t append_off, float c, float* lds) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int kv = blockIdx.y;
+  const uint16_t* k_new = (const uint16_t*)tl.k_new + kv * kHeadDim;
+  const uint16_t* v_new = (const uint16_t*)tl.v_new + kv * kHeadDim;
+  float* w = lds;                                  // [n_part][G] maxima, then weights, of the partials
+  float* sum = lds + 8 * kTailMaxParts;            // [n_part][G] sums
+  const int64_t part_pitch = (int64_t)G * kPartialFloats;
+  const int dim = 2 * lane;                        // a wavefront takes query heads wave and wave + 4, a lane two dims
+  float2 ml = make_float2(0.f, 0.f);
+  if (tid < n_part * G) ml = load_shared2(part + (int64_t)tid * kPartialFloats + kHeadDim);
+  float2 o[2][kTailMaxParts];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int g = wave + 4 * h;
+    if (g < G) {
+#pragma unroll
+      for (int p = 0; p < kTailMaxParts; ++p)      // (past the last partial: its values again, with weight 0)
+        o[h][p] = load_shared2(part + (p < n_part ? p : n_part - 1) * part_pitch + g * kPartialFloats + dim);
+    }
+  }
+  const uint32_t k2 = *(const uint32_t*)(k_new + dim), v2 = *(const uint32_t*)(v_new + dim);
+  if (tl.k_append != nullptr && wave == 0) {
+    *(uint32_t*)((char*)tl.k_append + append_off + 2 * dim) = k2;
+    *(uint32_t*)((char*)tl.v_append + append_off + 2 * dim) = v2;
+  }
+  if (tid < n_part * G) {
+    w[tid] = ml.x;
+    sum[tid] = ml.y;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int g = wave + 4 * h;
+    if (g >= G) break;
+    const uint32_t q2 = *(const uint32_t*)(q + g * kHeadDim + dim);
+    float d = __uint_as_float(q2 << 16) * __uint_as_float(k2 << 16) +
+              __uint_as_float(q2 & 0xFFFF0000u) * __uint_as_float(k2 & 0xFFFF0000u);
+    for (int off = 32; off > 0; off >>= 1) d += __shfl_xor(d, off);
+    const float m = lane < n_part ? w[lane * G + g] : kNegBig;
+    float mx = fmaxf(d, m);
+    for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
+    const float wp = lane < n_part ? fast_exp2((m - mx) * c) : 0.f;
+    float l = lane < n_part ? wp * sum[lane * G + g] : 0.f;
+    for (int off = 32; off > 0; off >>= 1) l += __shfl_xor(l, off);
+    const float p_new = fast_exp2((d - mx) * c);
+    const float inv = 1.0f / (l + p_new);
+    float2 acc = make_float2(p_new * __uint_as_float(v2 << 16), p_new * __uint_as_float(v2 & 0xFFFF0000u));
+#pragma unroll
+    for (int p = 0; p < kTailMaxParts; ++p) {
+      const float x = __shfl(wp, p);
+      acc.x = __builtin_fmaf(x, o[h][p].x, acc.x);
+      acc.y = __builtin_fmaf(x, o[h][p].y, acc.y);
+    }
+    acc.x *= inv;
+    acc.y *= inv;
+    const int64_t at = ((int64_t)kv * G + g) * kHeadDim + dim;
+    if (tl.out_fp32) *(float2*)((float*)tl.out + at) = acc;
+    else *(uint32_t*)((uint16_t*)tl.out + at) = (uint32_t)float_to_bf16_bits(acc.x) | ((uint32_t)float_to_bf16_bits(acc.y) << 16);
+  }
+}
+
+// Lens = DecodeLens: the heads of the launch have their own numbers of rows (sequences of different lengths served as
+// more KV heads); a head with fewer 16-row blocks than the grid has wavefronts leaves neutral partials.
+// TAIL: this launch writes all partials of its heads, few enough of them (kTailMaxParts) for one workgroup to combine: the
+// workgroup of a head that finishes last does so, and no combine launch follows.
+template <class Lens, bool TAIL>
 __global__ __launch_bounds__(256) void decode_partial_kernel(const uint16_t* __restrict__ q, int G,
                                                              const char* __restrict__ k, const char* __restrict__ v,
-                                                             int64_t n, float* __restrict__ partials, int part0,
+                                                             int64_t n, float* partials, int part0,
                                                              float c, int64_t kv_head_stride,
                                                              int64_t part_head_stride, int64_t skip_row,
-                                                             DecodeLens lens) {
+                                                             DecodeTail tail, Lens lens) {
   // group launches: blockIdx.y is the head
-  if (RAGGED) n = lens.n[blockIdx.y];
+  if constexpr (kRagged<Lens>) n = lens.n[blockIdx.y];
   q += (int64_t)blockIdx.y * G * kHeadDim;
   k += blockIdx.y * kv_head_stride;
   v += blockIdx.y * kv_head_stride;
@@ -61,6 +142,19 @@ __global__ __launch_bounds__(256) void decode_partial_kernel(const uint16_t* __r
   const int head = lane & 15;
   const int g4 = lane >> 4;
 
+  // 16-row blocks are dealt round-robin to the wavefronts of the grid, so at any moment the whole chip reads one
+  // compact window of the K and V streams (friendlier to HBM pages and TLBs than one far-apart range per wave)
+  const int64_t n_blocks = (n + kDecBlockRows - 1) / kDecBlockRows;
+  const int64_t n_waves = (int64_t)gridDim.x * 4;
+  const int64_t wid = (int64_t)blockIdx.x * 4 + wave;
+  const int64_t cnt = wid < n_blocks ? (n_blocks - wid + n_waves - 1) / n_waves : 0;   // blocks of this wave
+  const int64_t skip_blk = skip_row >= 0 ? skip_row / kDecBlockRows : -1;
+
+  // prologue: up to three blocks in flight, before the queries are asked for (one wait for both: over a short history
+  // two memory latencies in a row were a third of the kernel)
+  for (int s = 0; s < kDecStages - 1; ++s)
+    if (s < cnt) dec_issue_block(k, v, wid + s * n_waves, n, wlds + s * kDecStageBytes, lane);
+
   // Q^T as the B operand of S^T = K Q^T: lane holds q[head][32*kk + 8*g4 .. +7]; heads >= G are zero columns
   bf16x8 qf[4];
 #pragma unroll
@@ -73,22 +167,10 @@ __global__ __launch_bounds__(256) void decode_partial_kernel(const uint16_t* __r
 #pragma unroll
   for (int kk = 0; kk < 4; ++kk) asm volatile("" : "+v"(qf[kk]));
 
-  // 16-row blocks are dealt round-robin to the wavefronts of the grid, so at any moment the whole chip reads one
-  // compact window of the K and V streams (friendlier to HBM pages and TLBs than one far-apart range per wave)
-  const int64_t n_blocks = (n + kDecBlockRows - 1) / kDecBlockRows;
-  const int64_t n_waves = (int64_t)gridDim.x * 4;
-  const int64_t wid = (int64_t)blockIdx.x * 4 + wave;
-  const int64_t cnt = wid < n_blocks ? (n_blocks - wid + n_waves - 1) / n_waves : 0;   // blocks of this wave
-  const int64_t skip_blk = skip_row >= 0 ? skip_row / kDecBlockRows : -1;
-
   float m = kNegBig, l = 0.f;
   f32x4 o[8];
 #pragma unroll
   for (int i = 0; i < 8; ++i) o[i] = (f32x4){0.f, 0.f, 0.f, 0.f};
-
-  // prologue: up to three blocks in flight
-  for (int s = 0; s < kDecStages - 1; ++s)
-    if (s < cnt) dec_issue_block(k, v, wid + s * n_waves, n, wlds + s * kDecStageBytes, lane);
 
   // lane-constant LDS offsets of the operand reads
   const int k_tok = lane & 15;
@@ -192,11 +274,34 @@ __global__ __launch_bounds__(256) void decode_partial_kernel(const uint16_t* __r
       acc += wgt * red[(w * 16 + h) * kPartialFloats + dim];
       L += wgt * red[(w * 16 + h) * kPartialFloats + kHeadDim + 1];
     }
-    dst[h * kPartialFloats + dim] = acc;
+    auto put = [&](float* p, float x) { if (TAIL) store_shared(p, x); else *p = x; };
+    put(dst + h * kPartialFloats + dim, acc);
     if (dim == 0) {
-      dst[h * kPartialFloats + kHeadDim] = M;
-      dst[h * kPartialFloats + kHeadDim + 1] = L;
+      put(dst + h * kPartialFloats + kHeadDim, M);
+      put(dst + h * kPartialFloats + kHeadDim + 1, L);
     }
+  }
+  if constexpr (TAIL) {
+    // Every wavefront's partials have arrived before the count goes up; the last workgroup of the head resets it.  The
+    // partials are written and read by device-scope accesses that no L2 keeps a copy of, so that the wait for the stores,
+    // the barrier and the count order them; a release or acquire of everything else would walk the whole L2 once per
+    // workgroup (measured: 2 us more at 128 workgroups, 3 at 256).
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    int* flag = (int*)lds_raw;
+    if (threadIdx.x == 0) {
+      const int before = __hip_atomic_fetch_add(tail.counters + blockIdx.y, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const int last = before == (int)gridDim.x - 1;
+      if (last) __hip_atomic_store(tail.counters + blockIdx.y, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      *flag = last;
+    }
+    __syncthreads();
+    const bool last = *flag != 0;
+    __syncthreads();
+    if (!last) return;
+    int64_t off = blockIdx.y * tail.append_head_stride;
+    if constexpr (kRagged<Lens>) off += n * kRowBytes;      // (k_append / v_append point at row 0 of the first head)
+    decode_tail(q, G, partials, (int)gridDim.x, tail, off, c, (float*)lds_raw);
   }
 }
 
@@ -206,6 +311,7 @@ __global__ __launch_bounds__(256) void decode_partial_kernel(const uint16_t* __r
 constexpr int kCombDims = 16;
 constexpr int kCombLanes = 256 / kCombDims;
 
+template <class Lens>
 __global__ __launch_bounds__(256) void decode_combine_kernel(const uint16_t* __restrict__ q, int G,
                                                              const uint16_t* __restrict__ k_new,
                                                              const uint16_t* __restrict__ v_new,
@@ -214,7 +320,7 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(const uint16_t* __r
                                                              uint16_t* __restrict__ k_append,
                                                              uint16_t* __restrict__ v_append,
                                                              int64_t part_head_stride, int64_t append_head_stride,
-                                                             int ragged, DecodeLens lens) {
+                                                             Lens lens) {
   // group launches: blockIdx.z is the head
   q += (int64_t)blockIdx.z * G * kHeadDim;
   k_new += blockIdx.z * kHeadDim;
@@ -223,7 +329,8 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(const uint16_t* __r
   out = (char*)out + (int64_t)blockIdx.z * G * kHeadDim * (out_fp32 ? 4 : 2);
   if (k_append != nullptr) {
     // (ragged: k_append / v_append point at row 0 of the first head; each head appends at its own length)
-    const int64_t row_off = ragged ? lens.n[blockIdx.z] * kRowBytes : 0;
+    int64_t row_off = 0;
+    if constexpr (kRagged<Lens>) row_off = lens.n[blockIdx.z] * kRowBytes;
     k_append = (uint16_t*)((char*)k_append + blockIdx.z * append_head_stride + row_off);
     v_append = (uint16_t*)((char*)v_append + blockIdx.z * append_head_stride + row_off);
   }
@@ -283,30 +390,63 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(const uint16_t* __r
 }
 
 
+// Counters of the contexts that exist: a slot each of a built-in array, all zero whenever no launch of their context is
+// in flight.  A slot that is given back keeps the event of its context's last unit until that has finished.
+constexpr int kTailSlots = 64;
+static __device__ int tail_counters[kTailSlots * kTailMaxHeads];
+namespace {
+std::mutex tail_mu;
+struct TailSlot { bool taken; hipEvent_t busy_until; } tail_slots[kTailSlots];
+}  // namespace
+
+int* tail_counters_take(int* slot) {
+  void* base = nullptr;
+  if (hipGetSymbolAddress(&base, HIP_SYMBOL(tail_counters)) != hipSuccess || !base) { (void)hipGetLastError(); return nullptr; }
+  std::lock_guard<std::mutex> lock(tail_mu);
+  for (int i = 0; i < kTailSlots; ++i) {
+    if (tail_slots[i].taken) continue;
+    if (tail_slots[i].busy_until) {
+      if (hipEventQuery(tail_slots[i].busy_until) != hipSuccess) { (void)hipGetLastError(); continue; }
+      (void)hipEventDestroy(tail_slots[i].busy_until);
+      tail_slots[i].busy_until = nullptr;
+    }
+    tail_slots[i].taken = true;
+    *slot = i;
+    return (int*)base + i * kTailMaxHeads;
+  }
+  return nullptr;
+}
+
+void tail_counters_give(int slot, void* busy_until) {
+  std::lock_guard<std::mutex> lock(tail_mu);
+  tail_slots[slot].busy_until = (hipEvent_t)busy_until;
+  tail_slots[slot].taken = false;
+}
+
 hi_status launch_decode_partial(void* stream, const void* q, int G, const void* k, const void* v, int64_t n,
                                 int n_split, void* partials, int part0, bool q_prescaled, int n_heads,
                                 int64_t kv_head_stride, int64_t part_head_stride, int64_t skip_row,
-                                const DecodeLens* lens) {
+                                const DecodeLens* lens, const DecodeTail* tail) {
   if (n <= 0 || n_split <= 0 || n_heads < 1 || (lens && n_heads > kDecodeMaxRagged)) { set_last_error("decode partial: empty launch"); return HI_ERR_ARG; }
+  if (tail && (part0 != 0 || n_split > kTailMaxParts || n_heads > kTailMaxHeads || !tail->counters)) { set_last_error("decode partial: too many partials to combine in the launch"); return HI_ERR_ARG; }
   static std::once_flag attr_once;      // contexts on different host threads may get here together
   static hipError_t attr_err = hipSuccess;
   std::call_once(attr_once, [] {
-    attr_err = hipFuncSetAttribute((const void*)decode_partial_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                   kDecLdsBytes);
-    if (attr_err == hipSuccess)
-      attr_err = hipFuncSetAttribute((const void*)decode_partial_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                     kDecLdsBytes);
+    const void* kernels[4] = {(const void*)decode_partial_kernel<NoLens, false>, (const void*)decode_partial_kernel<NoLens, true>,
+                              (const void*)decode_partial_kernel<DecodeLens, false>, (const void*)decode_partial_kernel<DecodeLens, true>};
+    for (int i = 0; i < 4 && attr_err == hipSuccess; ++i)
+      attr_err = hipFuncSetAttribute(kernels[i], hipFuncAttributeMaxDynamicSharedMemorySize, kDecLdsBytes);
   });
   if (attr_err != hipSuccess) { set_last_error("hipFuncSetAttribute: %s", hipGetErrorString(attr_err)); return HI_ERR_HIP; }
-  static const DecodeLens no_lens = {};
-  if (lens)
-    hipLaunchKernelGGL(decode_partial_kernel<true>, dim3(n_split, n_heads), dim3(256), kDecLdsBytes, (hipStream_t)stream,
-                       (const uint16_t*)q, G, (const char*)k, (const char*)v, n, (float*)partials, part0, softmax_scale_log2(q_prescaled),
-                       kv_head_stride, part_head_stride, skip_row, *lens);
-  else
-    hipLaunchKernelGGL(decode_partial_kernel<false>, dim3(n_split, n_heads), dim3(256), kDecLdsBytes, (hipStream_t)stream,
-                       (const uint16_t*)q, G, (const char*)k, (const char*)v, n, (float*)partials, part0, softmax_scale_log2(q_prescaled),
-                       kv_head_stride, part_head_stride, skip_row, no_lens);
+  auto go = [&](auto kernel, auto lens_arg) {
+    hipLaunchKernelGGL(kernel, dim3(n_split, n_heads), dim3(256), kDecLdsBytes, (hipStream_t)stream, (const uint16_t*)q, G,
+                       (const char*)k, (const char*)v, n, (float*)partials, part0, softmax_scale_log2(q_prescaled),
+                       kv_head_stride, part_head_stride, skip_row, tail ? *tail : DecodeTail(), lens_arg);
+  };
+  if (lens && tail) go(decode_partial_kernel<DecodeLens, true>, *lens);
+  else if (lens) go(decode_partial_kernel<DecodeLens, false>, *lens);
+  else if (tail) go(decode_partial_kernel<NoLens, true>, NoLens());
+  else go(decode_partial_kernel<NoLens, false>, NoLens());
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) { set_last_error("decode_partial launch: %s", hipGetErrorString(e)); return HI_ERR_HIP; }
   return HI_OK;
@@ -316,12 +456,15 @@ hi_status launch_decode_combine(void* stream, const void* q, int G, const void* 
                                 const void* partials, int n_part, void* out, int out_fp32, void* k_append,
                                 void* v_append, bool q_prescaled, int n_heads, int64_t part_head_stride,
                                 int64_t append_head_stride, const DecodeLens* lens) {
-  static const DecodeLens no_lens = {};
   if (lens && n_heads > kDecodeMaxRagged) { set_last_error("decode combine: too many heads of their own length"); return HI_ERR_ARG; }
-  hipLaunchKernelGGL(decode_combine_kernel, dim3(G, kHeadDim / kCombDims, n_heads), dim3(256), 0, (hipStream_t)stream,
-                     (const uint16_t*)q, G, (const uint16_t*)k_new, (const uint16_t*)v_new, (const float*)partials,
-                     n_part, out, out_fp32, softmax_scale_log2(q_prescaled), (uint16_t*)k_append, (uint16_t*)v_append, part_head_stride,
-                     append_head_stride, lens ? 1 : 0, lens ? *lens : no_lens);
+  auto go = [&](auto kernel, auto lens_arg) {
+    hipLaunchKernelGGL(kernel, dim3(G, kHeadDim / kCombDims, n_heads), dim3(256), 0, (hipStream_t)stream,
+                       (const uint16_t*)q, G, (const uint16_t*)k_new, (const uint16_t*)v_new, (const float*)partials,
+                       n_part, out, out_fp32, softmax_scale_log2(q_prescaled), (uint16_t*)k_append, (uint16_t*)v_append,
+                       part_head_stride, append_head_stride, lens_arg);
+  };
+  if (lens) go(decode_combine_kernel<DecodeLens>, *lens);
+  else go(decode_combine_kernel<NoLens>, NoLens());
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) { set_last_error("decode_combine launch: %s", hipGetErrorString(e)); return HI_ERR_HIP; }
   return HI_OK;

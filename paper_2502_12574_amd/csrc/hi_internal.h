@@ -239,6 +239,22 @@ inline float softmax_scale_log2(bool q_prescaled) { return q_prescaled ? 1.0f : 
 constexpr int kDecodeMaxRagged = 64;
 struct DecodeLens { int64_t n[kDecodeMaxRagged]; };
 
+// The combine step carried by the partial launch itself (see decode_partial_kernel): the arguments launch_decode_combine
+// takes, and one counter per head of the launch, zero between launches.
+constexpr int kTailMaxParts = 16;            // partitions of a head that one workgroup combines
+constexpr int kTailMaxHeads = 128;           // KV heads of such a launch
+struct DecodeTail {
+  const void* k_new; const void* v_new;
+  void* out; int out_fp32;
+  void* k_append; void* v_append; int64_t append_head_stride;
+  int* counters;
+};
+
+// A context's counters (kTailMaxHeads ints of the current device, zero): null when all slots are taken.  They are given
+// back with the hipEvent_t that marks the end of the context's last unit (null: it ran none), which is then theirs.
+int* tail_counters_take(int* slot);
+void tail_counters_give(int slot, void* busy_until);
+
 // Split-KV decode over rows [0, n) of one slice: writes n_split partials starting at partial index part0.
 // n_heads > 1: q is [n_heads][G][128], the heads' K (V) rows kv_head_stride bytes apart, their partials
 // part_head_stride floats apart.
@@ -246,7 +262,9 @@ struct DecodeLens { int64_t n[kDecodeMaxRagged]; };
 hi_status launch_decode_partial(void* stream, const void* q, int G, const void* k, const void* v, int64_t n,
                                 int n_split, void* partials, int part0, bool q_prescaled, int n_heads = 1,
                                 int64_t kv_head_stride = 0,
-                                int64_t part_head_stride = 0, int64_t skip_row = -1, const DecodeLens* lens = nullptr);
+                                int64_t part_head_stride = 0, int64_t skip_row = -1, const DecodeLens* lens = nullptr,
+                                const DecodeTail* tail = nullptr);
+// tail != null (part0 = 0, n_split <= kTailMaxParts): the launch combines its partials too.
 // lens != null: head h has lens->n[h] rows instead of n (n = the largest of them), and launch_decode_combine appends
 // head h's row at row lens->n[h] behind k_append / v_append (which then point at row 0 of the first head)
 // Merge n_part partials with the token's own row and write out[G][128]; if k_append/v_append are not null the

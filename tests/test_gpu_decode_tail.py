@@ -1,0 +1,115 @@
+"""Decode launches that combine their own partials (the workgroup of a head that finishes last does it) against the oracle:
+one partition and many, both sides of the limit above which a combine launch follows, several tokens in a row (the
+counters go back to zero), heads of different lengths, streaming heads whose store has just filled up, and the same
+calls replayed from a graph."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import attention as oa
+from paper_2502_12574_amd import binding as hb
+from paper_2502_12574_amd import synth
+from paper_2502_12574_amd.session import Session
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+MAX_ABS, REL_L2 = 1e-2, 5e-3          # the bounds of the parity tests
+
+
+def _check(got, ref, what):
+    err, rel = float(np.abs(got - ref).max()), float(np.sqrt(((got - ref) ** 2).sum() / (ref ** 2).sum()))
+    assert err <= MAX_ABS and rel <= REL_L2, (what, err, rel)
+
+
+def _head(seed, h, G, n):
+    return ([synth.draw_q(seed, 0, h * G + g, 0, n) for g in range(G)], synth.draw_k(seed, 0, h, 0, n, peaked=True),
+            synth.draw_v(seed, 0, h, 0, n))
+
+
+# heads and lengths such that a head has 1 .. 16 partitions (one launch) and 17 and more (two)
+@pytest.mark.parametrize("G,H,past", [(4, 8, 1), (4, 8, 64), (4, 8, 65), (4, 8, 1022), (4, 3, 1100), (4, 17, 5000),
+                                      (1, 1, 900), (1, 2, 1023), (8, 1, 2048), (8, 2, 700), (8, 18, 3000), (2, 5, 640)])
+def test_tokens_in_a_row(G, H, past):
+    seed, nt = 53000, 3
+    heads = [_head(seed, h, G, past + nt) for h in range(H)]
+    with Session(1, H, G, max(past + nt, 256), 1, mode=hb.HI_MODE_RESIDENT, out_fp32=1) as ss:
+        view = ss.cache_view()[:, :, :, :past + nt]
+        for h, (_, k, v) in enumerate(heads):
+            view[0, h, 0, :past] = k[:past].to(DEV)
+            view[0, h, 1, :past] = v[:past].to(DEV)
+        out = torch.full((nt, H, G, 128), float("nan"), device=DEV)
+        rows = [(torch.stack([torch.stack([q[g][past + t] for g in range(G)]) for q, _, _ in heads]).to(DEV),
+                 torch.stack([k[past + t] for _, k, _ in heads]).to(DEV),
+                 torch.stack([v[past + t] for _, _, v in heads]).to(DEV)) for t in range(nt)]
+        ss.s_compute.wait_stream(torch.cuda.current_stream())
+        for t in range(nt):
+            ss.decode_group(0, 0, H, *rows[t], past + t, out[t])
+        ss.sync()
+        assert ss.stats().n_combine_kernels == nt
+        for h, (_, k, v) in enumerate(heads):
+            assert torch.equal(view[0, h, 0].cpu(), k) and torch.equal(view[0, h, 1].cpu(), v)
+    for h, (q, k, v) in enumerate(heads):
+        for g in range(G):
+            ref = oa.attn_rows(synth.to_f64(q[g][past:]), synth.to_f64(k), synth.to_f64(v), range(past, past + nt))
+            _check(out[:, h, g].cpu().double().numpy(), ref, (h, g))
+
+
+def test_different_lengths_and_replays_from_a_graph():
+    """A ragged step and a uniform one, captured once and replayed; eager work and synchronisations in between."""
+    seed, G, H, cap = 53100, 4, 6, 2300
+    lens = [0, 1, 64, 700, 1999, 2048]
+    heads = [_head(seed, h, G, cap) for h in range(H)]
+    with Session(1, H, G, cap, 1, mode=hb.HI_MODE_RESIDENT, out_fp32=1) as ss:
+        hb.hi_ctx_set_run_ahead(ss.ctx, 0)
+        view = ss.cache_view()
+        for h, (_, k, v) in enumerate(heads):
+            view[0, h, 0], view[0, h, 1] = k.to(DEV), v.to(DEV)
+        q = torch.stack([torch.stack([q[g][lens[h]] for g in range(G)]) for h, (q, _, _) in enumerate(heads)]).to(DEV)
+        k = torch.stack([k[lens[h]] for h, (_, k, _) in enumerate(heads)]).to(DEV)
+        v = torch.stack([v[lens[h]] for h, (_, _, v) in enumerate(heads)]).to(DEV)
+        out, uni = torch.zeros(H, G, 128, device=DEV), torch.zeros(H, G, 128, device=DEV)
+
+        def step():
+            hb.hi_decode_group_ragged(ss.ctx, 0, 0, H, q, k, v, lens, out)
+
+        torch.cuda.synchronize()
+        step()
+        ss.sync()
+        want = out.clone()
+        ref = [oa.attn_rows(synth.to_f64(qs[g][n:n + 1]), synth.to_f64(kk), synth.to_f64(vv), [n])[0]
+               for (qs, kk, vv), n in zip(heads, lens) for g in range(G)]
+        _check(want.cpu().double().numpy().reshape(-1, 128), np.stack(ref), "eager")
+        graph = torch.cuda.CUDAGraph()
+        torch.cuda.synchronize()
+        with torch.cuda.graph(graph, stream=ss.s_compute):
+            step()
+        for _ in range(4):
+            out.zero_()
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(out, want)
+            ss.decode_group(0, 0, H, q, k, v, 2100, uni)
+            ss.sync()
+            for h in range(H):               # the uniform step replaced row 2100 of every head: no ragged length reaches it
+                assert torch.equal(view[0, h, 0, 2100], k[h])
+
+
+def test_more_contexts_than_counter_slots():
+    """Contexts beyond the built-in counters keep the second launch; closed contexts give their counters back."""
+    past, G, H = 130, 4, 2
+    q, k, v = (torch.randn(s, device=DEV).to(torch.bfloat16) for s in ((H, G, 128), (H, 128), (H, 128)))
+    rows = torch.randn(1, H, 2, past, 128, device=DEV).to(torch.bfloat16)
+    outs = []
+    for _ in range(2):
+        open_ = [Session(1, H, G, 256, 1, mode=hb.HI_MODE_RESIDENT, out_fp32=1) for _ in range(70)]
+        for ss in open_:
+            ss.cache_view()[:, :, :, :past] = rows
+            out = torch.empty(H, G, 128, device=DEV)
+            ss.s_compute.wait_stream(torch.cuda.current_stream())
+            ss.decode_group(0, 0, H, q, k, v, past, out)
+            outs.append(out)
+        for ss in open_:
+            ss.close()
+    for out in outs:                    # three partials, summed in the same order by either way up to fp32 rounding
+        assert (out - outs[0]).abs().max() <= 1e-5
