@@ -59,6 +59,8 @@ struct ProjArgs {
   void* y; int64_t y_stride;          // [C][y_stride] elements
 };
 
+struct RopeFreqs { double inv[64]; };      // theta^(-i / 64)
+
 // tile j of the grid: groups of ga A-tiles; inside a group B-major with the A-tile index fastest, so that any run of
 // consecutive j is a compact block
 __device__ __forceinline__ void pj_tile_of(const ProjArgs& p, int j, int& ta, int& tb) {
@@ -590,7 +592,6 @@ __global__ __launch_bounds__(256, 1) void proj_gemm_small_kernel(ProjArgs p) {
 
 // (cos, sin) of position (past + t) times theta^(-i / 64) for i < 64, in double precision: at a million tokens the
 // angle of the fastest pair is a million radians, beyond what fp32 can reduce
-struct RopeFreqs { double inv[64]; };
 __global__ __launch_bounds__(256) void rope_table_kernel(float2* __restrict__ out, int64_t past, int n, RopeFreqs f) {
   const int idx = blockIdx.x * blockDim.x + threadIdx.x;
   if (idx >= n * 64) return;
@@ -598,6 +599,185 @@ __global__ __launch_bounds__(256) void rope_table_kernel(float2* __restrict__ ou
   double s, c;
   sincos((double)(past + t) * f.inv[i], &s, &c);
   out[((int64_t)(i >> 2) * n + t) * 4 + (i & 3)] = make_float2((float)c, (float)s);   // [i / 4][token][i % 4]
+}
+
+// ---- 2 to 64 tokens: the read of the weights is the bound (50 MB of Q/K/V at a hidden size of 4096), and the 128-row tiles
+// would leave it to 48 compute units.  A workgroup takes 16 RB weight rows (of Q/K/V: 8 RB rotary pairs of a head) and all
+// tokens, NT blocks of 16; its 4 wavefronts share the contraction in turns of 64 elements and add their sums through LDS at
+// the end.  Each wavefront streams its rows through an LDS ring of its own (direct-to-LDS loads, partial vmcnt waits, no
+// barrier in the loop).  The rotation's angles are formed in double precision while the first loads are in flight; no table
+// is needed.  One row block and two workgroups per compute unit (17 KB per wavefront) up to 16 tokens, and for the output
+// projection up to 32; with more tokens the activations are most of what a workgroup reads, so Q/K/V takes two row blocks,
+// and one workgroup has all of LDS (36 KB per wavefront).
+// Measured at 2 / 16 / 32 / 64 tokens (weights of 6 layers in turn, hidden size 4096, 32 + 16 heads; the 256-row tiles took
+// 87 to 91 and 74 us, the 128-row tiles 30 to 33 and 23): Q/K/V 12.2 / 13.6 / 16.0 / 18.5 us (4.1 TB/s of weights at 2),
+// output 7.9 / 8.0 / 8.5 / 10.3 us.  Q/K/V of 16 tokens with two row blocks: 15.4 us; of 64 with one: 24.0.
+template <int MODE, int NT> constexpr int kPfwRowBlocks = MODE == kPjQkv && NT > 1 ? 2 : 1;
+template <int MODE, int NT> constexpr int kPfwStageBytes = (kPfwRowBlocks<MODE, NT> + NT) * 16 * kPjRowBytes;
+template <int MODE, int NT> constexpr int kPfwWaveBytes = (kPfwRowBlocks<MODE, NT> == 1 && NT <= 2 ? 17 : 36) * 1024;
+template <int MODE, int NT> constexpr int kPfwStages =
+    kPfwWaveBytes<MODE, NT> / kPfwStageBytes<MODE, NT> < 8 ? kPfwWaveBytes<MODE, NT> / kPfwStageBytes<MODE, NT> : 8;
+template <int MODE, int NT> constexpr int kPfwRings = 4 * kPfwStages<MODE, NT> * kPfwStageBytes<MODE, NT>;
+template <int MODE, int NT> constexpr int kPfwLdsBytes = kPfwRings<MODE, NT> + 16 * 16 * NT * 8;     // then (cos, sin) of the pairs
+constexpr int kPfwMaxTokens = 64;
+
+template <int MODE, int NT>
+__global__ __launch_bounds__(256, 1) void proj_few_kernel(ProjArgs p, int64_t past, RopeFreqs f, int rotate_heads) {
+  constexpr int RB = kPfwRowBlocks<MODE, NT>, kPairs = 8 * RB;
+  constexpr int kStage = kPfwStageBytes<MODE, NT>, kStages = kPfwStages<MODE, NT>, kLoads = 2 * (RB + NT);
+  static_assert(kStages >= 2 && (kStages - 1) * kLoads < 64 && kPfwLdsBytes<MODE, NT> <= 160 * 1024, "ring");
+  static_assert(4 * 16 * RB * 16 * NT * 4 <= kPfwRings<MODE, NT>, "the sums take the rings' place");
+  extern __shared__ __attribute__((aligned(1024))) char lds_dyn[];
+  const uint32_t lds_base = (uint32_t)(uintptr_t)(lds_char*)lds_dyn;
+  const int lane = lane_id();
+  const int wave = wave_id();
+  const int c16 = lane & 15, g4 = lane >> 4;
+  const uint32_t ring = lds_base + wave * (kStages * kStage);
+
+  // weight row of tile row r: the first half of the Q/K/V rows are dims i0 .. of the head, the second their partners i0 + 64 ..
+  const int head = blockIdx.x / (64 / kPairs), i0 = blockIdx.x % (64 / kPairs) * kPairs;
+  auto weight_row = [&](int r) { return MODE == kPjQkv ? head * kHeadDim + i0 + r % kPairs + 64 * (r / kPairs) : (int)blockIdx.x * 16 + r; };
+  uint32_t off[kLoads];          // this lane's byte offset of each load instruction (8 rows of 128 bytes)
+#pragma unroll
+  for (int u = 0; u < kLoads; ++u) {
+    const int r = 8 * u + (lane >> 3);
+    const int chunk = (lane & 7) ^ ((r >> 1) & 7);
+    if (u < 2 * RB) {
+      int row = weight_row(r);
+      row = row < p.a_rows ? row : p.a_rows - 1;
+      off[u] = (uint32_t)row * p.a_stride + (chunk << 4);
+    } else {
+      int row = r - 16 * RB;
+      row = row < p.b_rows ? row : p.b_rows - 1;
+      off[u] = (uint32_t)row * p.b_stride + (chunk << 4);
+    }
+  }
+  const int T = p.K / kPjK;
+  const int cnt = wave < T ? (T - wave + 3) / 4 : 0;           // steps of this wavefront: wave, wave + 4, ...
+  auto issue = [&](int i, int stage) __attribute__((always_inline)) {
+    const int k0 = (wave + 4 * i) * kPjK;
+    const char* ab = p.a + (int64_t)k0 * 2;
+    const char* bb = MODE == kPjOut ? p.b + (int64_t)(k0 >> 7) * p.b_head_stride + (k0 & 127) * 2 : p.b + (int64_t)k0 * 2;
+    const uint32_t dst = ring + stage * kStage;
+#pragma unroll
+    for (int u = 0; u < kLoads; ++u) g2lds16_s<0>(u < 2 * RB ? ab : bb, off[u], dst + u * 1024);
+  };
+#pragma unroll
+  for (int i = 0; i < kStages - 1; ++i)
+    if (i < cnt) issue(i, i);
+
+  // (cos, sin) of pair i0 + tid % 16 at tokens tid / 16 + 16 n: the first angle, then steps of 16 positions, all in double
+  float2* trig = (float2*)(lds_dyn + kPfwRings<MODE, NT>);
+  const bool rotate = MODE == kPjQkv && head < rotate_heads;
+  const int my_pair = threadIdx.x & 15, t0 = threadIdx.x >> 4;
+  if (rotate && my_pair < kPairs) {
+    const double w = f.inv[i0 + my_pair];
+    double s, c, s16 = 0.0, c16d = 1.0;
+    sincos((double)(past + t0) * w, &s, &c);
+    if (NT > 1) sincos(16.0 * w, &s16, &c16d);
+#pragma unroll
+    for (int n = 0; n < NT; ++n) {
+      trig[my_pair * (16 * NT) + t0 + 16 * n] = make_float2((float)c, (float)s);
+      const double cn = c * c16d - s * s16;
+      s = s * c16d + c * s16;
+      c = cn;
+    }
+  }
+
+  f32x4 acc[RB][NT];
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) acc[rb][nt] = (f32x4){0.f, 0.f, 0.f, 0.f};
+  uint32_t rd[2];                // operand reads: row c16 of a 16-row block, chunk 4 kk + g4
+#pragma unroll
+  for (int kk = 0; kk < 2; ++kk) rd[kk] = ring + c16 * kPjRowBytes + (((4 * kk + g4) ^ ((c16 >> 1) & 7)) << 4);
+  int stage = 0, fill = kStages - 1;
+  for (int i = 0; i < cnt; ++i) {
+    if (i + kStages - 1 < cnt) {
+      issue(i + kStages - 1, fill);
+      wait_vmcnt<(kStages - 1) * kLoads>();          // the oldest stage has landed
+    } else {
+      wait_vmcnt<0>();
+    }
+    const uint32_t at = stage * kStage;
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk) {
+      bf16x8 a[RB];
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb) a[rb] = *(lds_bf16x8_p)((lds_char*)(uintptr_t)(rd[kk] + at) + rb * 2048);
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) {
+        const bf16x8 b = *(lds_bf16x8_p)((lds_char*)(uintptr_t)(rd[kk] + at) + (RB + nt) * 2048);
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) acc[rb][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[rb], b, acc[rb][nt], 0, 0, 0);
+      }
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // done reading before the stage is filled again
+    stage = stage + 1 < kStages ? stage + 1 : 0;
+    fill = fill + 1 < kStages ? fill + 1 : 0;
+  }
+
+  // sums of the four wavefronts, [wavefront][row][token]
+  __syncthreads();
+  float* red = (float*)lds_dyn;
+  constexpr int kTok = 16 * NT, kPlane = 16 * RB * kTok;
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) red[wave * kPlane + (16 * rb + 4 * g4 + r) * kTok + 16 * nt + c16] = acc[rb][nt][r];
+  __syncthreads();
+  const int j4 = threadIdx.x & 3, tok = threadIdx.x >> 2;      // this thread writes features (or pairs) 4 j4 .. + 3 of token tok
+  if (tok >= p.b_rows || tok >= kTok || (MODE == kPjQkv && 4 * j4 >= kPairs)) return;
+  float v[2][4];                 // Q/K/V: the pairs' first and second members
+#pragma unroll
+  for (int half = 0; half < (MODE == kPjQkv ? 2 : 1); ++half)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float* src = red + (kPairs * half + 4 * j4 + e) * kTok + tok;
+      v[half][e] = (src[0] + src[kPlane]) + (src[2 * kPlane] + src[3 * kPlane]);
+    }
+  const int esz = p.out_fp32 ? 4 : 2;
+  if (MODE == kPjQkv) {
+    char* base;
+    int hh;
+    float osc = 1.0f;
+    if (head < p.n_q_heads) { base = (char*)p.q_out; hh = head; osc = p.q_scale; }
+    else if (head < p.n_q_heads + p.n_kv_heads) { base = (char*)p.k_out; hh = head - p.n_q_heads; }
+    else { base = (char*)p.v_out; hh = head - p.n_q_heads - p.n_kv_heads; }
+    base += (((int64_t)hh * p.b_rows + tok) * kHeadDim + i0 + 4 * j4) * esz;
+    float lo[4], hi[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float x = v[0][e], y = v[1][e];
+      const float2 t = rotate ? trig[(4 * j4 + e) * kTok + tok] : make_float2(1.f, 0.f);
+      lo[e] = (rotate ? pj_rot_lo(x, y, t.x, t.y) : x) * osc;
+      hi[e] = (rotate ? pj_rot_hi(x, y, t.x, t.y) : y) * osc;
+    }
+    if (p.out_fp32) {
+      *(float4*)base = make_float4(lo[0], lo[1], lo[2], lo[3]);
+      *(float4*)(base + 64 * 4) = make_float4(hi[0], hi[1], hi[2], hi[3]);
+    } else {
+      *(uint2*)base = make_uint2(pj_pack2(lo[0], lo[1]), pj_pack2(lo[2], lo[3]));
+      *(uint2*)(base + 64 * 2) = make_uint2(pj_pack2(hi[0], hi[1]), pj_pack2(hi[2], hi[3]));
+    }
+  } else {
+    const int row = blockIdx.x * 16 + 4 * j4;
+    char* base = (char*)p.y + ((int64_t)tok * p.y_stride + row) * esz;
+    if (row + 4 <= p.a_rows && p.y_stride % 4 == 0) {
+      if (p.out_fp32) *(float4*)base = make_float4(v[0][0], v[0][1], v[0][2], v[0][3]);
+      else *(uint2*)base = make_uint2(pj_pack2(v[0][0], v[0][1]), pj_pack2(v[0][2], v[0][3]));
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (row + e < p.a_rows) {
+          if (p.out_fp32) ((float*)base)[e] = v[0][e];
+          else ((uint16_t*)base)[e] = float_to_bf16_bits(v[0][e]);
+        }
+    }
+  }
 }
 
 // ---- one token (decode): the same two projections as matrix-vector products, bound by the HBM read of the weights.
@@ -748,6 +928,28 @@ static hi_status pj_launch(void* stream, ProjArgs& p, int mode) {
   return HI_OK;
 }
 
+template <int MODE, int NT>
+static hipError_t pj_few_go(void* stream, const ProjArgs& p, int64_t past, const RopeFreqs& f, int rotate_heads) {
+  constexpr int lds = kPfwLdsBytes<MODE, NT>;
+  static std::once_flag once;
+  static hipError_t attr = hipSuccess;
+  std::call_once(once, [] { attr = hipFuncSetAttribute((const void*)proj_few_kernel<MODE, NT>, hipFuncAttributeMaxDynamicSharedMemorySize, lds); });
+  if (attr != hipSuccess) return attr;
+  const unsigned wgs = (unsigned)ceil_div(p.a_rows, 16 * kPfwRowBlocks<MODE, NT>);
+  hipLaunchKernelGGL((proj_few_kernel<MODE, NT>), dim3(wgs), dim3(256), lds, (hipStream_t)stream, p, past, f, rotate_heads);
+  return hipGetLastError();
+}
+
+// rotate_heads: the leading heads (queries, then keys) that are rotated
+template <int MODE>
+static hi_status pj_few_launch(void* stream, const ProjArgs& p, int64_t past, const RopeFreqs& f, int rotate_heads) {
+  const hipError_t e = p.b_rows <= 16 ? pj_few_go<MODE, 1>(stream, p, past, f, rotate_heads)
+                     : p.b_rows <= 32 ? pj_few_go<MODE, 2>(stream, p, past, f, rotate_heads)
+                                      : pj_few_go<MODE, 4>(stream, p, past, f, rotate_heads);
+  if (e != hipSuccess) { set_last_error("projection (few tokens) launch: %s", hipGetErrorString(e)); return HI_ERR_HIP; }
+  return HI_OK;
+}
+
 static bool pj_aligned16(const void* q) { return (reinterpret_cast<uintptr_t>(q) & 15u) == 0; }
 
 #define HI_PJ_TRY(call)               \
@@ -814,9 +1016,11 @@ static hi_status qkv_rope_impl(void* stream, const void* x_dev, const void* w_qk
   p.n_q_heads = n_q_heads; p.n_kv_heads = n_kv_heads;
   p.rope = nullptr;
   p.q_scale = q_scale;
-  if (rope_theta > 0) {
-    RopeFreqs f;
+  RopeFreqs f = {};
+  if (rope_theta > 0)
     for (int i = 0; i < 64; ++i) f.inv[i] = pow(rope_theta, -(double)i / 64.0);
+  if (chunk_len <= kPfwMaxTokens) return pj_few_launch<kPjQkv>(stream, p, past_len, f, rope_theta > 0 ? n_q_heads + n_kv_heads : 0);
+  if (rope_theta > 0) {
     hipLaunchKernelGGL(rope_table_kernel, dim3((unsigned)ceil_div((int64_t)chunk_len * 64, 256)), dim3(256), 0,
                        (hipStream_t)stream, (float2*)workspace_dev, past_len, chunk_len, f);
     hipError_t e = hipGetLastError();
@@ -908,5 +1112,6 @@ extern "C" hi_status hi_out_proj(void* stream, const void* attn_dev, const void*
   p.K = (int)K;
   p.out_fp32 = out_fp32;
   p.y = y_out_dev; p.y_stride = d_model;
+  if (chunk_len <= kPfwMaxTokens) return pj_few_launch<kPjOut>(stream, p, 0, RopeFreqs(), 0);
   return pj_launch(stream, p, kPjOut);
 }
