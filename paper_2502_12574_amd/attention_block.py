@@ -40,38 +40,38 @@ class AttentionBlock:
         self.calls = [(h, min(g, n_ret - h)) for h in range(0, n_ret, g)]
         self.calls += [(h, min(g, self.Hkv - h)) for h in range(n_ret, self.Hkv, g)]
 
-    def _views(self, n):
-        q = self.q[:self.Hq * n * 128].view(self.Hkv, self.G, n, 128)
-        k = self.kv[self.turn][0][:self.Hkv * n * 128].view(self.Hkv, n, 128)
-        v = self.kv[self.turn][1][:self.Hkv * n * 128].view(self.Hkv, n, 128)
-        o = self.attn[:self.Hq * n * 128].view(self.Hkv, self.G, n, 128)
-        return q, k, v, o
-
     def forward(self, x: torch.Tensor, past_len: int, y: torch.Tensor, nxt=None):
         """x [n][d_model] bf16 hidden states of the tokens at positions past_len .., n = 1 for a decode step;
         y [n][d_model] bf16 receives the block's output.  nxt: the (layer, first head, heads, past) unit that will
-        be called after this block's last one, for the prefetch.  Enqueues on the Session's compute stream."""
+        be called after this block's last one, for the prefetch.  Enqueues on the Session's compute stream.
+
+        A generated token is 4 to 5 launches of about 10 us each, so the calls hand addresses to the library instead of
+        slicing views for every head group: head-major q and output are [Hkv][G][n][128], k and v [Hkv][n][128]."""
         ss, n = self.ss, x.shape[0]
         assert ss.out_dtype == torch.bfloat16, "the output projection reads bf16 attention outputs"
-        q, k, v, o = self._views(n)
-        s = ss.s_compute
-        if self.kv_done[self.turn] is not None:
+        k, v = self.kv[self.turn]
+        q, k, v, o = self.q.data_ptr(), k.data_ptr(), v.data_ptr(), self.attn.data_ptr()
+        s, row = ss.s_compute, n * 256                       # bytes of one head's rows of this call
+        offload = ss.mode == hb.HI_MODE_OFFLOAD              # (resident heads are appended on the compute stream itself)
+        if offload and self.kv_done[self.turn] is not None:
             s.wait_event(self.kv_done[self.turn])
-        with torch.cuda.stream(s):
-            # the softmax scale rides on the queries when the Session's attention calls expect it there
-            hb.hi_qkv_rope(s, x, self.w_qkv, self.D, self.Hq, self.Hkv, n, past_len, self.theta, 0, q, k, v, self.ws,
-                           q_scale=hb.HI_Q_PRESCALE if ss.problem.q_prescaled else 1.0)
-            for i, (h0, nh) in enumerate(self.calls):
-                hint = (self.layer, self.calls[i + 1][0], self.calls[i + 1][1], past_len) if i + 1 < len(self.calls) else nxt
-                if n == 1:
-                    ss.decode_group(self.layer, h0, nh, q[h0:h0 + nh, :, 0], k[h0:h0 + nh, 0], v[h0:h0 + nh, 0], past_len,
-                                    o[h0:h0 + nh, :, 0], hint)
-                else:
-                    ss.prefill_group(self.layer, h0, nh, q[h0:h0 + nh], k[h0:h0 + nh], v[h0:h0 + nh], past_len,
-                                     o[h0:h0 + nh], hint)
-            hb.hi_out_proj(s, o, self.w_o, self.Hq, self.D, n, 0, y)
-        ev = torch.cuda.Event()
-        ev.record(ss.s_d2h)
-        self.kv_done[self.turn] = ev
+        # the softmax scale rides on the queries when the Session's attention calls expect it there
+        hb.hi_qkv_rope(s, x, self.w_qkv, self.D, self.Hq, self.Hkv, n, past_len, self.theta, 0, q, k, v, self.ws,
+                       q_scale=hb.HI_Q_PRESCALE if ss.problem.q_prescaled else 1.0)
+        for i, (h0, nh) in enumerate(self.calls):
+            hint = (self.layer, self.calls[i + 1][0], self.calls[i + 1][1], past_len) if i + 1 < len(self.calls) else nxt
+            nl, nhead, nheads, npast = hint if hint is not None else (-1, 0, 1, 0)
+            at, at_q = h0 * row, h0 * self.G * row
+            if n == 1:
+                hb.hi_decode_group(ss.ctx, self.layer, h0, nh, q + at_q, k + at, v + at, past_len, o + at_q, nl, nhead,
+                                   nheads, npast)
+            else:
+                hb.hi_prefill_group(ss.ctx, self.layer, h0, nh, q + at_q, k + at, v + at, past_len, n, o + at_q, nl, nhead,
+                                    nheads, npast)
+        hb.hi_out_proj(s, o, self.w_o, self.Hq, self.D, n, 0, y)
+        if offload:
+            if self.kv_done[self.turn] is None:
+                self.kv_done[self.turn] = torch.cuda.Event()
+            self.kv_done[self.turn].record(ss.s_d2h)
         self.turn ^= 1
         return y
