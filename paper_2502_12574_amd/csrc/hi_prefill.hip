@@ -183,19 +183,29 @@ __device__ __forceinline__ void pf_write_row(void* out, int out_fp32, int C, int
 }
 
 
+// Operands that the 4-wave kernels read ahead of their MFMAs (scores, weighted V): left to itself the compiler keeps two
+// in flight and the MFMAs wait for LDS.  1000 rows of 8 heads behind 1000: 60.0 -> 55.7 us; 6 or 8 ahead are no faster.
+constexpr int kPf4AheadK = 4, kPf4AheadV = 4;
+
 // S^T = K Q^T for one 64-row K tile at kt: register r of sub-block sb is tile row 32*sb + 8*(r/4) + 4*hl + r%4
 // (query row = lane % 32).  The two sub-blocks' accumulation chains alternate, so consecutive MFMAs never
 // depend on each other.
 __device__ __forceinline__ void pf_scores(lds_char* kt, const PfLaneConst& lc, const bf16x8 (&qf)[8],
                                           f32x16 (&s)[2]) {
+  constexpr int A = kPf4AheadK;
+  bf16x8 op[A + 1];
+  auto read = [&](int i) __attribute__((always_inline)) { return *(lds_bf16x8*)(kt + lc.koff[i >> 1] + (i & 1) * 8192); };
 #pragma unroll
   for (int r = 0; r < 16; ++r) { s[0][r] = 0.f; s[1][r] = 0.f; }
+  __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-  for (int kk = 0; kk < 8; ++kk) {
-    const bf16x8 k0 = *(lds_bf16x8*)(kt + lc.koff[kk]);
-    const bf16x8 k1 = *(lds_bf16x8*)(kt + lc.koff[kk] + 8192);
-    s[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k0, qf[kk], s[0], 0, 0, 0);
-    s[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k1, qf[kk], s[1], 0, 0, 0);
+  for (int i = 0; i < A; ++i) op[i] = read(i);
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    if (i + A < 16) op[(i + A) % (A + 1)] = read(i + A);
+    s[i & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op[i % (A + 1)], qf[i >> 1], s[i & 1], 0, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
   }
 }
 
@@ -312,18 +322,23 @@ __device__ __forceinline__ void pf_softmax_fast(f32x16 (&s)[2], PfState& st, flo
 // O^T += V^T P^T for one 64-row V tile at vt: contraction index 8*hl + j of MFMA (sb,u) is tile row
 // 32*sb + 16*u + 8*(j/4) + 4*hl + j%4.
 __device__ __forceinline__ void pf_pv(lds_char* vt, const PfLaneConst& lc, const bf16x8 (&pb)[2][2], PfState& st) {
+  constexpr int A = kPf4AheadV;
+  bf16x8 op[A + 1];
+  auto read = [&](int i) __attribute__((always_inline)) {           // MFMA i: dim block i % 4, contraction group i / 4
+    lds_char* p = vt + lc.voff[i & 3] + (i >> 2) * 4096;
+    const bf16x4 v0 = lds_read_tr8(p), v1 = lds_read_tr8(p + 2048);
+    return (bf16x8)__builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7);
+  };
+  __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-  for (int sb = 0; sb < 2; ++sb)
+  for (int i = 0; i < A; ++i) op[i] = read(i);
+  __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-#pragma unroll
-      for (int db = 0; db < 4; ++db) {
-        const bf16x4 v0 = lds_read_tr8(vt + lc.voff[db] + sb * 8192 + u * 4096);
-        const bf16x4 v1 = lds_read_tr8(vt + lc.voff[db] + sb * 8192 + u * 4096 + 2048);
-        const bf16x8 vf = __builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7);
-        st.o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pb[sb][u], st.o[db], 0, 0, 0);
-      }
-    }
+  for (int i = 0; i < 16; ++i) {
+    if (i + A < 16) op[(i + A) % (A + 1)] = read(i + A);
+    st.o[i & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op[i % (A + 1)], pb[i >> 3][(i >> 2) & 1], st.o[i & 3], 0, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+  }
 }
 
 // ---- helpers of the 8-wave kernel.  Its LDS holds a ring of K tiles at [0, 64 KiB) and a ring of V tiles at
@@ -1647,19 +1662,26 @@ struct PrefillWindowArgs {
   int64_t s_head_stride;  // bytes between the heads' stores
 };
 
-// pf_softmax for a tile in which lane-dependent sets of rows are hidden: row is visible iff row <= hi and
-// (row < sk or row >= lo).  A lane may see nothing of the tile (and nothing so far): hidden entries contribute
-// exactly zero whatever the running maximum is.
-__device__ __forceinline__ void pf_softmax_window(f32x16 (&s)[2], PfState& st, float c, bool masked, int hi, int sk,
-                                                  int lo, int hl, bf16x8 (&pb)[2][2]) {
+// Rows [0, n) of a tile as a bit mask.
+__device__ __forceinline__ uint64_t pf_rows_below(int n) { return n <= 0 ? 0 : n >= 64 ? ~0ull : (1ull << n) - 1; }
+
+// pf_softmax for a tile in which lane-dependent sets of rows are hidden: bit 8 (r / 4) + r % 4 of seen[sb] says whether the
+// lane's row r of sub-block sb is visible.  A lane may see nothing of the tile (and nothing so far): hidden entries
+// contribute exactly zero whatever the running maximum is.  The bits are applied as bit operations: as comparisons and
+// selects per element the compiler made branches of them, for tiles that need no mask too (83 -> 77 us a launch over 4 heads
+// x 8192 rows, sink 128 + recent 512).
+__device__ __forceinline__ void pf_softmax_window(f32x16 (&s)[2], PfState& st, float c, bool masked,
+                                                  const uint32_t (&seen)[2], bf16x8 (&pb)[2][2]) {
+  auto bit = [&](int sb, int r) __attribute__((always_inline)) {       // all ones if visible, else 0
+    return (uint32_t)__builtin_amdgcn_sbfe((int)seen[sb], 8 * (r >> 2) + (r & 3), 1);
+  };
   if (masked) {
 #pragma unroll
     for (int sb = 0; sb < 2; ++sb)
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const int row = 32 * sb + 8 * (r >> 2) + 4 * hl + (r & 3);
-        const bool vis = row <= hi && (row < sk || row >= lo);
-        if (!vis) s[sb][r] = kNegBig;
+        const uint32_t t = bit(sb, r);
+        s[sb][r] = __uint_as_float((__float_as_uint(s[sb][r]) & t) | (__float_as_uint(kNegBig) & ~t));
       }
   }
   float mx = s[0][0];
@@ -1679,21 +1701,36 @@ __device__ __forceinline__ void pf_softmax_window(f32x16 (&s)[2], PfState& st, f
     st.m = m_new;
   }
   const float mc = st.m * c;
-  float lsum = 0.f;
+#pragma unroll
+  for (int sb = 0; sb < 2; ++sb)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) s[sb][r] = fast_exp2(__builtin_fmaf(s[sb][r], c, -mc));
+  if (masked) {
+#pragma unroll
+    for (int sb = 0; sb < 2; ++sb)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) s[sb][r] = __uint_as_float(__float_as_uint(s[sb][r]) & bit(sb, r));
+  }
+  float lq[4];
 #pragma unroll
   for (int sb = 0; sb < 2; ++sb)
 #pragma unroll
     for (int u = 0; u < 2; ++u)
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
-        float p = fast_exp2(__builtin_fmaf(s[sb][8 * u + j], c, -mc));
-        if (masked && s[sb][8 * u + j] == kNegBig) p = 0.f;
-        lsum += p;
+        const float p = s[sb][8 * u + j];
+        lq[2 * sb + u] = j == 0 ? p : lq[2 * sb + u] + p;
         pb[sb][u][j] = (__bf16)p;
       }
-  st.l += lsum;
+  st.l += (lq[0] + lq[1]) + (lq[2] + lq[3]);
 }
 
+// Where the time of a launch over 4 heads x 8192 rows (1024 workgroups, two rounds of two per compute unit) goes: 1.85 us per
+// tile and round, near the 4-wave kernel's rate, and about 9 us a round to fetch queries and first tiles and to write the
+// rows, which two resident workgroups hide only in part.  Asking for the first tile before the queries and keeping
+// neighbouring blocks on one XCD took it from 72 to 66 us; a ring of four stages with one workgroup of 8 wavefronts, or of
+// three K and two V tiles with two of 4, was no faster (87, 84 against 83 us), and starting the scores from minus the
+// running reference spilled registers (89).
 __global__ __launch_bounds__(256, 2) void prefill_window_kernel(PrefillWindowArgs a) {
   __shared__ __attribute__((aligned(1024))) char lds_raw[kPfLdsBytes];
   lds_char* lds = (lds_char*)lds_raw;
@@ -1705,7 +1742,8 @@ __global__ __launch_bounds__(256, 2) void prefill_window_kernel(PrefillWindowArg
 
   const int gl = a.G < 4 ? a.G : 4;
   const int strip = 32 * (4 / gl);
-  const int bx = blockIdx.x;
+  // neighbouring blocks of positions read the same rows: let them share an XCD's L2
+  const int bx = pf_wg_index(blockIdx.x, gridDim.x, gridDim.x % 8 == 0);
   const int head = blockIdx.y / a.gy;
   {  // group launches: this workgroup's head
     const int64_t rows = (int64_t)head * a.C;
@@ -1725,12 +1763,6 @@ __global__ __launch_bounds__(256, 2) void prefill_window_kernel(PrefillWindowArg
 
   const PfLaneConst lc = pf_lane_const_4w(wave, lane);
 
-  bf16x8 qf[8];
-  {
-    const uint16_t* qrow = a.q + ((int64_t)g * a.C + qi) * kHeadDim + 8 * hl;
-#pragma unroll
-    for (int kk = 0; kk < 8; ++kk) qf[kk] = __builtin_bit_cast(bf16x8, *(const uint4*)(qrow + 16 * kk));
-  }
   PfState st;
   st.m = kNegBig;
   st.l = 0.f;
@@ -1738,8 +1770,6 @@ __global__ __launch_bounds__(256, 2) void prefill_window_kernel(PrefillWindowArg
   for (int db = 0; db < 4; ++db)
 #pragma unroll
     for (int r = 0; r < 16; ++r) st.o[db][r] = 0.f;
-#pragma unroll
-  for (int kk = 0; kk < 8; ++kk) asm volatile("" : "+v"(qf[kk]));
 
   // tiles this workgroup visits: A [0, a1) and [a2, ta), then B [0, b1) and [b2, tb)
   const int nA = a.ns + a.m;
@@ -1797,7 +1827,15 @@ __global__ __launch_bounds__(256, 2) void prefill_window_kernel(PrefillWindowArg
     }
   };
 
-  issue(0);
+  issue(0);                    // before the queries: one wait for both
+  bf16x8 qf[8];
+  {
+    const uint16_t* qrow = a.q + ((int64_t)g * a.C + qi) * kHeadDim + 8 * hl;
+#pragma unroll
+    for (int kk = 0; kk < 8; ++kk) qf[kk] = __builtin_bit_cast(bf16x8, *(const uint4*)(qrow + 16 * kk));
+  }
+#pragma unroll
+  for (int kk = 0; kk < 8; ++kk) asm volatile("" : "+v"(qf[kk]));
   const float c = a.c;
   auto step = [&](int v, auto stage_tag) __attribute__((always_inline)) {
     constexpr int STAGE = decltype(stage_tag)::value;
@@ -1825,7 +1863,13 @@ __global__ __launch_bounds__(256, 2) void prefill_window_kernel(PrefillWindowArg
     f32x16 s[2];
     bf16x8 pb[2][2];
     pf_scores(kt, lc, qf, s);
-    pf_softmax_window(s, st, c, !full, hi, sk, lo, hl, pb);
+    uint32_t seen[2];
+    {
+      const uint64_t rows = (pf_rows_below(hi + 1) & (pf_rows_below(sk) | ~pf_rows_below(lo))) >> (4 * hl);
+      seen[0] = (uint32_t)rows;
+      seen[1] = (uint32_t)(rows >> 32);
+    }
+    pf_softmax_window(s, st, c, !full, seen, pb);
     pf_pv(kt + kPfTileBytes, lc, pb, st);
   };
   int v = 0;
