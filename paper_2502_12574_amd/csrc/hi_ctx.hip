@@ -406,54 +406,37 @@ hi_status write_back_packed(hi_ctx* c, int layer, int head, int nh, const void* 
 // k_new / v_new: [nh][len][128]
 hi_status write_back(hi_ctx* c, int layer, int head, int nh, const void* k_new, const void* v_new, int64_t past,
                      int64_t len) {
-  const bool resident = unit_resident(c, layer, head);
-  if (!resident && link_packed(c)) return write_back_packed(c, layer, head, nh, k_new, v_new, past, len);
-  const bool timed = !resident && (c->flags & HI_FLAG_TIME_KERNELS) != 0;
+  if (unit_resident(c, layer, head))
+    return launch_kv_append(c->sc, k_new, v_new, res_plane(c, layer, head, 0) + past * kRowBytes,
+                            res_plane(c, layer, head, 1) + past * kRowBytes, len, nh, 2 * c->prob.max_context * kRowBytes);
+  if (link_packed(c)) return write_back_packed(c, layer, head, nh, k_new, v_new, past, len);
+  const bool timed = (c->flags & HI_FLAG_TIME_KERNELS) != 0;
   TimedSpan sp;
-  if (!resident) {
-    // the new rows were produced by earlier work on the compute stream
-    HI_HIP(hipEventRecord(c->ev_entry, c->sc));
-    HI_HIP(hipStreamWaitEvent(c->sd, c->ev_entry, 0));
-    if (timed) HI_TRY(span_begin(c, 3, &sp, c->sd));
-  }
-  if (nh > 1) {
-    // the heads' K planes (and V planes) are two planes apart in the cache: one strided copy each
-    const hipMemcpyKind kind = resident ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost;
-    hipStream_t st = resident ? c->sc : c->sd;
-    if (resident || !(c->flags & HI_FLAG_SKIP_COPIES)) {
-      const size_t dpitch = (size_t)(2 * c->prob.max_context * kRowBytes), w = (size_t)(len * kRowBytes);
-      char* dk = resident ? res_plane(c, layer, head, 0) : cache_plane(c, layer, head, 0);
-      char* dv = resident ? res_plane(c, layer, head, 1) : cache_plane(c, layer, head, 1);
-      HI_HIP(hipMemcpy2DAsync(dk + past * kRowBytes, dpitch, k_new, w, w, (size_t)nh, kind, st));
-      HI_HIP(hipMemcpy2DAsync(dv + past * kRowBytes, dpitch, v_new, w, w, (size_t)nh, kind, st));
-      if (!resident) {
-        c->stats.bytes_d2h += 2 * len * kRowBytes * nh;
-        c->stats.n_d2h_copies += 2;
-      }
+  // the new rows were produced by earlier work on the compute stream
+  HI_HIP(hipEventRecord(c->ev_entry, c->sc));
+  HI_HIP(hipStreamWaitEvent(c->sd, c->ev_entry, 0));
+  if (timed) HI_TRY(span_begin(c, 3, &sp, c->sd));
+  if (!(c->flags & HI_FLAG_SKIP_COPIES)) {
+    char* dk = cache_plane(c, layer, head, 0) + past * kRowBytes;
+    char* dv = cache_plane(c, layer, head, 1) + past * kRowBytes;
+    const size_t w = (size_t)(len * kRowBytes);
+    if (nh > 1) {
+      // the heads' K planes (and V planes) are two planes apart in the cache: one strided copy each
+      const size_t dpitch = (size_t)(2 * c->prob.max_context * kRowBytes);
+      HI_HIP(hipMemcpy2DAsync(dk, dpitch, k_new, w, w, (size_t)nh, hipMemcpyDeviceToHost, c->sd));
+      HI_HIP(hipMemcpy2DAsync(dv, dpitch, v_new, w, w, (size_t)nh, hipMemcpyDeviceToHost, c->sd));
+    } else {
+      HI_HIP(hipMemcpyAsync(dk, k_new, w, hipMemcpyDeviceToHost, c->sd));
+      HI_HIP(hipMemcpyAsync(dv, v_new, w, hipMemcpyDeviceToHost, c->sd));
     }
+    c->stats.bytes_d2h += 2 * len * kRowBytes * nh;
+    c->stats.n_d2h_copies += 2;
   }
-  for (int j = 0; j < (nh > 1 ? 0 : 1); ++j) {
-    char* dk = (resident ? res_plane(c, layer, head + j, 0) : cache_plane(c, layer, head + j, 0)) + past * kRowBytes;
-    char* dv = (resident ? res_plane(c, layer, head + j, 1) : cache_plane(c, layer, head + j, 1)) + past * kRowBytes;
-    const char* sk = (const char*)k_new + j * len * kRowBytes;
-    const char* sv = (const char*)v_new + j * len * kRowBytes;
-    if (resident) {
-      HI_HIP(hipMemcpyAsync(dk, sk, len * kRowBytes, hipMemcpyDeviceToDevice, c->sc));
-      HI_HIP(hipMemcpyAsync(dv, sv, len * kRowBytes, hipMemcpyDeviceToDevice, c->sc));
-    } else if (!(c->flags & HI_FLAG_SKIP_COPIES)) {
-      HI_HIP(hipMemcpyAsync(dk, sk, len * kRowBytes, hipMemcpyDeviceToHost, c->sd));
-      HI_HIP(hipMemcpyAsync(dv, sv, len * kRowBytes, hipMemcpyDeviceToHost, c->sd));
-      c->stats.bytes_d2h += 2 * len * kRowBytes;
-      c->stats.n_d2h_copies += 2;
-    }
-  }
-  if (!resident) {
-    if (timed) HI_TRY(span_end(c, sp, c->sd));
-    for (int j = 0; j < nh; ++j) {
-      const int idx = layer * c->prob.n_kv_heads + head + j;
-      HI_HIP(hipEventRecord(c->ev_wb[idx], c->sd));
-      c->wb_valid[idx] = 1;
-    }
+  if (timed) HI_TRY(span_end(c, sp, c->sd));
+  for (int j = 0; j < nh; ++j) {
+    const int idx = layer * c->prob.n_kv_heads + head + j;
+    HI_HIP(hipEventRecord(c->ev_wb[idx], c->sd));
+    c->wb_valid[idx] = 1;
   }
   return HI_OK;
 }

@@ -231,6 +231,10 @@ hi_status launch_prefill(void* stream, const void* q, int G, int chunk_len, cons
                          const PrefillSegment& b, int first, int last, void* carry, void* out, int out_fp32,
                          int variant, const PrefillLaunch& unit, int n_heads, int64_t carry_bytes);
 
+// Rows [n_heads][rows][128] of K and of V to the heads' places in an HBM cache, head_stride bytes apart.
+hi_status launch_kv_append(void* stream, const void* k_new, const void* v_new, void* k_dst, void* v_dst, int64_t rows,
+                           int n_heads, int64_t head_stride);
+
 // The factor between a query-key dot product and the base-2 exponent of its softmax weight: log2(e) / sqrt(128) for
 // the q of Eq. 3, 1 for queries that already carry that factor (hi_problem.q_prescaled).
 inline float softmax_scale_log2(bool q_prescaled) { return q_prescaled ? 1.0f : 1.4426950408889634f / 11.313708498984761f; }
