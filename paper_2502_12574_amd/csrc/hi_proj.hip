@@ -400,8 +400,9 @@ __global__ __launch_bounds__(256, 1) void proj_gemm_kernel(ProjArgs p) {
 // ---- chunks too short to fill the chip with 256 x 256 tiles: the same contraction in 128 x 128 tiles, one per workgroup.
 // 600 tokens of Llama-3-8B are 72 (Q/K/V) and 48 (output) of the large tiles on 256 compute units, 240 and 160 of these.
 // A wavefront owns 64 x 64 (2 x 2 blocks of the 32x32x16 MFMA; its A rows are 32 wa .. +31 and 64 + 32 wa .. +31, so that
-// rotary pairs still meet in one lane).  Per 16 contraction elements it reads 4 KB of operands for 4 MFMAs: the tile is
-// bound by the LDS read rate.  One workgroup per compute unit has to cover the latency of its loads itself: four stages of
+// rotary pairs still meet in one lane).  A step of 64 contraction elements moves 32 KB into LDS and 64 KB out of it, 750
+// cycles at its 128 bytes a cycle, which is the 0.31 us measured per step (the 16 MFMAs of a wavefront take 512): a fifth
+// stage changed nothing.  One workgroup per compute unit has to cover the latency of its loads itself: four stages of
 // 32 KB, loads three steps (of 64 elements) ahead, operand reads two sub-steps ahead.  The order of every sum is the large
 // tile's, so the results are the same bits.  Measured (hidden size 4096, 32 + 16 heads, weights of 6 layers in turn;
 // large tile -> small): Q/K/V with its table at 64 / 600 / 1000 / 2000 tokens 90 -> 33, 97 -> 40, 102 -> 69, 110 -> 108 us,
