@@ -928,15 +928,14 @@ extern "C" hi_status hi_decode_group_ragged(hi_ctx* c, int32_t layer, int32_t kv
   const int G = c->prob.gqa_group;
   const int64_t part_stride = decode_part_head_stride(c->prob.max_context, c->slice_tokens, c->plan.n_split_decode, G);
   const int64_t part_cap = part_stride / (G * kPartialFloats);
-  int n_split = c->plan.n_split_decode / n_heads > 0 ? c->plan.n_split_decode / n_heads : 1;
-  const int64_t need = ceil_div(longest, 64);
-  if (need < n_split) n_split = (int)need;
+  DecodeLens lens = {};
+  for (int j = 0; j < n_heads; ++j) lens.n[j] = (uint32_t)past_lens[j];
+  int n_split;           // partitions of the longest head
+  const int n_wgs = decode_cut(lens, n_heads, c->plan.n_split_decode, &n_split);
   if (n_split > part_cap) { set_last_error("decode: the partial workspace cannot hold %d partitions", n_split); return HI_ERR_UNSUPPORTED; }
   return guarded(c, [&]() -> hi_status {
     c->enqueuing = true;
     if (c->flags & HI_FLAG_SKIP_KERNELS) { set_last_error("a ragged call has no copies to time"); return HI_ERR_UNSUPPORTED; }
-    DecodeLens lens = {};
-    for (int j = 0; j < n_heads; ++j) lens.n[j] = past_lens[j];
     float* partials = (float*)(c->ws + c->plan.ws_partials_offset);
     const int64_t plane2 = 2 * c->prob.max_context * kRowBytes;
     const bool timed = (c->flags & HI_FLAG_TIME_KERNELS) != 0;
@@ -948,7 +947,7 @@ extern "C" hi_status hi_decode_group_ragged(hi_ctx* c, int32_t layer, int32_t kv
       TimedSpan sp;
       if (timed) HI_TRY(span_begin(c, 1, &sp));
       HI_TRY(launch_decode_partial(c->sc, q_dev, G, rk, rv, longest, n_split, partials, 0, q_pre(c), n_heads, plane2, part_stride,
-                                   -1, &lens, fused ? &tail : nullptr));
+                                   -1, &lens, fused ? &tail : nullptr, n_wgs));
       if (timed) HI_TRY(span_end(c, sp));
       c->stats.n_decode_kernels += 1;
     }

@@ -53,10 +53,9 @@ __device__ __forceinline__ float2 load_shared2(const float* p) {      // 8-byte 
 // What decode_combine_kernel does, for all G query heads of one KV head, by the workgroup that finished its partial last.
 // Bound by the latency of its loads (the partials come from beyond the L2), so all of them are asked for at once: that is
 // why a launch has to have few partitions for it.  lds: 2 * 8 * kTailMaxParts floats.
-__device__ __forceinline__ void decode_tail(const uint16_t* q, int G, const float* part, int n_part, const DecodeTail& tl,
+__device__ __forceinline__ void decode_tail(int kv, const uint16_t* q, int G, const float* part, int n_part, const DecodeTail& tl,
                                             int64_t append_off, float c, float* lds) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int kv = blockIdx.y;
   const uint16_t* k_new = (const uint16_t*)tl.k_new + kv * kHeadDim;
   const uint16_t* v_new = (const uint16_t*)tl.v_new + kv * kHeadDim;
   float* w = lds;                                  // [n_part][G] maxima, then weights, of the partials
@@ -117,7 +116,7 @@ __device__ __forceinline__ void decode_tail(const uint16_t* q, int G, const floa
 }
 
 // Lens = DecodeLens: the heads of the launch have their own numbers of rows (sequences of different lengths served as
-// more KV heads); a head with fewer 16-row blocks than the grid has wavefronts leaves neutral partials.
+// more KV heads), and partitions in proportion or the same number each (see decode_cut).
 // TAIL: this launch writes all partials of its heads, few enough of them (kTailMaxParts) for one workgroup to combine: the
 // workgroup of a head that finishes last does so, and no combine launch follows.
 template <class Lens, bool TAIL>
@@ -127,12 +126,35 @@ __global__ __launch_bounds__(256) void decode_partial_kernel(const uint16_t* __r
                                                              float c, int64_t kv_head_stride,
                                                              int64_t part_head_stride, int64_t skip_row,
                                                              DecodeTail tail, Lens lens) {
-  // group launches: blockIdx.y is the head
-  if constexpr (kRagged<Lens>) n = lens.n[blockIdx.y];
-  q += (int64_t)blockIdx.y * G * kHeadDim;
-  k += blockIdx.y * kv_head_stride;
-  v += blockIdx.y * kv_head_stride;
-  partials += blockIdx.y * part_head_stride;
+  // group launches: blockIdx.y is the head; partitions in proportion (rows_per_wg > 0) lie one head after the other along x,
+  // so that the hardware deals the workgroups evenly to the XCDs
+  int head_i = blockIdx.y, part = blockIdx.x, n_part = gridDim.x;
+  if constexpr (kRagged<Lens>) {
+   if (lens.rows_per_wg > 0) {
+    // The head of this workgroup: eight by eight (63 comparisons in a row were 1 us of scalar instructions).  The cache lines of
+    // all that is looked up later are asked for at once, so that the later look-ups do not wait for the argument memory again.
+    static_assert(kDecodeMaxRagged == 64, "eight groups of eight");
+    uint32_t lines = lens.first[0] ^ lens.first[32];
+#pragma unroll
+    for (int j = 0; j < kDecodeMaxRagged; j += 16) lines ^= lens.n[j];
+    asm volatile("" : : "s"(lines));
+    int oct = 0;
+#pragma unroll
+    for (int j = 1; j < 8; ++j) oct += blockIdx.x >= lens.first[8 * j] ? 1 : 0;
+    oct = __builtin_amdgcn_readfirstlane(oct);
+    head_i = 8 * oct;
+#pragma unroll
+    for (int j = 1; j < 8; ++j) head_i += blockIdx.x >= lens.first[8 * oct + j] ? 1 : 0;
+    head_i = __builtin_amdgcn_readfirstlane(head_i);
+    part = (int)blockIdx.x - lens.first[head_i];
+    n_part = decode_parts(lens.n[head_i], lens.rows_per_wg);
+   }
+   n = lens.n[head_i];
+  }
+  q += (int64_t)head_i * G * kHeadDim;
+  k += head_i * kv_head_stride;
+  v += head_i * kv_head_stride;
+  partials += head_i * part_head_stride;
   extern __shared__ __attribute__((aligned(1024))) char lds_raw[];
   lds_char* lds = (lds_char*)lds_raw;
   const int lane = lane_id();
@@ -145,8 +167,8 @@ __global__ __launch_bounds__(256) void decode_partial_kernel(const uint16_t* __r
   // 16-row blocks are dealt round-robin to the wavefronts of the grid, so at any moment the whole chip reads one
   // compact window of the K and V streams (friendlier to HBM pages and TLBs than one far-apart range per wave)
   const int64_t n_blocks = (n + kDecBlockRows - 1) / kDecBlockRows;
-  const int64_t n_waves = (int64_t)gridDim.x * 4;
-  const int64_t wid = (int64_t)blockIdx.x * 4 + wave;
+  const int64_t n_waves = (int64_t)n_part * 4;
+  const int64_t wid = (int64_t)part * 4 + wave;
   const int64_t cnt = wid < n_blocks ? (n_blocks - wid + n_waves - 1) / n_waves : 0;   // blocks of this wave
   const int64_t skip_blk = skip_row >= 0 ? skip_row / kDecBlockRows : -1;
 
@@ -258,7 +280,7 @@ __global__ __launch_bounds__(256) void decode_partial_kernel(const uint16_t* __r
     mine[head * kPartialFloats + kHeadDim + 1] = l;
   }
   __syncthreads();
-  float* dst = partials + (int64_t)(part0 + blockIdx.x) * G * kPartialFloats;
+  float* dst = partials + (int64_t)(part0 + part) * G * kPartialFloats;
   for (int idx = threadIdx.x; idx < G * kHeadDim; idx += blockDim.x) {
     const int h = idx >> 7, dim = idx & 127;
     float mw[4], M = kNegBig;
@@ -290,18 +312,18 @@ __global__ __launch_bounds__(256) void decode_partial_kernel(const uint16_t* __r
     __syncthreads();
     int* flag = (int*)lds_raw;
     if (threadIdx.x == 0) {
-      const int before = __hip_atomic_fetch_add(tail.counters + blockIdx.y, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      const int last = before == (int)gridDim.x - 1;
-      if (last) __hip_atomic_store(tail.counters + blockIdx.y, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const int before = __hip_atomic_fetch_add(tail.counters + head_i, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const int last = before == n_part - 1;
+      if (last) __hip_atomic_store(tail.counters + head_i, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       *flag = last;
     }
     __syncthreads();
     const bool last = *flag != 0;
     __syncthreads();
     if (!last) return;
-    int64_t off = blockIdx.y * tail.append_head_stride;
+    int64_t off = head_i * tail.append_head_stride;
     if constexpr (kRagged<Lens>) off += n * kRowBytes;      // (k_append / v_append point at row 0 of the first head)
-    decode_tail(q, G, partials, (int)gridDim.x, tail, off, c, (float*)lds_raw);
+    decode_tail(head_i, q, G, partials, n_part, tail, off, c, (float*)lds_raw);
   }
 }
 
@@ -322,6 +344,8 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(const uint16_t* __r
                                                              int64_t part_head_stride, int64_t append_head_stride,
                                                              Lens lens) {
   // group launches: blockIdx.z is the head
+  if constexpr (kRagged<Lens>)
+    if (lens.rows_per_wg > 0 && n_part > 0) n_part = decode_parts(lens.n[blockIdx.z], lens.rows_per_wg);
   q += (int64_t)blockIdx.z * G * kHeadDim;
   k_new += blockIdx.z * kHeadDim;
   v_new += blockIdx.z * kHeadDim;
@@ -330,7 +354,7 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(const uint16_t* __r
   if (k_append != nullptr) {
     // (ragged: k_append / v_append point at row 0 of the first head; each head appends at its own length)
     int64_t row_off = 0;
-    if constexpr (kRagged<Lens>) row_off = lens.n[blockIdx.z] * kRowBytes;
+    if constexpr (kRagged<Lens>) row_off = (int64_t)lens.n[blockIdx.z] * kRowBytes;
     k_append = (uint16_t*)((char*)k_append + blockIdx.z * append_head_stride + row_off);
     v_append = (uint16_t*)((char*)v_append + blockIdx.z * append_head_stride + row_off);
   }
@@ -426,8 +450,8 @@ void tail_counters_give(int slot, void* busy_until) {
 hi_status launch_decode_partial(void* stream, const void* q, int G, const void* k, const void* v, int64_t n,
                                 int n_split, void* partials, int part0, bool q_prescaled, int n_heads,
                                 int64_t kv_head_stride, int64_t part_head_stride, int64_t skip_row,
-                                const DecodeLens* lens, const DecodeTail* tail) {
-  if (n <= 0 || n_split <= 0 || n_heads < 1 || (lens && n_heads > kDecodeMaxRagged)) { set_last_error("decode partial: empty launch"); return HI_ERR_ARG; }
+                                const DecodeLens* lens, const DecodeTail* tail, int n_wgs) {
+  if (n <= 0 || n_split <= 0 || n_heads < 1 || (lens && (n_heads > kDecodeMaxRagged || (lens->rows_per_wg > 0 && n_wgs < n_heads)))) { set_last_error("decode partial: empty launch"); return HI_ERR_ARG; }
   if (tail && (part0 != 0 || n_split > kTailMaxParts || n_heads > kTailMaxHeads || !tail->counters)) { set_last_error("decode partial: too many partials to combine in the launch"); return HI_ERR_ARG; }
   static std::once_flag attr_once;      // contexts on different host threads may get here together
   static hipError_t attr_err = hipSuccess;
@@ -439,7 +463,7 @@ hi_status launch_decode_partial(void* stream, const void* q, int G, const void* 
   });
   if (attr_err != hipSuccess) { set_last_error("hipFuncSetAttribute: %s", hipGetErrorString(attr_err)); return HI_ERR_HIP; }
   auto go = [&](auto kernel, auto lens_arg) {
-    hipLaunchKernelGGL(kernel, dim3(n_split, n_heads), dim3(256), kDecLdsBytes, (hipStream_t)stream, (const uint16_t*)q, G,
+    hipLaunchKernelGGL(kernel, lens && lens->rows_per_wg > 0 ? dim3(n_wgs) : dim3(n_split, n_heads), dim3(256), kDecLdsBytes, (hipStream_t)stream, (const uint16_t*)q, G,
                        (const char*)k, (const char*)v, n, (float*)partials, part0, softmax_scale_log2(q_prescaled),
                        kv_head_stride, part_head_stride, skip_row, tail ? *tail : DecodeTail(), lens_arg);
   };

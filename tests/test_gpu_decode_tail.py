@@ -113,3 +113,25 @@ def test_more_contexts_than_counter_slots():
             ss.close()
     for out in outs:                    # three partials, summed in the same order by either way up to fp32 rounding
         assert (out - outs[0]).abs().max() <= 1e-5
+
+
+@pytest.mark.parametrize("lens", [[5000, 3, 0, 64, 65, 1290], [70000, 1, 1, 20000], [2000] * 20, [15, 16, 17, 0, 1, 900, 4000, 129]])
+def test_partitions_follow_the_lengths(lens):
+    """A batch whose lengths are far apart: every head gets partitions in proportion, the shortest ones a single one."""
+    G, H, cap, seed = 2, len(lens), max(lens) + 1, 53200
+    with Session(1, H, G, cap, 1, mode=hb.HI_MODE_RESIDENT, out_fp32=1) as ss:
+        view = ss.cache_view()
+        gen = torch.Generator(device=DEV).manual_seed(seed)
+        view.copy_(torch.randn(view.shape, device=DEV, generator=gen, dtype=torch.bfloat16))
+        q = torch.randn(H, G, 128, device=DEV, generator=gen).to(torch.bfloat16)
+        k, v = (torch.randn(H, 128, device=DEV, generator=gen).to(torch.bfloat16) for _ in range(2))
+        out = torch.full((H, G, 128), float("nan"), device=DEV)
+        ss.s_compute.wait_stream(torch.cuda.current_stream())
+        for _ in range(2):
+            hb.hi_decode_group_ragged(ss.ctx, 0, 0, H, q, k, v, lens, out)
+        ss.sync()
+        for h, n in enumerate(lens):
+            K, V = synth.to_f64(view[0, h, 0, :n + 1]), synth.to_f64(view[0, h, 1, :n + 1])
+            assert np.array_equal(K[n], synth.to_f64(k[h])) and np.array_equal(V[n], synth.to_f64(v[h]))
+            ref = oa.attn_rows(synth.to_f64(q[h]), K, V, [n] * G)
+            _check(out[h].cpu().double().numpy(), ref, (h, n))
