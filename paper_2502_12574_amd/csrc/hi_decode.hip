@@ -52,12 +52,11 @@ __device__ __forceinline__ float2 load_shared2(const float* p) {      // 8-byte 
 
 // What decode_combine_kernel does, for all G query heads of one KV head, by the workgroup that finished its partial last.
 // Bound by the latency of its loads (the partials come from beyond the L2), so all of them are asked for at once: that is
-// why a launch has to have few partitions for it.  lds: 2 * 8 * kTailMaxParts floats.
+// why a launch has to have few partitions for it.  lds: 2 * 8 * kTailMaxParts floats; k2, v2: the lane's two dims of the
+// token's own K and V row.
 __device__ __forceinline__ void decode_tail(int kv, const uint16_t* q, int G, const float* part, int n_part, const DecodeTail& tl,
-                                            int64_t append_off, float c, float* lds) {
+                                            int64_t append_off, float c, float* lds, uint32_t k2, uint32_t v2) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const uint16_t* k_new = (const uint16_t*)tl.k_new + kv * kHeadDim;
-  const uint16_t* v_new = (const uint16_t*)tl.v_new + kv * kHeadDim;
   float* w = lds;                                  // [n_part][G] maxima, then weights, of the partials
   float* sum = lds + 8 * kTailMaxParts;            // [n_part][G] sums
   const int64_t part_pitch = (int64_t)G * kPartialFloats;
@@ -74,7 +73,6 @@ __device__ __forceinline__ void decode_tail(int kv, const uint16_t* q, int G, co
         o[h][p] = load_shared2(part + (p < n_part ? p : n_part - 1) * part_pitch + g * kPartialFloats + dim);
     }
   }
-  const uint32_t k2 = *(const uint32_t*)(k_new + dim), v2 = *(const uint32_t*)(v_new + dim);
   if (tl.k_append != nullptr && wave == 0) {
     *(uint32_t*)((char*)tl.k_append + append_off + 2 * dim) = k2;
     *(uint32_t*)((char*)tl.v_append + append_off + 2 * dim) = v2;
@@ -185,6 +183,13 @@ __global__ __launch_bounds__(256) void decode_partial_kernel(const uint16_t* __r
     if (head < G) raw = *(const uint4*)(q + head * kHeadDim + 32 * kk + 8 * g4);
     qf[kk] = __builtin_bit_cast(bf16x8, raw);
   }
+  // the token's own row, for the tail: asked for now, so that a cold first touch is not a latency of its own there
+  uint32_t k2 = 0, v2 = 0;
+  if constexpr (TAIL) {
+    k2 = *(const uint32_t*)((const uint16_t*)tail.k_new + head_i * kHeadDim + 2 * lane);
+    v2 = *(const uint32_t*)((const uint16_t*)tail.v_new + head_i * kHeadDim + 2 * lane);
+  }
+  asm volatile("" : "+v"(k2), "+v"(v2));
   // make the compiler wait for these loads here, not inside the loop (a vmcnt(0) there would drain the ring)
 #pragma unroll
   for (int kk = 0; kk < 4; ++kk) asm volatile("" : "+v"(qf[kk]));
@@ -323,7 +328,7 @@ __global__ __launch_bounds__(256) void decode_partial_kernel(const uint16_t* __r
     if (!last) return;
     int64_t off = head_i * tail.append_head_stride;
     if constexpr (kRagged<Lens>) off += n * kRowBytes;      // (k_append / v_append point at row 0 of the first head)
-    decode_tail(head_i, q, G, partials, n_part, tail, off, c, (float*)lds_raw);
+    decode_tail(head_i, q, G, partials, n_part, tail, off, c, (float*)lds_raw, k2, v2);
   }
 }
 
@@ -416,7 +421,7 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(const uint16_t* __r
 
 // Counters of the contexts that exist: a slot each of a built-in array, all zero whenever no launch of their context is
 // in flight.  A slot that is given back keeps the event of its context's last unit until that has finished.
-constexpr int kTailSlots = 64;
+constexpr int kTailSlots = 64, kTailDevices = 64;
 static __device__ int tail_counters[kTailSlots * kTailMaxHeads];
 namespace {
 std::mutex tail_mu;
@@ -424,9 +429,16 @@ struct TailSlot { bool taken; hipEvent_t busy_until; } tail_slots[kTailSlots];
 }  // namespace
 
 int* tail_counters_take(int* slot) {
-  void* base = nullptr;
-  if (hipGetSymbolAddress(&base, HIP_SYMBOL(tail_counters)) != hipSuccess || !base) { (void)hipGetLastError(); return nullptr; }
+  static void* address[kTailDevices] = {};            // looking it up takes tens of microseconds: once per device
+  int dev = -1;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kTailDevices) { (void)hipGetLastError(); return nullptr; }
   std::lock_guard<std::mutex> lock(tail_mu);
+  void*& base = address[dev];
+  if (!base && (hipGetSymbolAddress(&base, HIP_SYMBOL(tail_counters)) != hipSuccess || !base)) {
+    (void)hipGetLastError();
+    base = nullptr;
+    return nullptr;
+  }
   for (int i = 0; i < kTailSlots; ++i) {
     if (tail_slots[i].taken) continue;
     if (tail_slots[i].busy_until) {
