@@ -37,9 +37,9 @@ enum { HI_REGIME_COMPUTE = 0, HI_REGIME_LINK = 1, HI_REGIME_HBM = 2 };
 /* debug/measurement switches for hi_ctx_set_flags: skip the attention kernels (transfer-only timing) or
  * skip the H2D/D2H copies (compute-only timing on stale staging contents) - results are meaningless then;
  * time the attention kernels with HIP events; force a prefill kernel variant (by default the library picks by
- * chunk length and group size between DEEP: 8 wavefronts per workgroup alternating matrix and softmax phases,
- * split over the K/V rows when the chunk alone would not fill the chip, and NARROW: 4 wavefronts, for very short
- * chunks); with the DEEP kernel, PAIRED / UNPAIRED force or forbid the balanced partition of the causal triangle
+ * what the unit sweeps between DEEP: 8 wavefronts per workgroup alternating matrix and softmax phases,
+ * split over the K/V rows when the chunk alone would not fill the chip, and NARROW: 4 wavefronts, for short
+ * units); with the DEEP kernel, PAIRED / UNPAIRED force or forbid the balanced partition of the causal triangle
  * (deep and shallow blocks of query positions share their tiles), which the library otherwise picks when it saves
  * the deepest workgroups at least a few tiles. Do not change the variant between the calls of one (chunk, head) unit. */
 enum { HI_FLAG_SKIP_KERNELS = 1, HI_FLAG_SKIP_COPIES = 2, HI_FLAG_TIME_KERNELS = 4, HI_FLAG_PREFILL_NARROW = 8,
@@ -47,7 +47,7 @@ enum { HI_FLAG_SKIP_KERNELS = 1, HI_FLAG_SKIP_COPIES = 2, HI_FLAG_TIME_KERNELS =
        HI_FLAG_PREFILL_MFMA32 = 256 /* the DEEP kernel in its 32x32x16 MFMA form (by default it uses 16x16x32) */,
        HI_FLAG_PREFILL_8WAVE = 512, HI_FLAG_PREFILL_WIDE = 1024 /* the 16x16x32 DEEP kernel has two forms: 8 wavefronts of
           32 query rows, and 4 wavefronts of 64 (half the LDS operand reads per MFMA, but slow first and last tiles); by
-          default each launch takes the second when it sweeps at least 640 K/V tiles; these flags force one (their
+          default each launch takes the second when its workgroups sweep at least 640 K/V tiles each; these flags force one (their
           state images are the same, so a unit's launches may mix them) */,
        HI_FLAG_PREFILL_SINGLE_SLICES = 2048 /* one attention launch per staging slice, also where the library would hand
           two short slices to one launch (measurement) */,

@@ -299,7 +299,7 @@ int pf_variant(const hi_ctx* c) {
 
 // A decode launch of np partitions per head combines them itself where it has few of them (a short history) and the
 // context has counters for it.  What that saves is the second launch, 2.5 us of host time, which is what bounds a token at
-// short contexts (32 layers of 8 heads at 1K: 14.4 us a layer against 16.4); on the GPU it is even (9.0 us against 5.6 + 3.9).
+// short contexts (32 layers of 8 heads at 1K: 13.6 us a layer against 16.6); on the GPU it is 8.4 us against 5.6 + 3.9.
 // With 32 partitions the last workgroup alone takes 6.4 us where the combine kernel, spread over the chip, takes 4.
 bool can_tail(const hi_ctx* c, int np, int nh) { return c->counters && np <= kTailMaxParts && nh <= kTailMaxHeads; }
 

@@ -25,8 +25,9 @@ inline int prefill_grid_y(int G) { return G > 4 ? G / 4 : 1; }
 
 // The 8-wave prefill kernel covers 2 * strip positions per workgroup.  When a chunk gives it fewer workgroups than
 // would fill the chip, `split` workgroups share each block of positions and divide the tiles of every launch
-// between them (their states are merged after the unit's last launch).  The launcher picks that kernel when
-// workgroups * split reaches kPrefillDeepMinWorkgroups, the 4-wave kernel otherwise.
+// between them (their states are merged after the unit's last launch).  prefill_split and prefill_launch_shape are the
+// choice by the chunk alone, which sizes the plan's workspace: the 8-wave kernel when workgroups * split reaches
+// kPrefillDeepMinWorkgroups, the 4-wave kernel otherwise.  What a unit runs is prefill_unit_shape's choice.
 constexpr int kPrefillFillWorkgroups = 192;
 constexpr int kPrefillDeepMinWorkgroups = 128;
 constexpr int kPrefillMaxSplit = 8;
@@ -41,7 +42,7 @@ inline int prefill_split(int G, int64_t chunk_len, int n_heads = 1) {
 // shallow blocks in every last launch that has two blocks, + 8: never pair (measurement); + 16: the 8-wave kernel in
 // its 32x32x16 MFMA form instead of the 16x16x32 one; + 64 / + 128: the 16x16x32 kernel with 8 wavefronts of 32 query rows
 // (prefill_kernel_deep16) / with 4 wavefronts of 64 (prefill_kernel_wide) whatever the launch's length (by default the
-// second for launches of kPrefillWideMinTiles tiles and more).
+// second for launches whose workgroups sweep kPrefillWideMinTiles tiles and more).
 constexpr int kPrefillWideMinTiles = 640;
 constexpr int kPdLanes = 512;                   // lanes of an 8-wave workgroup
 constexpr int kPrefillPairMinTiles = 4;         // pair when it saves the deepest workgroup at least this many tiles
