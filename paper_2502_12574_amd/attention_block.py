@@ -49,6 +49,8 @@ class AttentionBlock:
         slicing views for every head group: head-major q and output are [Hkv][G][n][128], k and v [Hkv][n][128]."""
         ss, n = self.ss, x.shape[0]
         assert ss.out_dtype == torch.bfloat16, "the output projection reads bf16 attention outputs"
+        if n > ss.problem.chunk:                 # before anything is enqueued: the projection would write past these buffers
+            raise RuntimeError(f"{n} rows in one call: the block's buffers hold the Session's chunk of {ss.problem.chunk}")
         k, v = self.kv[self.turn]
         q, k, v, o = self.q.data_ptr(), k.data_ptr(), v.data_ptr(), self.attn.data_ptr()
         s, row = ss.s_compute, n * 256                       # bytes of one head's rows of this call
