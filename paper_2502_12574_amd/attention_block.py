@@ -51,29 +51,33 @@ class AttentionBlock:
         assert ss.out_dtype == torch.bfloat16, "the output projection reads bf16 attention outputs"
         if n > ss.problem.chunk:                 # before anything is enqueued: the projection would write past these buffers
             raise RuntimeError(f"{n} rows in one call: the block's buffers hold the Session's chunk of {ss.problem.chunk}")
-        k, v = self.kv[self.turn]
-        q, k, v, o = self.q.data_ptr(), k.data_ptr(), v.data_ptr(), self.attn.data_ptr()
-        s, row = ss.s_compute, n * 256                       # bytes of one head's rows of this call
-        offload = ss.mode == hb.HI_MODE_OFFLOAD              # (resident heads are appended on the compute stream itself)
-        if offload and self.kv_done[self.turn] is not None:
-            s.wait_event(self.kv_done[self.turn])
-        # the softmax scale rides on the queries when the Session's attention calls expect it there
-        hb.hi_qkv_rope(s, x, self.w_qkv, self.D, self.Hq, self.Hkv, n, past_len, self.theta, 0, q, k, v, self.ws,
-                       q_scale=hb.HI_Q_PRESCALE if ss.problem.q_prescaled else 1.0)
-        for i, (h0, nh) in enumerate(self.calls):
-            hint = (self.layer, self.calls[i + 1][0], self.calls[i + 1][1], past_len) if i + 1 < len(self.calls) else nxt
-            nl, nhead, nheads, npast = hint if hint is not None else (-1, 0, 1, 0)
-            at, at_q = h0 * row, h0 * self.G * row
-            if n == 1:
-                hb.hi_decode_group(ss.ctx, self.layer, h0, nh, q + at_q, k + at, v + at, past_len, o + at_q, nl, nhead,
-                                   nheads, npast)
-            else:
-                hb.hi_prefill_group(ss.ctx, self.layer, h0, nh, q + at_q, k + at, v + at, past_len, n, o + at_q, nl, nhead,
-                                    nheads, npast)
-        hb.hi_out_proj(s, o, self.w_o, self.Hq, self.D, n, 0, y)
-        if offload:
-            if self.kv_done[self.turn] is None:
-                self.kv_done[self.turn] = torch.cuda.Event()
-            self.kv_done[self.turn].record(ss.s_d2h)
+        # a launch goes to a stream of the current device: make it the Session's, whatever the caller's is
+        with torch.cuda.device(ss.s_compute.device_index):
+            k, v = self.kv[self.turn]
+            q, k, v, o = self.q.data_ptr(), k.data_ptr(), v.data_ptr(), self.attn.data_ptr()
+            s, row = ss.s_compute, n * 256                       # bytes of one head's rows of this call
+            offload = ss.mode == hb.HI_MODE_OFFLOAD              # (resident heads are appended on the compute stream itself)
+            if offload and self.kv_done[self.turn] is not None:
+                s.wait_event(self.kv_done[self.turn])
+            # the softmax scale rides on the queries when the Session's attention calls expect it there
+            hb.hi_qkv_rope(s, x, self.w_qkv, self.D, self.Hq, self.Hkv, n, past_len, self.theta, 0, q, k, v, self.ws,
+                           q_scale=hb.HI_Q_PRESCALE if ss.problem.q_prescaled else 1.0)
+            for i, (h0, nh) in enumerate(self.calls):
+                hint = nxt
+                if i + 1 < len(self.calls):
+                    hint = (self.layer, self.calls[i + 1][0], self.calls[i + 1][1], past_len)
+                nl, nhead, nheads, npast = hint if hint is not None else (-1, 0, 1, 0)
+                at, at_q = h0 * row, h0 * self.G * row
+                if n == 1:
+                    hb.hi_decode_group(ss.ctx, self.layer, h0, nh, q + at_q, k + at, v + at, past_len, o + at_q, nl,
+                                       nhead, nheads, npast)
+                else:
+                    hb.hi_prefill_group(ss.ctx, self.layer, h0, nh, q + at_q, k + at, v + at, past_len, n, o + at_q, nl,
+                                        nhead, nheads, npast)
+            hb.hi_out_proj(s, o, self.w_o, self.Hq, self.D, n, 0, y)
+            if offload:
+                if self.kv_done[self.turn] is None:
+                    self.kv_done[self.turn] = torch.cuda.Event()
+                self.kv_done[self.turn].record(ss.s_d2h)
         self.turn ^= 1
         return y

@@ -11,16 +11,33 @@ HKV, G, D, CHUNK = 2, 2, 256, 64
 
 
 class _Stream:
+    device_index = 3
+
     def wait_event(self, ev):
         pass
+
+
+class _Device:
+    """Stands for torch.cuda.device: the device that is current, 0 outside."""
+    current = 0
+
+    def __init__(self, index):
+        self.index = index
+
+    def __enter__(self):
+        self.before, _Device.current = _Device.current, self.index
+
+    def __exit__(self, *exc):
+        _Device.current = self.before
 
 
 @pytest.fixture
 def block(monkeypatch):
     """A block over CPU buffers, and the list of library calls its forward makes."""
     calls = []
+    monkeypatch.setattr(torch.cuda, "device", _Device)
     for name in ("hi_qkv_rope", "hi_prefill_group", "hi_decode_group", "hi_out_proj"):
-        monkeypatch.setattr(hb, name, lambda *a, _name=name, **kw: calls.append((_name, a)))
+        monkeypatch.setattr(hb, name, lambda *a, _name=name, **kw: calls.append((_name, a, _Device.current)))
     ss = SimpleNamespace(problem=hb.make_problem(1, HKV, G, 256, CHUNK), plan=SimpleNamespace(heads_per_group=HKV),
                          device=torch.device("cpu"), out_dtype=torch.bfloat16, mode=hb.HI_MODE_RESIDENT, ctx=None,
                          s_compute=_Stream(), s_d2h=_Stream())
@@ -54,3 +71,11 @@ def test_up_to_the_chunk_every_address_range_lies_in_its_buffer(block, n):
     for addr, heads in [(qkv[10], HKV * G), (qkv[11], HKV), (qkv[12], HKV), (attn[4], HKV * G), (attn[5], HKV), (attn[6], HKV),
                         (calls[2][1][1], HKV * G)]:
         assert heads * n * 256 <= room[addr]
+
+
+@pytest.mark.parametrize("n", [1, 5])
+def test_the_calls_run_on_the_sessions_device(block, n):
+    """The caller may have another device current; a launch into a stream of a device that is not current fails."""
+    blk, calls = block
+    blk.forward(_x(n), 0, _x(n))
+    assert len(calls) == 3 and {c[2] for c in calls} == {_Stream.device_index} and _Device.current == 0
