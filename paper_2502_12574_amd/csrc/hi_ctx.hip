@@ -792,9 +792,9 @@ static hi_status decode_impl(hi_ctx* c, int32_t layer, int32_t kv_head, int32_t 
     const DecodeTail tail{k_new_dev, v_new_dev, out_dev, c->prob.out_fp32, k_append, v_append, kv_stride, c->counters};
     const bool fused = rows > 0 && can_tail(c, np, nh);
     if (rows > 0) HI_TRY(partial(k, v, rows, np, 0, kv_stride, skip_row, fused ? &tail : nullptr));
-    if (!fused)
-      HI_TRY(launch_decode_combine(c->sc, q_dev, G, k_new_dev, v_new_dev, partials, np, out_dev, c->prob.out_fp32, k_append,
-                                   v_append, q_pre(c), nh, part_stride, kv_stride));
+    if (fused) return HI_OK;
+    HI_TRY(launch_decode_combine(c->sc, q_dev, G, k_new_dev, v_new_dev, partials, np, out_dev, c->prob.out_fp32, k_append,
+                                 v_append, q_pre(c), nh, part_stride, kv_stride));
     c->stats.n_combine_kernels += 1;
     return HI_OK;
   };
@@ -951,9 +951,9 @@ extern "C" hi_status hi_decode_group_ragged(hi_ctx* c, int32_t layer, int32_t kv
       if (timed) HI_TRY(span_end(c, sp));
       c->stats.n_decode_kernels += 1;
     }
-    if (!fused)
-      HI_TRY(launch_decode_combine(c->sc, q_dev, G, k_new_dev, v_new_dev, partials, longest > 0 ? n_split : 0, out_dev,
-                                   c->prob.out_fp32, rk, rv, q_pre(c), n_heads, part_stride, plane2, &lens));
+    if (fused) return HI_OK;
+    HI_TRY(launch_decode_combine(c->sc, q_dev, G, k_new_dev, v_new_dev, partials, longest > 0 ? n_split : 0, out_dev,
+                                 c->prob.out_fp32, rk, rv, q_pre(c), n_heads, part_stride, plane2, &lens));
     c->stats.n_combine_kernels += 1;
     return HI_OK;
   });
