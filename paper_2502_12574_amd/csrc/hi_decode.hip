@@ -69,7 +69,7 @@ __device__ __forceinline__ void decode_tail(int kv, const uint16_t* q, int G, co
     const int g = wave + 4 * h;
     if (g < G) {
 #pragma unroll
-      for (int p = 0; p < kTailMaxParts; ++p)      // (past the last partial: its values again, with weight 0)
+      for (int p = 0; p < kTailMaxParts; ++p)      // (past the last partial: its values again, not used)
         o[h][p] = load_shared2(part + (p < n_part ? p : n_part - 1) * part_pitch + g * kPartialFloats + dim);
     }
   }
@@ -102,8 +102,10 @@ __device__ __forceinline__ void decode_tail(int kv, const uint16_t* q, int G, co
 #pragma unroll
     for (int p = 0; p < kTailMaxParts; ++p) {
       const float x = __shfl(wp, p);
-      acc.x = __builtin_fmaf(x, o[h][p].x, acc.x);
-      acc.y = __builtin_fmaf(x, o[h][p].y, acc.y);
+      if (p < n_part) {                            // (not left to a weight of 0: a partial may be infinite)
+        acc.x = __builtin_fmaf(x, o[h][p].x, acc.x);
+        acc.y = __builtin_fmaf(x, o[h][p].y, acc.y);
+      }
     }
     acc.x *= inv;
     acc.y *= inv;

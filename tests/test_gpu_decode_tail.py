@@ -138,3 +138,31 @@ def test_partitions_follow_the_lengths(lens):
             assert np.array_equal(K[n], synth.to_f64(k[h])) and np.array_equal(V[n], synth.to_f64(v[h]))
             ref = oa.attn_rows(synth.to_f64(q[h]), K, V, [n] * G)
             _check(out[h].cpu().double().numpy(), ref, (h, n))
+
+
+def _integer_rows(H, G, cap, seed):
+    """A resident cache of small whole numbers and queries of zeros: every weight is 1 and every sum exact."""
+    gen = torch.Generator(device=DEV).manual_seed(seed)
+    rows = torch.randint(-8, 9, (1, H, 2, cap, 128), device=DEV, generator=gen).to(torch.bfloat16)
+    return rows, torch.zeros(H, G, 128, dtype=torch.bfloat16, device=DEV)
+
+
+@pytest.mark.parametrize("H,G,past", [(8, 4, 3), (8, 4, 130), (1, 8, 700), (2, 2, 1022), (2, 2, 1030)])
+def test_an_infinite_value_stays_infinite(H, G, past):
+    """An infinite channel of a visible V row makes that channel infinite and no other, whatever partition holds the row."""
+    rows, q = _integer_rows(H, G, past + 1, 53400)
+    # the first row of the last 16-row block (the last row itself also stands in for the rows behind the end, with weight 0)
+    at = (past - 2) // 16 * 16
+    rows[0, :, 1, at, 5] = float("inf")
+    rows[0, :, 1, at, 77] = float("-inf")
+    with Session(1, H, G, max(past + 1, 256), 1, mode=hb.HI_MODE_RESIDENT, out_fp32=1) as ss:
+        ss.cache_view()[:, :, :, :past] = rows[:, :, :, :past]
+        k, v = rows[0, :, 0, past].contiguous(), rows[0, :, 1, past].contiguous()
+        out = torch.full((H, G, 128), float("nan"), device=DEV)
+        ss.s_compute.wait_stream(torch.cuda.current_stream())
+        ss.decode_group(0, 0, H, q, k, v, past, out)
+        ss.sync()
+    want = (rows[0, :, 1].double().sum(dim=1) / (past + 1)).float()
+    assert torch.isinf(want).sum() == 2 * H
+    assert torch.equal(torch.isinf(out), torch.isinf(want)[:, None].expand(H, G, 128))
+    assert (out[:, :, 5] == float("inf")).all() and (out[:, :, 77] == float("-inf")).all() and not torch.isnan(out).any()
