@@ -97,7 +97,7 @@ __device__ __forceinline__ void decode_tail(int kv, const uint16_t* q, int G, co
     float l = lane < n_part ? wp * sum[lane * G + g] : 0.f;
     for (int off = 32; off > 0; off >>= 1) l += __shfl_xor(l, off);
     const float p_new = fast_exp2((d - mx) * c);
-    const float inv = 1.0f / (l + p_new);
+    const float total = l + p_new;
     float2 acc = make_float2(p_new * __uint_as_float(v2 << 16), p_new * __uint_as_float(v2 & 0xFFFF0000u));
 #pragma unroll
     for (int p = 0; p < kTailMaxParts; ++p) {
@@ -107,8 +107,8 @@ __device__ __forceinline__ void decode_tail(int kv, const uint16_t* q, int G, co
         acc.y = __builtin_fmaf(x, o[h][p].y, acc.y);
       }
     }
-    acc.x *= inv;
-    acc.y *= inv;
+    acc.x /= total;
+    acc.y /= total;
     const int64_t at = ((int64_t)kv * G + g) * kHeadDim + dim;
     if (tl.out_fp32) *(float2*)((float*)tl.out + at) = acc;
     else *(uint32_t*)((uint16_t*)tl.out + at) = (uint32_t)float_to_bf16_bits(acc.x) | ((uint32_t)float_to_bf16_bits(acc.y) << 16);

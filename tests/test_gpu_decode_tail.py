@@ -147,6 +147,28 @@ def _integer_rows(H, G, cap, seed):
     return rows, torch.zeros(H, G, 128, dtype=torch.bfloat16, device=DEV)
 
 
+# 1, 2, 3, 11, 16 partitions of a head (one launch), and 17 (two)
+@pytest.mark.parametrize("H,G,past", [(8, 4, 5), (8, 4, 101), (3, 8, 130), (2, 1, 700), (8, 4, 1022), (4, 2, 1030)])
+@pytest.mark.parametrize("ragged", [False, True])
+def test_quotients_are_rounded_once(H, G, past, ragged):
+    """Whole sums over a whole number of rows: the fp32 result is the correctly rounded quotient, by either way."""
+    rows, q = _integer_rows(H, G, past + 1, 53300)
+    with Session(1, H, G, max(past + 1, 256), 1, mode=hb.HI_MODE_RESIDENT, out_fp32=1) as ss:
+        ss.cache_view()[:, :, :, :past] = rows[:, :, :, :past]
+        k, v = rows[0, :, 0, past].contiguous(), rows[0, :, 1, past].contiguous()
+        out = torch.full((H, G, 128), float("nan"), device=DEV)
+        ss.s_compute.wait_stream(torch.cuda.current_stream())
+        if ragged:
+            hb.hi_decode_group_ragged(ss.ctx, 0, 0, H, q, k, v, [past] * H, out)
+        else:
+            ss.decode_group(0, 0, H, q, k, v, past, out)
+        ss.sync()
+        assert ss.stats().n_combine_kernels == (1 if -(-past // 64) > MAX_PARTS else 0)
+    # (53 bits are more than 2 * 24 + 2: rounding the double quotient to single is the one correct rounding)
+    want = (rows[0, :, 1].double().sum(dim=1) / (past + 1)).float()
+    assert torch.equal(out, want[:, None].expand(H, G, 128))
+
+
 @pytest.mark.parametrize("H,G,past", [(8, 4, 3), (8, 4, 130), (1, 8, 700), (2, 2, 1022), (2, 2, 1030)])
 def test_an_infinite_value_stays_infinite(H, G, past):
     """An infinite channel of a visible V row makes that channel infinite and no other, whatever partition holds the row."""
