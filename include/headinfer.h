@@ -185,12 +185,17 @@ hi_status hi_offload_plan(const hi_problem* problem, hi_plan* plan);
  *                  hi_problem.resident_heads > 0 its tail holds those heads' K/V: units of a resident head read
  *                  and append there, move nothing over the link and leave the host cache rows of that head
  *                  untouched; a head group must be all resident or all offloaded.
- *   hbm_workspace  DEVICE, plan.workspace_bytes.
+ *   hbm_workspace  DEVICE, plan.workspace_bytes.  Scratch of one unit at a time: a prefill unit may also use the room of
+ *                  the decode partials for its state images; nothing in it outlives a unit.
  *   stream_*       hipStream_t handles (as void*), all at default priority.  Kernels run on stream_compute,
  *                  host-to-device prefetches on stream_h2d, write-backs on stream_d2h.
  * With hi_problem.link_kv_bits = 4 the cache layout is [layer][kv_head][K|V][S_max][plan.link_row_bytes] bytes.
  * A context is used by one host thread at a time (its calls mutate the ring's bookkeeping without locks); different
- * contexts are independent.  Errors: HI_ERR_ARG, HI_ERR_NOT_PINNED, HI_ERR_UNSUPPORTED, HI_ERR_HIP.
+ * contexts are independent.  The only device memory the library has of its own (besides hi_qkv_rope_static's table) are
+ * counters for 64 contexts per process, which decode steps over short HBM-resident histories use instead of a second
+ * launch; a 65th context, and a step that is being captured into a graph, take the second launch.  A captured step of
+ * HBM-resident heads so holds no memory but the caller's, and its graph may be replayed after hi_ctx_destroy.
+ * Errors: HI_ERR_ARG, HI_ERR_NOT_PINNED, HI_ERR_UNSUPPORTED, HI_ERR_HIP.
  * kv_cache may be null when every layer's rows are given by hi_ctx_set_layer_cache before the layer is first used.
  */
 hi_status hi_ctx_create(const hi_problem* problem, const hi_plan* plan, int32_t mode, void* kv_cache,

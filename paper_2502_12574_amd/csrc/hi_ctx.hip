@@ -50,8 +50,10 @@ struct hi_ctx {
   bool enqueuing = false;    // the running call has passed its checks and started to enqueue
   char* staging = nullptr;
   char* ws = nullptr;
-  int* counters = nullptr;   // device, for decode launches that combine their own partials (may be null)
+  int* counters = nullptr;   // device, for decode launches that combine their own partials; taken by the first of them
   int counter_slot = -1;
+  bool counters_refused = false;     // (none were left)
+  bool capturing = false;    // the running call's compute stream is being captured into a graph
   hipStream_t sc = nullptr, sh = nullptr, sd = nullptr;
 
   int n_slots = 0;
@@ -81,7 +83,7 @@ struct hi_ctx {
   // bounded run-ahead of the calling thread: a call first waits until the unit `run_ahead` calls earlier has
   // finished on the compute stream (its successor's history is already being prefetched by then)
   int run_ahead = 2;
-  std::vector<hipEvent_t> ev_unit;             // ring of "unit finished" events
+  std::vector<hipEvent_t> ev_unit;             // ring of "unit finished" events, of units that were not captured
   int64_t n_units = 0;
 
   hi_stats stats;
@@ -285,6 +287,7 @@ hi_status pace_begin(hi_ctx* c) {
 }
 
 hi_status pace_end(hi_ctx* c) {
+  if (c->capturing) return HI_OK;         // (an event recorded into a graph marks nothing that can be waited for)
   HI_HIP(hipEventRecord(c->ev_unit[c->n_units % kUnitRing], c->sc));
   c->n_units += 1;
   return HI_OK;
@@ -300,8 +303,17 @@ int pf_variant(const hi_ctx* c) {
 // A decode launch of np partitions per head combines them itself where it has few of them (a short history) and the
 // context has counters for it.  What that saves is the second launch, 2.5 us of host time, which is what bounds a token at
 // short contexts (32 layers of 8 heads at 1K: 13.6 us a layer against 16.6); on the GPU it is 8.4 us against 5.6 + 3.9.
-// With 32 partitions the last workgroup alone takes 6.4 us where the combine kernel, spread over the chip, takes 4.
-bool can_tail(const hi_ctx* c, int np, int nh) { return c->counters && np <= kTailMaxParts && nh <= kTailMaxHeads; }
+// With 32 partitions the last workgroup alone takes 6.4 us where the combine kernel, spread over the chip, takes 4
+// (between 16 and 32 nothing was measured).  A captured step keeps the second launch: a graph may outlive the context, and
+// then its launches must hold no memory but the caller's.
+bool can_tail(hi_ctx* c, int np, int nh) {
+  if (np > kTailMaxParts || nh > kTailMaxHeads || c->capturing || c->counters_refused) return false;
+  if (!c->counters) {
+    c->counters = tail_counters_take(c->sc, &c->counter_slot);
+    c->counters_refused = !c->counters;
+  }
+  return c->counters != nullptr;
+}
 
 bool q_pre(const hi_ctx* c) { return c->prob.q_prescaled != 0; }
 
@@ -516,7 +528,6 @@ extern "C" hi_status hi_ctx_create(const hi_problem* problem, const hi_plan* pla
     hi_ctx_destroy(c);
     return (hi_status)HI_ERR_HIP;
   };
-  c->counters = tail_counters_take(&c->counter_slot);      // (none left: decode keeps its second launch)
   c->ev_unit.assign(kUnitRing, nullptr);
   for (int i = 0; i < kUnitRing; ++i)
     if ((e = hipEventCreateWithFlags(&c->ev_unit[i], hipEventDisableTiming)) != hipSuccess) return fail(e, "hipEventCreate");
@@ -543,8 +554,7 @@ extern "C" hi_status hi_ctx_create(const hi_problem* problem, const hi_plan* pla
 
 extern "C" hi_status hi_ctx_destroy(hi_ctx* c) {
   if (!c) return HI_OK;
-  // a context that failed half-way may have left its counters in any state: its slot is not given back
-  if (c->counters && !c->failed) {
+  if (c->counters) {
     hipEvent_t last = nullptr;
     if (c->n_units > 0) std::swap(last, c->ev_unit[(c->n_units - 1) % kUnitRing]);
     tail_counters_give(c->counter_slot, last);
@@ -627,13 +637,23 @@ static hi_status prefetch_hint(hi_ctx* c, const hi_ctx::Unit& next) {
 template <class F>
 static hi_status guarded(hi_ctx* c, F&& body) {
   c->enqueuing = false;
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  c->capturing = hipStreamIsCapturing(c->sc, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone;
+  if (c->capturing) (void)hipGetLastError();        // (a legacy stream cannot say while another one is being captured)
   hi_status st = pace_begin(c);
   if (st == HI_OK) st = body();
   if (st == HI_OK) {
     c->enqueuing = true;
     st = pace_end(c);
   }
-  if (st != HI_OK && c->enqueuing) c->failed = true;
+  if (st != HI_OK && c->enqueuing) {
+    c->failed = true;
+    // what did get enqueued may use the counters: without a marker behind it they are not given back
+    if (c->counters && !c->capturing) {
+      if (hipEventRecord(c->ev_unit[c->n_units % kUnitRing], c->sc) == hipSuccess) c->n_units += 1;
+      else { (void)hipGetLastError(); c->counters = nullptr; }
+    }
+  }
   c->enqueuing = false;
   return st;
 }
@@ -789,8 +809,8 @@ static hi_status decode_impl(hi_ctx* c, int32_t layer, int32_t kv_head, int32_t 
   auto whole = [&](const void* k, const void* v, int64_t rows, int64_t kv_stride, int64_t skip_row, char* k_append,
                    char* v_append) -> hi_status {
     const int np = rows > 0 ? splits_for(rows) : 0;
-    const DecodeTail tail{k_new_dev, v_new_dev, out_dev, c->prob.out_fp32, k_append, v_append, kv_stride, c->counters};
     const bool fused = rows > 0 && can_tail(c, np, nh);
+    const DecodeTail tail{k_new_dev, v_new_dev, out_dev, c->prob.out_fp32, k_append, v_append, kv_stride, c->counters};
     if (rows > 0) HI_TRY(partial(k, v, rows, np, 0, kv_stride, skip_row, fused ? &tail : nullptr));
     if (fused) return HI_OK;
     HI_TRY(launch_decode_combine(c->sc, q_dev, G, k_new_dev, v_new_dev, partials, np, out_dev, c->prob.out_fp32, k_append,
@@ -941,8 +961,8 @@ extern "C" hi_status hi_decode_group_ragged(hi_ctx* c, int32_t layer, int32_t kv
     const bool timed = (c->flags & HI_FLAG_TIME_KERNELS) != 0;
     char* const rk = res_plane(c, layer, kv_head, 0);
     char* const rv = res_plane(c, layer, kv_head, 1);
-    const DecodeTail tail{k_new_dev, v_new_dev, out_dev, c->prob.out_fp32, rk, rv, plane2, c->counters};
     const bool fused = longest > 0 && can_tail(c, n_split, n_heads);
+    const DecodeTail tail{k_new_dev, v_new_dev, out_dev, c->prob.out_fp32, rk, rv, plane2, c->counters};
     if (longest > 0) {
       TimedSpan sp;
       if (timed) HI_TRY(span_begin(c, 1, &sp));

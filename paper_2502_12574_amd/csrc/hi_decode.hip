@@ -421,8 +421,9 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(const uint16_t* __r
 }
 
 
-// Counters of the contexts that exist: a slot each of a built-in array, all zero whenever no launch of their context is
-// in flight.  A slot that is given back keeps the event of its context's last unit until that has finished.
+// Counters of contexts: a slot each of a built-in array, all zero whenever no launch of their context is in flight.  A slot
+// that is given back keeps the event of its context's last unit, which the next owner's stream waits for (no query: one from
+// a thread beside a stream capture would break the capture).
 constexpr int kTailSlots = 64, kTailDevices = 64;
 static __device__ int tail_counters[kTailSlots * kTailMaxHeads];
 namespace {
@@ -430,7 +431,7 @@ std::mutex tail_mu;
 struct TailSlot { bool taken; hipEvent_t busy_until; } tail_slots[kTailSlots];
 }  // namespace
 
-int* tail_counters_take(int* slot) {
+int* tail_counters_take(void* stream, int* slot) {
   static void* address[kTailDevices] = {};            // looking it up takes tens of microseconds: once per device
   int dev = -1;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kTailDevices) { (void)hipGetLastError(); return nullptr; }
@@ -442,13 +443,14 @@ int* tail_counters_take(int* slot) {
     return nullptr;
   }
   for (int i = 0; i < kTailSlots; ++i) {
-    if (tail_slots[i].taken) continue;
-    if (tail_slots[i].busy_until) {
-      if (hipEventQuery(tail_slots[i].busy_until) != hipSuccess) { (void)hipGetLastError(); continue; }
-      (void)hipEventDestroy(tail_slots[i].busy_until);
-      tail_slots[i].busy_until = nullptr;
+    TailSlot& s = tail_slots[i];
+    if (s.taken) continue;
+    if (s.busy_until) {
+      if (hipStreamWaitEvent((hipStream_t)stream, s.busy_until, 0) != hipSuccess) { (void)hipGetLastError(); continue; }
+      (void)hipEventDestroy(s.busy_until);
+      s.busy_until = nullptr;
     }
-    tail_slots[i].taken = true;
+    s.taken = true;
     *slot = i;
     return (int*)base + i * kTailMaxHeads;
   }

@@ -301,9 +301,10 @@ struct DecodeTail {
   int* counters;
 };
 
-// A context's counters (kTailMaxHeads ints of the current device, zero): null when all slots are taken.  They are given
-// back with the hipEvent_t that marks the end of the context's last unit (null: it ran none), which is then theirs.
-int* tail_counters_take(int* slot);
+// Counters for one context (kTailMaxHeads ints of the current device, zero for work enqueued on `stream` from now on; the
+// stream is not being captured): null when all slots are taken.  They are given back with the hipEvent_t that marks the end
+// of the context's last launch that used them, which is then theirs.
+int* tail_counters_take(void* stream, int* slot);
 void tail_counters_give(int slot, void* busy_until);
 
 // Split-KV decode over rows [0, n) of one slice: writes n_split partials starting at partial index part0.

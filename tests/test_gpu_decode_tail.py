@@ -188,3 +188,65 @@ def test_an_infinite_value_stays_infinite(H, G, past):
     assert torch.isinf(want).sum() == 2 * H
     assert torch.equal(torch.isinf(out), torch.isinf(want)[:, None].expand(H, G, 128))
     assert (out[:, :, 5] == float("inf")).all() and (out[:, :, 77] == float("-inf")).all() and not torch.isnan(out).any()
+
+
+def _step_session():
+    ss = Session(1, 2, 4, 256, 1, mode=hb.HI_MODE_RESIDENT, out_fp32=1)
+    hb.hi_ctx_set_run_ahead(ss.ctx, 0)
+    ss.cache_view().zero_()
+    q, k, v = (torch.ones(s, dtype=torch.bfloat16, device=DEV) for s in ((2, 4, 128), (2, 128), (2, 128)))
+    out = torch.zeros(2, 4, 128, device=DEV)
+    ss.s_compute.wait_stream(torch.cuda.current_stream())
+    return ss, lambda: ss.decode_group(0, 0, 2, q, k, v, 130, out), out
+
+
+def test_a_captured_step_holds_no_counters():
+    """A graph may be replayed when its context is gone and another one owns the counters: its launches are the two that use
+    the caller's buffers only."""
+    ss, step, out = _step_session()
+    step()
+    ss.sync()
+    assert ss.stats().n_combine_kernels == 0
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=ss.s_compute):
+        step()
+    assert ss.stats().n_combine_kernels == 1
+    want = out.clone()
+    step()
+    ss.sync()
+    assert ss.stats().n_combine_kernels == 1
+    ss.close()
+    other, step2, out2 = _step_session()
+    for _ in range(3):
+        out.zero_()
+        torch.cuda.synchronize()
+        graph.replay()
+        step2()
+        torch.cuda.synchronize()
+        assert (out - want).abs().max() <= 1e-6 and (out2 - want).abs().max() <= 1e-6
+    assert other.stats().n_combine_kernels == 0
+    other.close()
+
+
+@pytest.mark.parametrize("last_unit", ["captured", "failed"])
+def test_counters_come_back_whatever_the_last_unit_was(last_unit):
+    """More contexts one after the other than there are counter slots; each ends with a captured or a failed unit."""
+    for i in range(70):
+        ss, step, _ = _step_session()
+        step()
+        if last_unit == "captured":
+            torch.cuda.synchronize()
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph, stream=ss.s_compute):
+                step()
+        else:
+            hb.hi_ctx_set_flags(ss.ctx, hb.HI_FLAG_INJECT_FAILURE)
+            with pytest.raises(hb.HiError):
+                step()
+        ss.close()
+    ss, step, _ = _step_session()
+    step()
+    ss.sync()
+    assert ss.stats().n_combine_kernels == 0
+    ss.close()
