@@ -263,8 +263,11 @@ hi_status hi_decode_head(hi_ctx* ctx, int32_t layer, int32_t kv_head, const void
  * q_dev   DEVICE bf16 [n_heads][G][len][D_h]; k_new_dev, v_new_dev DEVICE bf16 [n_heads][len][D_h];
  * out_dev DEVICE [n_heads][G][len][D_h]  (len = chunk_len, or 1 with that axis dropped for decode).
  * The hint names the next group (first head and size).  hi_prefill_head / hi_decode_head are the n_heads = 1
- * case; results are identical whatever the grouping.  Extra errors: HI_ERR_HBM_BUDGET when a slice cannot hold
- * 64 rows of every head of the group.
+ * case.  The grouping, and whether the rows come from HBM or through the staging ring, decide how a head's rows are cut
+ * into partial sums, so results agree to the rounding of those sums and of the bf16 softmax weights.  Prefill calls of fewer
+ * than 16 blocks of 256 query rows (up to 960 rows of one head or 64 rows of eight with G = 4) give the same bits, with
+ * the default flags and bf16 rows, in both modes and in any grouping: their cut depends on hi_problem, past_len and
+ * chunk_len alone.  Extra errors: HI_ERR_HBM_BUDGET when a slice cannot hold 64 rows of every head of the group.
  */
 hi_status hi_prefill_group(hi_ctx* ctx, int32_t layer, int32_t kv_head, int32_t n_heads, const void* q_dev,
                            const void* k_new_dev, const void* v_new_dev, int64_t past_len, int32_t chunk_len,

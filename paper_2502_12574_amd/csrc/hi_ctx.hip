@@ -671,7 +671,7 @@ static hi_status prefill_impl(hi_ctx* c, int32_t layer, int32_t kv_head, int32_t
   // the state images of a unit may also take the room of the decode partials behind the carry: decode units run on the
   // same stream, and their partials do not outlive them
   const PrefillLaunch unit = prefill_unit_shape(G, chunk_len, nh, pf_variant(c), past_len, from_ring ? rows_of(c, nh) : 0,
-                                                c->plan.ws_writeback_offset);
+                                                c->plan.ws_writeback_offset, c->prob.n_kv_heads);
   auto launch = [&](const PrefillSegment& seg, const PrefillSegment& own, int first, int last) -> hi_status {
     TimedSpan sp;
     if (timed) HI_TRY(span_begin(c, 0, &sp));
@@ -741,7 +741,7 @@ static hi_status prefill_impl(hi_ctx* c, int32_t layer, int32_t kv_head, int32_t
   // a jump inside the past segment): a launch costs a round trip of the softmax state through HBM, a ring to fill
   // and a tail to drain, about 30 us, which is 7 % of a launch over one 16 384-row slice of two heads.  Two slots are
   // half the ring, so the copies of the next pair still run under the kernel of this one.
-  const bool pairs = unit.deep && !(pf_variant(c) & 16) && c->n_slots >= 4 && st / 64 < kPrefillWideMinTiles &&
+  const bool pairs = (unit.deep ? !(pf_variant(c) & 16) : unit.split > 1) && c->n_slots >= 4 && st / 64 < kPrefillWideMinTiles &&
                      !(c->flags & HI_FLAG_PREFILL_SINGLE_SLICES);
   for (int64_t i = 0; i < ns;) {
     HI_TRY(top_up(c, cur, next));          // guarantees slice i has been fetched
@@ -761,6 +761,7 @@ static hi_status prefill_impl(hi_ctx* c, int32_t layer, int32_t kv_head, int32_t
       if (two) HI_TRY(expand_slice(c, slot2, rows2, nh));
       const bool is_last = (i + (two ? 2 : 1) == ns);
       PrefillSegment seg{slot_k(c, slot), slot_v(c, slot, nh), rows + (two ? rows2 : 0), 0, head_pitch(c, nh)};
+      seg.tile0 = i * st / 64;
       if (two) {
         seg.jump_rows = st;
         seg.jump_bytes = jump;

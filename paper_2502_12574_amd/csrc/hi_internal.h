@@ -55,6 +55,7 @@ struct PrefillLaunch {
   int64_t carry_bytes; // state images the launches of this unit address in the carry
   int img_row;         // state images of one grid row (a head, a quad of query heads)
   int xcd;             // the workgroups of a grid row are numbered so that neighbours share an XCD (pf_wg_index)
+  int past_tiles;      // 4-wave kernel, split > 1: tiles of the unit's cached rows
 };
 inline PrefillLaunch prefill_launch_shape(int G, int64_t chunk_len, int n_heads, int variant, int last, int has_own) {
   PrefillLaunch p;
@@ -62,7 +63,7 @@ inline PrefillLaunch prefill_launch_shape(int G, int64_t chunk_len, int n_heads,
   p.split = prefill_split(G, chunk_len, n_heads);
   p.nbk = (int)ceil_div(chunk_len, 2 * strip);
   p.deep = base == 3 || (base == 0 && (int64_t)p.nbk * gy * n_heads * p.split >= kPrefillDeepMinWorkgroups);
-  p.paired = p.merge = p.xcd = 0;
+  p.paired = p.merge = p.xcd = p.past_tiles = 0;
   p.img_row = 2 * p.nbk * p.split;
   if (p.deep) {
     // tiles the workgroups of the deepest block sweep beyond the average (the causal triangle), which pairing removes
@@ -77,6 +78,41 @@ inline PrefillLaunch prefill_launch_shape(int G, int64_t chunk_len, int n_heads,
   return p;
 }
 
+constexpr int kPrefillUnitMaxSplit = 64;
+constexpr int kPrefillCus = 256;
+
+// Ranges the 4-wave kernel cuts a unit's tiles into, where the chunk alone would pick that kernel (few blocks of positions):
+// fixed in tiles of the unit and chosen without regard to the launches the unit comes in or to the heads of the call, so
+// that offloaded and resident results, and those of different head groups, agree bit for bit.  The least time by this model,
+// in microseconds: 4 to start, load and store the state, 1.3 per tile with one workgroup per compute unit, 1.9 with two; the
+// merge 5 + 0.03 per image; for the largest group this kernel serves at this chunk length (all_heads: heads of a layer).
+// Measured, uncut -> cut (the 8-wave kernel at its best split): 30 rows of 8 heads behind 100 thousand 1795 -> 110 us (127),
+// 64 rows 1788 -> 142 (134), 64 rows behind 5000 107 -> 28 (36); one head: 512 rows behind 1536 48 -> 23, 900 rows behind 20
+// thousand 389 -> 62 (71), behind 60 thousand 1093 -> 135 (124).
+inline int prefill_narrow_split(int G, int64_t C, int64_t past, int64_t capacity, int all_heads) {
+  const int strip = prefill_strip(G), gy = prefill_grid_y(G);
+  int64_t heads = (kPrefillDeepMinWorkgroups / kPrefillMaxSplit - 1) / (ceil_div(C, 2 * strip) * gy);
+  if (heads > all_heads) heads = all_heads;
+  if (heads < 1) heads = 1;
+  const int64_t blocks = ceil_div(C, strip) * gy * heads, image = (int64_t)kWgThreads * kCarryFloatsPerLane * 4;
+  const int64_t past_tiles = ceil_div(past, 64), tiles = past_tiles + ceil_div(C, 64);
+  int best = 1;
+  double best_us = 1e30;
+  for (int split = 1; split <= kPrefillUnitMaxSplit && (split == 1 || 4 * (int64_t)split <= past_tiles); ++split) {
+    const int64_t wgs = blocks * split, full = wgs / (2 * kPrefillCus), rest = wgs % (2 * kPrefillCus);
+    if (split > 1 && wgs * image > capacity) break;
+    const double range = (double)ceil_div(tiles, split);
+    double us = (double)full * (4.0 + 1.9 * range);
+    if (rest) us += 4.0 + (rest > kPrefillCus ? 1.9 : 1.3) * range;
+    if (split > 1) us += 5.0 + 0.03 * (double)wgs;
+    if (us < best_us) {
+      best_us = us;
+      best = split;
+    }
+  }
+  return best;
+}
+
 // The split and the pairing of one unit, chosen for what the unit sweeps: `past` cached rows in launches of up to
 // `slice` of them (0: one launch), then the chunk's own rows.  capacity: bytes the state images may take (the plan's
 // carry holds what prefill_launch_shape asks for; the decode partials behind it are idle while a prefill unit runs).
@@ -88,11 +124,9 @@ inline PrefillLaunch prefill_launch_shape(int G, int64_t chunk_len, int n_heads,
 // 1.9 per tile for its first 14 tiles (ring fill, masked and alignment tiles), then 1.1 per tile while at most 190 run and
 // up to 1.45 on a full chip (power).  A paired launch makes two passes (12 more).  The merge: 5 + 0.035 per image.  The
 // 4-wave kernel: 4 + 1.3 per tile with one workgroup per compute unit, 1.9 with two.
-// What it replaces sized the split by the chunk alone, in powers of two up to 8: 30 rows of 8 heads behind 100 thousand
-// ran on 16 workgroups of the 4-wave kernel (1952 us with the append, now 120), 77 rows on 128 (302 -> 178), 600 rows
-// behind 3000 in two rounds of workgroups (92 -> 70), 2400 rows behind 5000 likewise (333 -> 277).
-constexpr int kPrefillUnitMaxSplit = 64;
-constexpr int kPrefillCus = 256;
+// What it replaces sized the split by the chunk alone, in powers of two up to 8: 77 rows of 8 heads behind 100 thousand ran
+// on 128 workgroups (302 us, now 178), 600 rows behind 3000 in two rounds of workgroups (92 -> 70), 2400 rows behind 5000
+// likewise (333 -> 277).  Chunks that the rule by the chunk alone gives to the 4-wave kernel stay there, cut into ranges.
 inline PrefillLaunch prefill_launch_of(PrefillLaunch unit, int last, int has_own) {
   if (unit.deep && !(last && has_own)) unit.paired = 0;
   if (unit.paired) unit.xcd = 0;           // pairs are numbered range by range already
@@ -100,12 +134,21 @@ inline PrefillLaunch prefill_launch_of(PrefillLaunch unit, int last, int has_own
   return unit;
 }
 inline PrefillLaunch prefill_unit_shape(int G, int64_t C, int n_heads, int variant, int64_t past, int64_t slice,
-                                        int64_t capacity) {
+                                        int64_t capacity, int all_heads = 0) {
   PrefillLaunch best = prefill_launch_shape(G, C, n_heads, variant, 1, 1);
   const int strip = prefill_strip(G), rows = prefill_grid_y(G) * n_heads, base = variant & 3;
-  // 2048 rows in all: the 4-wave kernel where the chunk alone would pick it - it sums a row's keys in one order whether they
-  // come from HBM or slice by slice, so offloaded and resident results of short contexts agree bit for bit
-  if (base == 1 || (base == 0 && !best.deep && past + C <= 2048)) return best;
+  if (!best.deep) {
+    best.split = 1;
+    if (base == 1) return best;
+    const int strips = (int)ceil_div(C, strip);
+    best.split = prefill_narrow_split(G, C, past, capacity, all_heads > n_heads ? all_heads : n_heads);
+    best.merge = best.split > 1;
+    best.img_row = strips * best.split;
+    best.carry_bytes *= best.split;
+    best.past_tiles = (int)ceil_div(past, 64);
+    best.xcd = best.img_row % 8 == 0;
+    return best;
+  }
   const int64_t launches = past > 0 && slice > 0 ? ceil_div(past, slice) : 1;
   const double tiles_past = (double)ceil_div(past, 64) / (double)launches;       // of one launch
   const int64_t own = ceil_div(C, 64), m = 2 * strip / 64, image = (int64_t)kPdLanes * kCarryFloatsPerLane * 4;
@@ -129,11 +172,8 @@ inline PrefillLaunch prefill_unit_shape(int G, int64_t C, int n_heads, int varia
     if (split > 1 || paired) us += 5.0 + (double)wgs * 0.035;
     return us;
   };
-  double best_us = 1e30;
-  if (best.deep) {
-    best_us = 0.97 * cost(best.split, best.paired);          // a clear gain, or stay with the default
-  }
-  if (base != 3 && !(best.deep && (variant & (4 | 8 | 16 | 64 | 128)))) {       // (those flags name forms of the 8-wave kernel)
+  double best_us = 0.97 * cost(best.split, best.paired);     // a clear gain, or stay with the default
+  if (base != 3 && !(variant & (4 | 8 | 16 | 64 | 128))) {       // (those flags name forms of the 8-wave kernel)
     const int64_t wgs = ceil_div(C, strip) * rows;
     const double us = (double)launches * ((double)ceil_div(wgs, 2 * kPrefillCus) *
                                           (4.0 + (tiles_past + (double)own) * (wgs > kPrefillCus ? 1.9 : 1.3)));
@@ -216,9 +256,10 @@ struct PrefillSegment {
   int64_t head_stride = 0;   // bytes from one head's K (V) rows to the next head's, for launches over a head group
   // A past segment may consist of two pieces (two staging slots in one launch): rows [0, jump_rows) start at k / v,
   // the rows after them jump_bytes further on than they would in one piece.  jump_rows is a multiple of 64; 0: one
-  // piece.  Only the 16x16x32 8-wave and 4-wave kernels take such a segment.
+  // piece.  The 16x16x32 kernels and the 4-wave kernel with split > 1 take such a segment.
   int64_t jump_rows = 0;
   int64_t jump_bytes = 0;
+  int64_t tile0 = 0;         // past segment: its first tile, counted over the unit's cached rows
 };
 
 // One launch of the prefill kernel over up to two KV segments.  first: start from an empty softmax state

@@ -44,13 +44,14 @@ struct PrefillArgs {
   void* out;              // [G][C][128]
   int G, C, first, last, out_fp32;
   float c;                // log2(e) / sqrt(d)
-  int split;              // 8-wave kernel: workgroups per block of positions (they divide the block's tile sequence)
+  int split;              // workgroups per block of positions (they divide the block's tile sequence)
   int gy;                 // grid y per head; blockIdx.y / gy is the head of a group launch
   int64_t a_head_stride;  // bytes between the heads' rows in the past segment
   int paired;             // 8-wave kernel: deep and shallow blocks of the causal triangle share their tiles
   int nbk;                // 8-wave kernel: blocks of positions per head
-  int img_row;            // 8-wave kernel: state images per grid row
-  int xcd;                // 8-wave kernel: see pf_wg_index
+  int img_row;            // state images per grid row (8-wave kernel; 4-wave kernel with split > 1)
+  int xcd;                // see pf_wg_index
+  int tile0, past_tiles;  // 4-wave kernel with split > 1: first tile of the past segment in the unit, past tiles of the unit
   int a_jump_tile;        // the past segment's tiles from this one on lie a_jump_bytes further on (0: one piece)
   int64_t a_jump_bytes;
 };
@@ -469,6 +470,9 @@ __device__ __forceinline__ void pf_compute_tile(lds_char* kt, const PfLaneConst&
   pf_pv(kt + kPfTileBytes, lc, pb, st);
 }
 
+// SPLIT: a.split workgroups per block of positions, each on its range of the unit's tiles (pf_narrow_range) with a state
+// image of its own, merged after the last launch (prefill_merge4_kernel).
+template <bool SPLIT>
 __global__ __launch_bounds__(256, 2) void prefill_kernel(PrefillArgs a) {
   __shared__ __attribute__((aligned(1024))) char lds_raw[kPfLdsBytes];
   lds_char* lds = (lds_char*)lds_raw;
@@ -480,7 +484,26 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(PrefillArgs a) {
 
   const int gl = a.G < 4 ? a.G : 4;
   const int strip = 32 * (4 / gl);
-  const int bx = gridDim.x - 1 - blockIdx.x;        // deepest causal rows are dispatched first
+  int bx = gridDim.x - 1 - blockIdx.x;              // deepest causal rows are dispatched first
+  int64_t image = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
+  bool fresh = a.first != 0;
+  int a0 = 0, b0 = 0, ta_range = 0, t_range = 0;    // SPLIT: first past and own tile of this workgroup, its tiles
+  if constexpr (SPLIT) {
+    const int blocks = a.img_row / a.split;         // neighbours in the numbering sweep the same range
+    const int w = pf_wg_index(blockIdx.x, gridDim.x, a.xcd), k = w / blocks;
+    bx = blocks - 1 - w % blocks;
+    const int own = (int)(((a.C < bx * strip + strip ? a.C : bx * strip + strip) + kPfTileRows - 1) / kPfTileRows);
+    const int ta_launch = (int)((a.na + kPfTileRows - 1) / kPfTileRows);
+    const PfRange r = pf_narrow_range(a.past_tiles, own, k, a.split, a.tile0, ta_launch, a.last);
+    if (r.lo >= r.hi) return;
+    fresh = r.fresh != 0;
+    image = (int64_t)blockIdx.y * a.img_row + k * blocks + bx;
+    a0 = r.lo - a.tile0;
+    b0 = r.lo > a.past_tiles ? r.lo - a.past_tiles : 0;
+    ta_range = (r.hi < a.past_tiles ? r.hi : a.past_tiles) - r.lo;
+    if (ta_range < 0) ta_range = 0;
+    t_range = r.hi - r.lo;
+  }
   const int g = pf_select_head(a) * 4 + (wave % gl);
   const int i0 = bx * strip + 32 * (wave / gl);     // first query position of this wave
   const int i_hi = bx * strip + strip - 1;          // last query position of the workgroup
@@ -499,9 +522,8 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(PrefillArgs a) {
   }
 
   PfState st;
-  const int64_t wg_linear = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
-  float* carry = a.carry + wg_linear * (kCarryFloatsPerLane * kWgThreads) + threadIdx.x;
-  if (a.first) {
+  float* carry = a.carry + image * (kCarryFloatsPerLane * kWgThreads) + threadIdx.x;
+  if (fresh) {
     st.m = kNegBig;
     st.l = 0.f;
 #pragma unroll
@@ -524,20 +546,19 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(PrefillArgs a) {
   for (int db = 0; db < 4; ++db) asm volatile("" : "+v"(st.o[db]));
 
   // tiles: segment A (all of it), then the part of segment B at or below the workgroup's causal boundary
-  const int ta = (int)((a.na + kPfTileRows - 1) / kPfTileRows);
   const int64_t nb_vis = a.nb < (int64_t)i_hi + 1 ? a.nb : (int64_t)i_hi + 1;
-  const int tb = (int)((nb_vis + kPfTileRows - 1) / kPfTileRows);
-  const int T = ta + tb;
+  const int ta = SPLIT ? ta_range : (int)((a.na + kPfTileRows - 1) / kPfTileRows);
+  const int T = SPLIT ? t_range : ta + (int)((nb_vis + kPfTileRows - 1) / kPfTileRows);
 
   auto issue = [&](int t) {
     const uint32_t stage = lds_base + (uint32_t)(t & (kPfStages - 1)) * kPfStageBytes;
     if (t < ta) {
-      const int64_t row0 = (int64_t)t * kPfTileRows;
+      const int64_t row0 = (int64_t)(a0 + t) * kPfTileRows;
       const int64_t left = a.na - row0;
-      pf_issue_tile<4>(a.ka + row0 * kRowBytes, a.va + row0 * kRowBytes, left < kPfTileRows ? (int)left : kPfTileRows,
-                       stage, wave, lane, lc);
+      const int64_t at = row0 * kRowBytes + (SPLIT && a.a_jump_tile > 0 && a0 + t >= a.a_jump_tile ? a.a_jump_bytes : 0);
+      pf_issue_tile<4>(a.ka + at, a.va + at, left < kPfTileRows ? (int)left : kPfTileRows, stage, wave, lane, lc);
     } else {
-      const int64_t row0 = (int64_t)(t - ta) * kPfTileRows;
+      const int64_t row0 = (int64_t)(b0 + t - ta) * kPfTileRows;
       const int64_t left = a.nb - row0;
       pf_issue_tile<4>(a.kb + row0 * kRowBytes, a.vb + row0 * kRowBytes, left < kPfTileRows ? (int)left : kPfTileRows,
                        stage, wave, lane, lc);
@@ -557,7 +578,7 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(PrefillArgs a) {
     if (t + 1 < T) issue(t + 1);
     // masks: rows past the end of the segment, and (chunk's own rows) rows after the query's position
     const bool in_b = t >= ta;
-    const int64_t j0 = (int64_t)(in_b ? (t - ta) : t) * kPfTileRows;
+    const int64_t j0 = (int64_t)(in_b ? (b0 + t - ta) : a0 + t) * kPfTileRows;
     const int64_t n_seg = in_b ? a.nb : a.na;
     const bool masked = (j0 + kPfTileRows > n_seg) || (in_b && (j0 + kPfTileRows - 1 > i0));
     int rel = kPfTileRows;
@@ -576,7 +597,7 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(PrefillArgs a) {
   }
   if (t < T) step(t, std::integral_constant<int, 0>());
 
-  if (!a.last) {
+  if (SPLIT || !a.last) {
 #pragma unroll
     for (int db = 0; db < 4; ++db)
 #pragma unroll
@@ -1636,6 +1657,42 @@ __global__ __launch_bounds__(512) void prefill_merge_kernel(PrefillArgs a) {
   pf_write_row_db(a.out, a.out_fp32, a.C, g, my_i, hl, db, o, l);
 }
 
+// Merge of the ranges of the 4-wave kernel: grid (blocks, grid rows, 4 dim blocks), that kernel's own lane layout.  A lane
+// whose query sees none of a range's keys (own rows only, all behind it) left its image's sums at what masked scores add up
+// to; it takes no part.  Bound by the read of the images (70 KB each); four of them in flight per lane.
+__global__ __launch_bounds__(256) void prefill_merge4_kernel(PrefillArgs a) {
+  const int lane = lane_id();
+  const int wave = wave_id();
+  const int gl = a.G < 4 ? a.G : 4;
+  const int strip = 32 * (4 / gl);
+  const int blocks = gridDim.x, bx = blockIdx.x, db = blockIdx.z;
+  const int g = pf_select_head(a) * 4 + (wave % gl);
+  const int my_i = bx * strip + 32 * (wave / gl) + (lane & 31);
+  constexpr int kImageFloats = kCarryFloatsPerLane * kWgThreads;
+  const float* images = a.carry + ((int64_t)blockIdx.y * a.img_row + bx) * kImageFloats + threadIdx.x;
+  float m = kNegBig;
+#pragma unroll 4
+  for (int k = 0; k < a.split; ++k) m = fmaxf(m, images[(int64_t)k * blocks * kImageFloats + 64 * kWgThreads]);
+  f32x16 o;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) o[r] = 0.f;
+  float l = 0.f;
+#pragma unroll 4
+  for (int k = 0; k < a.split; ++k) {
+    const float* im = images + (int64_t)k * blocks * kImageFloats;
+    const float mk = im[64 * kWgThreads], lk = im[65 * kWgThreads];
+    const float w = fast_exp2((mk - m) * a.c);
+    const bool seen = mk > kNegBig;
+    l += seen ? w * lk : 0.f;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const float x = im[(db * 16 + r) * kWgThreads];
+      o[r] += seen ? w * x : 0.f;
+    }
+  }
+  pf_write_row_db(a.out, a.out_fp32, a.C, g, my_i, lane >> 5, db, o, l);
+}
+
 // ---------------------------------------------------------------------------------------------------------
 // Streaming heads (Appendix E, head-wise sparsity: a streaming head keeps only recent tokens - here n_sink initial
 // tokens and the n_recent most recent ones - and lives in HBM).  Query row at absolute position p sees key j iff
@@ -1962,7 +2019,15 @@ hi_status launch_prefill(void* stream, const void* q, int G, int chunk_len, cons
   a.nbk = pl.nbk;
   a.img_row = pl.img_row;
   a.xcd = pl.xcd;
-  if (sa.jump_rows != 0 && !(pl.deep && (variant & 16) == 0)) {
+  a.tile0 = (int)sa.tile0;
+  a.past_tiles = pl.past_tiles;
+  if (!pl.deep && pl.split > 1 && (sa.tile0 < 0 || sa.tile0 + ceil_div(sa.n, kPfTileRows) > pl.past_tiles ||
+                                   (last && (sa.tile0 + ceil_div(sa.n, kPfTileRows) != pl.past_tiles || sb.n < 1)) ||
+                                   (int64_t)pl.img_row != (int64_t)pl.split * ceil_div(chunk_len, strip))) {
+    set_last_error("prefill launch: the segment does not fit the unit's tiles");
+    return HI_ERR_ARG;
+  }
+  if (sa.jump_rows != 0 && !(pl.deep ? (variant & 16) == 0 : pl.split > 1)) {
     set_last_error("prefill launch: this kernel takes its past segment in one piece");
     return HI_ERR_UNSUPPORTED;
   }
@@ -2004,8 +2069,17 @@ hi_status launch_prefill(void* stream, const void* q, int G, int chunk_len, cons
       else hipLaunchKernelGGL(prefill_merge16_kernel, dim3((unsigned)pl.nbk, grid.y, 8), dim3(kPdWaves * 64), 0, (hipStream_t)stream, a);
     }
   } else {
-    dim3 grid((unsigned)ceil_div(chunk_len, strip), (unsigned)(gy * n_heads));
-    hipLaunchKernelGGL(prefill_kernel, grid, dim3(kWgThreads), 0, (hipStream_t)stream, a);
+    const dim3 blocks((unsigned)ceil_div(chunk_len, strip), (unsigned)(gy * n_heads));
+    if (pl.split > 1) {
+      hipLaunchKernelGGL(prefill_kernel<true>, dim3(blocks.x * (unsigned)pl.split, blocks.y), dim3(kWgThreads), 0, (hipStream_t)stream, a);
+      if (pl.merge) {
+        hipError_t e1 = hipGetLastError();
+        if (e1 != hipSuccess) { set_last_error("prefill launch: %s", hipGetErrorString(e1)); return HI_ERR_HIP; }
+        hipLaunchKernelGGL(prefill_merge4_kernel, dim3(blocks.x, blocks.y, 4), dim3(kWgThreads), 0, (hipStream_t)stream, a);
+      }
+    } else {
+      hipLaunchKernelGGL(prefill_kernel<false>, blocks, dim3(kWgThreads), 0, (hipStream_t)stream, a);
+    }
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) { set_last_error("prefill launch: %s", hipGetErrorString(e)); return HI_ERR_HIP; }

@@ -158,4 +158,21 @@ HI_HD void pf_block_images(const PfShape& s, int b, int& n_e, int& n_x) {
   n_x = nc > s.split ? nc - s.split : 0;
 }
 
+// The 4-wave kernel: the tiles of a block of positions - all past tiles of the UNIT, then the own tiles up to the block's
+// causal boundary - are cut into `split` ranges, whatever the launches the unit comes in.  A launch that was given past tiles
+// [tile0, tile0 + ta) of the unit, and the own tiles if it is the last one, works on [lo, hi) of range k (in tiles of the
+// unit; empty: not this workgroup's turn).  Every range is swept in one order from an empty state, so the result does not
+// depend on where the launches end.
+struct PfRange { int lo, hi; int fresh; };
+HI_HD PfRange pf_narrow_range(int past_tiles, int own_tiles, int k, int split, int tile0, int ta, int last) {
+  const int total = past_tiles + own_tiles;
+  const int x0 = pf_cut(total, k, split), x1 = pf_cut(total, k + 1, split);
+  const int end = last ? total : tile0 + ta;
+  PfRange r;
+  r.lo = x0 > tile0 ? x0 : tile0;
+  r.hi = x1 < end ? x1 : end;
+  r.fresh = x0 >= tile0;
+  return r;
+}
+
 }  // namespace hi

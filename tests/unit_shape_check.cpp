@@ -15,6 +15,56 @@ static long fails = 0;
 
 struct Image { int block = -1; std::multiset<long> tiles; };
 
+// Units of the 4-wave kernel: the ranges of every block, swept launch by launch, are the ranges of one launch over everything,
+// each swept in order; a range loads its image exactly where an earlier launch has begun it; no image lies beyond the row.
+static long narrow = 0, narrow_most = 0;
+static void run_narrow(int G, int C, int nh, int variant, long past, long slice, long capacity, int all_heads) {
+  const PrefillLaunch unit = prefill_unit_shape(G, C, nh, variant, past, slice, capacity, all_heads);
+  if (unit.deep || unit.split == 1) return;
+  ++narrow;
+  if (unit.split > narrow_most) narrow_most = unit.split;
+  const int strip = prefill_strip(G), blocks = (int)ceil_div(C, strip), rows = prefill_grid_y(G) * nh;
+  CHECK(unit.carry_bytes <= capacity && unit.carry_bytes == (long)rows * blocks * unit.split * kWgThreads * kCarryFloatsPerLane * 4, "images");
+  CHECK(unit.img_row == blocks * unit.split && unit.merge && unit.past_tiles == (past + 63) / 64, "shape");
+  for (int h = 1; h <= all_heads; ++h)
+    for (long sl : {0L, 64L, 1024L}) {
+      const PrefillLaunch other = prefill_unit_shape(G, C, h, variant, past, sl, capacity, all_heads);
+      CHECK(prefill_launch_shape(G, C, h, variant, 1, 1).deep || other.split == unit.split, "split of %d heads: %d, not %d", h, other.split, unit.split);
+    }
+  std::vector<std::vector<int>> swept(unit.img_row);
+  const int launches = slice > 0 ? (int)ceil_div(past, slice) : 1;
+  for (int l = 0; l < launches; ++l) {
+    const int last = l == launches - 1, tile0 = launches == 1 ? 0 : (int)(l * slice / 64);
+    const long na = launches == 1 ? past : (past - l * slice < slice ? past - l * slice : slice);
+    const PrefillLaunch pl = prefill_launch_of(unit, last, last);
+    CHECK(pl.merge == last && pl.split == unit.split && pl.img_row == unit.img_row, "launch");
+    std::set<int> numbers;
+    for (int x = 0; x < unit.img_row; ++x) {
+      const int w = pf_wg_index(x, unit.img_row, pl.xcd), k = w / blocks, bx = blocks - 1 - w % blocks;
+      CHECK(w >= 0 && w < unit.img_row && numbers.insert(w).second, "workgroup number");
+      const int own = ((C < (bx + 1) * strip ? C : (bx + 1) * strip) + 63) / 64;
+      const PfRange r = pf_narrow_range(unit.past_tiles, own, k, unit.split, tile0, (int)((na + 63) / 64), last);
+      if (r.lo >= r.hi) continue;
+      std::vector<int>& seq = swept[k * blocks + bx];
+      CHECK(r.fresh == (int)seq.empty(), "range %d of block %d: fresh %d after %zu tiles", k, bx, r.fresh, seq.size());
+      CHECK(r.lo >= tile0 && (r.hi <= tile0 + (na + 63) / 64 || last), "tiles outside the launch");
+      for (int t = r.lo; t < r.hi; ++t) seq.push_back(t);
+    }
+  }
+  for (int bx = 0; bx < blocks; ++bx) {
+    const int own = ((C < (bx + 1) * strip ? C : (bx + 1) * strip) + 63) / 64;
+    int at = 0;
+    for (int k = 0; k < unit.split; ++k) {
+      const PfRange whole = pf_narrow_range(unit.past_tiles, own, k, unit.split, 0, unit.past_tiles, 1);
+      const std::vector<int>& seq = swept[k * blocks + bx];
+      CHECK(whole.fresh && whole.lo == at && whole.hi > whole.lo && (int)seq.size() == whole.hi - whole.lo, "range %d of block %d", k, bx);
+      for (size_t i = 0; i < seq.size(); ++i) CHECK(seq[i] == whole.lo + (int)i, "order");
+      at = whole.hi;
+    }
+    CHECK(at == unit.past_tiles + own, "block %d ends at tile %d of %d", bx, at, unit.past_tiles + own);
+  }
+}
+
 static void run_unit(int G, int C, int nh, int variant, long past, long slice, long capacity, int* split_out) {
   const PrefillLaunch unit = prefill_unit_shape(G, C, nh, variant, past, slice, capacity);
   const PrefillLaunch base = prefill_launch_shape(G, C, nh, variant, 1, 1);
@@ -93,6 +143,10 @@ int main() {
       if (split > most) most = split;
     }
   CHECK(uneven > 0 && most > 8, "splits that are no power of two: %ld, largest %ld", uneven, most);
+  for (int G : {1, 2, 4, 8}) for (int C : {1, 33, 64, 77, 300, 512, 960}) for (int nh : {1, 2, 8}) for (int variant : {0, 4, 8, 64})
+    for (long past : {0L, 100L, 1536L, 2049L, 3001L, 20000L, 131072L, 1000003L}) for (long slice : {0L, 512L, 4096L, 65536L}) for (long room : {1L, 8L, 64L})
+      run_narrow(G, C, nh, variant, past, slice, prefill_carry_bound(G, C, 8) + room * (1L << 20), 8);
+  CHECK(narrow > 1000 && narrow_most > 40, "%ld units of the 4-wave kernel cut, into %ld at most", narrow, narrow_most);
   for (int nbk : {2, 3, 7, 10}) for (int m : {1, 2, 4}) for (int ta : {0, 1, 5, 47, 200}) for (int split : {1, 2, 3, 5, 11, 40}) for (int clip : {0, 1}) {
     PfShape s{nbk, m, ta, nbk * m - clip, split, 1, 0};
     for (int p = 0; p < nbk / 2; ++p) for (int sw = 0; sw < 2; ++sw) {
