@@ -50,14 +50,17 @@ __device__ __forceinline__ float2 load_shared2(const float* p) {      // 8-byte 
   return make_float2(__uint_as_float((uint32_t)v), __uint_as_float((uint32_t)(v >> 32)));
 }
 
-// What decode_combine_kernel does, for all G query heads of one KV head, by the workgroup that finished its partial last.
+// What decode_combine_kernel does, for all G query heads of one KV head, by the workgroup that finished its partial last, in
+// that kernel's order of operations (at most one partition per lane there): the same bits, so that a captured step, which
+// takes two launches, agrees with an eager one.
 // Bound by the latency of its loads (the partials come from beyond the L2), so all of them are asked for at once: that is
-// why a launch has to have few partitions for it.  lds: 2 * 8 * kTailMaxParts floats; k2, v2: the lane's two dims of the
-// token's own K and V row.
+// why a launch has to have few partitions for it.  lds: 2 * 8 * kTailMaxParts floats; k_lo, k_hi: dims lane and lane + 64 of
+// the token's own K row; v2: dims 2 lane and 2 lane + 1 of its V row.
 __device__ __forceinline__ void decode_tail(int kv, const uint16_t* q, int G, const float* part, int n_part, const DecodeTail& tl,
-                                            int64_t append_off, float c, float* lds, uint32_t k2, uint32_t v2) {
+                                            int64_t append_off, float c, float* lds, uint16_t k_lo, uint16_t k_hi, uint32_t v2) {
+#pragma clang fp contract(off)
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  float* w = lds;                                  // [n_part][G] maxima, then weights, of the partials
+  float* w = lds;                                  // [n_part][G] maxima of the partials
   float* sum = lds + 8 * kTailMaxParts;            // [n_part][G] sums
   const int64_t part_pitch = (int64_t)G * kPartialFloats;
   const int dim = 2 * lane;                        // a wavefront takes query heads wave and wave + 4, a lane two dims
@@ -74,7 +77,9 @@ __device__ __forceinline__ void decode_tail(int kv, const uint16_t* q, int G, co
     }
   }
   if (tl.k_append != nullptr && wave == 0) {
-    *(uint32_t*)((char*)tl.k_append + append_off + 2 * dim) = k2;
+    uint16_t* const k_row = (uint16_t*)((char*)tl.k_append + append_off);
+    k_row[lane] = k_lo;
+    k_row[lane + 64] = k_hi;
     *(uint32_t*)((char*)tl.v_append + append_off + 2 * dim) = v2;
   }
   if (tid < n_part * G) {
@@ -86,27 +91,30 @@ __device__ __forceinline__ void decode_tail(int kv, const uint16_t* q, int G, co
   for (int h = 0; h < 2; ++h) {
     const int g = wave + 4 * h;
     if (g >= G) break;
-    const uint32_t q2 = *(const uint32_t*)(q + g * kHeadDim + dim);
-    float d = __uint_as_float(q2 << 16) * __uint_as_float(k2 << 16) +
-              __uint_as_float(q2 & 0xFFFF0000u) * __uint_as_float(k2 & 0xFFFF0000u);
+    // (the products of two bf16 numbers are exact: this is the combine kernel's dot product, fused or not)
+    float d = bf16_bits_to_float(q[g * kHeadDim + lane]) * bf16_bits_to_float(k_lo) +
+              bf16_bits_to_float(q[g * kHeadDim + 64 + lane]) * bf16_bits_to_float(k_hi);
     for (int off = 32; off > 0; off >>= 1) d += __shfl_xor(d, off);
     const float m = lane < n_part ? w[lane * G + g] : kNegBig;
     float mx = fmaxf(d, m);
     for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
     const float wp = lane < n_part ? fast_exp2((m - mx) * c) : 0.f;
-    float l = lane < n_part ? wp * sum[lane * G + g] : 0.f;
-    for (int off = 32; off > 0; off >>= 1) l += __shfl_xor(l, off);
+    const float lp = lane < n_part ? wp * sum[lane * G + g] : 0.f;
     const float p_new = fast_exp2((d - mx) * c);
-    const float total = l + p_new;
-    float2 acc = make_float2(p_new * __uint_as_float(v2 << 16), p_new * __uint_as_float(v2 & 0xFFFF0000u));
+    float2 acc = make_float2(0.f, 0.f);
+    float total = 0.f;
 #pragma unroll
     for (int p = 0; p < kTailMaxParts; ++p) {
-      const float x = __shfl(wp, p);
+      const float x = __shfl(wp, p), l = __shfl(lp, p);
       if (p < n_part) {                            // (not left to a weight of 0: a partial may be infinite)
-        acc.x = __builtin_fmaf(x, o[h][p].x, acc.x);
-        acc.y = __builtin_fmaf(x, o[h][p].y, acc.y);
+        acc.x += x * o[h][p].x;
+        acc.y += x * o[h][p].y;
+        total += l;
       }
     }
+    acc.x = __builtin_fmaf(p_new, __uint_as_float(v2 << 16), acc.x);
+    acc.y = __builtin_fmaf(p_new, __uint_as_float(v2 & 0xFFFF0000u), acc.y);
+    total += p_new;
     acc.x /= total;
     acc.y /= total;
     const int64_t at = ((int64_t)kv * G + g) * kHeadDim + dim;
@@ -186,12 +194,14 @@ __global__ __launch_bounds__(256) void decode_partial_kernel(const uint16_t* __r
     qf[kk] = __builtin_bit_cast(bf16x8, raw);
   }
   // the token's own row, for the tail: asked for now, so that a cold first touch is not a latency of its own there
-  uint32_t k2 = 0, v2 = 0;
+  uint32_t k_lo = 0, k_hi = 0, v2 = 0;
   if constexpr (TAIL) {
-    k2 = *(const uint32_t*)((const uint16_t*)tail.k_new + head_i * kHeadDim + 2 * lane);
+    const uint16_t* const k_row = (const uint16_t*)tail.k_new + head_i * kHeadDim;
+    k_lo = k_row[lane];
+    k_hi = k_row[lane + 64];
     v2 = *(const uint32_t*)((const uint16_t*)tail.v_new + head_i * kHeadDim + 2 * lane);
   }
-  asm volatile("" : "+v"(k2), "+v"(v2));
+  asm volatile("" : "+v"(k_lo), "+v"(k_hi), "+v"(v2));
   // make the compiler wait for these loads here, not inside the loop (a vmcnt(0) there would drain the ring)
 #pragma unroll
   for (int kk = 0; kk < 4; ++kk) asm volatile("" : "+v"(qf[kk]));
@@ -330,7 +340,7 @@ __global__ __launch_bounds__(256) void decode_partial_kernel(const uint16_t* __r
     if (!last) return;
     int64_t off = head_i * tail.append_head_stride;
     if constexpr (kRagged<Lens>) off += n * kRowBytes;      // (k_append / v_append point at row 0 of the first head)
-    decode_tail(head_i, q, G, partials, n_part, tail, off, c, (float*)lds_raw, k2, v2);
+    decode_tail(head_i, q, G, partials, n_part, tail, off, c, (float*)lds_raw, (uint16_t)k_lo, (uint16_t)k_hi, v2);
   }
 }
 
@@ -412,7 +422,7 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(const uint16_t* __r
 #pragma unroll
     for (int i = 0; i < kCombLanes; ++i) { a += red_o[i][tid]; lsum += red_o[i][kCombDims]; }
     const float p_new = fast_exp2((s_new - M) * c);
-    a += p_new * bf16_bits_to_float(v_new[dim]);
+    a = __builtin_fmaf(p_new, bf16_bits_to_float(v_new[dim]), a);
     lsum += p_new;
     const float r = a / lsum;
     if (out_fp32) ((float*)out)[g * kHeadDim + dim] = r;

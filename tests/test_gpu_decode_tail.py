@@ -250,3 +250,35 @@ def test_counters_come_back_whatever_the_last_unit_was(last_unit):
     ss.sync()
     assert ss.stats().n_combine_kernels == 0
     ss.close()
+
+
+# 1, 2, 3, 11, 16 partitions of a head, every group size, bf16 and fp32 outputs, plain and scaled queries
+@pytest.mark.parametrize("H,G,past,fp32,pre", [(8, 4, 5, 1, False), (8, 4, 101, 0, True), (3, 8, 130, 1, True), (2, 1, 700, 1, False),
+                                               (8, 4, 1022, 1, True), (16, 2, 1020, 0, False), (4, 4, 1023, 1, False)])
+def test_one_launch_and_two_give_the_same_bits(H, G, past, fp32, pre):
+    """An eager step combines its partials in the launch, a captured one in a launch of its own."""
+    gen = torch.Generator(device=DEV).manual_seed(53500 + past)
+    with Session(1, H, G, max(past + 1, 256), 1, mode=hb.HI_MODE_RESIDENT, out_fp32=fp32, q_prescaled=pre) as ss:
+        hb.hi_ctx_set_run_ahead(ss.ctx, 0)
+        view = ss.cache_view()
+        view.copy_(torch.randn(view.shape, device=DEV, generator=gen))
+        q = (torch.randn(H, G, 128, device=DEV, generator=gen) * (hb.HI_Q_PRESCALE if pre else 1.0)).to(torch.bfloat16)
+        k, v = (torch.randn(H, 128, device=DEV, generator=gen).to(torch.bfloat16) for _ in range(2))
+        out = torch.zeros(H, G, 128, dtype=ss.out_dtype, device=DEV)
+        torch.cuda.synchronize()
+        ss.decode_group(0, 0, H, q, k, v, past, out)
+        ss.sync()
+        assert ss.stats().n_combine_kernels == 0
+        want = out.clone()
+        graph = torch.cuda.CUDAGraph()
+        torch.cuda.synchronize()
+        with torch.cuda.graph(graph, stream=ss.s_compute):
+            ss.decode_group(0, 0, H, q, k, v, past, out)
+        assert ss.stats().n_combine_kernels == 1
+        for _ in range(3):
+            out.zero_()
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(out, want)
+            assert torch.equal(view[0, :, 0, past], k) and torch.equal(view[0, :, 1, past], v)
