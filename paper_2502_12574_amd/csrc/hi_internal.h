@@ -86,9 +86,9 @@ constexpr int kPrefillCus = 256;
 // that offloaded and resident results, and those of different head groups, agree bit for bit.  The least time by this model,
 // in microseconds: 4 to start, load and store the state, 1.3 per tile with one workgroup per compute unit, 1.9 with two; the
 // merge 5 + 0.03 per image; for the largest group this kernel serves at this chunk length (all_heads: heads of a layer).
-// Measured, uncut -> cut (the 8-wave kernel at its best split): 30 rows of 8 heads behind 100 thousand 1795 -> 110 us (127),
-// 64 rows 1788 -> 142 (134), 64 rows behind 5000 107 -> 28 (36); one head: 512 rows behind 1536 48 -> 23, 900 rows behind 20
-// thousand 389 -> 62 (71), behind 60 thousand 1093 -> 135 (124).
+// Measured, uncut -> cut (the 8-wave kernel at its best split): 30 rows of 8 heads behind 100 thousand 1795 -> 104 us (127),
+// 64 rows 1788 -> 141 (134), 64 rows behind 5000 107 -> 25 (36); one head: 512 rows behind 1536 48 -> 23, 900 rows behind 20
+// thousand 389 -> 63 (71), behind 60 thousand 1093 -> 139 (124).
 inline int prefill_narrow_split(int G, int64_t C, int64_t past, int64_t capacity, int all_heads) {
   const int strip = prefill_strip(G), gy = prefill_grid_y(G);
   int64_t heads = (kPrefillDeepMinWorkgroups / kPrefillMaxSplit - 1) / (ceil_div(C, 2 * strip) * gy);

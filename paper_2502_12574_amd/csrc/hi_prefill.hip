@@ -1657,40 +1657,53 @@ __global__ __launch_bounds__(512) void prefill_merge_kernel(PrefillArgs a) {
   pf_write_row_db(a.out, a.out_fp32, a.C, g, my_i, hl, db, o, l);
 }
 
-// Merge of the ranges of the 4-wave kernel: grid (blocks, grid rows, 4 dim blocks), that kernel's own lane layout.  A lane
-// whose query sees none of a range's keys (own rows only, all behind it) left its image's sums at what masked scores add up
-// to; it takes no part.  Bound by the read of the images (70 KB each); four of them in flight per lane.
+// Merge of the ranges of the 4-wave kernel: grid (blocks, grid rows, 16), z = 4 (dim block) + quarter: four of its
+// registers, dims 32 db + 8 rq + 4 hl ..; that kernel's own lane layout.  A lane whose query sees none of a range's keys (own
+// rows only, all behind it) left its image's sums at what masked scores add up to; it takes no part.
+// Bound by the latency of its reads (70 KB per image, up to 64 images of a block, and few blocks where there are many), so
+// the grid splits an image finely and many images are in flight per lane: 63 images of 8 blocks take 18 us, 16 images
+// of 16 blocks 6.4 (30 and 9.3 with whole dim blocks and four images in flight).
 __global__ __launch_bounds__(256) void prefill_merge4_kernel(PrefillArgs a) {
   const int lane = lane_id();
   const int wave = wave_id();
+  const int hl = lane >> 5;
   const int gl = a.G < 4 ? a.G : 4;
   const int strip = 32 * (4 / gl);
-  const int blocks = gridDim.x, bx = blockIdx.x, db = blockIdx.z;
+  const int blocks = gridDim.x, bx = blockIdx.x, db = blockIdx.z >> 2, rq = blockIdx.z & 3;
   const int g = pf_select_head(a) * 4 + (wave % gl);
   const int my_i = bx * strip + 32 * (wave / gl) + (lane & 31);
   constexpr int kImageFloats = kCarryFloatsPerLane * kWgThreads;
   const float* images = a.carry + ((int64_t)blockIdx.y * a.img_row + bx) * kImageFloats + threadIdx.x;
+  const int64_t pitch = (int64_t)blocks * kImageFloats;
   float m = kNegBig;
-#pragma unroll 4
-  for (int k = 0; k < a.split; ++k) m = fmaxf(m, images[(int64_t)k * blocks * kImageFloats + 64 * kWgThreads]);
-  f32x16 o;
-#pragma unroll
-  for (int r = 0; r < 16; ++r) o[r] = 0.f;
-  float l = 0.f;
-#pragma unroll 4
+#pragma unroll 16
+  for (int k = 0; k < a.split; ++k) m = fmaxf(m, images[k * pitch + 64 * kWgThreads]);
+  float o[4] = {0.f, 0.f, 0.f, 0.f}, l = 0.f;
+#pragma unroll 8
   for (int k = 0; k < a.split; ++k) {
-    const float* im = images + (int64_t)k * blocks * kImageFloats;
+    const float* im = images + k * pitch;
     const float mk = im[64 * kWgThreads], lk = im[65 * kWgThreads];
     const float w = fast_exp2((mk - m) * a.c);
     const bool seen = mk > kNegBig;
     l += seen ? w * lk : 0.f;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const float x = im[(db * 16 + r) * kWgThreads];
+    for (int r = 0; r < 4; ++r) {
+      const float x = im[(db * 16 + 4 * rq + r) * kWgThreads];
       o[r] += seen ? w * x : 0.f;
     }
   }
-  pf_write_row_db(a.out, a.out_fp32, a.C, g, my_i, lane >> 5, db, o, l);
+  const float inv = 1.0f / sum_halves(l);
+  if (my_i >= a.C) return;
+  const int64_t at = ((int64_t)g * a.C + my_i) * kHeadDim + 32 * db + 8 * rq + 4 * hl;
+  const float x0 = o[0] * inv, x1 = o[1] * inv, x2 = o[2] * inv, x3 = o[3] * inv;
+  if (a.out_fp32) {
+    *(float4*)((float*)a.out + at) = make_float4(x0, x1, x2, x3);
+  } else {
+    uint2 pk;
+    pk.x = (uint32_t)float_to_bf16_bits(x0) | ((uint32_t)float_to_bf16_bits(x1) << 16);
+    pk.y = (uint32_t)float_to_bf16_bits(x2) | ((uint32_t)float_to_bf16_bits(x3) << 16);
+    *(uint2*)((uint16_t*)a.out + at) = pk;
+  }
 }
 
 // ---------------------------------------------------------------------------------------------------------
@@ -2075,7 +2088,7 @@ hi_status launch_prefill(void* stream, const void* q, int G, int chunk_len, cons
       if (pl.merge) {
         hipError_t e1 = hipGetLastError();
         if (e1 != hipSuccess) { set_last_error("prefill launch: %s", hipGetErrorString(e1)); return HI_ERR_HIP; }
-        hipLaunchKernelGGL(prefill_merge4_kernel, dim3(blocks.x, blocks.y, 4), dim3(kWgThreads), 0, (hipStream_t)stream, a);
+        hipLaunchKernelGGL(prefill_merge4_kernel, dim3(blocks.x, blocks.y, 16), dim3(kWgThreads), 0, (hipStream_t)stream, a);
       }
     } else {
       hipLaunchKernelGGL(prefill_kernel<false>, blocks, dim3(kWgThreads), 0, (hipStream_t)stream, a);
