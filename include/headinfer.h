@@ -222,7 +222,7 @@ hi_status hi_ctx_set_run_ahead(hi_ctx* ctx, int32_t units);
  * T1 + K1 + T3 - one prefill unit: one chunk, one KV head, its G query heads (Algorithm 1, prefill phase, the
  * body of the head loop; Eq. 9).  Appends, then attends:
  *   - rows [past_len, past_len + chunk_len) of (layer, kv_head) in the cache receive k_new / v_new
- *     (asynchronous write-back on stream_d2h; a device copy in resident mode);
+ *     (asynchronous write-back on stream_d2h; a launch on stream_compute for an HBM-resident head);
  *   - out[g][i][:] = softmax_j<=past_len+i( q[g][i] . K[j] / sqrt(D_h) ) V[j]  over the head's rows 0..past_len+i,
  *     the past rows streamed from the cache through the staging ring, the chunk's own rows read from k_new/v_new.
  * q_dev   DEVICE bf16 [G][chunk_len][D_h]; k_new_dev, v_new_dev DEVICE bf16 [chunk_len][D_h];
@@ -246,7 +246,8 @@ hi_status hi_prefill_head(hi_ctx* ctx, int32_t layer, int32_t kv_head, const voi
  * T1 + K2 + K3 + T3 - one decode unit: one new token, one KV head, its G query rows (Algorithm 1, decode phase).
  * Appends the token's K/V row at row past_len, then attends over rows 0..past_len inclusive (the token sees
  * itself).  Split-KV: each partition of the streamed rows yields a partial (max, sum, weighted V); a combine
- * kernel merges the partials of all partitions and slices with the new row.
+ * kernel merges the partials of all partitions and slices with the new row (a head whose rows in HBM make at most 16
+ * partitions is merged by the split-KV launch itself: the same bits; hi_stats.n_combine_kernels counts launches).
  * q_dev DEVICE bf16 [G][D_h]; k_new_dev, v_new_dev DEVICE bf16 [D_h]; out_dev DEVICE [G][D_h].
  * Same asynchrony, ownership, hint and error rules as hi_prefill_head.
  */
@@ -282,8 +283,9 @@ hi_status hi_decode_group(hi_ctx* ctx, int32_t layer, int32_t kv_head, int32_t n
  * sequences of different lengths served as more KV heads (the paper runs batch 1; Section 3.2 notes the head-wise
  * partition extends to the batch dimension): head j has past_lens[j] rows (HOST array, read before the call returns),
  * its token's row is appended at row past_lens[j] and attends over rows 0..past_lens[j].  One split-KV launch over
- * all heads (a head with fewer rows than partitions leaves neutral partials), one combine launch.  Buffers as in
- * hi_decode_group.  HI_ERR_UNSUPPORTED for offloaded or streaming heads (the heads of an offloaded group share
+ * all heads - partitions in proportion to the lengths where these are far apart, the same number for every head otherwise
+ * (a head with fewer rows than partitions leaves neutral partials) - and one combine launch, which short histories do
+ * without as in hi_decode_head.  Buffers as in hi_decode_group.  HI_ERR_UNSUPPORTED for offloaded or streaming heads (the heads of an offloaded group share
  * staging slices of one length: call those one by one, each at its own past_len).
  */
 hi_status hi_decode_group_ragged(hi_ctx* ctx, int32_t layer, int32_t kv_head, int32_t n_heads, const void* q_dev,
@@ -325,7 +327,8 @@ hi_status hi_decode_group_ragged(hi_ctx* ctx, int32_t layer, int32_t kv_head, in
  *   attn [n_q_heads][chunk_len][128] (the out_dev of the attention calls) and W_o [d_model][n_q_heads * 128].
  * d_model must be a multiple of 128; every operand must be smaller than 4 GiB; all pointers 16-byte aligned.
  * Both enqueue on `stream` (a hipStream_t) and return.  Errors: HI_ERR_ARG, HI_ERR_UNSUPPORTED, HI_ERR_HIP.
- * chunk_len = 1 (decode) takes a matrix-vector kernel bound by the HBM read of the weights (workspace not used).
+ * chunk_len = 1 (decode) takes a matrix-vector kernel, 2 to 64 one that streams the weights through the whole chip: both are
+ * bound by the read of the weights, and neither uses the workspace (which 2 to 64 rotated rows still have to pass).
  */
 hi_status hi_proj_workspace_bytes(int32_t chunk_len, int64_t* bytes);
 hi_status hi_qkv_rope(void* stream, const void* x_dev, const void* w_qkv_dev, int32_t d_model, int32_t n_q_heads,

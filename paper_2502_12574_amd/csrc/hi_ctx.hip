@@ -304,7 +304,8 @@ int pf_variant(const hi_ctx* c) {
 // context has counters for it.  What that saves is the second launch, 2.5 us of host time, which is what bounds a token at
 // short contexts (32 layers of 8 heads at 1K: 13.6 us a layer against 16.6); on the GPU it is 8.4 us against 5.6 + 3.9.
 // With 32 partitions the last workgroup alone takes 6.4 us where the combine kernel, spread over the chip, takes 4
-// (between 16 and 32 nothing was measured).  A captured step keeps the second launch: a graph may outlive the context, and
+// (where between the two ways cross was not measured: 8 heads of 1024 rows, one launch, and of 1025, two, both take 10.9 us
+// of a caller that waits for neither).  A captured step keeps the second launch: a graph may outlive the context, and
 // then its launches must hold no memory but the caller's.
 bool can_tail(hi_ctx* c, int np, int nh) {
   if (np > kTailMaxParts || nh > kTailMaxHeads || c->capturing || c->counters_refused) return false;
@@ -929,7 +930,8 @@ extern "C" hi_status hi_decode_group(hi_ctx* c, int32_t layer, int32_t kv_head, 
 }
 
 // One token of n_heads HBM-resident KV heads whose histories differ in length (a batch of sequences served as more KV
-// heads): one split-KV launch over all of them, each head reading its own number of rows, one combine launch.
+// heads): one split-KV launch over all of them, each head reading its own number of rows, and one combine launch unless no
+// head has more partitions than the split-KV launch combines itself.
 extern "C" hi_status hi_decode_group_ragged(hi_ctx* c, int32_t layer, int32_t kv_head, int32_t n_heads, const void* q_dev,
                                             const void* k_new_dev, const void* v_new_dev, const int64_t* past_lens,
                                             void* out_dev) {

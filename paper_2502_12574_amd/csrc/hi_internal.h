@@ -3,6 +3,7 @@
 #include <cstdint>
 #include <cstddef>
 #include "headinfer.h"
+#include "hi_prefill_part.h"
 
 namespace hi {
 
@@ -64,7 +65,7 @@ inline PrefillLaunch prefill_launch_shape(int G, int64_t chunk_len, int n_heads,
   p.nbk = (int)ceil_div(chunk_len, 2 * strip);
   p.deep = base == 3 || (base == 0 && (int64_t)p.nbk * gy * n_heads * p.split >= kPrefillDeepMinWorkgroups);
   p.paired = p.merge = p.xcd = p.past_tiles = 0;
-  p.img_row = 2 * p.nbk * p.split;
+  p.img_row = pf_images_per_row(p.nbk, p.split);
   if (p.deep) {
     // tiles the workgroups of the deepest block sweep beyond the average (the causal triangle), which pairing removes
     const int64_t saved = (int64_t)(2 * strip / 64) * (p.nbk - 1) / (2 * p.split);

@@ -20,7 +20,7 @@
 #include <cstdint>
 
 #if defined(__HIPCC__)
-#define HI_HD __host__ __device__ __forceinline__
+#define HI_HD __host__ __device__ inline __attribute__((always_inline))
 #else
 #define HI_HD inline
 #endif

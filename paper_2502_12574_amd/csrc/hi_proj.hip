@@ -401,8 +401,11 @@ __global__ __launch_bounds__(256, 1) void proj_gemm_kernel(ProjArgs p) {
 // 600 tokens of Llama-3-8B are 72 (Q/K/V) and 48 (output) of the large tiles on 256 compute units, 240 and 160 of these.
 // A wavefront owns 64 x 64 (2 x 2 blocks of the 32x32x16 MFMA; its A rows are 32 wa .. +31 and 64 + 32 wa .. +31, so that
 // rotary pairs still meet in one lane).  A step of 64 contraction elements moves 32 KB into LDS and 64 KB out of it, 750
-// cycles at its 128 bytes a cycle, which is the 0.31 us measured per step (the 16 MFMAs of a wavefront take 512): a fifth
-// stage changed nothing.  One workgroup per compute unit has to cover the latency of its loads itself: four stages of
+// cycles or 0.31 us at its 128 bytes a cycle (the 16 MFMAs of a wavefront take 512).  Measured over contractions of 1024 to
+// 8192 at 600 tokens, kernel time is 5 to 6 us to launch, fill the ring and write, and per step 0.53 us with weights from
+// HBM and 0.43 with weights from the caches for the 240 workgroups of Q/K/V, 0.45 and 0.35 for the 160 of the output: it
+// grows with the workgroups that load, 15 to 18 TB/s out of the L2s, so what binds is the feed of the ring, not the LDS
+// (a fifth stage changed nothing).  One workgroup per compute unit has to cover the latency of its loads itself: four stages of
 // 32 KB, loads three steps (of 64 elements) ahead, operand reads two sub-steps ahead.  The order of every sum is the large
 // tile's, so the results are the same bits.  Measured (hidden size 4096, 32 + 16 heads, weights of 6 layers in turn;
 // large tile -> small): Q/K/V with its table at 64 / 600 / 1000 / 2000 tokens 90 -> 33, 97 -> 40, 102 -> 69, 110 -> 108 us,

@@ -103,7 +103,7 @@ def test_more_contexts_than_counter_slots():
     past, G, H = 130, 4, 2
     q, k, v = (torch.randn(s, device=DEV).to(torch.bfloat16) for s in ((H, G, 128), (H, 128), (H, 128)))
     rows = torch.randn(1, H, 2, past, 128, device=DEV).to(torch.bfloat16)
-    outs = []
+    outs, one_launch = [], []
     for _ in range(2):
         open_ = [Session(1, H, G, 256, 1, mode=hb.HI_MODE_RESIDENT, out_fp32=1) for _ in range(70)]
         for ss in open_:
@@ -113,9 +113,13 @@ def test_more_contexts_than_counter_slots():
             ss.decode_group(0, 0, H, q, k, v, past, out)
             outs.append(out)
         for ss in open_:
+            ss.sync()
+        one_launch.append(sum(ss.stats().n_combine_kernels == 0 for ss in open_))
+        for ss in open_:
             ss.close()
-    for out in outs:                    # three partials, summed in the same order by either way up to fp32 rounding
-        assert (out - outs[0]).abs().max() <= 1e-5
+    assert one_launch == [64, 64]
+    for out in outs:                    # three partials, summed in the same order by either way
+        assert torch.equal(out, outs[0])
 
 
 @pytest.mark.parametrize("lens", [[5000, 3, 0, 64, 65, 1290], [70000, 1, 1, 20000], [2000] * 20, [15, 16, 17, 0, 1, 900, 4000, 129]])

@@ -1,4 +1,4 @@
-// Host-side check of prefill_unit_shape (compiled and run by test_prefill_partition_cpu.py): the launches of a unit with
+// Host-side check of prefill_unit_shape (compiled and run by test_prefill_unit_shape.py): the launches of a unit with
 // the split and pairing chosen for it are replayed on sets of tile ids, as partition_check.cpp does for the default
 // shape - every block of positions must have seen each of its tiles exactly once, no image may lie outside the
 // capacity, and the closed form of pf_contributors must agree with counting.
