@@ -529,6 +529,7 @@ extern "C" hi_status hi_ctx_create(const hi_problem* problem, const hi_plan* pla
     hi_ctx_destroy(c);
     return (hi_status)HI_ERR_HIP;
   };
+  if (mode == HI_MODE_RESIDENT || problem->resident_heads > 0 || count_streaming(*problem) > 0) tail_counters_prepare();
   c->ev_unit.assign(kUnitRing, nullptr);
   for (int i = 0; i < kUnitRing; ++i)
     if ((e = hipEventCreateWithFlags(&c->ev_unit[i], hipEventDisableTiming)) != hipSuccess) return fail(e, "hipEventCreate");

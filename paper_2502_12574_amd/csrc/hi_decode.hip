@@ -439,19 +439,30 @@ static __device__ int tail_counters[kTailSlots * kTailMaxHeads];
 namespace {
 std::mutex tail_mu;
 struct TailSlot { bool taken; hipEvent_t busy_until; } tail_slots[kTailSlots];
-}  // namespace
 
-int* tail_counters_take(void* stream, int* slot) {
-  static void* address[kTailDevices] = {};            // looking it up takes tens of microseconds: once per device
+// the array on the current device (tail_mu held); looking it up takes half a millisecond: once per device
+void* tail_array() {
+  static void* address[kTailDevices] = {};
   int dev = -1;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kTailDevices) { (void)hipGetLastError(); return nullptr; }
-  std::lock_guard<std::mutex> lock(tail_mu);
   void*& base = address[dev];
   if (!base && (hipGetSymbolAddress(&base, HIP_SYMBOL(tail_counters)) != hipSuccess || !base)) {
     (void)hipGetLastError();
     base = nullptr;
-    return nullptr;
   }
+  return base;
+}
+}  // namespace
+
+void tail_counters_prepare() {
+  std::lock_guard<std::mutex> lock(tail_mu);
+  (void)tail_array();
+}
+
+int* tail_counters_take(void* stream, int* slot) {
+  std::lock_guard<std::mutex> lock(tail_mu);
+  void* const base = tail_array();
+  if (!base) return nullptr;
   for (int i = 0; i < kTailSlots; ++i) {
     TailSlot& s = tail_slots[i];
     if (s.taken) continue;

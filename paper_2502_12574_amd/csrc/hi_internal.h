@@ -346,6 +346,8 @@ struct DecodeTail {
 // Counters for one context (kTailMaxHeads ints of the current device, zero for work enqueued on `stream` from now on; the
 // stream is not being captured): null when all slots are taken.  They are given back with the hipEvent_t that marks the end
 // of the context's last launch that used them, which is then theirs.
+// tail_counters_prepare does what only the first taking on a device has to do.
+void tail_counters_prepare();
 int* tail_counters_take(void* stream, int* slot);
 void tail_counters_give(int slot, void* busy_until);
 
