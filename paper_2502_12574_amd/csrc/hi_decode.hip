@@ -64,6 +64,15 @@ __device__ __forceinline__ void decode_tail(int kv, const uint16_t* q, int G, co
   float* sum = lds + 8 * kTailMaxParts;            // [n_part][G] sums
   const int64_t part_pitch = (int64_t)G * kPartialFloats;
   const int dim = 2 * lane;                        // a wavefront takes query heads wave and wave + 4, a lane two dims
+  uint16_t q_lo[2] = {0, 0}, q_hi[2] = {0, 0};     // asked for first: the scores are formed while the partials arrive
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int g = wave + 4 * h;
+    if (g < G) {
+      q_lo[h] = q[g * kHeadDim + lane];
+      q_hi[h] = q[g * kHeadDim + 64 + lane];
+    }
+  }
   float2 ml = make_float2(0.f, 0.f);
   if (tid < n_part * G) ml = load_shared2(part + (int64_t)tid * kPartialFloats + kHeadDim);
   float2 o[2][kTailMaxParts];
@@ -72,8 +81,10 @@ __device__ __forceinline__ void decode_tail(int kv, const uint16_t* q, int G, co
     const int g = wave + 4 * h;
     if (g < G) {
 #pragma unroll
-      for (int p = 0; p < kTailMaxParts; ++p)      // (past the last partial: its values again, not used)
-        o[h][p] = load_shared2(part + (p < n_part ? p : n_part - 1) * part_pitch + g * kPartialFloats + dim);
+      for (int p = 0; p < kTailMaxParts; ++p) {    // (past the last partial: zeros, as the combine kernel adds there)
+        o[h][p] = make_float2(0.f, 0.f);
+        if (p < n_part) o[h][p] = load_shared2(part + p * part_pitch + g * kPartialFloats + dim);
+      }
     }
   }
   if (tl.k_append != nullptr && wave == 0) {
@@ -81,6 +92,14 @@ __device__ __forceinline__ void decode_tail(int kv, const uint16_t* q, int G, co
     k_row[lane] = k_lo;
     k_row[lane + 64] = k_hi;
     *(uint32_t*)((char*)tl.v_append + append_off + 2 * dim) = v2;
+  }
+  // (the products of two bf16 numbers are exact: these are the combine kernel's dot products, fused or not)
+  float score[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    score[h] = bf16_bits_to_float(q_lo[h]) * bf16_bits_to_float(k_lo) + bf16_bits_to_float(q_hi[h]) * bf16_bits_to_float(k_hi);
+    if (4 * h < G)
+      for (int off = 32; off > 0; off >>= 1) score[h] += __shfl_xor(score[h], off);
   }
   if (tid < n_part * G) {
     w[tid] = ml.x;
@@ -91,10 +110,7 @@ __device__ __forceinline__ void decode_tail(int kv, const uint16_t* q, int G, co
   for (int h = 0; h < 2; ++h) {
     const int g = wave + 4 * h;
     if (g >= G) break;
-    // (the products of two bf16 numbers are exact: this is the combine kernel's dot product, fused or not)
-    float d = bf16_bits_to_float(q[g * kHeadDim + lane]) * bf16_bits_to_float(k_lo) +
-              bf16_bits_to_float(q[g * kHeadDim + 64 + lane]) * bf16_bits_to_float(k_hi);
-    for (int off = 32; off > 0; off >>= 1) d += __shfl_xor(d, off);
+    const float d = score[h];
     const float m = lane < n_part ? w[lane * G + g] : kNegBig;
     float mx = fmaxf(d, m);
     for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
@@ -106,11 +122,9 @@ __device__ __forceinline__ void decode_tail(int kv, const uint16_t* q, int G, co
 #pragma unroll
     for (int p = 0; p < kTailMaxParts; ++p) {
       const float x = __shfl(wp, p), l = __shfl(lp, p);
-      if (p < n_part) {                            // (not left to a weight of 0: a partial may be infinite)
-        acc.x += x * o[h][p].x;
-        acc.y += x * o[h][p].y;
-        total += l;
-      }
+      acc.x += x * o[h][p].x;
+      acc.y += x * o[h][p].y;
+      total += l;
     }
     acc.x = __builtin_fmaf(p_new, __uint_as_float(v2 << 16), acc.x);
     acc.y = __builtin_fmaf(p_new, __uint_as_float(v2 & 0xFFFF0000u), acc.y);
