@@ -11,13 +11,14 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
-def _run(mode, G, H, nh, past, C, seed, budget):
+def _run(mode, G, H, nh, past, C, seed, budget, flags=0):
     gen = torch.Generator(device=DEV).manual_seed(seed)
     rows = torch.randn(H, 2, past + C, 128, device=DEV, generator=gen).to(torch.bfloat16)
     rows[:, 0][torch.rand(H, past + C, device=DEV, generator=gen) < 0.05] *= 4
     q = torch.randn(H, G, C, 128, device=DEV, generator=gen).to(torch.bfloat16)
     out = torch.full((H, G, C, 128), float("nan"), device=DEV)
     with Session(1, H, G, past + C, C, mode=mode, out_fp32=1, gpu_kv_budget_heads=budget) as ss:
+        hb.hi_ctx_set_flags(ss.ctx, flags)
         ss.cache_view()[0, :, :, :past] = rows[:, :, :past].to(ss.cache_view().device)
         torch.cuda.synchronize()
         k, v = rows[:, 0, past:].contiguous(), rows[:, 1, past:].contiguous()
@@ -41,6 +42,8 @@ def test_same_bits_in_both_modes_and_any_grouping(G, H, nh, past, C, budget):
     a, (q, rows), _ = _run(hb.HI_MODE_RESIDENT, G, H, nh, past, C, seed, budget)
     b, _, slices = _run(hb.HI_MODE_OFFLOAD, G, H, nh, past, C, seed, budget)
     assert slices > 1 and torch.equal(a, b)
+    c, _, _ = _run(hb.HI_MODE_OFFLOAD, G, H, nh, past, C, seed, budget, hb.HI_FLAG_PREFILL_SINGLE_SLICES)
+    assert torch.equal(a, c)                # (by default two short slices go into one launch)
     one, _, _ = _run(hb.HI_MODE_RESIDENT, G, H, 1, past, C, seed, budget)
     assert torch.equal(a, one)
     # and the right ones: fp64 on the same rows, the parity tests' bounds
