@@ -285,8 +285,8 @@ hi_status hi_decode_group(hi_ctx* ctx, int32_t layer, int32_t kv_head, int32_t n
  * its token's row is appended at row past_lens[j] and attends over rows 0..past_lens[j].  One split-KV launch over
  * all heads - partitions in proportion to the lengths where these are far apart, the same number for every head otherwise
  * (a head with fewer rows than partitions leaves neutral partials) - and one combine launch, which short histories do
- * without as in hi_decode_head.  Buffers as in hi_decode_group.  HI_ERR_UNSUPPORTED for offloaded or streaming heads (the heads of an offloaded group share
- * staging slices of one length: call those one by one, each at its own past_len).
+ * without as in hi_decode_head.  Buffers as in hi_decode_group.  HI_ERR_UNSUPPORTED for offloaded or streaming heads
+ * (the heads of an offloaded group share staging slices of one length: call those one by one, each at its own past_len).
  */
 hi_status hi_decode_group_ragged(hi_ctx* ctx, int32_t layer, int32_t kv_head, int32_t n_heads, const void* q_dev,
                                  const void* k_new_dev, const void* v_new_dev, const int64_t* past_lens, void* out_dev);
