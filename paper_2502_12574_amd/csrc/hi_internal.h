@@ -89,7 +89,8 @@ constexpr int kPrefillCus = 256;
 // merge 5 + 0.03 per image; for the largest group this kernel serves at this chunk length (all_heads: heads of a layer).
 // Measured, uncut -> cut (the 8-wave kernel at its best split): 30 rows of 8 heads behind 100 thousand 1795 -> 104 us (127),
 // 64 rows 1788 -> 141 (134), 64 rows behind 5000 107 -> 25 (36); one head: 512 rows behind 1536 48 -> 23, 900 rows behind 20
-// thousand 389 -> 63 (71), behind 60 thousand 1093 -> 139 (124).
+// thousand 389 -> 63 (71), behind 60 thousand 1093 -> 139 (124).  Error against 64 bits over 24 shapes (mean of the relative
+// 2-norms): 0.00122 -> 0.00099 (0.00110).
 inline int prefill_narrow_split(int G, int64_t C, int64_t past, int64_t capacity, int all_heads) {
   const int strip = prefill_strip(G), gy = prefill_grid_y(G);
   int64_t heads = (kPrefillDeepMinWorkgroups / kPrefillMaxSplit - 1) / (ceil_div(C, 2 * strip) * gy);
