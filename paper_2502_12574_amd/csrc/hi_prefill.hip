@@ -52,6 +52,7 @@ struct PrefillArgs {
   int img_row;            // state images per grid row (8-wave kernel; 4-wave kernel with split > 1)
   int xcd;                // see pf_wg_index
   int tile0, past_tiles;  // 4-wave kernel with split > 1: first tile of the past segment in the unit, past tiles of the unit
+  uint32_t by_split, by_nbk;       // 8-wave kernel: see pf_magic
   int a_jump_tile;        // the past segment's tiles from this one on lie a_jump_bytes further on (0: one piece)
   int64_t a_jump_bytes;
 };
@@ -67,6 +68,17 @@ __device__ __forceinline__ int pf_select_head(PrefillArgs& a) {
   a.kb += rows * kRowBytes;
   a.vb += rows * kRowBytes;
   return blockIdx.y - head * a.gy;
+}
+
+// The launch's shape as the work partition takes it (strip: positions per block).
+__host__ __device__ __forceinline__ PfShape pf_shape_of(const PrefillArgs& a, int strip) {
+  PfShape sh;
+  sh.nbk = a.nbk; sh.m = strip / kPfTileRows;
+  sh.ta = (int)((a.na + kPfTileRows - 1) / kPfTileRows);
+  sh.tb_all = (int)((a.nb + kPfTileRows - 1) / kPfTileRows);
+  sh.split = a.split; sh.paired = a.paired; sh.carried = !a.first;
+  sh.by_split = a.by_split; sh.by_nbk = a.by_nbk;
+  return sh;
 }
 
 __device__ __forceinline__ int swz_k(int row) { return row & 15; }
@@ -152,6 +164,7 @@ __device__ __forceinline__ void pf_issue_tile(const char* kt, const char* vt, in
 
 typedef __attribute__((address_space(3))) bf16x8 lds_bf16x8;
 typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
+typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 
 struct PfState {
   f32x16 o[4];
@@ -656,11 +669,7 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel_deep(PrefillArgs a) {
   // How the launch divides its tiles among workgroups is pure arithmetic on the launch's shape: at most two passes
   // per workgroup, each over a range of one block's tile sequence (its past tiles, then the chunk's own tiles up to
   // the block's causal boundary), each with a softmax state of its own.
-  PfShape sh;
-  sh.nbk = a.nbk; sh.m = strip / kPfTileRows;
-  sh.ta = (int)((a.na + kPfTileRows - 1) / kPfTileRows);
-  sh.tb_all = (int)((a.nb + kPfTileRows - 1) / kPfTileRows);
-  sh.split = a.split; sh.paired = a.paired; sh.carried = !a.first;
+  const PfShape sh = pf_shape_of(a, strip);
   constexpr int kLanes = kPdWaves * 64;
   constexpr int kImageFloats = kCarryFloatsPerLane * kLanes;
   float* const images = a.carry + (int64_t)blockIdx.y * a.img_row * kImageFloats + threadIdx.x;
@@ -948,13 +957,15 @@ __device__ __forceinline__ void q4_set(f32x16& v, int k, const f32x4& x) {
   v[4 * k] = x[0]; v[4 * k + 1] = x[1]; v[4 * k + 2] = x[2]; v[4 * k + 3] = x[3];
 }
 
+// NQ: blocks of 16 query rows the wavefront works on (2; 1 where the chunk's end leaves the second one empty)
+template <int NQ>
 struct PfState16 {
-  f32x16 o[4];        // tile (db, qb) is quarter (2 db + qb) % 4 of o[(2 db + qb) / 4]
-  float m[2], l[2];
+  f32x16 o[2 * NQ];   // tile (db, qb) is quarter (NQ db + qb) % 4 of o[(NQ db + qb) / 4]
+  float m[NQ], l[NQ];
 };
-// element r of accumulator tile (db, qb) of O^T, and of score tile (kb, qb) in f32x16 s[2]
-#define PF16_O(st, db, qb, r) (st).o[(2 * (db) + (qb)) >> 2][4 * ((2 * (db) + (qb)) & 3) + (r)]
-#define PF16_S(s, kb, qb, r) (s)[(2 * (kb) + (qb)) >> 2][4 * ((2 * (kb) + (qb)) & 3) + (r)]
+// element r of accumulator tile (db, qb) of O^T, and of score tile (kb, qb) in f32x16 s[NQ]
+#define PF16_O(st, db, qb, r) (st).o[(NQ * (db) + (qb)) >> 2][4 * ((NQ * (db) + (qb)) & 3) + (r)]
+#define PF16_S(s, kb, qb, r) (s)[(NQ * (kb) + (qb)) >> 2][4 * ((NQ * (kb) + (qb)) & 3) + (r)]
 
 __device__ __forceinline__ void pf16_issue_k(const char* kt, int rows, uint32_t lds_tile, int wave, int lane,
                                              const PfLane16& lc) {
@@ -1015,11 +1026,11 @@ __device__ __forceinline__ void pd16_preread(uint32_t v_off, const PfLane16& lc,
 // The matrix phase: O^T += V^T P^T of the previous tile, then S^T = K Q^T of the next - 64 MFMAs, their 32 LDS operands
 // read kPfAhead operands ahead.  LOADS: 0 = the phase issues the global loads that ld names (either may be null),
 // 1 = both unconditionally.  Other switches as in pd_matrix_phase.
-template <int LOADS, bool PREREAD, bool CINIT, bool EARLY_BARRIER = false>
+template <int LOADS, bool PREREAD, bool CINIT, bool EARLY_BARRIER, int NQ>
 __device__ __forceinline__ void pd16_matrix_phase(uint32_t v_off, uint32_t k_off, const PfLane16& lc,
-                                                  const bf16x8 (&qf)[4][2], const bf16x8 (&pb)[2][2], PfState16& st,
-                                                  f32x16 (&s)[2], const PfPhaseLoads& ld,
-                                                  const bf16x8 (&pre)[kPfAhead], const f32x4 (&cinit)[2]) {
+                                                  const bf16x8 (&qf)[4][NQ], const bf16x8 (&pb)[2][NQ], PfState16<NQ>& st,
+                                                  f32x16 (&s)[NQ], const PfPhaseLoads& ld,
+                                                  const bf16x8 (&pre)[kPfAhead], const f32x4 (&cinit)[NQ]) {
   bf16x8 op[kPfAhead + 1];
 #pragma unroll
   for (int i = 0; i < kPfAhead; ++i) op[i] = PREREAD ? pre[i] : pd16_operand(i, v_off, k_off, lc);
@@ -1036,55 +1047,60 @@ __device__ __forceinline__ void pd16_matrix_phase(uint32_t v_off, uint32_t k_off
     if (i < 16) {
       const int kp = pd16_kp(i), db = pd16_db(i);
 #pragma unroll
-      for (int qb = 0; qb < 2; ++qb) {
-        const int t4 = 2 * db + qb;
+      for (int qb = 0; qb < NQ; ++qb) {
+        const int t4 = NQ * db + qb;
         q4_set(st.o[t4 >> 2], t4 & 3,
                __builtin_amdgcn_mfma_f32_16x16x32_bf16(x, pb[kp][qb], q4_get(st.o[t4 >> 2], t4 & 3), 0, 0, 0));
       }
     } else {
       const int kk = pd16_kk(i), kb = pd16_kb(i);
 #pragma unroll
-      for (int qb = 0; qb < 2; ++qb) {
-        const int t4 = 2 * kb + qb;
+      for (int qb = 0; qb < NQ; ++qb) {
+        const int t4 = NQ * kb + qb;
         const f32x4 z = {0.f, 0.f, 0.f, 0.f};
         const f32x4 c0 = kk == 0 ? (CINIT ? cinit[qb] : z) : q4_get(s[t4 >> 2], t4 & 3);
         q4_set(s[t4 >> 2], t4 & 3, __builtin_amdgcn_mfma_f32_16x16x32_bf16(x, qf[kk][qb], c0, 0, 0, 0));
       }
     }
-    if (i == 1 && (LOADS == 1 || ld.k)) g2lds16_s<0>(ld.k, lc.gk[0], ld.ldk);
-    if (i == 3 && (LOADS == 1 || ld.k)) g2lds16_s<0>(ld.k, lc.gk[1], ld.ldk + 1024);
-    if (i == 5 && (LOADS == 1 || ld.v)) g2lds16_s<0>(ld.v, lc.gv[0], ld.ldv);
-    if (i == 7 && (LOADS == 1 || ld.v)) g2lds16_s<0>(ld.v, lc.gv[1], ld.ldv + 1024);
+    if (i == 1 && (LOADS == 1 || (LOADS == 0 && ld.k))) g2lds16_s<0>(ld.k, lc.gk[0], ld.ldk);
+    if (i == 3 && (LOADS == 1 || (LOADS == 0 && ld.k))) g2lds16_s<0>(ld.k, lc.gk[1], ld.ldk + 1024);
+    if (i == 5 && (LOADS == 1 || (LOADS == 0 && ld.v))) g2lds16_s<0>(ld.v, lc.gv[0], ld.ldv);
+    if (i == 7 && (LOADS == 1 || (LOADS == 0 && ld.v))) g2lds16_s<0>(ld.v, lc.gv[1], ld.ldv + 1024);
     __builtin_amdgcn_sched_barrier(0);
   }
 }
 
-// maximum over the four 16-lane groups that hold the key rows of one query
+// combine the values of the four 16-lane groups that hold the key rows of one query: rows of 16 lanes, then halves, change
+// places inside the register file (no LDS round trip)
 __device__ __forceinline__ float max_groups16(float x) {
-  x = fmaxf(x, __shfl_xor(x, 16));
-  return fmaxf(x, __shfl_xor(x, 32));
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return max_halves(fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1])));
 }
 __device__ __forceinline__ float sum_groups16(float x) {
-  x += __shfl_xor(x, 16);
-  return x + __shfl_xor(x, 32);
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return sum_halves(__uint_as_float(r[0]) + __uint_as_float(r[1]));
 }
 
 // Online softmax of one tile (general form: raw scores, running maximum moved when it must, masks).  rel[qb]: key
 // rows of the tile with index > rel[qb] are hidden from the lane's query of block qb.
-__device__ __forceinline__ void pf16_softmax(f32x16 (&s)[2], PfState16& st, float c, bool masked, const int (&rel)[2],
-                                             int g16, bf16x8 (&pb)[2][2]) {
-  if (masked) {
+template <int NQ>
+__device__ __forceinline__ void pf16_mask(f32x16 (&s)[NQ], const int (&rel)[NQ], int g16) {
 #pragma unroll
-    for (int kb = 0; kb < 4; ++kb)
+  for (int kb = 0; kb < 4; ++kb)
 #pragma unroll
-      for (int qb = 0; qb < 2; ++qb)
+    for (int qb = 0; qb < NQ; ++qb)
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
-          if (16 * kb + 4 * g16 + r > rel[qb]) PF16_S(s, kb, qb, r) = kNegBig;
-  }
-  float m_new[2];
+      for (int r = 0; r < 4; ++r)
+        if (16 * kb + 4 * g16 + r > rel[qb]) PF16_S(s, kb, qb, r) = kNegBig;
+}
+
+template <int NQ>
+__device__ __forceinline__ void pf16_softmax(f32x16 (&s)[NQ], PfState16<NQ>& st, float c, bool masked, const int (&rel)[NQ],
+                                             int g16, bf16x8 (&pb)[2][NQ]) {
+  if (masked) pf16_mask<NQ>(s, rel, g16);
+  float m_new[NQ];
 #pragma unroll
-  for (int qb = 0; qb < 2; ++qb) {
+  for (int qb = 0; qb < NQ; ++qb) {
     float mx = PF16_S(s, 0, qb, 0);
 #pragma unroll
     for (int kb = 0; kb < 4; ++kb)
@@ -1092,9 +1108,9 @@ __device__ __forceinline__ void pf16_softmax(f32x16 (&s)[2], PfState16& st, floa
       for (int r = 0; r < 4; ++r) mx = fmaxf(mx, PF16_S(s, kb, qb, r));
     m_new[qb] = fmaxf(st.m[qb], max_groups16(mx));
   }
-  if (__builtin_amdgcn_ballot_w64(m_new[0] > st.m[0] || m_new[1] > st.m[1]) != 0) {
+  if (__builtin_amdgcn_ballot_w64(m_new[0] > st.m[0] || m_new[NQ - 1] > st.m[NQ - 1]) != 0) {
 #pragma unroll
-    for (int qb = 0; qb < 2; ++qb) {
+    for (int qb = 0; qb < NQ; ++qb) {
       const float alpha = fast_exp2((st.m[qb] - m_new[qb]) * c);
       st.l[qb] *= alpha;
 #pragma unroll
@@ -1105,7 +1121,7 @@ __device__ __forceinline__ void pf16_softmax(f32x16 (&s)[2], PfState16& st, floa
     }
   }
 #pragma unroll
-  for (int qb = 0; qb < 2; ++qb) {
+  for (int qb = 0; qb < NQ; ++qb) {
     const float mc = st.m[qb] * c;
     float lsum = 0.f;
 #pragma unroll
@@ -1121,7 +1137,7 @@ __device__ __forceinline__ void pf16_softmax(f32x16 (&s)[2], PfState16& st, floa
 #pragma unroll
   for (int kp = 0; kp < 2; ++kp)
 #pragma unroll
-    for (int qb = 0; qb < 2; ++qb) asm volatile("" : "+v"(pb[kp][qb]));
+    for (int qb = 0; qb < NQ; ++qb) asm volatile("" : "+v"(pb[kp][qb]));
 }
 
 // Softmax phase of a steady-state tile: the scores left the matrix pipe relative to the running reference (the
@@ -1129,19 +1145,24 @@ __device__ __forceinline__ void pf16_softmax(f32x16 (&s)[2], PfState16& st, floa
 // it must (see pf_softmax_fast).  The scores are scaled in place first, so that the 32 multiplications and the 32
 // exponentials are independent instructions (with a shared temporary they formed one dependent chain).
 // PRESCALED: the queries carry the softmax scale already (c is 1): the scores are exponents as they leave the matrix pipe.
-template <bool PRESCALED>
-__device__ __forceinline__ void pf16_softmax_fast(f32x16 (&s)[2], PfState16& st, float c, f32x4 (&cinit)[2],
-                                                  bf16x8 (&pb)[2][2]) {
+// least: kPfSumLimit, or 1 in short passes, where the reference also moves when a lane's sum of this tile exceeds 1 and half of
+// all it has summed before.  A row that one
+// key dominates then has that key at exactly 1, which bf16 holds exactly; against a lower reference the rounding of
+// its weight is the row's whole error (600 rows behind 3000, one key in ten scaled by four: relative error 1.4e-3 against
+// 64 bits).  Rows whose weight is spread do not get there, and need not.
+template <bool PRESCALED, int NQ>
+__device__ __forceinline__ void pf16_softmax_fast(f32x16 (&s)[NQ], PfState16<NQ>& st, float c, float least,
+                                                  f32x4 (&cinit)[NQ], bf16x8 (&pb)[2][NQ]) {
   if (!PRESCALED) {
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int j = 0; j < NQ; ++j)
 #pragma unroll
       for (int r = 0; r < 16; ++r) s[j][r] *= c;
   }
-  float ls[2];
+  float ls[NQ];
   auto probs = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int qb = 0; qb < 2; ++qb) {
+    for (int qb = 0; qb < NQ; ++qb) {
       float lq[2];
 #pragma unroll
       for (int kb = 0; kb < 4; ++kb)
@@ -1155,10 +1176,13 @@ __device__ __forceinline__ void pf16_softmax_fast(f32x16 (&s)[2], PfState16& st,
     }
   };
   probs();
-  if (__builtin_amdgcn_ballot_w64(!(ls[0] <= kPfSumLimit) || !(ls[1] <= kPfSumLimit)) != 0) {    // also inf and NaN
+  float limit[NQ];
+#pragma unroll
+  for (int qb = 0; qb < NQ; ++qb) limit[qb] = __builtin_amdgcn_fmed3f(0.5f * st.l[qb], least, kPfSumLimit);
+  if (__builtin_amdgcn_ballot_w64(!(ls[0] <= limit[0]) || !(ls[NQ - 1] <= limit[NQ - 1])) != 0) {    // also inf and NaN
     const float inv_c = 1.0f / c;
 #pragma unroll
-    for (int qb = 0; qb < 2; ++qb) {
+    for (int qb = 0; qb < NQ; ++qb) {
       float mx = PF16_S(s, 0, qb, 0);
 #pragma unroll
       for (int kb = 0; kb < 4; ++kb)
@@ -1184,12 +1208,12 @@ __device__ __forceinline__ void pf16_softmax_fast(f32x16 (&s)[2], PfState16& st,
     }
     probs();
   }
-  st.l[0] += ls[0];
-  st.l[1] += ls[1];
+#pragma unroll
+  for (int qb = 0; qb < NQ; ++qb) st.l[qb] += ls[qb];
 #pragma unroll
   for (int kp = 0; kp < 2; ++kp)
 #pragma unroll
-    for (int qb = 0; qb < 2; ++qb) asm volatile("" : "+v"(pb[kp][qb]));
+    for (int qb = 0; qb < NQ; ++qb) asm volatile("" : "+v"(pb[kp][qb]));
 }
 
 // Normalise and write the lane's parts of the query row of block QB: dims 16 (db0 + d) + 4 g16 + 0..3 for d < NDB
@@ -1216,19 +1240,28 @@ __device__ __forceinline__ void pf16_write_row(void* out, int out_fp32, int C, i
   }
 }
 
-template <bool PRESCALED>
-__global__ __launch_bounds__(512, 2) void prefill_kernel_deep16(PrefillArgs a) {
-  extern __shared__ __attribute__((aligned(1024))) char lds_dyn[];
-  lds_char* lds = (lds_char*)lds_dyn;
-  const uint32_t lds_base = (uint32_t)(uintptr_t)lds;
-  const int lane = lane_id();
-  const int wave = wave_id();
+// Passes up to here move their references early throughout (see pf16_softmax_fast).  Longer ones do so in their first eight tiles
+// only: with peaked keys most tiles of a pass would (77 rows behind 100 thousand, 98 tiles: 242 us instead of 175).
+constexpr int kPd16ShortTiles = 32;
+
+// One pass of a workgroup of prefill_kernel_deep16: the tiles of `ps` on a softmax state of their own, by a wavefront that
+// has NQ blocks of 16 query rows before the chunk's end (NQ = 0: it has none, and only takes its share of the tile loads and
+// the barriers).  Rows that are not there cost matrix instructions, and with them clock: the kernel runs at the power limit.
+// What a pass costs, by time stamps of 600 rows of 8 heads behind 3000 (240 workgroups of 17 tiles): 6.5 us until the first
+// tile is done (the fill of 144 KB per workgroup), 1.8 us for each of the next three, 1.5 for every other one, 2 to
+// store the state; 42 us in all.  Before, only groups of four tiles that were full, unmasked and followed by full ones ran the
+// steady routine; the others, 11 of 17 here, took one of 2.6 us that took the maxima, chose its ring slot and its loads tile by
+// tile and added every operand's address between the MFMAs, and integer divisions took 3 us at the start: 59 us.  Now
+// every tile from the fifth on is a steady one, with two scalar counters and a comparison more.
+template <bool PRESCALED, int NQ>
+__device__ __forceinline__ void pd16_pass(const PrefillArgs& a, const PfPass& ps, uint32_t lds_base, int lane,
+                                          int wave, int g, int strip, int i0, float* images) {
+  constexpr int kLanes = kPdWaves * 64;
+  constexpr int kImageFloats = kCarryFloatsPerLane * kLanes;
+  constexpr int NS = NQ > 0 ? NQ : 1;                 // array sizes
+  asm volatile("" : "+v"(lane));                      // lane constants are formed in the pass, not kept across passes
   const int g16 = lane >> 4;
   const int c16 = lane & 15;
-
-  const int gl = a.G < 4 ? a.G : 4;
-  const int strip = 32 * (kPdWaves / gl);
-  const int g = pf_select_head(a) * 4 + (wave % gl);
 
   PfLane16 lc;
   {
@@ -1251,23 +1284,348 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel_deep16(PrefillArgs a) {
     }
   }
 
-  PfShape sh;
-  sh.nbk = a.nbk; sh.m = strip / kPfTileRows;
-  sh.ta = (int)((a.na + kPfTileRows - 1) / kPfTileRows);
-  sh.tb_all = (int)((a.nb + kPfTileRows - 1) / kPfTileRows);
-  sh.split = a.split; sh.paired = a.paired; sh.carried = !a.first;
+  PfSweep sw;
+  const char *ka_p = a.ka, *va_p = a.va;
+  {
+    const int64_t start = pf_sweep_of(sw, ps, a.na, a.nb, a.a_jump_tile, a.a_jump_bytes);
+    ka_p += start;
+    va_p += start;
+  }
+  const int T = sw.T;
+
+  auto issue = [&](int t, int which) __attribute__((always_inline)) {
+    if (t >= T) return;
+    const uint32_t slot = lds_base + (uint32_t)(t & (kPdStages - 1)) * kPfTileBytes;
+    if (which == 0) pf16_issue_k((t >= sw.ta ? a.kb : ka_p) + pf_tile_offset(sw, t), pf_tile_rows(sw, t), slot, wave, lane, lc);
+    else pf16_issue_v((t >= sw.ta ? a.vb : va_p) + pf_tile_offset(sw, t), pf_tile_rows(sw, t), slot + kPdVRing, wave, lane, lc);
+  };
+  auto wait_landed = [&](int t) __attribute__((always_inline)) {
+    if (t + 3 < T) wait_vmcnt<4>();
+    else wait_vmcnt<0>();
+  };
+  auto phase_barrier = [&]() __attribute__((always_inline)) {
+    __builtin_amdgcn_sched_barrier(0);
+    __syncthreads();
+    __builtin_amdgcn_sched_barrier(0);
+  };
+
+  // the alternating schedule, barrier protocol and ring discipline of prefill_kernel_deep
+  const int group = wave >> 2;
+  const float c = a.c;
+  wait_vmcnt<0>();                   // the waits below count this pass's tile loads only (a previous pass's stores are done)
+  issue(0, 0);                       // asked for before the queries: one latency for both
+  issue(1, 0); issue(0, 1);
+  issue(2, 0); issue(1, 1);
+
+  if constexpr (NQ == 0) {
+    wait_landed(-1);
+    phase_barrier();
+    if (group == 1) phase_barrier();
+    for (int t = 0; t < T; ++t) {
+      issue(t + 3, 0);
+      issue(t + 2, 1);
+      phase_barrier();
+      wait_landed(t);
+      phase_barrier();
+    }
+    if (group == 0) phase_barrier();
+    if (ps.store >= 0 && !a.last) {          // a later launch may read the image in a kernel that works on all rows
+      float* im = images + (int64_t)ps.store * kImageFloats;
+#pragma unroll
+      for (int i = 0; i < 64; ++i) im[i * kLanes] = 0.f;
+      im[64 * kLanes] = im[65 * kLanes] = kNegBig;
+      im[66 * kLanes] = im[67 * kLanes] = 0.f;
+    }
+    return;
+  }
+
+  // Q^T operands: lane holds q[g][qi[qb]][32*kk + 8*g16 .. +7]
+  int my_i[NS];
+  bf16x8 qf[4][NS];
+#pragma unroll
+  for (int qb = 0; qb < NQ; ++qb) {
+    my_i[qb] = i0 + 16 * qb + c16;
+    const int qi = my_i[qb] > a.C - 1 ? a.C - 1 : my_i[qb];
+    const uint16_t* qrow = a.q + ((int64_t)g * a.C + qi) * kHeadDim + 8 * g16;
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) qf[kk][qb] = __builtin_bit_cast(bf16x8, *(const uint4*)(qrow + 32 * kk));
+  }
+
+  PfState16<NS> st;
+  if (ps.load < 0) {
+#pragma unroll
+    for (int qb = 0; qb < NQ; ++qb) {
+      st.m[qb] = kNegBig;
+      st.l[qb] = 0.f;
+    }
+#pragma unroll
+    for (int j = 0; j < 2 * NQ; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) st.o[j][r] = 0.f;
+  } else {
+    const float* im = images + (int64_t)ps.load * kImageFloats;
+#pragma unroll
+    for (int db = 0; db < 8; ++db)
+#pragma unroll
+      for (int qb = 0; qb < NQ; ++qb)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) PF16_O(st, db, qb, r) = im[((2 * db + qb) * 4 + r) * kLanes];
+#pragma unroll
+    for (int qb = 0; qb < NQ; ++qb) {
+      st.m[qb] = im[(64 + qb) * kLanes];
+      st.l[qb] = im[(66 + qb) * kLanes];
+    }
+  }
+  // the compiler's own waits for the loads above belong here
+#pragma unroll
+  for (int qb = 0; qb < NQ; ++qb) {
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) asm volatile("" : "+v"(qf[kk][qb]));
+    asm volatile("" : "+v"(st.m[qb]), "+v"(st.l[qb]));
+  }
+#pragma unroll
+  for (int j = 0; j < 2 * NQ; ++j) asm volatile("" : "+v"(st.o[j]));
+
+  wait_landed(-1);                   // K(0), K(1), V(0)
+  phase_barrier();
+  if (group == 1) phase_barrier();
+
+  f32x16 sc[NS];
+  bf16x8 pb[2][NS];
+  // is tile t partly hidden from a row of this wavefront, and which of its rows each query sees (up to rel)
+  auto hidden = [&](int t) __attribute__((always_inline)) {
+    return pf_tile_rows(sw, t) < kPfTileRows || (t >= sw.ta && (t + sw.own0) * kPfTileRows + kPfTileRows - 1 > i0);
+  };
+  auto last_seen = [&](int t, int (&rel)[NS]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int qb = 0; qb < NQ; ++qb) {
+      int lim = pf_tile_rows(sw, t) - 1;
+      if (t >= sw.ta) {
+        const int d = my_i[qb] - (t + sw.own0) * kPfTileRows;
+        lim = d < lim ? d : lim;
+      }
+      rel[qb] = lim;
+    }
+  };
+  // a tile's softmax that takes its maximum first: the first tile of a pass, and passes without a reference (see below)
+  auto softmax_phase = [&](int t) __attribute__((always_inline)) {
+    int rel[NS];
+    const bool h = hidden(t);
+    if (h) last_seen(t, rel);
+    pf16_softmax<NS>(sc, st, c, h, rel, g16, pb);
+  };
+  // tile 0: nothing to accumulate yet
+  issue(3, 0);
+  issue(2, 1);
+#pragma unroll
+  for (int i = 16; i < 32; ++i) {
+    const bf16x8 x = pd16_operand(i, 0, 0, lc);
+    const int kk = pd16_kk(i), kb = pd16_kb(i);
+    const f32x4 z = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int qb = 0; qb < NQ; ++qb) {
+      const int t4 = NQ * kb + qb;
+      q4_set(sc[t4 >> 2], t4 & 3,
+             __builtin_amdgcn_mfma_f32_16x16x32_bf16(x, qf[kk][qb], kk == 0 ? z : q4_get(sc[t4 >> 2], t4 & 3), 0, 0, 0));
+    }
+  }
+  phase_barrier();
+  softmax_phase(0);
+  wait_landed(0);
+  phase_barrier();
+  bf16x8 pre[kPfAhead];
+  f32x4 cinit[NS];     // minus the running references, the start values of the score accumulators behind the first tiles
+  pd16_preread(0, lc, pre);
+  // The tiles a tile's matrix phase asks for, K(t+3) and V(t+2), as two streams (see PfStream): every tile issues the same four
+  // loads and waits for the same number, and all but a few per pass cost a pointer increment, in the softmax phase.
+  PfStream sk, sv;
+  auto clamp_rows = [&](uint32_t (&g)[2], int rows, bool is_v) __attribute__((always_inline)) {
+    const int r_in = lane >> 4, cpos = lane & 15;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int r = (wave * 2 + i) * 4 + r_in;
+      g[i] = (uint32_t)((r < rows ? r : rows - 1) * kRowBytes + ((cpos ^ (is_v ? swz_v16(r) : swz_k(r))) << 4));
+    }
+  };
+  pf_stream_start(sk, sw, 4, ka_p, a.kb);
+  pf_stream_start(sv, sw, 3, va_p, a.vb);
+  clamp_rows(lc.gk, sk.rows, false);
+  clamp_rows(lc.gv, sv.rows, true);
+  // tiles this wavefront does not see in full: from mask_t on (own rows), and the partial past tile
+  const int part_a = sw.full_a < sw.ta ? sw.full_a : -1;
+  int mask_t = (i0 + 1) / kPfTileRows - sw.own0;
+  if (mask_t < sw.ta) mask_t = sw.ta;
+  const uint32_t ld_wave = lds_base + wave * 2048;
+  float least = 1.0f;                            // of the first eight tiles, and of short passes
+  // Tile t: its matrix phase, which passes the barrier in its middle itself; `after` between the barrier and the softmax.
+  // GENERAL: the softmax takes its maximum first and the scores start from zero.
+  auto tile = [&](int t, uint32_t v_off, uint32_t k_off, uint32_t ldk, uint32_t ldv, auto general_tag, auto after) __attribute__((always_inline)) {
+    constexpr bool GENERAL = decltype(general_tag)::value;
+    PfPhaseLoads ld;
+    ld.k = sk.p;
+    ld.v = sv.p;
+    ld.ldk = ld_wave + ldk;
+    ld.ldv = ld_wave + kPdVRing + ldv;
+    __builtin_amdgcn_s_setprio(2);
+    pd16_matrix_phase<1, true, !GENERAL, true, NS>(v_off, k_off, lc, qf, pb, st, sc, ld, pre, cinit);
+    __builtin_amdgcn_s_setprio(0);
+    after();                                     // V(t)'s first operands, for the next matrix phase
+    __builtin_amdgcn_sched_barrier(0);
+    if (GENERAL) {
+      softmax_phase(t);
+    } else {
+      if (t >= mask_t || t == part_a) {
+        int rel[NS];
+        last_seen(t, rel);
+        pf16_mask<NS>(sc, rel, g16);
+      }
+      pf16_softmax_fast<PRESCALED, NS>(sc, st, c, least, cinit, pb);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    sk.p += sk.step;
+    sv.p += sv.step;
+    if (--sk.left == 0) {
+      pf_stream_meet(sk, sw, t + 4, ka_p, a.kb);
+      clamp_rows(lc.gk, sk.rows, false);
+    }
+    if (--sv.left == 0) {
+      pf_stream_meet(sv, sw, t + 3, va_p, a.vb);
+      clamp_rows(lc.gv, sv.rows, true);
+    }
+    wait_vmcnt<4>();                             // everything up to V(t+1) has landed
+    phase_barrier();
+  };
+  // The first four tiles take their maxima: the largest weight of a row is then exactly 1 where one of them holds it, as under
+  // a decaying bias.  From there on every row has a reference - it has seen a past row, or an own row at or before the first
+  // position of this wavefront; a range of own tiles that begins behind that may leave rows without one, and goes on so.
+  const bool no_reference = sw.ta == 0 && ps.b0 * kPfTileRows > i0;
+  const int general = no_reference || T < 4 ? T : 4;
+  int t = 1;
+  uint32_t slot = 0;                             // ring offset of tile t - 1; the operand addresses move with it
+#pragma nounroll
+  for (; t < general; ++t) {
+    const uint32_t next = (slot + kPfTileBytes) & (kPdStages * kPfTileBytes - 1);
+    const uint32_t d = next - slot, prev = (slot - kPfTileBytes) & (kPdStages * kPfTileBytes - 1);
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) lc.koff[kk] += d;
+    tile(t, 0, 0, slot, prev, std::true_type(), [&]() __attribute__((always_inline)) {
+#pragma unroll
+      for (int db = 0; db < 8; ++db) lc.voff[db] += d;
+      pd16_preread(0, lc, pre);
+    });
+    slot = next;
+  }
+  if (t < T) {                                   // t = 4: the rings are back at their starts
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) {
+      lc.koff[kk] -= 3 * kPfTileBytes;
+      asm volatile("" : "+v"(lc.koff[kk]));      // (the compiler would carry the difference into every operand's address)
+    }
+#pragma unroll
+    for (int db = 0; db < 8; ++db) {
+      lc.voff[db] -= 3 * kPfTileBytes;
+      asm volatile("" : "+v"(lc.voff[db]));
+    }
+#pragma unroll
+    for (int qb = 0; qb < NQ; ++qb)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) cinit[qb][r] = -st.m[qb];
+    // Tile t in ring slot S = t % 4, a compile-time constant: every LDS address is an immediate.
+    auto steady = [&](auto stage_tag) __attribute__((always_inline)) {
+      constexpr uint32_t S = decltype(stage_tag)::value, kT = kPfTileBytes;
+      tile(t, ((S + 3) & 3) * kT, S * kT, ((S + 3) & 3) * kT, ((S + 2) & 3) * kT, std::false_type(),
+           [&]() __attribute__((always_inline)) { pd16_preread(S * kT, lc, pre); });
+      return ++t >= T;
+    };
+#pragma nounroll
+    for (;;) {
+      if (steady(std::integral_constant<uint32_t, 0>())) break;
+      if (steady(std::integral_constant<uint32_t, 1>())) break;
+      if (steady(std::integral_constant<uint32_t, 2>())) break;
+      if (steady(std::integral_constant<uint32_t, 3>())) break;
+      if (T > kPd16ShortTiles) least = kPfSumLimit;
+    }
+    slot = (uint32_t)((T - 1) & (kPdStages - 1)) * kPfTileBytes;
+#pragma unroll
+    for (int db = 0; db < 8; ++db) lc.voff[db] += slot;
+  }
+  {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const bf16x8 x = pd16_operand(i, 0, 0, lc);
+      const int kp2 = pd16_kp(i), db = pd16_db(i);
+#pragma unroll
+      for (int qb = 0; qb < NQ; ++qb) {
+        const int t4 = NQ * db + qb;
+        q4_set(st.o[t4 >> 2], t4 & 3,
+               __builtin_amdgcn_mfma_f32_16x16x32_bf16(x, pb[kp2][qb], q4_get(st.o[t4 >> 2], t4 & 3), 0, 0, 0));
+      }
+    }
+  }
+  wait_vmcnt<0>();                   // no load may reach the LDS of a workgroup that has ended
+  if (group == 0) phase_barrier();
+
+  if (ps.store >= 0) {
+    float* im = images + (int64_t)ps.store * kImageFloats;
+#pragma unroll
+    for (int db = 0; db < 8; ++db)
+#pragma unroll
+      for (int qb = 0; qb < NQ; ++qb)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) im[((2 * db + qb) * 4 + r) * kLanes] = PF16_O(st, db, qb, r);
+#pragma unroll
+    for (int qb = 0; qb < NQ; ++qb) {
+      im[(64 + qb) * kLanes] = st.m[qb];
+      im[(66 + qb) * kLanes] = st.l[qb];
+    }
+    if (NQ == 1 && !a.last) {                // the empty block's state, as above
+#pragma unroll
+      for (int db = 0; db < 8; ++db)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) im[((2 * db + 1) * 4 + r) * kLanes] = 0.f;
+      im[65 * kLanes] = kNegBig;
+      im[67 * kLanes] = 0.f;
+    }
+  } else {
+#pragma unroll
+    for (int qb = 0; qb < NQ; ++qb) {
+      f32x4 rows[8];
+#pragma unroll
+      for (int db = 0; db < 8; ++db) rows[db] = q4_get(st.o[(NQ * db + qb) >> 2], (NQ * db + qb) & 3);
+      pf16_write_row<8>(a.out, a.out_fp32, a.C, g, my_i[qb], g16, 0, rows, st.l[qb]);
+    }
+  }
+}
+
+template <bool PRESCALED>
+__global__ __launch_bounds__(512, 2) void prefill_kernel_deep16(PrefillArgs a) {
+  extern __shared__ __attribute__((aligned(1024))) char lds_dyn[];
+  lds_char* lds = (lds_char*)lds_dyn;
+  const uint32_t lds_base = (uint32_t)(uintptr_t)lds;
+  const int lane = lane_id();
+  const int wave = wave_id();
+  const int gl = a.G < 4 ? a.G : 4;
+  const int strip = 32 * (kPdWaves / gl);
+  const int g = pf_select_head(a) * 4 + (wave % gl);
+
+  const PfShape sh = pf_shape_of(a, strip);
   constexpr int kLanes = kPdWaves * 64;
   constexpr int kImageFloats = kCarryFloatsPerLane * kLanes;
   float* const images = a.carry + (int64_t)blockIdx.y * a.img_row * kImageFloats + threadIdx.x;
   const int wg = pf_wg_index(blockIdx.x, gridDim.x, a.xcd);
-  int first_which = 0;
-  {
-    const PfPass d = pf_pass(sh, wg, 0, a.last), sw = pf_pass(sh, wg, 1, a.last);
-    if (sw.run && sw.a1 > sw.a0 && !(d.run && d.a1 > d.a0)) first_which = 1;
+  // the pass that holds past tiles goes first, so that the workgroups of a range walk the past rows in step
+  PfPass ps = pf_pass(sh, wg, 0, a.last), other;
+  other.run = other.init = 0;
+  if (a.paired) {
+    other = pf_pass(sh, wg, 1, a.last);
+    if (other.run && other.a1 > other.a0 && !(ps.run && ps.a1 > ps.a0)) {
+      const PfPass x = ps;
+      ps = other;
+      other = x;
+    }
   }
 #pragma nounroll
   for (int pi = 0; pi < 2; ++pi) {
-    const PfPass ps = pf_pass(sh, wg, first_which ^ pi, a.last);
     if (ps.init) {
       float* im = images + (int64_t)ps.store * kImageFloats;
 #pragma unroll
@@ -1277,259 +1635,16 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel_deep16(PrefillArgs a) {
       im[66 * kLanes] = 0.f;
       im[67 * kLanes] = 0.f;
     }
-    if (!ps.run) continue;
-    __syncthreads();
-    const int bx = ps.bx;
-    const int i0 = bx * strip + 32 * (wave / gl);
-    int my_i[2], qi[2];
-#pragma unroll
-    for (int qb = 0; qb < 2; ++qb) {
-      my_i[qb] = i0 + 16 * qb + c16;
-      qi[qb] = my_i[qb] > a.C - 1 ? a.C - 1 : my_i[qb];
+    if (ps.run) {
+      __syncthreads();               // the LDS rings are free again (a previous pass may still be reading V tiles)
+      const int i0 = ps.bx * strip + 32 * (wave / gl);
+      const int left = a.C - i0;     // rows of this wavefront's 32 that exist
+      if (left > 16) pd16_pass<PRESCALED, 2>(a, ps, lds_base, lane, wave, g, strip, i0, images);
+      else if (left > 0) pd16_pass<PRESCALED, 1>(a, ps, lds_base, lane, wave, g, strip, i0, images);
+      else pd16_pass<PRESCALED, 0>(a, ps, lds_base, lane, wave, g, strip, i0, images);
     }
-
-    // Q^T operands: lane holds q[g][qi[qb]][32*kk + 8*g16 .. +7]
-    bf16x8 qf[4][2];
-#pragma unroll
-    for (int qb = 0; qb < 2; ++qb) {
-      const uint16_t* qrow = a.q + ((int64_t)g * a.C + qi[qb]) * kHeadDim + 8 * g16;
-#pragma unroll
-      for (int kk = 0; kk < 4; ++kk) qf[kk][qb] = __builtin_bit_cast(bf16x8, *(const uint4*)(qrow + 32 * kk));
-    }
-
-    // a past segment in two pieces: the pass's tiles from jr on lie a.a_jump_bytes further on
-    int jr = a.a_jump_tile > 0 ? a.a_jump_tile - ps.a0 : 0x7fffffff;
-    const int64_t jump0 = jr <= 0 ? a.a_jump_bytes : 0;        // the whole pass is behind the jump
-    if (jr <= 0) jr = 0x7fffffff;
-    const char* const ka_p = a.ka + (int64_t)ps.a0 * kPfTileBytes + jump0;
-    const char* const va_p = a.va + (int64_t)ps.a0 * kPfTileBytes + jump0;
-    auto a_jump = [&](int t) { return t >= jr ? a.a_jump_bytes : (int64_t)0; };
-    int64_t na_p = (int64_t)ps.a1 * kPfTileRows;
-    if (na_p > a.na) na_p = a.na;
-    na_p -= (int64_t)ps.a0 * kPfTileRows;
-    const int b_t0 = ps.b0;
-    const int tb = ps.b1 - ps.b0;
-
-    PfState16 st;
-    if (ps.load < 0) {
-      st.m[0] = st.m[1] = kNegBig;
-      st.l[0] = st.l[1] = 0.f;
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) st.o[j][r] = 0.f;
-    } else {
-      const float* im = images + (int64_t)ps.load * kImageFloats;
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) st.o[j][r] = im[(16 * j + r) * kLanes];     // = ((2 db + qb) * 4 + r)
-      st.m[0] = im[64 * kLanes];
-      st.m[1] = im[65 * kLanes];
-      st.l[0] = im[66 * kLanes];
-      st.l[1] = im[67 * kLanes];
-    }
-#pragma unroll
-    for (int kk = 0; kk < 4; ++kk) asm volatile("" : "+v"(qf[kk][0]), "+v"(qf[kk][1]));
-    asm volatile("" : "+v"(st.m[0]), "+v"(st.m[1]), "+v"(st.l[0]), "+v"(st.l[1]));
-#pragma unroll
-    for (int j = 0; j < 4; ++j) asm volatile("" : "+v"(st.o[j]));
-
-    const int ta = (int)((na_p + kPfTileRows - 1) / kPfTileRows);
-    const int T = ta + tb;
-    const int tb_base = b_t0 - ta;
-
-    auto issue = [&](int t, int which) __attribute__((always_inline)) {
-      if (t >= T) return;
-      const bool in_b = t >= ta;
-      const int64_t row0 = (int64_t)(in_b ? t + tb_base : t) * kPfTileRows;
-      const int64_t left = (in_b ? a.nb : na_p) - row0;
-      const int rows = left < kPfTileRows ? (int)left : kPfTileRows;
-      const uint32_t slot = lds_base + (uint32_t)(t & (kPdStages - 1)) * kPfTileBytes;
-      if (which == 0) pf16_issue_k((in_b ? a.kb : ka_p + a_jump(t)) + row0 * kRowBytes, rows, slot, wave, lane, lc);
-      else pf16_issue_v((in_b ? a.vb : va_p + a_jump(t)) + row0 * kRowBytes, rows, slot + kPdVRing, wave, lane, lc);
-    };
-    auto wait_landed = [&](int t) {
-      if (t + 3 < T) wait_vmcnt<4>();
-      else wait_vmcnt<0>();
-    };
-    auto phase_barrier = [&]() {
-      __builtin_amdgcn_sched_barrier(0);
-      __syncthreads();
-      __builtin_amdgcn_sched_barrier(0);
-    };
-
-    // the alternating schedule, barrier protocol and ring discipline of prefill_kernel_deep
-    const int group = wave >> 2;
-    const float c = a.c;
-    wait_vmcnt<0>();
-    issue(0, 0);
-    issue(1, 0); issue(0, 1);
-    issue(2, 0); issue(1, 1);
-    wait_landed(-1);
-    phase_barrier();
-    if (group == 1) phase_barrier();
-
-    f32x16 sc[2];
-    bf16x8 pb[2][2];
-    auto softmax_phase = [&](int t) __attribute__((always_inline)) {
-      const bool in_b = t >= ta;
-      const int64_t j0 = (int64_t)(in_b ? t + tb_base : t) * kPfTileRows;
-      const int64_t n_seg = in_b ? a.nb : na_p;
-      const bool masked = (j0 + kPfTileRows > n_seg) || (in_b && (j0 + kPfTileRows - 1 > i0));
-      int rel[2] = {kPfTileRows, kPfTileRows};
-      if (masked) {
-#pragma unroll
-        for (int qb = 0; qb < 2; ++qb) {
-          int64_t lim = n_seg - 1;
-          if (in_b && (int64_t)my_i[qb] < lim) lim = my_i[qb];
-          const int64_t d = lim - j0;
-          rel[qb] = d < -1 ? -1 : (d > kPfTileRows ? kPfTileRows : (int)d);
-        }
-      }
-      pf16_softmax(sc, st, c, masked, rel, g16, pb);
-    };
-    // tile 0: nothing to accumulate yet
-    issue(3, 0);
-    issue(2, 1);
-#pragma unroll
-    for (int i = 16; i < 32; ++i) {
-      const bf16x8 x = pd16_operand(i, 0, 0, lc);
-      const int kk = pd16_kk(i), kb = pd16_kb(i);
-      const f32x4 z = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int qb = 0; qb < 2; ++qb) {
-        const int t4 = 2 * kb + qb;
-        q4_set(sc[t4 >> 2], t4 & 3,
-               __builtin_amdgcn_mfma_f32_16x16x32_bf16(x, qf[kk][qb], kk == 0 ? z : q4_get(sc[t4 >> 2], t4 & 3), 0, 0, 0));
-      }
-    }
-    phase_barrier();
-    softmax_phase(0);
-    wait_landed(0);
-    phase_barrier();
-    bf16x8 pre[kPfAhead];
-    f32x4 cinit[2];      // minus the running references, the start values of the steady-state score accumulators
-    cinit[0] = cinit[1] = (f32x4){0.f, 0.f, 0.f, 0.f};
-    auto generic_tile = [&](int t) __attribute__((always_inline)) {
-      PfPhaseLoads ld;
-      ld.k = ld.v = nullptr;
-      const int tk = t + 3, tv = t + 2;
-      const bool kb = tk >= ta, vb = tv >= ta;
-      const int64_t krow0 = (int64_t)(kb ? tk + tb_base : tk) * kPfTileRows;
-      const int64_t vrow0 = (int64_t)(vb ? tv + tb_base : tv) * kPfTileRows;
-      const bool kfull = tk < T && (kb ? a.nb : na_p) - krow0 >= kPfTileRows;
-      const bool vfull = tv < T && (vb ? a.nb : na_p) - vrow0 >= kPfTileRows;
-      if (kfull) ld.k = (kb ? a.kb : ka_p + a_jump(tk)) + krow0 * kRowBytes; else issue(tk, 0);
-      if (vfull) ld.v = (vb ? a.vb : va_p + a_jump(tv)) + vrow0 * kRowBytes; else issue(tv, 1);
-      ld.ldk = lds_base + (uint32_t)(tk & (kPdStages - 1)) * kPfTileBytes + wave * 2048;
-      ld.ldv = lds_base + kPdVRing + (uint32_t)(tv & (kPdStages - 1)) * kPfTileBytes + wave * 2048;
-      pd16_matrix_phase<0, false, false>((uint32_t)((t - 1) & (kPdStages - 1)) * kPfTileBytes,
-                                             (uint32_t)(t & (kPdStages - 1)) * kPfTileBytes, lc, qf, pb, st, sc, ld, pre,
-                                             cinit);
-      phase_barrier();
-      softmax_phase(t);
-      wait_landed(t);
-      phase_barrier();
-    };
-    const char* kp = ka_p;
-    const char* vp = va_p;
-    const uint32_t ld_wave = lds_base + wave * 2048;
-    auto fast_tile = [&](auto stage_tag) __attribute__((always_inline)) {
-      constexpr int S = decltype(stage_tag)::value;
-      PfPhaseLoads ld;
-      ld.k = kp;
-      ld.v = vp;
-      ld.ldk = ld_wave + ((S + 3) & 3) * kPfTileBytes;
-      ld.ldv = ld_wave + kPdVRing + ((S + 2) & 3) * kPfTileBytes;
-      __builtin_amdgcn_s_setprio(2);
-      pd16_matrix_phase<1, true, true, true>(((S + 3) & 3) * kPfTileBytes, S * kPfTileBytes, lc, qf, pb, st, sc, ld,
-                                             pre, cinit);
-      __builtin_amdgcn_s_setprio(0);
-      pd16_preread(S * kPfTileBytes, lc, pre);
-      __builtin_amdgcn_sched_barrier(0);
-      pf16_softmax_fast<PRESCALED>(sc, st, c, cinit, pb);
-      wait_vmcnt<4>();
-      phase_barrier();
-      kp += kPfTileBytes;
-      vp += kPfTileBytes;
-    };
-    int t = 1;
-    // t_min: the run may not start before this tile (the tiles up to it go through the general routine first)
-    auto fast_run = [&](int t_end, const char* kbase, const char* vbase, int tile0, int t_min) __attribute__((always_inline)) {
-      if (t_end - (t > t_min ? t : t_min) < 8) return;
-      while ((t & 3) || t < t_min) { generic_tile(t); ++t; }
-      kp = kbase + (int64_t)(t + 3 - tile0) * kPfTileBytes;
-      vp = vbase + (int64_t)(t + 2 - tile0) * kPfTileBytes;
-      pd16_preread((uint32_t)((t - 1) & (kPdStages - 1)) * kPfTileBytes, lc, pre);
-#pragma unroll
-      for (int qb = 0; qb < 2; ++qb)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) cinit[qb][r] = -st.m[qb];
-      for (; t + 4 <= t_end; t += 4) {
-        fast_tile(std::integral_constant<int, 0>());
-        fast_tile(std::integral_constant<int, 1>());
-        fast_tile(std::integral_constant<int, 2>());
-        fast_tile(std::integral_constant<int, 3>());
-      }
-    };
-    {
-      // steady-state tiles load K(t+3) and V(t+2) through running pointers: a run stays on one side of a jump (one
-      // call site for both sides: every copy of the loop the compiler has to fit costs the others registers)
-      const int a_end = (int)(na_p / kPfTileRows) - 3;
-      const int pieces = jr < ta ? 2 : 1;
-#pragma nounroll
-      for (int piece = 0; piece < pieces; ++piece) {
-        const int64_t off = piece ? a.a_jump_bytes : 0;
-        int end = a_end;
-        if (piece == 0 && pieces == 2 && jr - 3 < end) end = jr - 3;
-        fast_run(end, ka_p + off, va_p + off, 0, piece ? jr - 2 : 0);
-      }
-    }
-    while (t < ta && t < T) { generic_tile(t); ++t; }
-    {
-      const int64_t unmasked = ((int64_t)bx * strip + 1) / kPfTileRows;
-      const int64_t loadable = a.nb / kPfTileRows - 3;
-      const int64_t j_end = unmasked < loadable ? unmasked : loadable;
-      const int64_t t_end = j_end - tb_base < T - 3 ? j_end - tb_base : T - 3;
-      fast_run((int)t_end, a.kb, a.vb, -tb_base, 0);
-    }
-    for (; t < T; ++t) generic_tile(t);
-    {
-      const uint32_t v_off = (uint32_t)((T - 1) & (kPdStages - 1)) * kPfTileBytes;
-#pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const bf16x8 x = pd16_operand(i, v_off, 0, lc);
-        const int kp2 = pd16_kp(i), db = pd16_db(i);
-#pragma unroll
-        for (int qb = 0; qb < 2; ++qb) {
-          const int t4 = 2 * db + qb;
-          q4_set(st.o[t4 >> 2], t4 & 3,
-                 __builtin_amdgcn_mfma_f32_16x16x32_bf16(x, pb[kp2][qb], q4_get(st.o[t4 >> 2], t4 & 3), 0, 0, 0));
-        }
-      }
-    }
-    if (group == 0) phase_barrier();
-
-    if (ps.store >= 0) {
-      float* im = images + (int64_t)ps.store * kImageFloats;
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) im[(16 * j + r) * kLanes] = st.o[j][r];
-      im[64 * kLanes] = st.m[0];
-      im[65 * kLanes] = st.m[1];
-      im[66 * kLanes] = st.l[0];
-      im[67 * kLanes] = st.l[1];
-    } else {
-#pragma unroll
-      for (int qb = 0; qb < 2; ++qb) {
-        f32x4 rows[8];
-#pragma unroll
-        for (int db = 0; db < 8; ++db) rows[db] = q4_get(st.o[(2 * db + qb) >> 2], (2 * db + qb) & 3);
-        pf16_write_row<8>(a.out, a.out_fp32, a.C, g, my_i[qb], g16, 0, rows, st.l[qb]);
-      }
-    }
+    ps = other;
+    other.run = other.init = 0;
   }
 }
 
@@ -1550,11 +1665,7 @@ __global__ __launch_bounds__(512) void prefill_merge16_kernel(PrefillArgs a) {
   if (i0 >= a.C) return;                    // rows past the chunk's end
   constexpr int kLanes = kPdWaves * 64;
   constexpr int kImageFloats = kCarryFloatsPerLane * kLanes;
-  PfShape sh;
-  sh.nbk = a.nbk; sh.m = strip / kPfTileRows;
-  sh.ta = (int)((a.na + kPfTileRows - 1) / kPfTileRows);
-  sh.tb_all = (int)((a.nb + kPfTileRows - 1) / kPfTileRows);
-  sh.split = a.split; sh.paired = a.paired; sh.carried = !a.first;
+  const PfShape sh = pf_shape_of(a, strip);
   int n_e, n_x;
   pf_block_images(sh, bx, n_e, n_x);
   if (n_e + n_x == 1 && a.split == 1) return;
@@ -1631,11 +1742,7 @@ __global__ __launch_bounds__(512) void prefill_merge_kernel(PrefillArgs a) {
   const int my_i = bx * strip + 32 * (wave / gl) + col;
   constexpr int kLanes = kPdWaves * 64;
   constexpr int kImageFloats = kCarryFloatsPerLane * kLanes;
-  PfShape sh;
-  sh.nbk = a.nbk; sh.m = strip / kPfTileRows;
-  sh.ta = (int)((a.na + kPfTileRows - 1) / kPfTileRows);
-  sh.tb_all = (int)((a.nb + kPfTileRows - 1) / kPfTileRows);
-  sh.split = a.split; sh.paired = a.paired; sh.carried = !a.first;
+  const PfShape sh = pf_shape_of(a, strip);
   int n_e, n_x;
   pf_block_images(sh, bx, n_e, n_x);
   if (n_e + n_x == 1 && a.split == 1) return;
@@ -2032,6 +2139,12 @@ hi_status launch_prefill(void* stream, const void* q, int G, int chunk_len, cons
   a.nbk = pl.nbk;
   a.img_row = pl.img_row;
   a.xcd = pl.xcd;
+  a.by_split = a.by_nbk = 0;
+  if (pl.deep) {
+    const PfShape sh = pf_shape_of(a, 2 * strip);
+    a.by_split = pf_magic((uint32_t)pl.split, pf_largest_cut(sh));
+    a.by_nbk = pf_magic((uint32_t)pl.nbk, (uint64_t)pl.nbk * (uint64_t)pl.split);
+  }
   a.tile0 = (int)sa.tile0;
   a.past_tiles = pl.past_tiles;
   if (!pl.deep && pl.split > 1 && (sa.tile0 < 0 || sa.tile0 + ceil_div(sa.n, kPfTileRows) > pl.past_tiles ||

@@ -35,7 +35,21 @@ struct PfShape {
   int split;    // workgroups per block
   int paired;   // balanced partition over (deep, shallow) pairs of blocks
   int carried;  // the images E hold states of earlier launches of the unit
+  uint32_t by_split = 0, by_nbk = 0;    // pf_magic of split and nbk (0: divide)
 };
+
+// x / d as one multiplication: the kernels divide by split and nbk before they can ask for their first byte, and the
+// compiler's division is about 40 dependent instructions of a lone wavefront (0.3 us each: 3 us of a 59 us launch of 600 rows
+// behind 3000 went to this arithmetic).  With magic = floor(2^32 / d) + 1 the quotient is exact for x d < 2^32; pf_magic gives
+// 0, and pf_div divides, where x can be larger.
+HI_HD uint32_t pf_magic(uint32_t d, uint64_t x_max) {
+  return d > 1 && x_max * d < (1ull << 32) ? (uint32_t)((1ull << 32) / d + 1) : 0;
+}
+HI_HD uint32_t pf_div(uint32_t x, uint32_t d, uint32_t magic) {
+  return magic ? (uint32_t)(((uint64_t)x * magic) >> 32) : d == 1 ? x : x / d;
+}
+// the largest number that pf_pass divides by split (the ranges' boundaries) in a launch of this shape
+HI_HD uint64_t pf_largest_cut(const PfShape& s) { return 2ull * ((uint64_t)s.ta + s.tb_all) * (2ull * s.split) + 2ull * s.nbk * s.split; }
 
 struct PfPass {
   int run;      // 1: tiles to process
@@ -105,19 +119,22 @@ HI_HD PfPass pf_pass(const PfShape& s, int w, int which, int last) {
   int deep, shallow, nr, k;
   const int pairs = s.paired ? s.nbk / 2 : 0;
   if (w < pairs * 2 * s.split) {
-    const int p = w / (2 * s.split);
+    const int p = (int)(pf_div((uint32_t)w, (uint32_t)s.split, s.by_split) >> 1);
     deep = s.nbk - 1 - p; shallow = p; nr = 2 * s.split; k = w - p * nr;
   } else {
-    // blocks on their own: the deepest first, range z of every block before range z + 1 of any
+    // blocks on their own: the deepest first, range z of every block before range z + 1 of any (of pairs, one is left or none)
     const int singles = s.nbk - 2 * pairs;
     const int v = w - pairs * 2 * s.split;
-    deep = s.nbk - pairs - 1 - (v % singles); shallow = -1; nr = s.split; k = v / singles;
+    k = pairs ? v : (int)pf_div((uint32_t)v, (uint32_t)s.nbk, s.by_nbk);
+    deep = s.nbk - pairs - 1 - (v - k * singles); shallow = -1; nr = s.split;
   }
   if (which == 1 && shallow < 0) return g;
   const int od = pf_own_tiles(s, deep), ob = shallow >= 0 ? pf_own_tiles(s, shallow) : 0;
   const int Td = s.ta + od;
   const int L = Td + (shallow >= 0 ? s.ta + ob : 0);
-  const int x0 = pf_cut(L, k, nr), x1 = pf_cut(L, k + 1, nr);
+  const int half = shallow >= 0 ? 1 : 0;        // nr = split << half: boundary k is floor(L k / split) >> half
+  const int x0 = (int)(pf_div((uint32_t)L * (uint32_t)k, (uint32_t)s.split, s.by_split) >> half);
+  const int x1 = (int)(pf_div((uint32_t)L * (uint32_t)(k + 1), (uint32_t)s.split, s.by_split) >> half);
   auto clampi = [](int x, int lo, int hi) { return x < lo ? lo : (x > hi ? hi : x); };
   if (which == 0) {
     g.bx = deep;
@@ -173,6 +190,72 @@ HI_HD PfRange pf_narrow_range(int past_tiles, int own_tiles, int k, int split, i
   r.hi = x1 < end ? x1 : end;
   r.fresh = x0 >= tile0;
   return r;
+}
+
+// The tiles of one pass of prefill_kernel_deep16, in the order in which it sweeps them: past tiles [0, ta), of which [0, full_a)
+// are full, then own tiles; tile t >= ta is tile t + own0 of the chunk's own rows.  A past segment in two pieces: its tiles
+// from jr on lie `jump` bytes further on.
+constexpr int kPfSweepRows = 64;
+constexpr int64_t kPfSweepBytes = 16384;
+struct PfSweep {
+  int ta, T, full_a, own0, own_full, jr;      // own_full: end of the full own tiles of the sweep
+  int64_t na, nb, jump;                       // rows of the past part; rows of the chunk
+};
+// fills w; returns the byte offset of the pass's first past tile in the launch's past segment
+HI_HD int64_t pf_sweep_of(PfSweep& w, const PfPass& ps, int64_t na, int64_t nb, int jump_tile, int64_t jump_bytes) {
+  const bool behind = jump_tile > 0 && jump_tile <= ps.a0;         // the whole pass lies behind the jump
+  w.jr = jump_tile > 0 && !behind ? jump_tile - ps.a0 : 0x7fffffff;
+  w.jump = jump_bytes;
+  int64_t end = (int64_t)ps.a1 * kPfSweepRows;
+  if (end > na) end = na;
+  w.na = end - (int64_t)ps.a0 * kPfSweepRows;
+  w.nb = nb;
+  w.ta = (int)((w.na + kPfSweepRows - 1) / kPfSweepRows);
+  w.full_a = (int)(w.na / kPfSweepRows);
+  w.T = w.ta + ps.b1 - ps.b0;
+  w.own0 = ps.b0 - w.ta;
+  const int64_t full = nb / kPfSweepRows - w.own0;
+  w.own_full = (int)(full < w.T ? full : w.T);
+  return (int64_t)ps.a0 * kPfSweepBytes + (behind ? jump_bytes : 0);
+}
+// byte offset of tile t behind the pass's past rows (t < ta) or the chunk's own rows, and its rows
+HI_HD int64_t pf_tile_offset(const PfSweep& w, int t) {
+  return t >= w.ta ? (int64_t)(t + w.own0) * kPfSweepBytes : (int64_t)t * kPfSweepBytes + (t >= w.jr ? w.jump : 0);
+}
+HI_HD int pf_tile_rows(const PfSweep& w, int t) {
+  const int64_t left = t >= w.ta ? w.nb - (int64_t)(t + w.own0) * kPfSweepRows : w.na - (int64_t)t * kPfSweepRows;
+  return left < kPfSweepRows ? (int)left : kPfSweepRows;
+}
+
+// A stream of tile loads, one tile after the other: the next one lies at p and has `rows` rows (the lanes' addresses are clamped
+// to them).  The caller goes on with p += step; --left, and calls pf_stream_meet with the next tile's number when left is 0:
+// there the stream meets the next piece of the past, the own rows, a partial tile, or the pass's end.  At the end it stays at
+// its last tile, which then lands in ring slots that nobody reads any more.
+struct PfStream { const char* p; int64_t step; int left, rows; };
+HI_HD void pf_stream_to(PfStream& s, const PfSweep& w, int u, const char* past, const char* own) {
+  s.rows = pf_tile_rows(w, u);
+  s.p = (u >= w.ta ? own : past) + pf_tile_offset(w, u);
+  if (s.rows == kPfSweepRows) {
+    s.step = kPfSweepBytes;
+    s.left = (u >= w.ta ? w.own_full : u < w.jr && w.jr < w.ta && w.jr < w.full_a ? w.jr : w.full_a) - u;
+  } else {
+    s.step = 0;
+    s.left = 1;
+  }
+}
+HI_HD void pf_stream_meet(PfStream& s, const PfSweep& w, int u, const char* past, const char* own) {
+  if (u < w.T) { pf_stream_to(s, w, u, past, own); return; }
+  s.p -= s.step;
+  s.step = 0;
+  s.left = 0x7fffffff;
+}
+// the stream in front of tile u of a pass that has one tile at least
+HI_HD void pf_stream_start(PfStream& s, const PfSweep& w, int u, const char* past, const char* own) {
+  pf_stream_to(s, w, u < w.T ? u : w.T - 1, past, own);
+  if (u >= w.T) {
+    s.step = 0;
+    s.left = 0x7fffffff;
+  }
 }
 
 }  // namespace hi

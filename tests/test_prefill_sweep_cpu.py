@@ -1,0 +1,20 @@
+"""The work partition's division by multiplication against the compiler's, and the tile loads of a pass (csrc/hi_prefill_part.h), on the host."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.mark.parametrize("name", ["partition_magic_check", "prefill_sweep_check"])
+def test_on_the_host(tmp_path, name):
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("no host C++ compiler")
+    exe = str(tmp_path / name)
+    subprocess.run([gxx, "-O2", "-std=c++17", "-I", os.path.join(ROOT, "paper_2502_12574_amd", "csrc"),
+                    os.path.join(ROOT, "tests", name + ".cpp"), "-o", exe], check=True)
+    r = subprocess.run([exe], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=300)
+    assert r.returncode == 0 and " 0 failures" in r.stdout, r.stdout[-2000:]
