@@ -49,6 +49,7 @@ struct PrefillArgs {
   int64_t a_head_stride;  // bytes between the heads' rows in the past segment
   int paired;             // 8-wave kernel: deep and shallow blocks of the causal triangle share their tiles
   int nbk;                // 8-wave kernel: blocks of positions per head
+  int strip;              // prefill_kernel_deep16: positions of a block
   int img_row;            // state images per grid row (8-wave kernel; 4-wave kernel with split > 1)
   int xcd;                // see pf_wg_index
   int tile0, past_tiles;  // 4-wave kernel with split > 1: first tile of the past segment in the unit, past tiles of the unit
@@ -74,6 +75,7 @@ __device__ __forceinline__ int pf_select_head(PrefillArgs& a) {
 __host__ __device__ __forceinline__ PfShape pf_shape_of(const PrefillArgs& a, int strip) {
   PfShape sh;
   sh.nbk = a.nbk; sh.m = strip / kPfTileRows;
+  sh.strip = strip;
   sh.ta = (int)((a.na + kPfTileRows - 1) / kPfTileRows);
   sh.tb_all = (int)((a.nb + kPfTileRows - 1) / kPfTileRows);
   sh.split = a.split; sh.paired = a.paired; sh.carried = !a.first;
@@ -1240,9 +1242,26 @@ __device__ __forceinline__ void pf16_write_row(void* out, int out_fp32, int C, i
   }
 }
 
-// Passes up to here move their references early throughout (see pf16_softmax_fast).  Longer ones do so in their first eight tiles
-// only: with peaked keys most tiles of a pass would (77 rows behind 100 thousand, 98 tiles: 242 us instead of 175).
-constexpr int kPd16ShortTiles = 32;
+// Passes up to kPd16ShortTiles move their references early throughout (see pf16_softmax_fast), longer ones in their last
+// kPd16LastTiles tiles only: with peaked keys most tiles of a pass would (77 rows behind 100 thousand, 98 tiles: 242 us
+// instead of 175).  (Not in the first ones: a reference just below a row's largest key leaves that key's weight just above 1,
+// where bf16 is coarsest.)
+constexpr int kPd16ShortTiles = 32, kPd16LastTiles = 12;
+
+// Where the wavefront's two blocks of 16 query rows lie in a block of a.strip positions: next to each other where the block is
+// full (the layout prefill_kernel_wide shares); with fewer positions every wavefront's first block comes before any second one,
+// so that both groups have work.  NQ of them are there (before the end of the block and of the chunk).
+struct Pf16Rows { int i0, step, nq; };
+__device__ __forceinline__ Pf16Rows pf16_rows(const PrefillArgs& a, int bx, int gl, int wave) {
+  const int subs = kPdWaves / gl, sub = wave / gl;
+  const bool full = a.strip == 32 * subs;
+  Pf16Rows r;
+  r.step = full ? 16 : 16 * subs;
+  r.i0 = bx * a.strip + (full ? 32 : 16) * sub;
+  const int end = (bx + 1) * a.strip < a.C ? (bx + 1) * a.strip : a.C;
+  r.nq = end - r.i0 > r.step ? 2 : end > r.i0 ? 1 : 0;
+  return r;
+}
 
 // One pass of a workgroup of prefill_kernel_deep16: the tiles of `ps` on a softmax state of their own, by a wavefront that
 // has NQ blocks of 16 query rows before the chunk's end (NQ = 0: it has none, and only takes its share of the tile loads and
@@ -1255,7 +1274,7 @@ constexpr int kPd16ShortTiles = 32;
 // every tile from the fifth on is a steady one, with two scalar counters and a comparison more.
 template <bool PRESCALED, int NQ>
 __device__ __forceinline__ void pd16_pass(const PrefillArgs& a, const PfPass& ps, uint32_t lds_base, int lane,
-                                          int wave, int g, int strip, int i0, float* images) {
+                                          int wave, int g, int i0, int step, float* images) {
   constexpr int kLanes = kPdWaves * 64;
   constexpr int kImageFloats = kCarryFloatsPerLane * kLanes;
   constexpr int NS = NQ > 0 ? NQ : 1;                 // array sizes
@@ -1344,7 +1363,7 @@ __device__ __forceinline__ void pd16_pass(const PrefillArgs& a, const PfPass& ps
   bf16x8 qf[4][NS];
 #pragma unroll
   for (int qb = 0; qb < NQ; ++qb) {
-    my_i[qb] = i0 + 16 * qb + c16;
+    my_i[qb] = i0 + step * qb + c16;
     const int qi = my_i[qb] > a.C - 1 ? a.C - 1 : my_i[qb];
     const uint16_t* qrow = a.q + ((int64_t)g * a.C + qi) * kHeadDim + 8 * g16;
 #pragma unroll
@@ -1456,7 +1475,7 @@ __device__ __forceinline__ void pd16_pass(const PrefillArgs& a, const PfPass& ps
   int mask_t = (i0 + 1) / kPfTileRows - sw.own0;
   if (mask_t < sw.ta) mask_t = sw.ta;
   const uint32_t ld_wave = lds_base + wave * 2048;
-  float least = 1.0f;                            // of the first eight tiles, and of short passes
+  float least = 1.0f;
   // Tile t: its matrix phase, which passes the barrier in its middle itself; `after` between the barrier and the softmax.
   // GENERAL: the softmax takes its maximum first and the scores start from zero.
   auto tile = [&](int t, uint32_t v_off, uint32_t k_off, uint32_t ldk, uint32_t ldv, auto general_tag, auto after) __attribute__((always_inline)) {
@@ -1539,11 +1558,11 @@ __device__ __forceinline__ void pd16_pass(const PrefillArgs& a, const PfPass& ps
     };
 #pragma nounroll
     for (;;) {
+      least = T <= kPd16ShortTiles || T - t <= kPd16LastTiles ? 1.0f : kPfSumLimit;
       if (steady(std::integral_constant<uint32_t, 0>())) break;
       if (steady(std::integral_constant<uint32_t, 1>())) break;
       if (steady(std::integral_constant<uint32_t, 2>())) break;
       if (steady(std::integral_constant<uint32_t, 3>())) break;
-      if (T > kPd16ShortTiles) least = kPfSumLimit;
     }
     slot = (uint32_t)((T - 1) & (kPdStages - 1)) * kPfTileBytes;
 #pragma unroll
@@ -1605,10 +1624,9 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel_deep16(PrefillArgs a) {
   const int lane = lane_id();
   const int wave = wave_id();
   const int gl = a.G < 4 ? a.G : 4;
-  const int strip = 32 * (kPdWaves / gl);
   const int g = pf_select_head(a) * 4 + (wave % gl);
 
-  const PfShape sh = pf_shape_of(a, strip);
+  const PfShape sh = pf_shape_of(a, a.strip);
   constexpr int kLanes = kPdWaves * 64;
   constexpr int kImageFloats = kCarryFloatsPerLane * kLanes;
   float* const images = a.carry + (int64_t)blockIdx.y * a.img_row * kImageFloats + threadIdx.x;
@@ -1637,11 +1655,10 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel_deep16(PrefillArgs a) {
     }
     if (ps.run) {
       __syncthreads();               // the LDS rings are free again (a previous pass may still be reading V tiles)
-      const int i0 = ps.bx * strip + 32 * (wave / gl);
-      const int left = a.C - i0;     // rows of this wavefront's 32 that exist
-      if (left > 16) pd16_pass<PRESCALED, 2>(a, ps, lds_base, lane, wave, g, strip, i0, images);
-      else if (left > 0) pd16_pass<PRESCALED, 1>(a, ps, lds_base, lane, wave, g, strip, i0, images);
-      else pd16_pass<PRESCALED, 0>(a, ps, lds_base, lane, wave, g, strip, i0, images);
+      const Pf16Rows rows = pf16_rows(a, ps.bx, gl, wave);
+      if (rows.nq == 2) pd16_pass<PRESCALED, 2>(a, ps, lds_base, lane, wave, g, rows.i0, rows.step, images);
+      else if (rows.nq == 1) pd16_pass<PRESCALED, 1>(a, ps, lds_base, lane, wave, g, rows.i0, rows.step, images);
+      else pd16_pass<PRESCALED, 0>(a, ps, lds_base, lane, wave, g, rows.i0, rows.step, images);
     }
     ps = other;
     other.run = other.init = 0;
@@ -1657,15 +1674,14 @@ __global__ __launch_bounds__(512) void prefill_merge16_kernel(PrefillArgs a) {
   const int g16 = lane >> 4;
   const int c16 = lane & 15;
   const int gl = a.G < 4 ? a.G : 4;
-  const int strip = 32 * (kPdWaves / gl);
   const int bx = blockIdx.x;
   const int db = blockIdx.z;
   const int g = pf_select_head(a) * 4 + (wave % gl);
-  const int i0 = bx * strip + 32 * (wave / gl);
-  if (i0 >= a.C) return;                    // rows past the chunk's end
+  const Pf16Rows rows16 = pf16_rows(a, bx, gl, wave);
+  if (rows16.nq == 0) return;               // rows past the end
   constexpr int kLanes = kPdWaves * 64;
   constexpr int kImageFloats = kCarryFloatsPerLane * kLanes;
-  const PfShape sh = pf_shape_of(a, strip);
+  const PfShape sh = pf_shape_of(a, a.strip);
   int n_e, n_x;
   pf_block_images(sh, bx, n_e, n_x);
   if (n_e + n_x == 1 && a.split == 1) return;
@@ -1677,7 +1693,7 @@ __global__ __launch_bounds__(512) void prefill_merge16_kernel(PrefillArgs a) {
   for (int i = 0; i < n; ++i) {
     const float* im = image_of(i);
     m[0] = fmaxf(m[0], im[64 * kLanes]);
-    m[1] = fmaxf(m[1], im[65 * kLanes]);
+    if (rows16.nq == 2) m[1] = fmaxf(m[1], im[65 * kLanes]);
   }
   f32x4 o[2];
 #pragma unroll
@@ -1688,6 +1704,7 @@ __global__ __launch_bounds__(512) void prefill_merge16_kernel(PrefillArgs a) {
     const float* im = image_of(i);
 #pragma unroll
     for (int qb = 0; qb < 2; ++qb) {
+      if (qb >= rows16.nq) continue;
       const float w = fast_exp2((im[(64 + qb) * kLanes] - m[qb]) * a.c);
       l[qb] += w * im[(66 + qb) * kLanes];
 #pragma unroll
@@ -1697,7 +1714,7 @@ __global__ __launch_bounds__(512) void prefill_merge16_kernel(PrefillArgs a) {
 #pragma unroll
   for (int qb = 0; qb < 2; ++qb) {
     const f32x4 rows[1] = {o[qb]};
-    pf16_write_row<1>(a.out, a.out_fp32, a.C, g, i0 + 16 * qb + c16, g16, db, rows, l[qb]);
+    pf16_write_row<1>(a.out, a.out_fp32, a.C, g, qb < rows16.nq ? rows16.i0 + rows16.step * qb + c16 : a.C, g16, db, rows, l[qb]);
   }
 }
 
@@ -2137,11 +2154,12 @@ hi_status launch_prefill(void* stream, const void* q, int G, int chunk_len, cons
   a.split = pl.split;
   a.paired = pl.paired;
   a.nbk = pl.nbk;
+  a.strip = pl.strip > 0 ? pl.strip : 2 * strip;
   a.img_row = pl.img_row;
   a.xcd = pl.xcd;
   a.by_split = a.by_nbk = 0;
   if (pl.deep) {
-    const PfShape sh = pf_shape_of(a, 2 * strip);
+    const PfShape sh = pf_shape_of(a, a.strip);
     a.by_split = pf_magic((uint32_t)pl.split, pf_largest_cut(sh));
     a.by_nbk = pf_magic((uint32_t)pl.nbk, (uint64_t)pl.nbk * (uint64_t)pl.split);
   }
@@ -2181,7 +2199,8 @@ hi_status launch_prefill(void* stream, const void* q, int G, int chunk_len, cons
     const bool mfma32 = (variant & 16) != 0;        // the 32x32x16 form of the kernel (its state images differ)
     // the 4-wave, 64-rows-per-wavefront form of the 16x16x32 kernel: for workgroups that sweep enough tiles to pay for its
     // slow straight-line ones (it gains about 3 % per steady-state tile and loses about 20 tiles' worth at the ends)
-    const bool wide = !mfma32 && ((variant & 128) != 0 ||
+    if (pl.strip > 0 && mfma32) { set_last_error("prefill launch: this kernel takes full blocks of positions"); return HI_ERR_UNSUPPORTED; }
+    const bool wide = !mfma32 && pl.strip == 0 && ((variant & 128) != 0 ||
                                   ((variant & 64) == 0 && (sa.n + sb.n) / kPfTileRows >= (int64_t)kPrefillWideMinTiles * pl.split));
     if (mfma32) hipLaunchKernelGGL(prefill_kernel_deep, grid, dim3(kPdWaves * 64), kPdLdsBytes, (hipStream_t)stream, a);
     else if (wide && q_prescaled) hipLaunchKernelGGL(prefill_kernel_wide<true>, grid, dim3(kPwWaves * 64), kPdLdsBytes, (hipStream_t)stream, a);

@@ -1,5 +1,6 @@
 // The loads of prefill_kernel_deep16, replayed pass by pass (csrc/hi_prefill_part.h): the tiles that a pass asks for ahead are
 // the right ones, and no load - nor the ones behind a pass's last tile - leaves the rows that the launch was given.
+#include <algorithm>
 #include <cstdio>
 #include <random>
 #include "hi_prefill_part.h"
@@ -20,6 +21,10 @@ int main() {
     const int64_t na = nb == 0 ? 1 + pick(4000) : (i % 7 ? pick(4000) : 0);
     const int64_t C = nb ? nb : 1 + pick(1000);
     s.nbk = (int)((C + 64 * s.m - 1) / (64 * s.m));
+    if (pick(2)) {                                     // blocks of one height, a multiple of 16 positions
+      const int even = (int)(((C + s.nbk - 1) / s.nbk + 15) / 16 * 16);
+      if ((s.nbk - 1) * even < C) s.strip = even;
+    }
     s.ta = (int)((na + 63) / 64);
     s.tb_all = (int)((nb + 63) / 64);
     s.paired = nb > 0 && s.nbk >= 2 && pick(2);
@@ -36,6 +41,10 @@ int main() {
       if (at < edge) return at + rows * 256 <= edge && at + rows * 256 <= na * 256;
       return jump && at >= edge + far && at - far + rows * 256 <= na * 256;
     };
+    for (int b = 0; b < s.nbk && nb; ++b) {             // a block's last row sees the chunk's rows up to itself
+      const int64_t last = std::min<int64_t>((b + 1) * (s.strip ? s.strip : 64 * s.m), C) - 1;
+      CHECK(pf_own_tiles(s, b) == (int)(last / 64) + 1);
+    }
     for (int j = 0; j < 6; ++j) {
       const int w = (int)pick((int64_t)s.nbk * s.split);
       for (int which = 0; which < 2; ++which) {
