@@ -416,12 +416,16 @@ hi_status write_back_packed(hi_ctx* c, int layer, int head, int nh, const void* 
   return HI_OK;
 }
 
+PrefillAppend resident_append(const hi_ctx* c, int layer, int head, int nh, const void* k_new, const void* v_new, int64_t past,
+                              int64_t len) {
+  return {k_new, v_new, res_plane(c, layer, head, 0) + past * kRowBytes, res_plane(c, layer, head, 1) + past * kRowBytes, len, nh,
+          2 * c->prob.max_context * kRowBytes};
+}
+
 // k_new / v_new: [nh][len][128]
 hi_status write_back(hi_ctx* c, int layer, int head, int nh, const void* k_new, const void* v_new, int64_t past,
                      int64_t len) {
-  if (unit_resident(c, layer, head))
-    return launch_kv_append(c->sc, k_new, v_new, res_plane(c, layer, head, 0) + past * kRowBytes,
-                            res_plane(c, layer, head, 1) + past * kRowBytes, len, nh, 2 * c->prob.max_context * kRowBytes);
+  if (unit_resident(c, layer, head)) return launch_kv_append(c->sc, resident_append(c, layer, head, nh, k_new, v_new, past, len));
   if (link_packed(c)) return write_back_packed(c, layer, head, nh, k_new, v_new, past, len);
   const bool timed = (c->flags & HI_FLAG_TIME_KERNELS) != 0;
   TimedSpan sp;
@@ -674,11 +678,12 @@ static hi_status prefill_impl(hi_ctx* c, int32_t layer, int32_t kv_head, int32_t
   // same stream, and their partials do not outlive them
   const PrefillLaunch unit = prefill_unit_shape(G, chunk_len, nh, pf_variant(c), past_len, from_ring ? rows_of(c, nh) : 0,
                                                 c->plan.ws_writeback_offset, c->prob.n_kv_heads);
-  auto launch = [&](const PrefillSegment& seg, const PrefillSegment& own, int first, int last) -> hi_status {
+  auto launch = [&](const PrefillSegment& seg, const PrefillSegment& own, int first, int last,
+                    const PrefillAppend* append = nullptr) -> hi_status {
     TimedSpan sp;
     if (timed) HI_TRY(span_begin(c, 0, &sp));
     HI_TRY(launch_prefill(c->sc, q_dev, G, chunk_len, seg, own, first, last, c->ws, out_dev, c->prob.out_fp32,
-                          pf_variant(c), unit, nh, c->plan.ws_writeback_offset));
+                          pf_variant(c), unit, nh, c->plan.ws_writeback_offset, append));
     if (timed) HI_TRY(span_end(c, sp));
     c->stats.n_prefill_kernels += 1;
     return HI_OK;
@@ -728,8 +733,9 @@ static hi_status prefill_impl(hi_ctx* c, int32_t layer, int32_t kv_head, int32_t
     PrefillSegment pastseg{res_plane(c, layer, kv_head, 0), res_plane(c, layer, kv_head, 1), past_len, 0,
                            2 * c->prob.max_context * kRowBytes};
     HI_TRY(prefetch_hint(c, next));
-    if (run) HI_TRY(launch(pastseg, diag, 1, 1));
-    return write_back(c, layer, kv_head, nh, k_new_dev, v_new_dev, past_len, chunk_len);
+    if (!run) return write_back(c, layer, kv_head, nh, k_new_dev, v_new_dev, past_len, chunk_len);
+    const PrefillAppend append = resident_append(c, layer, kv_head, nh, k_new_dev, v_new_dev, past_len, chunk_len);
+    return launch(pastseg, diag, 1, 1, &append);
   }
 
   HI_TRY(adopt_unit(c, layer, kv_head, nh, past_len));

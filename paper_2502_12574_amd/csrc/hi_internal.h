@@ -272,6 +272,16 @@ struct PrefillSegment {
   int64_t tile0 = 0;         // past segment: its first tile, counted over the unit's cached rows
 };
 
+// Rows [heads][rows][128] of K and of V to the heads' places in an HBM cache, head_stride bytes apart: in a launch of its own, or
+// along with a unit's last prefill launch (which reads the cache only before those rows).
+struct PrefillAppend {
+  const void* k_new; const void* v_new;
+  void* k_dst; void* v_dst;
+  int64_t rows;
+  int heads;
+  int64_t head_stride;
+};
+
 // One launch of the prefill kernel over up to two KV segments.  first: start from an empty softmax state
 // instead of loading the carry; last: normalise and write `out` instead of storing the carry.
 // variant: as at prefill_launch_shape (+ 32: the queries are pre-scaled, see softmax_scale_log2); shape: the unit's, from
@@ -281,11 +291,9 @@ struct PrefillSegment {
 // segment's rows [n_heads][chunk_len][128], the other segment's heads head_stride bytes apart.
 hi_status launch_prefill(void* stream, const void* q, int G, int chunk_len, const PrefillSegment& a,
                          const PrefillSegment& b, int first, int last, void* carry, void* out, int out_fp32,
-                         int variant, const PrefillLaunch& unit, int n_heads, int64_t carry_bytes);
-
-// Rows [n_heads][rows][128] of K and of V to the heads' places in an HBM cache, head_stride bytes apart.
-hi_status launch_kv_append(void* stream, const void* k_new, const void* v_new, void* k_dst, void* v_dst, int64_t rows,
-                           int n_heads, int64_t head_stride);
+                         int variant, const PrefillLaunch& unit, int n_heads, int64_t carry_bytes,
+                         const PrefillAppend* append = nullptr);
+hi_status launch_kv_append(void* stream, const PrefillAppend& append);
 
 // The factor between a query-key dot product and the base-2 exponent of its softmax weight: log2(e) / sqrt(128) for
 // the q of Eq. 3, 1 for queries that already carry that factor (hi_problem.q_prescaled).

@@ -1665,57 +1665,108 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel_deep16(PrefillArgs a) {
   }
 }
 
+// The chunk's rows on their way into an HBM-resident cache, 16 bytes per thread: in the blocks of a merge launch from z = first_z
+// on, or in a launch of their own (kv_append_kernel).
+struct PrefillAppendArgs {
+  const char* k; const char* v;     // [heads][head_bytes]
+  char* dk; char* dv;               // row 0 of the first head's new rows; the heads head_stride bytes apart
+  int64_t head_bytes, head_stride;
+  int heads, first_z;
+};
+__device__ __forceinline__ void pf_append(const PrefillAppendArgs& p, int64_t unit) {
+  const int64_t per_head = p.head_bytes / 16, per_plane = per_head * p.heads;
+  const bool is_v = unit >= per_plane;
+  if (is_v) unit -= per_plane;
+  if (unit >= per_plane) return;
+  const int64_t head = per_plane >> 32 ? unit / per_head : (int64_t)((uint32_t)unit / (uint32_t)per_head);
+  const int64_t at = (unit - head * per_head) * 16;
+  *(uint4*)((is_v ? p.dv : p.dk) + head * p.head_stride + at) = *(const uint4*)((is_v ? p.v : p.k) + unit * 16);
+}
+// this block's share of the append, if it is one of the blocks that do nothing else
+__device__ __forceinline__ bool pf_append_block(const PrefillAppendArgs& p) {
+  if ((int)blockIdx.z < p.first_z) return false;
+  const int64_t block = ((int64_t)(blockIdx.z - p.first_z) * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
+  pf_append(p, block * blockDim.x + threadIdx.x);
+  return true;
+}
+
 // Merge of the states of prefill_kernel_deep16 (its own image layout): grid (blocks, grid rows, 8): z is one dim block
-// of both query rows of the lane.  Bound by the read of the images (139 KB each, up to 64 per block): 8 dim blocks per
-// image and four images in flight per lane, because the grid is small exactly where a block has many images.
-__global__ __launch_bounds__(512) void prefill_merge16_kernel(PrefillArgs a) {
+// of both query rows of the lane.  Bound by the read of the images (139 KB each, up to 64 per block), and where a block has
+// few of them by its latency: CH images are in flight per lane, in one pass.  8 heads of 2 blocks of 16 images take 7.6 us with
+// the append (maxima first and sums in a second pass: 11.4), of 10 blocks of 3 images 9.0 (10.0).  Behind the merge's blocks
+// others append the chunk's rows to the cache: as a launch of its own behind this one that took 4.3 us and the gap before it.
+template <int NQ, int CH>
+__device__ __forceinline__ void pf16_merge(const PrefillArgs& a, const PfShape& sh, const Pf16Rows& rows16, int bx, int db, int n_e,
+                                           int n, int g, int g16, int c16) {
+  constexpr int kLanes = kPdWaves * 64;
+  constexpr int kImageFloats = kCarryFloatsPerLane * kLanes;
+  const float* images = a.carry + (int64_t)blockIdx.y * a.img_row * kImageFloats + threadIdx.x;
+  float m[NQ], l[NQ];
+  f32x4 o[NQ];
+#pragma unroll
+  for (int qb = 0; qb < NQ; ++qb) {
+    m[qb] = kNegBig;
+    l[qb] = 0.f;
+    o[qb] = (f32x4){0.f, 0.f, 0.f, 0.f};
+  }
+#pragma nounroll
+  for (int i0 = 0; i0 < n; i0 += CH) {
+    float mi[CH][NQ], li[CH][NQ], oi[CH][NQ][4];
+#pragma unroll
+    for (int j = 0; j < CH; ++j) {                    // (behind the last image: the last one again, with weight 0)
+      const int i = i0 + j < n ? i0 + j : n - 1;
+      const float* im = images + (int64_t)(i < n_e ? pf_image_e(sh, bx, i) : pf_image_x(sh, bx, i - n_e)) * kImageFloats;
+#pragma unroll
+      for (int qb = 0; qb < NQ; ++qb) {
+        mi[j][qb] = im[(64 + qb) * kLanes];
+        li[j][qb] = im[(66 + qb) * kLanes];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) oi[j][qb][r] = im[((db * 2 + qb) * 4 + r) * kLanes];
+      }
+    }
+#pragma unroll
+    for (int qb = 0; qb < NQ; ++qb) {
+      float top = m[qb];
+#pragma unroll
+      for (int j = 0; j < CH; ++j) top = fmaxf(top, mi[j][qb]);
+      const float old = fast_exp2((m[qb] - top) * a.c);
+      m[qb] = top;
+      l[qb] *= old;
+      o[qb] *= old;
+#pragma unroll
+      for (int j = 0; j < CH; ++j) {
+        const float w = i0 + j < n ? fast_exp2((mi[j][qb] - top) * a.c) : 0.f;
+        l[qb] += w * li[j][qb];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) o[qb][r] += w * oi[j][qb][r];
+      }
+    }
+  }
+#pragma unroll
+  for (int qb = 0; qb < NQ; ++qb) {
+    const f32x4 rows[1] = {o[qb]};
+    pf16_write_row<1>(a.out, a.out_fp32, a.C, g, rows16.i0 + rows16.step * qb + c16, g16, db, rows, l[qb]);
+  }
+}
+
+__global__ __launch_bounds__(512) void prefill_merge16_kernel(PrefillArgs a, PrefillAppendArgs append) {
+  if (pf_append_block(append)) return;
   const int lane = lane_id();
   const int wave = wave_id();
-  const int g16 = lane >> 4;
-  const int c16 = lane & 15;
   const int gl = a.G < 4 ? a.G : 4;
   const int bx = blockIdx.x;
   const int db = blockIdx.z;
   const int g = pf_select_head(a) * 4 + (wave % gl);
   const Pf16Rows rows16 = pf16_rows(a, bx, gl, wave);
   if (rows16.nq == 0) return;               // rows past the end
-  constexpr int kLanes = kPdWaves * 64;
-  constexpr int kImageFloats = kCarryFloatsPerLane * kLanes;
   const PfShape sh = pf_shape_of(a, a.strip);
   int n_e, n_x;
   pf_block_images(sh, bx, n_e, n_x);
-  if (n_e + n_x == 1 && a.split == 1) return;
-  const float* images = a.carry + (int64_t)blockIdx.y * a.img_row * kImageFloats + threadIdx.x;
-  auto image_of = [&](int i) { return images + (int64_t)(i < n_e ? pf_image_e(sh, bx, i) : pf_image_x(sh, bx, i - n_e)) * kImageFloats; };
-  float m[2] = {kNegBig, kNegBig};
   const int n = n_e + n_x;
-#pragma unroll 4
-  for (int i = 0; i < n; ++i) {
-    const float* im = image_of(i);
-    m[0] = fmaxf(m[0], im[64 * kLanes]);
-    if (rows16.nq == 2) m[1] = fmaxf(m[1], im[65 * kLanes]);
-  }
-  f32x4 o[2];
-#pragma unroll
-  for (int qb = 0; qb < 2; ++qb) o[qb] = (f32x4){0.f, 0.f, 0.f, 0.f};
-  float l[2] = {0.f, 0.f};
-#pragma unroll 4
-  for (int i = 0; i < n; ++i) {
-    const float* im = image_of(i);
-#pragma unroll
-    for (int qb = 0; qb < 2; ++qb) {
-      if (qb >= rows16.nq) continue;
-      const float w = fast_exp2((im[(64 + qb) * kLanes] - m[qb]) * a.c);
-      l[qb] += w * im[(66 + qb) * kLanes];
-#pragma unroll
-      for (int r = 0; r < 4; ++r) o[qb][r] += w * im[((db * 2 + qb) * 4 + r) * kLanes];
-    }
-  }
-#pragma unroll
-  for (int qb = 0; qb < 2; ++qb) {
-    const f32x4 rows[1] = {o[qb]};
-    pf16_write_row<1>(a.out, a.out_fp32, a.C, g, qb < rows16.nq ? rows16.i0 + rows16.step * qb + c16 : a.C, g16, db, rows, l[qb]);
-  }
+  if (n == 1 && a.split == 1) return;
+  if (rows16.nq == 1) pf16_merge<1, 8>(a, sh, rows16, bx, db, n_e, n, g, lane >> 4, lane & 15);
+  else if (n <= 4) pf16_merge<2, 4>(a, sh, rows16, bx, db, n_e, n, g, lane >> 4, lane & 15);
+  else pf16_merge<2, 8>(a, sh, rows16, bx, db, n_e, n, g, lane >> 4, lane & 15);
 }
 
 #include "hi_prefill_wide.inc"
@@ -1746,7 +1797,8 @@ __device__ __forceinline__ void pf_write_row_db(void* out, int out_fp32, int C, 
 // own lane layout, so every lane combines its own register images - m = max m_i, O = sum O_i 2^(c (m_i - m)),
 // l likewise - then normalises and writes its part of out[g][i][:].  A block with a single state was written by
 // the pass that computed it.
-__global__ __launch_bounds__(512) void prefill_merge_kernel(PrefillArgs a) {
+__global__ __launch_bounds__(512) void prefill_merge_kernel(PrefillArgs a, PrefillAppendArgs append) {
+  if (pf_append_block(append)) return;
   const int lane = lane_id();
   const int wave = wave_id();
   const int hl = lane >> 5;
@@ -1787,7 +1839,8 @@ __global__ __launch_bounds__(512) void prefill_merge_kernel(PrefillArgs a) {
 // Bound by the latency of its reads (70 KB per image, up to 64 images of a block, and few blocks where there are many), so
 // the grid splits an image finely and many images are in flight per lane: 63 images of 8 blocks take 18 us, 16 images
 // of 16 blocks 6.4 (30 and 9.3 with whole dim blocks and four images in flight).
-__global__ __launch_bounds__(256) void prefill_merge4_kernel(PrefillArgs a) {
+__global__ __launch_bounds__(256) void prefill_merge4_kernel(PrefillArgs a, PrefillAppendArgs append) {
+  if (pf_append_block(append)) return;
   const int lane = lane_id();
   const int wave = wave_id();
   const int hl = lane >> 5;
@@ -2096,24 +2149,26 @@ __global__ __launch_bounds__(256) void stream_store_update_kernel(const char* __
 }
 
 
-// A chunk's K and V rows of a group of HBM-resident heads enter the cache: one launch in place of two strided device copies.
+// A chunk's K and V rows of a group of HBM-resident heads enter the cache, where no merge launch takes them along.
 // Bound by one load and one store latency: 16 bytes per thread (four guarded loads per thread ran one after the other, 12 us
-// for 600 rows of 8 heads against 5 + 4 for the copies).  grid (row blocks, heads, 2: K and V).
-__global__ __launch_bounds__(256) void kv_append_kernel(const char* __restrict__ k_new, const char* __restrict__ v_new,
-                                                        char* __restrict__ dk, char* __restrict__ dv, int64_t head_bytes,
-                                                        int64_t head_stride) {
-  const int64_t at = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 16;
-  if (at >= head_bytes) return;
-  const char* src = (blockIdx.z ? v_new : k_new) + (int64_t)blockIdx.y * head_bytes + at;
-  *(uint4*)((blockIdx.z ? dv : dk) + (int64_t)blockIdx.y * head_stride + at) = *(const uint4*)src;
+// for 600 rows of 8 heads against 4).
+__global__ __launch_bounds__(256) void kv_append_kernel(PrefillAppendArgs p) {
+  pf_append(p, (int64_t)blockIdx.x * 256 + threadIdx.x);
 }
 
-hi_status launch_kv_append(void* stream, const void* k_new, const void* v_new, void* k_dst, void* v_dst, int64_t rows,
-                           int n_heads, int64_t head_stride) {
-  const int64_t bytes = rows * kRowBytes, blocks = ceil_div(bytes, 4096);
-  if (rows < 1 || n_heads < 1 || blocks > 0x7FFFFFFF) { set_last_error("append launch: bad shape"); return HI_ERR_ARG; }
-  hipLaunchKernelGGL(kv_append_kernel, dim3((unsigned)blocks, (unsigned)n_heads, 2), dim3(256), 0, (hipStream_t)stream,
-                     (const char*)k_new, (const char*)v_new, (char*)k_dst, (char*)v_dst, bytes, head_stride);
+static hi_status append_args(const PrefillAppend& ap, PrefillAppendArgs& p, int64_t& units) {
+  p = {(const char*)ap.k_new, (const char*)ap.v_new, (char*)ap.k_dst, (char*)ap.v_dst, ap.rows * kRowBytes, ap.head_stride, ap.heads, 0};
+  units = 2 * ap.heads * (p.head_bytes / 16);
+  if (ap.rows < 1 || ap.heads < 1 || ceil_div(units, 256) > 0x7FFFFFFF) { set_last_error("append launch: bad shape"); return HI_ERR_ARG; }
+  return HI_OK;
+}
+
+hi_status launch_kv_append(void* stream, const PrefillAppend& ap) {
+  PrefillAppendArgs p;
+  int64_t units;
+  const hi_status st = append_args(ap, p, units);
+  if (st != HI_OK) return st;
+  hipLaunchKernelGGL(kv_append_kernel, dim3((unsigned)ceil_div(units, 256)), dim3(256), 0, (hipStream_t)stream, p);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) { set_last_error("append launch: %s", hipGetErrorString(e)); return HI_ERR_HIP; }
   return HI_OK;
@@ -2121,7 +2176,7 @@ hi_status launch_kv_append(void* stream, const void* k_new, const void* v_new, v
 
 hi_status launch_prefill(void* stream, const void* q, int G, int chunk_len, const PrefillSegment& sa,
                          const PrefillSegment& sb, int first, int last, void* carry, void* out, int out_fp32,
-                         int variant, const PrefillLaunch& unit, int n_heads, int64_t carry_bytes) {
+                         int variant, const PrefillLaunch& unit, int n_heads, int64_t carry_bytes, const PrefillAppend* append) {
   if (n_heads < 1 || (variant & 3) == 2) { set_last_error("prefill launch: head group or variant"); return HI_ERR_UNSUPPORTED; }
   if (chunk_len < 1 || !(G == 1 || G == 2 || G == 4 || G == 8)) { set_last_error("prefill launch: bad shape"); return HI_ERR_ARG; }
   if (sa.causal || (sb.n > 0 && !sb.causal)) { set_last_error("prefill launch: segment order"); return HI_ERR_ARG; }
@@ -2151,6 +2206,17 @@ hi_status launch_prefill(void* stream, const void* q, int G, int chunk_len, cons
     set_last_error("prefill launch: carry of %lld bytes needed, %lld provided", (long long)pl.carry_bytes, (long long)carry_bytes);
     return HI_ERR_ARG;
   }
+  // the rows to append ride on the merge launch, as blocks behind its z_merge x (threads) ones, or go in a launch of their own
+  PrefillAppendArgs app = {};
+  int64_t app_units = 0;
+  if (append) {
+    const hi_status st = append_args(*append, app, app_units);
+    if (st != HI_OK) return st;
+  }
+  auto merge_grid = [&](unsigned x, unsigned y, unsigned z_merge, int threads) {
+    app.first_z = (int)z_merge;
+    return dim3(x, y, z_merge + (unsigned)ceil_div(app_units, (int64_t)x * y * threads));
+  };
   a.split = pl.split;
   a.paired = pl.paired;
   a.nbk = pl.nbk;
@@ -2210,8 +2276,8 @@ hi_status launch_prefill(void* stream, const void* q, int G, int chunk_len, cons
     if (pl.merge) {
       hipError_t e1 = hipGetLastError();
       if (e1 != hipSuccess) { set_last_error("prefill launch: %s", hipGetErrorString(e1)); return HI_ERR_HIP; }
-      if (mfma32) hipLaunchKernelGGL(prefill_merge_kernel, dim3((unsigned)pl.nbk, grid.y, 4), dim3(kPdWaves * 64), 0, (hipStream_t)stream, a);
-      else hipLaunchKernelGGL(prefill_merge16_kernel, dim3((unsigned)pl.nbk, grid.y, 8), dim3(kPdWaves * 64), 0, (hipStream_t)stream, a);
+      if (mfma32) hipLaunchKernelGGL(prefill_merge_kernel, merge_grid((unsigned)pl.nbk, grid.y, 4, kPdWaves * 64), dim3(kPdWaves * 64), 0, (hipStream_t)stream, a, app);
+      else hipLaunchKernelGGL(prefill_merge16_kernel, merge_grid((unsigned)pl.nbk, grid.y, 8, kPdWaves * 64), dim3(kPdWaves * 64), 0, (hipStream_t)stream, a, app);
     }
   } else {
     const dim3 blocks((unsigned)ceil_div(chunk_len, strip), (unsigned)(gy * n_heads));
@@ -2220,7 +2286,7 @@ hi_status launch_prefill(void* stream, const void* q, int G, int chunk_len, cons
       if (pl.merge) {
         hipError_t e1 = hipGetLastError();
         if (e1 != hipSuccess) { set_last_error("prefill launch: %s", hipGetErrorString(e1)); return HI_ERR_HIP; }
-        hipLaunchKernelGGL(prefill_merge4_kernel, dim3(blocks.x, blocks.y, 16), dim3(kWgThreads), 0, (hipStream_t)stream, a);
+        hipLaunchKernelGGL(prefill_merge4_kernel, merge_grid(blocks.x, blocks.y, 16, kWgThreads), dim3(kWgThreads), 0, (hipStream_t)stream, a, app);
       }
     } else {
       hipLaunchKernelGGL(prefill_kernel<false>, blocks, dim3(kWgThreads), 0, (hipStream_t)stream, a);
@@ -2228,7 +2294,7 @@ hi_status launch_prefill(void* stream, const void* q, int G, int chunk_len, cons
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) { set_last_error("prefill launch: %s", hipGetErrorString(e)); return HI_ERR_HIP; }
-  return HI_OK;
+  return append && !pl.merge ? launch_kv_append(stream, *append) : HI_OK;
 }
 
 hi_status launch_prefill_window(void* stream, const void* q, int G, int chunk_len, const void* store_k,
