@@ -85,6 +85,7 @@ struct hi_ctx {
   int run_ahead = 2;
   std::vector<hipEvent_t> ev_unit;             // ring of "unit finished" events, of units that were not captured
   int64_t n_units = 0;
+  bool end_marked = false;   // the running call's last launch carries its unit's event
 
   hi_stats stats;
   std::vector<TimedSpan> spans;
@@ -286,9 +287,16 @@ hi_status pace_begin(hi_ctx* c) {
   return HI_OK;
 }
 
+// The event of the running unit, for its last launch on the compute stream to carry.
+void* unit_end(hi_ctx* c) {
+  if (c->capturing) return nullptr;       // (an event recorded into a graph marks nothing that can be waited for)
+  c->end_marked = true;
+  return c->ev_unit[c->n_units % kUnitRing];
+}
+
 hi_status pace_end(hi_ctx* c) {
-  if (c->capturing) return HI_OK;         // (an event recorded into a graph marks nothing that can be waited for)
-  HI_HIP(hipEventRecord(c->ev_unit[c->n_units % kUnitRing], c->sc));
+  if (c->capturing) return HI_OK;
+  if (!c->end_marked) HI_HIP(hipEventRecord(c->ev_unit[c->n_units % kUnitRing], c->sc));
   c->n_units += 1;
   return HI_OK;
 }
@@ -642,7 +650,7 @@ static hi_status prefetch_hint(hi_ctx* c, const hi_ctx::Unit& next) {
 // refused until the context is destroyed.
 template <class F>
 static hi_status guarded(hi_ctx* c, F&& body) {
-  c->enqueuing = false;
+  c->enqueuing = c->end_marked = false;
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
   c->capturing = hipStreamIsCapturing(c->sc, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone;
   if (c->capturing) (void)hipGetLastError();        // (a legacy stream cannot say while another one is being captured)
@@ -683,7 +691,7 @@ static hi_status prefill_impl(hi_ctx* c, int32_t layer, int32_t kv_head, int32_t
     TimedSpan sp;
     if (timed) HI_TRY(span_begin(c, 0, &sp));
     HI_TRY(launch_prefill(c->sc, q_dev, G, chunk_len, seg, own, first, last, c->ws, out_dev, c->prob.out_fp32,
-                          pf_variant(c), unit, nh, c->plan.ws_writeback_offset, append));
+                          pf_variant(c), unit, nh, c->plan.ws_writeback_offset, append, last ? unit_end(c) : nullptr));
     if (timed) HI_TRY(span_end(c, sp));
     c->stats.n_prefill_kernels += 1;
     return HI_OK;
@@ -727,7 +735,7 @@ static hi_status prefill_impl(hi_ctx* c, int32_t layer, int32_t kv_head, int32_t
       c->stats.n_prefill_kernels += 1;
     }
     return launch_stream_store_update(c->sc, k_new_dev, v_new_dev, chunk_len, past_len, c->prob.sink_tokens,
-                                      c->prob.recent_tokens, sk, sv, stream_head_stride(c), nh);
+                                      c->prob.recent_tokens, sk, sv, stream_head_stride(c), nh, unit_end(c));
   }
   if (unit_resident(c, layer, kv_head)) {
     PrefillSegment pastseg{res_plane(c, layer, kv_head, 0), res_plane(c, layer, kv_head, 1), past_len, 0,
@@ -808,7 +816,7 @@ static hi_status decode_impl(hi_ctx* c, int32_t layer, int32_t kv_head, int32_t 
     TimedSpan sp;
     if (timed) HI_TRY(span_begin(c, 1, &sp));
     HI_TRY(launch_decode_partial(c->sc, q_dev, G, k, v, rows, np, partials, part0, q_pre(c), nh, kv_stride, part_stride,
-                                 skip_row, nullptr, tail));
+                                 skip_row, nullptr, tail, 0, tail ? unit_end(c) : nullptr));
     if (timed) HI_TRY(span_end(c, sp));
     c->stats.n_decode_kernels += 1;
     return HI_OK;
@@ -823,7 +831,7 @@ static hi_status decode_impl(hi_ctx* c, int32_t layer, int32_t kv_head, int32_t 
     if (rows > 0) HI_TRY(partial(k, v, rows, np, 0, kv_stride, skip_row, fused ? &tail : nullptr));
     if (fused) return HI_OK;
     HI_TRY(launch_decode_combine(c->sc, q_dev, G, k_new_dev, v_new_dev, partials, np, out_dev, c->prob.out_fp32, k_append,
-                                 v_append, q_pre(c), nh, part_stride, kv_stride));
+                                 v_append, q_pre(c), nh, part_stride, kv_stride, nullptr, unit_end(c)));
     c->stats.n_combine_kernels += 1;
     return HI_OK;
   };
@@ -902,7 +910,7 @@ static hi_status decode_impl(hi_ctx* c, int32_t layer, int32_t kv_head, int32_t 
   }
   if (run) {
     HI_TRY(launch_decode_combine(c->sc, q_dev, G, k_new_dev, v_new_dev, partials, n_part, out_dev, c->prob.out_fp32,
-                                 nullptr, nullptr, q_pre(c), nh, part_stride, 0));
+                                 nullptr, nullptr, q_pre(c), nh, part_stride, 0, nullptr, unit_end(c)));
     c->stats.n_combine_kernels += 1;
   }
   cur.valid = false;
@@ -977,13 +985,13 @@ extern "C" hi_status hi_decode_group_ragged(hi_ctx* c, int32_t layer, int32_t kv
       TimedSpan sp;
       if (timed) HI_TRY(span_begin(c, 1, &sp));
       HI_TRY(launch_decode_partial(c->sc, q_dev, G, rk, rv, longest, n_split, partials, 0, q_pre(c), n_heads, plane2, part_stride,
-                                   -1, &lens, fused ? &tail : nullptr, n_wgs));
+                                   -1, &lens, fused ? &tail : nullptr, n_wgs, fused ? unit_end(c) : nullptr));
       if (timed) HI_TRY(span_end(c, sp));
       c->stats.n_decode_kernels += 1;
     }
     if (fused) return HI_OK;
     HI_TRY(launch_decode_combine(c->sc, q_dev, G, k_new_dev, v_new_dev, partials, longest > 0 ? n_split : 0, out_dev,
-                                 c->prob.out_fp32, rk, rv, q_pre(c), n_heads, part_stride, plane2, &lens));
+                                 c->prob.out_fp32, rk, rv, q_pre(c), n_heads, part_stride, plane2, &lens, unit_end(c)));
     c->stats.n_combine_kernels += 1;
     return HI_OK;
   });

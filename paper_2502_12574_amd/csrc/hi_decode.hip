@@ -501,7 +501,7 @@ void tail_counters_give(int slot, void* busy_until) {
 hi_status launch_decode_partial(void* stream, const void* q, int G, const void* k, const void* v, int64_t n,
                                 int n_split, void* partials, int part0, bool q_prescaled, int n_heads,
                                 int64_t kv_head_stride, int64_t part_head_stride, int64_t skip_row,
-                                const DecodeLens* lens, const DecodeTail* tail, int n_wgs) {
+                                const DecodeLens* lens, const DecodeTail* tail, int n_wgs, void* done) {
   if (n <= 0 || n_split <= 0 || n_heads < 1 || (lens && (n_heads > kDecodeMaxRagged || (lens->rows_per_wg > 0 && n_wgs < n_heads)))) { set_last_error("decode partial: empty launch"); return HI_ERR_ARG; }
   if (tail && (part0 != 0 || n_split > kTailMaxParts || n_heads > kTailMaxHeads || !tail->counters)) { set_last_error("decode partial: too many partials to combine in the launch"); return HI_ERR_ARG; }
   static std::once_flag attr_once;      // contexts on different host threads may get here together
@@ -514,9 +514,9 @@ hi_status launch_decode_partial(void* stream, const void* q, int G, const void* 
   });
   if (attr_err != hipSuccess) { set_last_error("hipFuncSetAttribute: %s", hipGetErrorString(attr_err)); return HI_ERR_HIP; }
   auto go = [&](auto kernel, auto lens_arg) {
-    hipLaunchKernelGGL(kernel, lens && lens->rows_per_wg > 0 ? dim3(n_wgs) : dim3(n_split, n_heads), dim3(256), kDecLdsBytes, (hipStream_t)stream, (const uint16_t*)q, G,
-                       (const char*)k, (const char*)v, n, (float*)partials, part0, softmax_scale_log2(q_prescaled),
-                       kv_head_stride, part_head_stride, skip_row, tail ? *tail : DecodeTail(), lens_arg);
+    launch_kernel(kernel, lens && lens->rows_per_wg > 0 ? dim3(n_wgs) : dim3(n_split, n_heads), dim3(256), kDecLdsBytes, stream,
+                  done, (const uint16_t*)q, G, (const char*)k, (const char*)v, n, (float*)partials, part0,
+                  softmax_scale_log2(q_prescaled), kv_head_stride, part_head_stride, skip_row, tail ? *tail : DecodeTail(), lens_arg);
   };
   if (lens && tail) go(decode_partial_kernel<DecodeLens, true>, *lens);
   else if (lens) go(decode_partial_kernel<DecodeLens, false>, *lens);
@@ -530,13 +530,13 @@ hi_status launch_decode_partial(void* stream, const void* q, int G, const void* 
 hi_status launch_decode_combine(void* stream, const void* q, int G, const void* k_new, const void* v_new,
                                 const void* partials, int n_part, void* out, int out_fp32, void* k_append,
                                 void* v_append, bool q_prescaled, int n_heads, int64_t part_head_stride,
-                                int64_t append_head_stride, const DecodeLens* lens) {
+                                int64_t append_head_stride, const DecodeLens* lens, void* done) {
   if (lens && n_heads > kDecodeMaxRagged) { set_last_error("decode combine: too many heads of their own length"); return HI_ERR_ARG; }
   auto go = [&](auto kernel, auto lens_arg) {
-    hipLaunchKernelGGL(kernel, dim3(G, kHeadDim / kCombDims, n_heads), dim3(256), 0, (hipStream_t)stream,
-                       (const uint16_t*)q, G, (const uint16_t*)k_new, (const uint16_t*)v_new, (const float*)partials,
-                       n_part, out, out_fp32, softmax_scale_log2(q_prescaled), (uint16_t*)k_append, (uint16_t*)v_append,
-                       part_head_stride, append_head_stride, lens_arg);
+    launch_kernel(kernel, dim3(G, kHeadDim / kCombDims, n_heads), dim3(256), 0, stream, done, (const uint16_t*)q, G,
+                  (const uint16_t*)k_new, (const uint16_t*)v_new, (const float*)partials, n_part, out, out_fp32,
+                  softmax_scale_log2(q_prescaled), (uint16_t*)k_append, (uint16_t*)v_append, part_head_stride, append_head_stride,
+                  lens_arg);
   };
   if (lens) go(decode_combine_kernel<DecodeLens>, *lens);
   else go(decode_combine_kernel<NoLens>, NoLens());

@@ -258,6 +258,7 @@ inline int64_t count_streaming(const hi_problem& p) {
 }
 
 // ---- kernel launchers (defined in the .hip files) ------------------------------------------------------
+// done: an event (hipEvent_t) that marks the end of the last kernel launched, see launch_kernel; null: none
 struct PrefillSegment {
   const void* k;      // device, [n][128] bf16 (first head of a group)
   const void* v;
@@ -292,8 +293,8 @@ struct PrefillAppend {
 hi_status launch_prefill(void* stream, const void* q, int G, int chunk_len, const PrefillSegment& a,
                          const PrefillSegment& b, int first, int last, void* carry, void* out, int out_fp32,
                          int variant, const PrefillLaunch& unit, int n_heads, int64_t carry_bytes,
-                         const PrefillAppend* append = nullptr);
-hi_status launch_kv_append(void* stream, const PrefillAppend& append);
+                         const PrefillAppend* append = nullptr, void* done = nullptr);
+hi_status launch_kv_append(void* stream, const PrefillAppend& append, void* done = nullptr);
 
 // The factor between a query-key dot product and the base-2 exponent of its softmax weight: log2(e) / sqrt(128) for
 // the q of Eq. 3, 1 for queries that already carry that factor (hi_problem.q_prescaled).
@@ -376,7 +377,7 @@ hi_status launch_decode_partial(void* stream, const void* q, int G, const void* 
                                 int n_split, void* partials, int part0, bool q_prescaled, int n_heads = 1,
                                 int64_t kv_head_stride = 0,
                                 int64_t part_head_stride = 0, int64_t skip_row = -1, const DecodeLens* lens = nullptr,
-                                const DecodeTail* tail = nullptr, int n_wgs = 0);
+                                const DecodeTail* tail = nullptr, int n_wgs = 0, void* done = nullptr);
 // tail != null (part0 = 0, n_split <= kTailMaxParts): the launch combines its partials too.
 // lens != null: head h has lens->n[h] rows instead of n (n = the largest of them), n_split is the largest number of
 // partitions of a head and n_wgs that of all workgroups (decode_cut), and launch_decode_combine appends
@@ -387,7 +388,7 @@ hi_status launch_decode_partial(void* stream, const void* q, int G, const void* 
 hi_status launch_decode_combine(void* stream, const void* q, int G, const void* k_new, const void* v_new,
                                 const void* partials, int n_part, void* out, int out_fp32, void* k_append,
                                 void* v_append, bool q_prescaled, int n_heads = 1, int64_t part_head_stride = 0,
-                                int64_t append_head_stride = 0, const DecodeLens* lens = nullptr);
+                                int64_t append_head_stride = 0, const DecodeLens* lens = nullptr, void* done = nullptr);
 
 // Streaming heads (Appendix E): a head that keeps n_sink initial and n_recent recent tokens in an HBM store of
 // n_sink + n_recent rows (sink token j at row j; token j >= n_sink at row n_sink + (j - n_sink) mod n_recent).
@@ -402,7 +403,7 @@ hi_status launch_prefill_window(void* stream, const void* q, int G, int chunk_le
 // The chunk's rows enter the store (run it after the chunk's attention, on the same stream).
 hi_status launch_stream_store_update(void* stream, const void* k_new, const void* v_new, int chunk_len,
                                      int64_t past_len, int n_sink, int n_recent, void* store_k, void* store_v,
-                                     int64_t store_head_stride, int n_heads);
+                                     int64_t store_head_stride, int n_heads, void* done = nullptr);
 
 // 4-bit rows of the host link: `planes` planes of `rows` rows each, plane p at base + p * pitch on either side
 // (bf16 rows of 256 bytes <-> encoded rows of kLinkRowBytes4 bytes).

@@ -2163,12 +2163,12 @@ static hi_status append_args(const PrefillAppend& ap, PrefillAppendArgs& p, int6
   return HI_OK;
 }
 
-hi_status launch_kv_append(void* stream, const PrefillAppend& ap) {
+hi_status launch_kv_append(void* stream, const PrefillAppend& ap, void* done) {
   PrefillAppendArgs p;
   int64_t units;
   const hi_status st = append_args(ap, p, units);
   if (st != HI_OK) return st;
-  hipLaunchKernelGGL(kv_append_kernel, dim3((unsigned)ceil_div(units, 256)), dim3(256), 0, (hipStream_t)stream, p);
+  launch_kernel(kv_append_kernel, dim3((unsigned)ceil_div(units, 256)), dim3(256), 0, stream, done, p);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) { set_last_error("append launch: %s", hipGetErrorString(e)); return HI_ERR_HIP; }
   return HI_OK;
@@ -2176,7 +2176,7 @@ hi_status launch_kv_append(void* stream, const PrefillAppend& ap) {
 
 hi_status launch_prefill(void* stream, const void* q, int G, int chunk_len, const PrefillSegment& sa,
                          const PrefillSegment& sb, int first, int last, void* carry, void* out, int out_fp32,
-                         int variant, const PrefillLaunch& unit, int n_heads, int64_t carry_bytes, const PrefillAppend* append) {
+                         int variant, const PrefillLaunch& unit, int n_heads, int64_t carry_bytes, const PrefillAppend* append, void* done) {
   if (n_heads < 1 || (variant & 3) == 2) { set_last_error("prefill launch: head group or variant"); return HI_ERR_UNSUPPORTED; }
   if (chunk_len < 1 || !(G == 1 || G == 2 || G == 4 || G == 8)) { set_last_error("prefill launch: bad shape"); return HI_ERR_ARG; }
   if (sa.causal || (sb.n > 0 && !sb.causal)) { set_last_error("prefill launch: segment order"); return HI_ERR_ARG; }
@@ -2217,6 +2217,7 @@ hi_status launch_prefill(void* stream, const void* q, int G, int chunk_len, cons
     app.first_z = (int)z_merge;
     return dim3(x, y, z_merge + (unsigned)ceil_div(app_units, (int64_t)x * y * threads));
   };
+  void* const kernel_done = pl.merge || append ? nullptr : done;      // the attention kernel, if nothing follows it
   a.split = pl.split;
   a.paired = pl.paired;
   a.nbk = pl.nbk;
@@ -2268,33 +2269,34 @@ hi_status launch_prefill(void* stream, const void* q, int G, int chunk_len, cons
     if (pl.strip > 0 && mfma32) { set_last_error("prefill launch: this kernel takes full blocks of positions"); return HI_ERR_UNSUPPORTED; }
     const bool wide = !mfma32 && pl.strip == 0 && ((variant & 128) != 0 ||
                                   ((variant & 64) == 0 && (sa.n + sb.n) / kPfTileRows >= (int64_t)kPrefillWideMinTiles * pl.split));
-    if (mfma32) hipLaunchKernelGGL(prefill_kernel_deep, grid, dim3(kPdWaves * 64), kPdLdsBytes, (hipStream_t)stream, a);
-    else if (wide && q_prescaled) hipLaunchKernelGGL(prefill_kernel_wide<true>, grid, dim3(kPwWaves * 64), kPdLdsBytes, (hipStream_t)stream, a);
-    else if (wide) hipLaunchKernelGGL(prefill_kernel_wide<false>, grid, dim3(kPwWaves * 64), kPdLdsBytes, (hipStream_t)stream, a);
-    else if (q_prescaled) hipLaunchKernelGGL(prefill_kernel_deep16<true>, grid, dim3(kPdWaves * 64), kPdLdsBytes, (hipStream_t)stream, a);
-    else hipLaunchKernelGGL(prefill_kernel_deep16<false>, grid, dim3(kPdWaves * 64), kPdLdsBytes, (hipStream_t)stream, a);
+    auto attend = [&](auto kernel, int waves) { launch_kernel(kernel, grid, dim3(waves * 64), kPdLdsBytes, stream, kernel_done, a); };
+    if (mfma32) attend(prefill_kernel_deep, kPdWaves);
+    else if (wide && q_prescaled) attend(prefill_kernel_wide<true>, kPwWaves);
+    else if (wide) attend(prefill_kernel_wide<false>, kPwWaves);
+    else if (q_prescaled) attend(prefill_kernel_deep16<true>, kPdWaves);
+    else attend(prefill_kernel_deep16<false>, kPdWaves);
     if (pl.merge) {
       hipError_t e1 = hipGetLastError();
       if (e1 != hipSuccess) { set_last_error("prefill launch: %s", hipGetErrorString(e1)); return HI_ERR_HIP; }
-      if (mfma32) hipLaunchKernelGGL(prefill_merge_kernel, merge_grid((unsigned)pl.nbk, grid.y, 4, kPdWaves * 64), dim3(kPdWaves * 64), 0, (hipStream_t)stream, a, app);
-      else hipLaunchKernelGGL(prefill_merge16_kernel, merge_grid((unsigned)pl.nbk, grid.y, 8, kPdWaves * 64), dim3(kPdWaves * 64), 0, (hipStream_t)stream, a, app);
+      if (mfma32) launch_kernel(prefill_merge_kernel, merge_grid((unsigned)pl.nbk, grid.y, 4, kPdWaves * 64), dim3(kPdWaves * 64), 0, stream, done, a, app);
+      else launch_kernel(prefill_merge16_kernel, merge_grid((unsigned)pl.nbk, grid.y, 8, kPdWaves * 64), dim3(kPdWaves * 64), 0, stream, done, a, app);
     }
   } else {
     const dim3 blocks((unsigned)ceil_div(chunk_len, strip), (unsigned)(gy * n_heads));
     if (pl.split > 1) {
-      hipLaunchKernelGGL(prefill_kernel<true>, dim3(blocks.x * (unsigned)pl.split, blocks.y), dim3(kWgThreads), 0, (hipStream_t)stream, a);
+      launch_kernel(prefill_kernel<true>, dim3(blocks.x * (unsigned)pl.split, blocks.y), dim3(kWgThreads), 0, stream, kernel_done, a);
       if (pl.merge) {
         hipError_t e1 = hipGetLastError();
         if (e1 != hipSuccess) { set_last_error("prefill launch: %s", hipGetErrorString(e1)); return HI_ERR_HIP; }
-        hipLaunchKernelGGL(prefill_merge4_kernel, merge_grid(blocks.x, blocks.y, 16, kWgThreads), dim3(kWgThreads), 0, (hipStream_t)stream, a, app);
+        launch_kernel(prefill_merge4_kernel, merge_grid(blocks.x, blocks.y, 16, kWgThreads), dim3(kWgThreads), 0, stream, done, a, app);
       }
     } else {
-      hipLaunchKernelGGL(prefill_kernel<false>, blocks, dim3(kWgThreads), 0, (hipStream_t)stream, a);
+      launch_kernel(prefill_kernel<false>, blocks, dim3(kWgThreads), 0, stream, kernel_done, a);
     }
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) { set_last_error("prefill launch: %s", hipGetErrorString(e)); return HI_ERR_HIP; }
-  return append && !pl.merge ? launch_kv_append(stream, *append) : HI_OK;
+  return append && !pl.merge ? launch_kv_append(stream, *append, done) : HI_OK;
 }
 
 hi_status launch_prefill_window(void* stream, const void* q, int G, int chunk_len, const void* store_k,
@@ -2332,7 +2334,7 @@ hi_status launch_prefill_window(void* stream, const void* q, int G, int chunk_le
 
 hi_status launch_stream_store_update(void* stream, const void* k_new, const void* v_new, int chunk_len,
                                      int64_t past_len, int n_sink, int n_recent, void* store_k, void* store_v,
-                                     int64_t store_head_stride, int n_heads) {
+                                     int64_t store_head_stride, int n_heads, void* done) {
   if (n_heads < 1 || chunk_len < 1 || past_len < 0 || n_sink < 0 || n_recent < 1) {
     set_last_error("store update launch: bad shape");
     return HI_ERR_ARG;
@@ -2343,9 +2345,8 @@ hi_status launch_stream_store_update(void* stream, const void* k_new, const void
   const int cr = chunk_len - u0r;
   if (cs + cr == 0) return HI_OK;
   dim3 grid((unsigned)ceil_div((int64_t)(cs + cr) * 16, 256), (unsigned)n_heads, 2);
-  hipLaunchKernelGGL(stream_store_update_kernel, grid, dim3(256), 0, (hipStream_t)stream, (const char*)k_new,
-                     (const char*)v_new, (char*)store_k, (char*)store_v, chunk_len, past_len, n_sink, n_recent, cs, u0r,
-                     cr, store_head_stride);
+  launch_kernel(stream_store_update_kernel, grid, dim3(256), 0, stream, done, (const char*)k_new, (const char*)v_new,
+                (char*)store_k, (char*)store_v, chunk_len, past_len, n_sink, n_recent, cs, u0r, cr, store_head_stride);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) { set_last_error("store update launch: %s", hipGetErrorString(e)); return HI_ERR_HIP; }
   return HI_OK;
