@@ -69,6 +69,21 @@ class HiError(RuntimeError):
 
 
 _lib = None
+_native = None       # _pycall, bound to the library: the calls of a token without ctypes (csrc/hi_pycall.cpp)
+
+
+def _load_native():
+    """The native marshalling; it returns None for arguments out of the ordinary, which then go through ctypes."""
+    global _native
+    L = lib()
+    try:
+        from . import _pycall
+    except ImportError as e:
+        raise RuntimeError("_pycall is missing: run `python -m paper_2502_12574_amd.build` first") from e
+    _pycall.bind(*[C.cast(f, C.c_void_p).value for f in (L.hi_prefill_group, L.hi_decode_group, L.hi_decode_group_ragged,
+                                                         L.hi_qkv_rope, L.hi_out_proj)], C.c_void_p)
+    _native = _pycall
+    return _native
 
 
 def lib() -> C.CDLL:
@@ -216,8 +231,11 @@ def hi_decode_head(ctx, layer, kv_head, q_dev, k_new_dev, v_new_dev, past_len, o
 
 def hi_prefill_group(ctx, layer, kv_head, n_heads, q_dev, k_new_dev, v_new_dev, past_len, chunk_len, out_dev,
                      next_layer=-1, next_kv_head=0, next_n_heads=1, next_past_len=0, check: bool = True):
-    st = lib().hi_prefill_group(ctx, layer, kv_head, n_heads, _ptr(q_dev), _ptr(k_new_dev), _ptr(v_new_dev), past_len,
-                                chunk_len, _ptr(out_dev), next_layer, next_kv_head, next_n_heads, next_past_len)
+    st = (_native or _load_native()).prefill_group(ctx, layer, kv_head, n_heads, q_dev, k_new_dev, v_new_dev, past_len, chunk_len,
+                                                      out_dev, next_layer, next_kv_head, next_n_heads, next_past_len)
+    if st is None:
+        st = lib().hi_prefill_group(ctx, layer, kv_head, n_heads, _ptr(q_dev), _ptr(k_new_dev), _ptr(v_new_dev), past_len,
+                                    chunk_len, _ptr(out_dev), next_layer, next_kv_head, next_n_heads, next_past_len)
     if check and st != HI_OK:
         raise HiError(st, "hi_prefill_group")
     return st
@@ -225,8 +243,11 @@ def hi_prefill_group(ctx, layer, kv_head, n_heads, q_dev, k_new_dev, v_new_dev, 
 
 def hi_decode_group(ctx, layer, kv_head, n_heads, q_dev, k_new_dev, v_new_dev, past_len, out_dev, next_layer=-1,
                     next_kv_head=0, next_n_heads=1, next_past_len=0, check: bool = True):
-    st = lib().hi_decode_group(ctx, layer, kv_head, n_heads, _ptr(q_dev), _ptr(k_new_dev), _ptr(v_new_dev), past_len,
-                               _ptr(out_dev), next_layer, next_kv_head, next_n_heads, next_past_len)
+    st = (_native or _load_native()).decode_group(ctx, layer, kv_head, n_heads, q_dev, k_new_dev, v_new_dev, past_len, out_dev,
+                                                     next_layer, next_kv_head, next_n_heads, next_past_len)
+    if st is None:
+        st = lib().hi_decode_group(ctx, layer, kv_head, n_heads, _ptr(q_dev), _ptr(k_new_dev), _ptr(v_new_dev), past_len,
+                                   _ptr(out_dev), next_layer, next_kv_head, next_n_heads, next_past_len)
     if check and st != HI_OK:
         raise HiError(st, "hi_decode_group")
     return st
@@ -234,9 +255,12 @@ def hi_decode_group(ctx, layer, kv_head, n_heads, q_dev, k_new_dev, v_new_dev, p
 
 def hi_decode_group_ragged(ctx, layer, kv_head, n_heads, q_dev, k_new_dev, v_new_dev, past_lens, out_dev,
                            check: bool = True):
-    lens = (C.c_int64 * n_heads)(*[int(x) for x in past_lens])
-    st = lib().hi_decode_group_ragged(ctx, layer, kv_head, n_heads, _ptr(q_dev), _ptr(k_new_dev), _ptr(v_new_dev), lens,
-                                      _ptr(out_dev))
+    st = (_native or _load_native()).decode_group_ragged(ctx, layer, kv_head, n_heads, q_dev, k_new_dev, v_new_dev, past_lens,
+                                                            out_dev)
+    if st is None:
+        lens = (C.c_int64 * n_heads)(*[int(x) for x in past_lens])
+        st = lib().hi_decode_group_ragged(ctx, layer, kv_head, n_heads, _ptr(q_dev), _ptr(k_new_dev), _ptr(v_new_dev), lens,
+                                          _ptr(out_dev))
     if check and st != HI_OK:
         raise HiError(st, "hi_decode_group_ragged")
     return st
@@ -252,9 +276,12 @@ def hi_proj_workspace_bytes(chunk_len: int) -> int:
 
 def hi_qkv_rope(stream, x_dev, w_qkv_dev, d_model, n_q_heads, n_kv_heads, chunk_len, past_len, rope_theta, out_fp32,
                 q_out_dev, k_out_dev, v_out_dev, workspace_dev, q_scale: float = 1.0, check: bool = True):
-    st = lib().hi_qkv_rope(_stream(stream), _ptr(x_dev), _ptr(w_qkv_dev), d_model, n_q_heads, n_kv_heads, chunk_len,
-                           past_len, float(rope_theta), out_fp32, _ptr(q_out_dev), _ptr(k_out_dev), _ptr(v_out_dev),
-                           _ptr(workspace_dev), float(q_scale))
+    st = (_native or _load_native()).qkv_rope(stream, x_dev, w_qkv_dev, d_model, n_q_heads, n_kv_heads, chunk_len, past_len,
+                                                 rope_theta, out_fp32, q_out_dev, k_out_dev, v_out_dev, workspace_dev, q_scale)
+    if st is None:
+        st = lib().hi_qkv_rope(_stream(stream), _ptr(x_dev), _ptr(w_qkv_dev), d_model, n_q_heads, n_kv_heads, chunk_len,
+                               past_len, float(rope_theta), out_fp32, _ptr(q_out_dev), _ptr(k_out_dev), _ptr(v_out_dev),
+                               _ptr(workspace_dev), float(q_scale))
     if check and st != HI_OK:
         raise HiError(st, "hi_qkv_rope")
     return st
@@ -271,8 +298,10 @@ def hi_qkv_rope_static(stream, x_dev, w_qkv_dev, d_model, n_q_heads, n_kv_heads,
 
 
 def hi_out_proj(stream, attn_dev, w_o_dev, n_q_heads, d_model, chunk_len, out_fp32, y_out_dev, check: bool = True):
-    st = lib().hi_out_proj(_stream(stream), _ptr(attn_dev), _ptr(w_o_dev), n_q_heads, d_model, chunk_len, out_fp32,
-                           _ptr(y_out_dev))
+    st = (_native or _load_native()).out_proj(stream, attn_dev, w_o_dev, n_q_heads, d_model, chunk_len, out_fp32, y_out_dev)
+    if st is None:
+        st = lib().hi_out_proj(_stream(stream), _ptr(attn_dev), _ptr(w_o_dev), n_q_heads, d_model, chunk_len, out_fp32,
+                               _ptr(y_out_dev))
     if check and st != HI_OK:
         raise HiError(st, "hi_out_proj")
     return st

@@ -1,15 +1,17 @@
-"""Compile the HIP sources into paper_2502_12574_amd/libheadinfer.so (gfx950 only)."""
+"""Compile the HIP sources into paper_2502_12574_amd/libheadinfer.so (gfx950 only), and the native call marshalling for Python."""
 from __future__ import annotations
 
 import os
 import shutil
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libheadinfer.so")
+PYCALL = os.path.join(HERE, "_pycall" + sysconfig.get_config_var("EXT_SUFFIX"))     # native marshalling for binding.py (host code)
 SOURCES = ["hi_plan.cpp", "hi_ctx.hip", "hi_decode.hip", "hi_prefill.hip", "hi_proj.hip", "hi_kvq.hip"]
 
 HIPCC_FLAGS = [
@@ -47,6 +49,13 @@ def build(verbose: bool = False) -> str:
             raise RuntimeError(f"hipcc failed on {src}:\n{out}")
         if verbose and out.strip():
             print(out)
+    tmp = PYCALL + ".tmp"
+    cmd = ["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-I", sysconfig.get_paths()["include"], "-I", os.path.join(ROOT, "include"),
+           os.path.join(CSRC, "hi_pycall.cpp"), "-o", tmp]
+    r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("g++ failed on hi_pycall.cpp:\n" + r.stdout)
+    os.replace(tmp, PYCALL)
     tmp = LIB + ".tmp"
     cmd = [hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp, *objs]
     r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
