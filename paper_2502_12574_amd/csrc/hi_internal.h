@@ -127,6 +127,9 @@ inline int prefill_narrow_split(int G, int64_t C, int64_t past, int64_t capacity
 // 1.9 per tile for its first 14 tiles (ring fill, masked and alignment tiles), then 1.1 per tile while at most 190 run and
 // up to 1.45 on a full chip (power).  A paired launch makes two passes (12 more).  The merge: 5 + 0.035 per image.  The
 // 4-wave kernel: 4 + 1.3 per tile with one workgroup per compute unit, 1.9 with two.
+// (The constants are those of the 8-wave kernel before its short launches became steady ones; constants re-fitted to it, 8 to
+// start, 0.35 more for each of four tiles, 1.15 to 1.5 per tile, 8 a second pass, chose worse ones: 0.79 to 1.02 times as fast
+// over 23 shapes.)
 // What it replaces sized the split by the chunk alone, in powers of two up to 8: 77 rows of 8 heads behind 100 thousand ran
 // on 128 workgroups (302 us, now 178), 600 rows behind 3000 in two rounds of workgroups (92 -> 70), 2400 rows behind 5000
 // likewise (333 -> 277).  Chunks that the rule by the chunk alone gives to the 4-wave kernel stay there, cut into ranges.
@@ -206,7 +209,8 @@ inline PrefillLaunch prefill_unit_shape(int G, int64_t C, int n_heads, int varia
   }
   // Blocks of one height instead of full ones and a rest: the rest's workgroups, with fewer matrix instructions per tile, would run
   // ahead through K/V rows that the others then fetch once more.  (prefill_kernel_deep16 only; a block is a multiple of 16
-  // positions.)  77 rows of 8 heads behind 100 thousand, 64 + 13 positions -> 48 + 29: see DESIGN
+  // positions.)  300 rows of 32 heads, one query head each: 256 + 44 positions -> 160 + 140, 204 -> 199 us behind 30 thousand, 76 ->
+  // 69 behind 3000; 77 rows of 32 heads behind 3000, 64 + 13 -> 48 + 29: 73 -> 67; of 8 heads behind 100 thousand the same.
   if (best.deep && !(variant & (16 | 128))) {
     const int64_t even = round_up(ceil_div(C, best.nbk), 16);
     if (even < 2 * strip && (best.nbk - 1) * even < C) best.strip = (int)even;

@@ -1147,11 +1147,9 @@ __device__ __forceinline__ void pf16_softmax(f32x16 (&s)[NQ], PfState16<NQ>& st,
 // it must (see pf_softmax_fast).  The scores are scaled in place first, so that the 32 multiplications and the 32
 // exponentials are independent instructions (with a shared temporary they formed one dependent chain).
 // PRESCALED: the queries carry the softmax scale already (c is 1): the scores are exponents as they leave the matrix pipe.
-// least: kPfSumLimit, or 1 in short passes, where the reference also moves when a lane's sum of this tile exceeds 1 and half of
-// all it has summed before.  A row that one
-// key dominates then has that key at exactly 1, which bf16 holds exactly; against a lower reference the rounding of
-// its weight is the row's whole error (600 rows behind 3000, one key in ten scaled by four: relative error 1.4e-3 against
-// 64 bits).  Rows whose weight is spread do not get there, and need not.
+// least: kPfSumLimit, or 1 where the reference also moves when a lane's sum of this tile exceeds 1 and half of all it has
+// summed before (short passes): a row that one key dominates then has that key at exactly 1, which bf16 holds exactly, where the
+// rounding of its weight against a lower reference is the row's whole error.
 template <bool PRESCALED, int NQ>
 __device__ __forceinline__ void pf16_softmax_fast(f32x16 (&s)[NQ], PfState16<NQ>& st, float c, float least,
                                                   f32x4 (&cinit)[NQ], bf16x8 (&pb)[2][NQ]) {
@@ -1242,11 +1240,14 @@ __device__ __forceinline__ void pf16_write_row(void* out, int out_fp32, int C, i
   }
 }
 
-// Passes up to kPd16ShortTiles move their references early throughout (see pf16_softmax_fast), longer ones in their last
-// kPd16LastTiles tiles only: with peaked keys most tiles of a pass would (77 rows behind 100 thousand, 98 tiles: 242 us
-// instead of 175).  (Not in the first ones: a reference just below a row's largest key leaves that key's weight just above 1,
-// where bf16 is coarsest.)
-constexpr int kPd16ShortTiles = 32, kPd16LastTiles = 12;
+// Passes up to kPd16ShortTiles take the maxima of their first eight tiles and move their references early behind them (see
+// pf16_softmax_fast), longer ones take those of four and move early in their last kPd16LastTiles tiles only: with peaked keys most
+// tiles of a pass would (77 rows behind 100 thousand, 98 tiles: 242 us instead of 175; 200 behind 15 thousand, 30 tiles: 104
+// instead of 93).  Relative error against 64 bits, as it was (maxima of every tile, or from 15 tiles on of about half of them) ->
+// now: 600 rows behind 3001 (17 tiles) 1.53e-3 -> 1.55e-3, with one key in ten scaled by four 0.98e-3 -> 0.31e-3; 300 behind
+// 4000 1.46e-3 -> 1.50e-3; 200 behind 50 thousand 1.64e-3 -> 1.66e-3.  Moving at a quarter instead of half brought the first to
+// 1.52e-3 and took 5 us more of 75.
+constexpr int kPd16ShortTiles = 24, kPd16LastTiles = 12;
 
 // Where the wavefront's two blocks of 16 query rows lie in a block of a.strip positions: next to each other where the block is
 // full (the layout prefill_kernel_wide shares); with fewer positions every wavefront's first block comes before any second one,
@@ -1514,11 +1515,11 @@ __device__ __forceinline__ void pd16_pass(const PrefillArgs& a, const PfPass& ps
     wait_vmcnt<4>();                             // everything up to V(t+1) has landed
     phase_barrier();
   };
-  // The first four tiles take their maxima: the largest weight of a row is then exactly 1 where one of them holds it, as under
+  // The first tiles take their maxima: the largest weight of a row is then exactly 1 where one of them holds it, as under
   // a decaying bias.  From there on every row has a reference - it has seen a past row, or an own row at or before the first
   // position of this wavefront; a range of own tiles that begins behind that may leave rows without one, and goes on so.
   const bool no_reference = sw.ta == 0 && ps.b0 * kPfTileRows > i0;
-  const int general = no_reference || T < 4 ? T : 4;
+  const int early = T <= kPd16ShortTiles ? 8 : 4, general = no_reference || T < early ? T : early;
   int t = 1;
   uint32_t slot = 0;                             // ring offset of tile t - 1; the operand addresses move with it
 #pragma nounroll
@@ -1534,7 +1535,7 @@ __device__ __forceinline__ void pd16_pass(const PrefillArgs& a, const PfPass& ps
     });
     slot = next;
   }
-  if (t < T) {                                   // t = 4: the rings are back at their starts
+  if (t < T) {                                   // t = 4 or 8: the rings are back at their starts
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) {
       lc.koff[kk] -= 3 * kPfTileBytes;
