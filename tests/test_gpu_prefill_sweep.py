@@ -1,17 +1,19 @@
-"""prefill_kernel_deep16 where its sweep can go wrong: passes of one tile and more on either side of the four that take their
+"""prefill_kernel_deep16 where its sweep can go wrong: passes of one tile and more on either side of the eight that take their
 maxima first, partial tiles at the end of the past and of the chunk, blocks of 16 query rows that the chunk leaves empty (in the
 last block of positions, across launches too), and ranges of own tiles whose first tile some rows do not see at all."""
 import pytest
+import torch
 
 from oracle import attention as oa
 from paper_2502_12574_amd import binding as hb
 from paper_2502_12574_amd import synth
+from paper_2502_12574_amd.session import Session
 from test_gpu_parity_small import check, one_unit
 
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("P", [0, 1, 64, 129, 256, 300, 321])
+@pytest.mark.parametrize("P", [0, 1, 64, 129, 256, 300, 321, 700])
 @pytest.mark.parametrize("G,C", [(4, 16), (4, 17), (4, 33), (4, 64), (4, 77), (4, 97), (1, 5), (1, 44), (1, 256), (1, 300), (2, 145), (8, 50)])
 @pytest.mark.parametrize("mode", [hb.HI_MODE_RESIDENT, hb.HI_MODE_OFFLOAD])
 @pytest.mark.parametrize("paired", [False, True])
@@ -21,3 +23,23 @@ def test_short_sweeps_and_empty_blocks(G, C, P, mode, paired):
     ref = oa.attn_head(synth.to_f64(Q), synth.to_f64(K), synth.to_f64(V), past_len=P)
     for g in range(G):
         check(out[g:g + 1], ref[g:g + 1], f"G={G} P={P} C={C} head {g}")
+
+
+# units with a merge launch, which takes the append along: of the 8-wave kernel (few blocks, many; two grid rows a head) and of
+# the 4-wave kernel's ranges
+@pytest.mark.parametrize("G,H,first,nh,past,C", [(1, 17, 1, 16, 3000, 150), (4, 8, 0, 8, 3001, 77), (8, 9, 2, 7, 1500, 130),
+                                                 (4, 8, 0, 8, 64, 1000), (4, 3, 1, 1, 4000, 33), (1, 2, 0, 2, 2500, 1)])
+def test_rows_land_in_place_along_with_a_merge(G, H, first, nh, past, C):
+    dev = "cuda:0"
+    with Session(1, H, G, past + C + 200, C, mode=hb.HI_MODE_RESIDENT, out_fp32=0) as ss:
+        view = ss.cache_view()
+        view.copy_(torch.randn(view.shape, device=dev).to(torch.bfloat16))
+        k, v = (torch.randn(nh, C, 128, device=dev).to(torch.bfloat16) for _ in range(2))
+        q = torch.randn(nh, G, C, 128, device=dev).to(torch.bfloat16)
+        out = torch.empty(nh, G, C, 128, dtype=torch.bfloat16, device=dev)
+        want = view.clone()
+        want[0, first:first + nh, 0, past:past + C], want[0, first:first + nh, 1, past:past + C] = k, v
+        ss.s_compute.wait_stream(torch.cuda.current_stream())
+        ss.prefill_group(0, first, nh, q, k, v, past, out)
+        ss.sync()
+        assert torch.equal(view, want) and torch.isfinite(out).all()
