@@ -1026,22 +1026,23 @@ __device__ __forceinline__ void pd16_preread(uint32_t v_off, const PfLane16& lc,
 }
 
 // The matrix phase: O^T += V^T P^T of the previous tile, then S^T = K Q^T of the next - 64 MFMAs, their 32 LDS operands
-// read kPfAhead operands ahead.  LOADS: 0 = the phase issues the global loads that ld names (either may be null),
-// 1 = both unconditionally.  Other switches as in pd_matrix_phase.
-template <int LOADS, bool PREREAD, bool CINIT, bool EARLY_BARRIER, int NQ>
+// read kPfAhead operands ahead; the caller has read the first of them into pre (during its softmax phase).  The phase issues the
+// global loads that ld names, and passes the workgroup barrier that ends it before its last MFMAs (as EARLY_BARRIER in
+// pd_matrix_phase).  CINIT: the score accumulators start from cinit instead of zero.
+template <bool CINIT, int NQ>
 __device__ __forceinline__ void pd16_matrix_phase(uint32_t v_off, uint32_t k_off, const PfLane16& lc,
                                                   const bf16x8 (&qf)[4][NQ], const bf16x8 (&pb)[2][NQ], PfState16<NQ>& st,
                                                   f32x16 (&s)[NQ], const PfPhaseLoads& ld,
                                                   const bf16x8 (&pre)[kPfAhead], const f32x4 (&cinit)[NQ]) {
   bf16x8 op[kPfAhead + 1];
 #pragma unroll
-  for (int i = 0; i < kPfAhead; ++i) op[i] = PREREAD ? pre[i] : pd16_operand(i, v_off, k_off, lc);
+  for (int i = 0; i < kPfAhead; ++i) op[i] = pre[i];
   __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
   for (int i = 0; i < 32; ++i) {
     if (i + kPfAhead < 32) op[(i + kPfAhead) % (kPfAhead + 1)] = pd16_operand(i + kPfAhead, v_off, k_off, lc);
     bf16x8 x = op[i % (kPfAhead + 1)];
-    if (EARLY_BARRIER && i == 31) {
+    if (i == 31) {
       asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(x) : : "memory");
       __builtin_amdgcn_s_barrier();
       __builtin_amdgcn_sched_barrier(0);
@@ -1064,10 +1065,10 @@ __device__ __forceinline__ void pd16_matrix_phase(uint32_t v_off, uint32_t k_off
         q4_set(s[t4 >> 2], t4 & 3, __builtin_amdgcn_mfma_f32_16x16x32_bf16(x, qf[kk][qb], c0, 0, 0, 0));
       }
     }
-    if (i == 1 && (LOADS == 1 || (LOADS == 0 && ld.k))) g2lds16_s<0>(ld.k, lc.gk[0], ld.ldk);
-    if (i == 3 && (LOADS == 1 || (LOADS == 0 && ld.k))) g2lds16_s<0>(ld.k, lc.gk[1], ld.ldk + 1024);
-    if (i == 5 && (LOADS == 1 || (LOADS == 0 && ld.v))) g2lds16_s<0>(ld.v, lc.gv[0], ld.ldv);
-    if (i == 7 && (LOADS == 1 || (LOADS == 0 && ld.v))) g2lds16_s<0>(ld.v, lc.gv[1], ld.ldv + 1024);
+    if (i == 1) g2lds16_s<0>(ld.k, lc.gk[0], ld.ldk);
+    if (i == 3) g2lds16_s<0>(ld.k, lc.gk[1], ld.ldk + 1024);
+    if (i == 5) g2lds16_s<0>(ld.v, lc.gv[0], ld.ldv);
+    if (i == 7) g2lds16_s<0>(ld.v, lc.gv[1], ld.ldv + 1024);
     __builtin_amdgcn_sched_barrier(0);
   }
 }
@@ -1268,11 +1269,11 @@ __device__ __forceinline__ Pf16Rows pf16_rows(const PrefillArgs& a, int bx, int 
 // has NQ blocks of 16 query rows before the chunk's end (NQ = 0: it has none, and only takes its share of the tile loads and
 // the barriers).  Rows that are not there cost matrix instructions, and with them clock: the kernel runs at the power limit.
 // What a pass costs, by time stamps of 600 rows of 8 heads behind 3000 (240 workgroups of 17 tiles): 6.5 us until the first
-// tile is done (the fill of 144 KB per workgroup), 1.8 us for each of the next three, 1.5 for every other one, 2 to
-// store the state; 42 us in all.  Before, only groups of four tiles that were full, unmasked and followed by full ones ran the
+// tile is done (the fill of 144 KB per workgroup), 2.3 us for each of the next seven, which take their maxima, 1.5 for every other
+// one, 2 to store the state.  Before, only groups of four tiles that were full, unmasked and followed by full ones ran the
 // steady routine; the others, 11 of 17 here, took one of 2.6 us that took the maxima, chose its ring slot and its loads tile by
-// tile and added every operand's address between the MFMAs, and integer divisions took 3 us at the start: 59 us.  Now
-// every tile from the fifth on is a steady one, with two scalar counters and a comparison more.
+// tile and added every operand's address between the MFMAs, and integer divisions took 3 us at the start: 59 us a
+// launch, now 48.  A steady tile has two scalar counters and a comparison more than it had.
 template <bool PRESCALED, int NQ>
 __device__ __forceinline__ void pd16_pass(const PrefillArgs& a, const PfPass& ps, uint32_t lds_base, int lane,
                                           int wave, int g, int i0, int step, float* images) {
@@ -1487,7 +1488,7 @@ __device__ __forceinline__ void pd16_pass(const PrefillArgs& a, const PfPass& ps
     ld.ldk = ld_wave + ldk;
     ld.ldv = ld_wave + kPdVRing + ldv;
     __builtin_amdgcn_s_setprio(2);
-    pd16_matrix_phase<1, true, !GENERAL, true, NS>(v_off, k_off, lc, qf, pb, st, sc, ld, pre, cinit);
+    pd16_matrix_phase<!GENERAL, NS>(v_off, k_off, lc, qf, pb, st, sc, ld, pre, cinit);
     __builtin_amdgcn_s_setprio(0);
     after();                                     // V(t)'s first operands, for the next matrix phase
     __builtin_amdgcn_sched_barrier(0);
