@@ -1694,15 +1694,22 @@ __device__ __forceinline__ bool pf_append_block(const PrefillAppendArgs& p) {
 
 // Merge of the states of prefill_kernel_deep16 (its own image layout): grid (blocks, grid rows, 8): z is one dim block
 // of both query rows of the lane.  Bound by the read of the images (139 KB each, up to 64 per block), and where a block has
-// few of them by its latency: CH images are in flight per lane, in one pass.  8 heads of 2 blocks of 16 images take 7.6 us with
-// the append (maxima first and sums in a second pass: 11.4), of 10 blocks of 3 images 9.0 (10.0).  Behind the merge's blocks
-// others append the chunk's rows to the cache: as a launch of its own behind this one that took 4.3 us and the gap before it.
+// few of them by its latency: CH images are in flight per lane, and behind the first CH the references of all others.  The largest
+// reference comes first, then the sums in the images' order, each image with one weight.  Shortest and median time with the
+// append: 8 heads of 2 blocks of 16 images 8.6 and 10.0 us, of 10 blocks of 3 images 9.2 and 10.3; 10.2 and 11.5, 9.4 and 10 without
+// the append where four images were in flight in two loops.  (A single pass that rescales what it has summed takes 7.6 and 8.8 for
+// the first, and other bits.)  Behind the merge's blocks others append the chunk's rows to the cache: as a launch of its own
+// behind this one that took 4.3 us and the gap before it.
 template <int NQ, int CH>
 __device__ __forceinline__ void pf16_merge(const PrefillArgs& a, const PfShape& sh, const Pf16Rows& rows16, int bx, int db, int n_e,
                                            int n, int g, int g16, int c16) {
   constexpr int kLanes = kPdWaves * 64;
   constexpr int kImageFloats = kCarryFloatsPerLane * kLanes;
   const float* images = a.carry + (int64_t)blockIdx.y * a.img_row * kImageFloats + threadIdx.x;
+  auto image_of = [&](int i) __attribute__((always_inline)) {
+    if (i >= n) i = n - 1;                            // (behind the last image: the last one again, which then takes no part)
+    return images + (int64_t)(i < n_e ? pf_image_e(sh, bx, i) : pf_image_x(sh, bx, i - n_e)) * kImageFloats;
+  };
   float m[NQ], l[NQ];
   f32x4 o[NQ];
 #pragma unroll
@@ -1715,9 +1722,8 @@ __device__ __forceinline__ void pf16_merge(const PrefillArgs& a, const PfShape& 
   for (int i0 = 0; i0 < n; i0 += CH) {
     float mi[CH][NQ], li[CH][NQ], oi[CH][NQ][4];
 #pragma unroll
-    for (int j = 0; j < CH; ++j) {                    // (behind the last image: the last one again, with weight 0)
-      const int i = i0 + j < n ? i0 + j : n - 1;
-      const float* im = images + (int64_t)(i < n_e ? pf_image_e(sh, bx, i) : pf_image_x(sh, bx, i - n_e)) * kImageFloats;
+    for (int j = 0; j < CH; ++j) {
+      const float* im = image_of(i0 + j);
 #pragma unroll
       for (int qb = 0; qb < NQ; ++qb) {
         mi[j][qb] = im[(64 + qb) * kLanes];
@@ -1726,21 +1732,39 @@ __device__ __forceinline__ void pf16_merge(const PrefillArgs& a, const PfShape& 
         for (int r = 0; r < 4; ++r) oi[j][qb][r] = im[((db * 2 + qb) * 4 + r) * kLanes];
       }
     }
+    if (i0 == 0) {
+#pragma nounroll
+      for (int k0 = CH; k0 < n; k0 += 6) {
+        float x[6][NQ];
 #pragma unroll
-    for (int qb = 0; qb < NQ; ++qb) {
-      float top = m[qb];
+        for (int j = 0; j < 6; ++j) {
+          const float* im = image_of(k0 + j);
 #pragma unroll
-      for (int j = 0; j < CH; ++j) top = fmaxf(top, mi[j][qb]);
-      const float old = fast_exp2((m[qb] - top) * a.c);
-      m[qb] = top;
-      l[qb] *= old;
-      o[qb] *= old;
+          for (int qb = 0; qb < NQ; ++qb) x[j][qb] = im[(64 + qb) * kLanes];
+        }
 #pragma unroll
-      for (int j = 0; j < CH; ++j) {
-        const float w = i0 + j < n ? fast_exp2((mi[j][qb] - top) * a.c) : 0.f;
-        l[qb] += w * li[j][qb];
+        for (int j = 0; j < 6; ++j)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) o[qb][r] += w * oi[j][qb][r];
+          for (int qb = 0; qb < NQ; ++qb) m[qb] = fmaxf(m[qb], x[j][qb]);
+      }
+#pragma unroll
+      for (int j = 0; j < CH; ++j)
+#pragma unroll
+        for (int qb = 0; qb < NQ; ++qb) m[qb] = fmaxf(m[qb], mi[j][qb]);
+    }
+#pragma unroll
+    for (int j = 0; j < CH; ++j) {
+      const bool there = i0 + j < n;                  // (a weight of 0 would make NaN of an infinite value)
+#pragma unroll
+      for (int qb = 0; qb < NQ; ++qb) {
+        const float w = fast_exp2((mi[j][qb] - m[qb]) * a.c);
+        const float ls = l[qb] + w * li[j][qb];
+        l[qb] = there ? ls : l[qb];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const float os = o[qb][r] + w * oi[j][qb][r];
+          o[qb][r] = there ? os : o[qb][r];
+        }
       }
     }
   }
@@ -1751,7 +1775,7 @@ __device__ __forceinline__ void pf16_merge(const PrefillArgs& a, const PfShape& 
   }
 }
 
-__global__ __launch_bounds__(512) void prefill_merge16_kernel(PrefillArgs a, PrefillAppendArgs append) {
+__global__ __launch_bounds__(512, 4) void prefill_merge16_kernel(PrefillArgs a, PrefillAppendArgs append) {
   if (pf_append_block(append)) return;
   const int lane = lane_id();
   const int wave = wave_id();

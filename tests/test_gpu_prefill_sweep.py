@@ -36,10 +36,44 @@ def test_rows_land_in_place_along_with_a_merge(G, H, first, nh, past, C):
         view.copy_(torch.randn(view.shape, device=dev).to(torch.bfloat16))
         k, v = (torch.randn(nh, C, 128, device=dev).to(torch.bfloat16) for _ in range(2))
         q = torch.randn(nh, G, C, 128, device=dev).to(torch.bfloat16)
-        out = torch.empty(nh, G, C, 128, dtype=torch.bfloat16, device=dev)
+        out = torch.full((nh, G, C, 128), float("nan"), dtype=torch.bfloat16, device=dev)
         want = view.clone()
         want[0, first:first + nh, 0, past:past + C], want[0, first:first + nh, 1, past:past + C] = k, v
         ss.s_compute.wait_stream(torch.cuda.current_stream())
         ss.prefill_group(0, first, nh, q, k, v, past, out)
         ss.sync()
         assert torch.equal(view, want) and torch.isfinite(out).all()
+
+
+# ranges of the 8-wave kernel (2, 3, 5, 16 and more images of a block: below, at and beyond what the merge has in flight), its other
+# forms, and the 4-wave kernel's ranges
+@pytest.mark.parametrize("G,H,past,C,flags", [(4, 8, 3001, 600, 0), (4, 8, 3001, 77, 0), (4, 8, 20003, 77, 0), (1, 16, 5000, 150, 0),
+                                              (4, 1, 4000, 300, hb.HI_FLAG_PREFILL_DEEP), (8, 2, 1500, 130, hb.HI_FLAG_PREFILL_DEEP),
+                                              (4, 2, 3001, 300, hb.HI_FLAG_PREFILL_DEEP | hb.HI_FLAG_PREFILL_PAIRED),
+                                              (4, 2, 3001, 300, hb.HI_FLAG_PREFILL_DEEP | hb.HI_FLAG_PREFILL_MFMA32),
+                                              (4, 2, 3001, 300, hb.HI_FLAG_PREFILL_DEEP | hb.HI_FLAG_PREFILL_WIDE), (4, 1, 4000, 33, 0)])
+@pytest.mark.parametrize("mode", [hb.HI_MODE_RESIDENT, hb.HI_MODE_OFFLOAD])
+def test_an_infinite_value_stays_infinite(G, H, past, C, flags, mode):
+    """An infinite channel of a cached V row makes that channel infinite and no other, whatever range of tiles holds the row."""
+    dev = "cuda:0"
+    gen = torch.Generator(device=dev).manual_seed(62000 + past + C)
+    rows = torch.randint(-8, 9, (H, 2, past + C, 128), device=dev, generator=gen).to(torch.bfloat16)
+    q = torch.zeros(H, G, C, 128, dtype=torch.bfloat16, device=dev)
+    ats = [0, past // 3, past // 2, past - 70, past - 2]         # (the last row stands in for rows behind the end, with weight 0)
+    want = rows[:, 1].double().cumsum(dim=1)[:, past:] / torch.arange(past + 1, past + C + 1, device=dev)[None, :, None]
+    with Session(1, H, G, past + C, C, mode=mode, out_fp32=1) as ss:
+        hb.hi_ctx_set_flags(ss.ctx, flags)
+        view = ss.cache_view()
+        k, v = (rows[:, w, past:].contiguous() for w in (0, 1))
+        for at in ats:
+            cached = rows[:, :, :past].clone()
+            cached[:, 1, at, 5], cached[:, 1, at, 77] = float("inf"), float("-inf")
+            view[0, :, :, :past] = cached.to(view.device)
+            out = torch.full((H, G, C, 128), float("nan"), device=dev)
+            torch.cuda.synchronize()
+            ss.prefill_group(0, 0, H, q, k, v, past, out)
+            ss.sync()
+            assert (out[..., 5] == float("inf")).all() and (out[..., 77] == float("-inf")).all(), at
+            out[..., 5], out[..., 77] = want[:, None, :, 5].float(), want[:, None, :, 77].float()
+            # whole sums in fp32, one quotient: two roundings of numbers up to 8
+            assert (out - want[:, None]).abs().max() <= 1e-5, at
