@@ -1087,20 +1087,17 @@ __device__ __forceinline__ float sum_groups16(float x) {
 // Online softmax of one tile (general form: raw scores, running maximum moved when it must, masks).  rel[qb]: key
 // rows of the tile with index > rel[qb] are hidden from the lane's query of block qb.
 template <int NQ>
-__device__ __forceinline__ void pf16_mask(f32x16 (&s)[NQ], const int (&rel)[NQ], int g16) {
-#pragma unroll
-  for (int kb = 0; kb < 4; ++kb)
-#pragma unroll
-    for (int qb = 0; qb < NQ; ++qb)
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-        if (16 * kb + 4 * g16 + r > rel[qb]) PF16_S(s, kb, qb, r) = kNegBig;
-}
-
-template <int NQ>
 __device__ __forceinline__ void pf16_softmax(f32x16 (&s)[NQ], PfState16<NQ>& st, float c, bool masked, const int (&rel)[NQ],
                                              int g16, bf16x8 (&pb)[2][NQ]) {
-  if (masked) pf16_mask<NQ>(s, rel, g16);
+  if (masked) {
+#pragma unroll
+    for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+      for (int qb = 0; qb < NQ; ++qb)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (16 * kb + 4 * g16 + r > rel[qb]) PF16_S(s, kb, qb, r) = kNegBig;
+  }
   float m_new[NQ];
 #pragma unroll
   for (int qb = 0; qb < NQ; ++qb) {
@@ -1148,12 +1145,9 @@ __device__ __forceinline__ void pf16_softmax(f32x16 (&s)[NQ], PfState16<NQ>& st,
 // it must (see pf_softmax_fast).  The scores are scaled in place first, so that the 32 multiplications and the 32
 // exponentials are independent instructions (with a shared temporary they formed one dependent chain).
 // PRESCALED: the queries carry the softmax scale already (c is 1): the scores are exponents as they leave the matrix pipe.
-// least: kPfSumLimit, or 1 where the reference also moves when a lane's sum of this tile exceeds 1 and half of all it has
-// summed before (short passes): a row that one key dominates then has that key at exactly 1, which bf16 holds exactly, where the
-// rounding of its weight against a lower reference is the row's whole error.
 template <bool PRESCALED, int NQ>
-__device__ __forceinline__ void pf16_softmax_fast(f32x16 (&s)[NQ], PfState16<NQ>& st, float c, float least,
-                                                  f32x4 (&cinit)[NQ], bf16x8 (&pb)[2][NQ]) {
+__device__ __forceinline__ void pf16_softmax_fast(f32x16 (&s)[NQ], PfState16<NQ>& st, float c, f32x4 (&cinit)[NQ],
+                                                  bf16x8 (&pb)[2][NQ]) {
   if (!PRESCALED) {
 #pragma unroll
     for (int j = 0; j < NQ; ++j)
@@ -1177,10 +1171,7 @@ __device__ __forceinline__ void pf16_softmax_fast(f32x16 (&s)[NQ], PfState16<NQ>
     }
   };
   probs();
-  float limit[NQ];
-#pragma unroll
-  for (int qb = 0; qb < NQ; ++qb) limit[qb] = __builtin_amdgcn_fmed3f(0.5f * st.l[qb], least, kPfSumLimit);
-  if (__builtin_amdgcn_ballot_w64(!(ls[0] <= limit[0]) || !(ls[NQ - 1] <= limit[NQ - 1])) != 0) {    // also inf and NaN
+  if (__builtin_amdgcn_ballot_w64(!(ls[0] <= kPfSumLimit) || !(ls[NQ - 1] <= kPfSumLimit)) != 0) {    // also inf and NaN
     const float inv_c = 1.0f / c;
 #pragma unroll
     for (int qb = 0; qb < NQ; ++qb) {
@@ -1241,15 +1232,6 @@ __device__ __forceinline__ void pf16_write_row(void* out, int out_fp32, int C, i
   }
 }
 
-// Passes up to kPd16ShortTiles take the maxima of their first eight tiles and move their references early behind them (see
-// pf16_softmax_fast), longer ones take those of four and move early in their last kPd16LastTiles tiles only: with peaked keys most
-// tiles of a pass would (77 rows behind 100 thousand, 98 tiles: 242 us instead of 175; 200 behind 15 thousand, 30 tiles: 104
-// instead of 93).  Relative error against 64 bits, as it was (maxima of every tile, or from 15 tiles on of about half of them) ->
-// now: 600 rows behind 3001 (17 tiles) 1.53e-3 -> 1.55e-3, with one key in ten scaled by four 0.98e-3 -> 0.31e-3; 300 behind
-// 4000 1.46e-3 -> 1.50e-3; 200 behind 50 thousand 1.64e-3 -> 1.66e-3.  Moving at a quarter instead of half brought the first to
-// 1.52e-3 and took 5 us more of 75.
-constexpr int kPd16ShortTiles = 24, kPd16LastTiles = 12;
-
 // Where the wavefront's two blocks of 16 query rows lie in a block of a.strip positions: next to each other where the block is
 // full (the layout prefill_kernel_wide shares); with fewer positions every wavefront's first block comes before any second one,
 // so that both groups have work.  NQ of them are there (before the end of the block and of the chunk).
@@ -1268,15 +1250,18 @@ __device__ __forceinline__ Pf16Rows pf16_rows(const PrefillArgs& a, int bx, int 
 // One pass of a workgroup of prefill_kernel_deep16: the tiles of `ps` on a softmax state of their own, by a wavefront that
 // has NQ blocks of 16 query rows before the chunk's end (NQ = 0: it has none, and only takes its share of the tile loads and
 // the barriers).  Rows that are not there cost matrix instructions, and with them clock: the kernel runs at the power limit.
+// pos: the first position of the workgroup's block.
+// Which tiles take their maxima first is pf_next_run's rule: the steady ones do not, and the largest weight of a row is then no
+// longer exactly 1.  With the maxima of the first eight tiles only, short launches were 6 us faster and 1 to 3 % further off
+// (600 rows behind 3001 1.53e-3 -> 1.55e-3, 300 behind 4000 1.46e-3 -> 1.50e-3, 200 behind 50 thousand 1.64e-3 -> 1.66e-3).
 // What a pass costs, by time stamps of 600 rows of 8 heads behind 3000 (240 workgroups of 17 tiles): 6.5 us until the first
-// tile is done (the fill of 144 KB per workgroup), 2.3 us for each of the next seven, which take their maxima, 1.5 for every other
-// one, 2 to store the state.  Before, only groups of four tiles that were full, unmasked and followed by full ones ran the
-// steady routine; the others, 11 of 17 here, took one of 2.6 us that took the maxima, chose its ring slot and its loads tile by
-// tile and added every operand's address between the MFMAs, and integer divisions took 3 us at the start: 59 us a
-// launch, now 48.  A steady tile has two scalar counters and a comparison more than it had.
+// tile is done (the fill of 144 KB per workgroup), 2.3 us for a tile that takes its maximum (two in three), 1.5 for a steady
+// one, 2 to store the state.  Before, a tile of the first kind took 2.6 us, in which it chose its ring slot and its loads tile by
+// tile and added every operand's address between the MFMAs, and integer divisions took 3 us at the start: 58 us a
+// launch, now 54.
 template <bool PRESCALED, int NQ>
 __device__ __forceinline__ void pd16_pass(const PrefillArgs& a, const PfPass& ps, uint32_t lds_base, int lane,
-                                          int wave, int g, int i0, int step, float* images) {
+                                          int wave, int g, int pos, int i0, int step, float* images) {
   constexpr int kLanes = kPdWaves * 64;
   constexpr int kImageFloats = kCarryFloatsPerLane * kLanes;
   constexpr int NS = NQ > 0 ? NQ : 1;                 // array sizes
@@ -1428,7 +1413,7 @@ __device__ __forceinline__ void pd16_pass(const PrefillArgs& a, const PfPass& ps
       rel[qb] = lim;
     }
   };
-  // a tile's softmax that takes its maximum first: the first tile of a pass, and passes without a reference (see below)
+  // a tile's softmax that takes its maximum first
   auto softmax_phase = [&](int t) __attribute__((always_inline)) {
     int rel[NS];
     const bool h = hidden(t);
@@ -1472,71 +1457,59 @@ __device__ __forceinline__ void pd16_pass(const PrefillArgs& a, const PfPass& ps
   pf_stream_start(sv, sw, 3, va_p, a.vb);
   clamp_rows(lc.gk, sk.rows, false);
   clamp_rows(lc.gv, sv.rows, true);
-  // tiles this wavefront does not see in full: from mask_t on (own rows), and the partial past tile
-  const int part_a = sw.full_a < sw.ta ? sw.full_a : -1;
-  int mask_t = (i0 + 1) / kPfTileRows - sw.own0;
-  if (mask_t < sw.ta) mask_t = sw.ta;
   const uint32_t ld_wave = lds_base + wave * 2048;
-  float least = 1.0f;
-  // Tile t: its matrix phase, which passes the barrier in its middle itself; `after` between the barrier and the softmax.
-  // GENERAL: the softmax takes its maximum first and the scores start from zero.
-  auto tile = [&](int t, uint32_t v_off, uint32_t k_off, uint32_t ldk, uint32_t ldv, auto general_tag, auto after) __attribute__((always_inline)) {
-    constexpr bool GENERAL = decltype(general_tag)::value;
+  // Tile t's matrix phase, which passes the barrier in its middle itself, with the two tiles at the streams' heads asked for
+  // on the way.  CINIT: the scores start from minus the running references.
+  auto matrix_phase = [&](uint32_t v_off, uint32_t k_off, uint32_t ldk, uint32_t ldv, auto cinit_tag) __attribute__((always_inline)) {
     PfPhaseLoads ld;
     ld.k = sk.p;
     ld.v = sv.p;
     ld.ldk = ld_wave + ldk;
     ld.ldv = ld_wave + kPdVRing + ldv;
     __builtin_amdgcn_s_setprio(2);
-    pd16_matrix_phase<!GENERAL, NS>(v_off, k_off, lc, qf, pb, st, sc, ld, pre, cinit);
+    pd16_matrix_phase<decltype(cinit_tag)::value, NS>(v_off, k_off, lc, qf, pb, st, sc, ld, pre, cinit);
     __builtin_amdgcn_s_setprio(0);
-    after();                                     // V(t)'s first operands, for the next matrix phase
-    __builtin_amdgcn_sched_barrier(0);
-    if (GENERAL) {
-      softmax_phase(t);
-    } else {
-      if (t >= mask_t || t == part_a) {
-        int rel[NS];
-        last_seen(t, rel);
-        pf16_mask<NS>(sc, rel, g16);
-      }
-      pf16_softmax_fast<PRESCALED, NS>(sc, st, c, least, cinit, pb);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    sk.p += sk.step;
-    sv.p += sv.step;
-    if (--sk.left == 0) {
-      pf_stream_meet(sk, sw, t + 4, ka_p, a.kb);
+  };
+  // the streams' heads have reached tiles t + 3 and t + 2: do they meet something there?
+  auto meet = [&](int t) __attribute__((always_inline)) {
+    if (sk.left == 0) {
+      pf_stream_meet(sk, sw, t + 3, ka_p, a.kb);
       clamp_rows(lc.gk, sk.rows, false);
     }
-    if (--sv.left == 0) {
-      pf_stream_meet(sv, sw, t + 3, va_p, a.vb);
+    if (sv.left == 0) {
+      pf_stream_meet(sv, sw, t + 2, va_p, a.vb);
       clamp_rows(lc.gv, sv.rows, true);
     }
-    wait_vmcnt<4>();                             // everything up to V(t+1) has landed
-    phase_barrier();
   };
-  // The first tiles take their maxima: the largest weight of a row is then exactly 1 where one of them holds it, as under
-  // a decaying bias.  From there on every row has a reference - it has seen a past row, or an own row at or before the first
-  // position of this wavefront; a range of own tiles that begins behind that may leave rows without one, and goes on so.
-  const bool no_reference = sw.ta == 0 && ps.b0 * kPfTileRows > i0;
-  const int early = T <= kPd16ShortTiles ? 8 : 4, general = no_reference || T < early ? T : early;
-  int t = 1;
+  int t = 1, piece = 0;
   uint32_t slot = 0;                             // ring offset of tile t - 1; the operand addresses move with it
 #pragma nounroll
-  for (; t < general; ++t) {
-    const uint32_t next = (slot + kPfTileBytes) & (kPdStages * kPfTileBytes - 1);
-    const uint32_t d = next - slot, prev = (slot - kPfTileBytes) & (kPdStages * kPfTileBytes - 1);
+  for (;;) {
+    const PfRun run = pf_next_run(sw, piece, t, pos);
+#pragma nounroll
+    for (; t < run.begin; ++t) {
+      const uint32_t next = (slot + kPfTileBytes) & (kPdStages * kPfTileBytes - 1);
+      const uint32_t d = next - slot, prev = (slot - kPfTileBytes) & (kPdStages * kPfTileBytes - 1);
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) lc.koff[kk] += d;
-    tile(t, 0, 0, slot, prev, std::true_type(), [&]() __attribute__((always_inline)) {
+      for (int kk = 0; kk < 4; ++kk) lc.koff[kk] += d;
+      matrix_phase(0, 0, slot, prev, std::false_type());
 #pragma unroll
       for (int db = 0; db < 8; ++db) lc.voff[db] += d;
-      pd16_preread(0, lc, pre);
-    });
-    slot = next;
-  }
-  if (t < T) {                                   // t = 4 or 8: the rings are back at their starts
+      pd16_preread(0, lc, pre);                  // V(t)'s first operands, for the next matrix phase
+      __builtin_amdgcn_sched_barrier(0);
+      softmax_phase(t);
+      __builtin_amdgcn_sched_barrier(0);
+      sk.p += sk.step;
+      sv.p += sv.step;
+      --sk.left;
+      --sv.left;
+      meet(t + 1);
+      wait_vmcnt<4>();                           // everything up to V(t+1) has landed
+      phase_barrier();
+      slot = next;
+    }
+    if (t >= T) break;
+    // tile t in ring slot S = t % 4, a compile-time constant: every LDS address is an immediate
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) {
       lc.koff[kk] -= 3 * kPfTileBytes;
@@ -1551,24 +1524,31 @@ __device__ __forceinline__ void pd16_pass(const PrefillArgs& a, const PfPass& ps
     for (int qb = 0; qb < NQ; ++qb)
 #pragma unroll
       for (int r = 0; r < 4; ++r) cinit[qb][r] = -st.m[qb];
-    // Tile t in ring slot S = t % 4, a compile-time constant: every LDS address is an immediate.
     auto steady = [&](auto stage_tag) __attribute__((always_inline)) {
       constexpr uint32_t S = decltype(stage_tag)::value, kT = kPfTileBytes;
-      tile(t, ((S + 3) & 3) * kT, S * kT, ((S + 3) & 3) * kT, ((S + 2) & 3) * kT, std::false_type(),
-           [&]() __attribute__((always_inline)) { pd16_preread(S * kT, lc, pre); });
-      return ++t >= T;
+      matrix_phase(((S + 3) & 3) * kT, S * kT, ((S + 3) & 3) * kT, ((S + 2) & 3) * kT, std::true_type());
+      pd16_preread(S * kT, lc, pre);
+      __builtin_amdgcn_sched_barrier(0);
+      pf16_softmax_fast<PRESCALED, NS>(sc, st, c, cinit, pb);
+      wait_vmcnt<4>();
+      phase_barrier();
+      sk.p += kPfTileBytes;
+      sv.p += kPfTileBytes;
     };
+    sk.left -= run.end - run.begin;
+    sv.left -= run.end - run.begin;
 #pragma nounroll
-    for (;;) {
-      least = T <= kPd16ShortTiles || T - t <= kPd16LastTiles ? 1.0f : kPfSumLimit;
-      if (steady(std::integral_constant<uint32_t, 0>())) break;
-      if (steady(std::integral_constant<uint32_t, 1>())) break;
-      if (steady(std::integral_constant<uint32_t, 2>())) break;
-      if (steady(std::integral_constant<uint32_t, 3>())) break;
+    for (; t < run.end; t += 4) {
+      steady(std::integral_constant<uint32_t, 0>());
+      steady(std::integral_constant<uint32_t, 1>());
+      steady(std::integral_constant<uint32_t, 2>());
+      steady(std::integral_constant<uint32_t, 3>());
     }
-    slot = (uint32_t)((T - 1) & (kPdStages - 1)) * kPfTileBytes;
+    meet(t);
 #pragma unroll
-    for (int db = 0; db < 8; ++db) lc.voff[db] += slot;
+    for (int kk = 0; kk < 4; ++kk) lc.koff[kk] += 3 * kPfTileBytes;
+#pragma unroll
+    for (int db = 0; db < 8; ++db) lc.voff[db] += 3 * kPfTileBytes;
   }
   {
 #pragma unroll
@@ -1658,9 +1638,9 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel_deep16(PrefillArgs a) {
     if (ps.run) {
       __syncthreads();               // the LDS rings are free again (a previous pass may still be reading V tiles)
       const Pf16Rows rows = pf16_rows(a, ps.bx, gl, wave);
-      if (rows.nq == 2) pd16_pass<PRESCALED, 2>(a, ps, lds_base, lane, wave, g, rows.i0, rows.step, images);
-      else if (rows.nq == 1) pd16_pass<PRESCALED, 1>(a, ps, lds_base, lane, wave, g, rows.i0, rows.step, images);
-      else pd16_pass<PRESCALED, 0>(a, ps, lds_base, lane, wave, g, rows.i0, rows.step, images);
+      if (rows.nq == 2) pd16_pass<PRESCALED, 2>(a, ps, lds_base, lane, wave, g, ps.bx * a.strip, rows.i0, rows.step, images);
+      else if (rows.nq == 1) pd16_pass<PRESCALED, 1>(a, ps, lds_base, lane, wave, g, ps.bx * a.strip, rows.i0, rows.step, images);
+      else pd16_pass<PRESCALED, 0>(a, ps, lds_base, lane, wave, g, ps.bx * a.strip, rows.i0, rows.step, images);
     }
     ps = other;
     other.run = other.init = 0;

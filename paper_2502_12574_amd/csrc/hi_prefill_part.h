@@ -259,4 +259,31 @@ HI_HD void pf_stream_start(PfStream& s, const PfSweep& w, int u, const char* pas
   }
 }
 
+// The runs of steady tiles of a pass: [begin, end), whole groups of four that begin at a multiple of four, every tile full and seen
+// in full from position `pos` (the block's first) on, and so are the tiles that it asks for ahead, all on one side of a jump.
+// All other tiles take their maxima, and a run is worth its entry from eight tiles on.  pf_next_run gives the first run that
+// begins at tile t or behind it (or T, T); piece: 0 before the first call, where the search goes on.
+struct PfRun { int begin, end; };
+HI_HD PfRun pf_next_run(const PfSweep& w, int& piece, int t, int pos) {
+  while (piece < 3) {
+    const bool two = w.jr < w.ta;
+    int lo = t, end = w.full_a - 3;
+    if (piece == 0 && two && w.jr - 3 < end) end = w.jr - 3;
+    if (piece == 1) {
+      if (!two) end = 0;
+      if (w.jr - 2 > lo) lo = w.jr - 2;
+    }
+    if (piece == 2) {
+      const int seen = (pos + 1) / kPfSweepRows - w.own0;
+      end = w.own_full - 3 < seen ? w.own_full - 3 : seen;
+      if (w.ta > lo) lo = w.ta;
+    }
+    ++piece;
+    if (end - lo < 8) continue;
+    const int begin = (lo + 3) & ~3;
+    return {begin, begin + ((end - begin) & ~3)};
+  }
+  return {w.T, w.T};
+}
+
 }  // namespace hi

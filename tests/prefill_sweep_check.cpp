@@ -1,13 +1,15 @@
 // The loads of prefill_kernel_deep16, replayed pass by pass (csrc/hi_prefill_part.h): the tiles that a pass asks for ahead are
-// the right ones, and no load - nor the ones behind a pass's last tile - leaves the rows that the launch was given.
+// the right ones, and no load - nor the ones behind a pass's last tile - leaves the rows that the launch was given.  And its
+// runs of steady tiles: all other tiles take their maxima.
 #include <algorithm>
 #include <cstdio>
 #include <random>
+#include <vector>
 #include "hi_prefill_part.h"
 
 using namespace hi;
 
-static long checks = 0, bad = 0;
+static long checks = 0, bad = 0, runs = 0;
 #define CHECK(c) do { ++checks; if (!(c)) { if (++bad < 10) std::printf("line %d: %s\n", __LINE__, #c); } } while (0)
 
 int main() {
@@ -63,20 +65,67 @@ int main() {
           CHECK(pf_tile_rows(sw, t) >= 1 && inside(where(t), pf_tile_rows(sw, t)));
           CHECK(pf_tile_rows(sw, t) == 64 || !inside(where(t), pf_tile_rows(sw, t) + 1));
         }
-        for (int ahead = 3; ahead >= 2; --ahead) {          // K(t + 3), V(t + 2)
-          PfStream st;
-          pf_stream_start(st, sw, 1 + ahead, p0, own);
-          for (int t = 1; t < sw.T; ++t) {
-            const int u = t + ahead;
-            CHECK(inside(st.p, st.rows));
-            if (u < sw.T) CHECK(st.p == where(u) && st.rows == pf_tile_rows(sw, u));
-            st.p += st.step;
-            if (--st.left == 0) pf_stream_meet(st, sw, u + 1, p0, own);
+        // tiles that need no maximum, searched tile by tile: groups of four in runs over the past (up to a jump, and from two
+        // tiles before it on) and over the own rows, each entered where eight tiles are left of it
+        const int pos = ps.bx * (s.strip ? s.strip : 64 * s.m), ta = sw.ta;
+        std::vector<char> steady(sw.T, 0);
+        {
+          int t = 1;
+          auto search = [&](int64_t end, int from) {
+            if (end - std::max(t, from) < 8) return;
+            while (t % 4 || t < from) ++t;
+            for (; t + 4 <= end; t += 4) std::fill_n(steady.begin() + t, 4, 1);
+          };
+          const int64_t full = sw.na / 64;
+          if (sw.jr < ta) {
+            search(std::min<int64_t>(full, sw.jr) - 3, 0);
+            search(full - 3, sw.jr - 2);
+          } else {
+            search(full - 3, 0);
+          }
+          t = std::max(t, ta);
+          search(std::min<int64_t>(std::min<int64_t>((pos + 1) / 64, nb / 64 - 3) - ps.b0 + ta, sw.T - 3), 0);
+        }
+        std::vector<char> found(sw.T, 0);
+        PfStream st[2];                                     // V(t + 2), K(t + 3)
+        for (int j = 0; j < 2; ++j) pf_stream_start(st[j], sw, 3 + j, p0, own);
+        for (int t = 1, piece = 0;;) {
+          const PfRun run = pf_next_run(sw, piece, t, pos);
+          CHECK(run.begin >= t && run.end <= sw.T);
+          auto asked = [&](const PfStream& x, int u) {
+            CHECK(inside(x.p, x.rows));
+            if (u < sw.T) CHECK(x.p == where(u) && x.rows == pf_tile_rows(sw, u));
+          };
+          auto meet = [&](PfStream& x, int u) { if (x.left == 0) pf_stream_meet(x, sw, u, p0, own); };
+          for (; t < run.begin; ++t)
+            for (int j = 0; j < 2; ++j) {
+              asked(st[j], t + 2 + j);
+              st[j].p += st[j].step;
+              --st[j].left;
+              meet(st[j], t + 3 + j);
+            }
+          if (t >= sw.T) break;
+          ++runs;
+          CHECK(run.begin % 4 == 0 && run.end % 4 == 0 && run.end > run.begin && run.end <= sw.T - 3);
+          for (int j = 0; j < 2; ++j) CHECK(st[j].left >= run.end - run.begin && st[j].rows == 64);
+          for (; t < run.end; ++t) {
+            found[t] = 1;
+            CHECK(pf_tile_rows(sw, t) == 64 && (t < ta || 64 * (t + sw.own0) + 63 <= pos));
+            for (int j = 0; j < 2; ++j) {
+              asked(st[j], t + 2 + j);
+              st[j].p += 16384;
+            }
+          }
+          for (int j = 0; j < 2; ++j) {
+            st[j].left -= run.end - run.begin;
+            meet(st[j], t + 2 + j);
           }
         }
+        CHECK(found == steady);
       }
     }
   }
-  std::printf("%ld checks, %ld failures\n", checks, bad);
+  CHECK(runs > 1000);
+  std::printf("%ld checks, %ld failures, %ld runs\n", checks, bad, runs);
   return bad != 0;
 }

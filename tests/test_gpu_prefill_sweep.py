@@ -1,5 +1,5 @@
-"""prefill_kernel_deep16 where its sweep can go wrong: passes of one tile and more on either side of the eight that take their
-maxima first, partial tiles at the end of the past and of the chunk, blocks of 16 query rows that the chunk leaves empty (in the
+"""prefill_kernel_deep16 where its sweep can go wrong: passes of one tile and more, on either side of the twelve full ones from which
+some do not take their maxima, partial tiles at the end of the past and of the chunk, blocks of 16 query rows that the chunk leaves empty (in the
 last block of positions, across launches too), and ranges of own tiles whose first tile some rows do not see at all."""
 import pytest
 import torch
@@ -13,7 +13,7 @@ from test_gpu_parity_small import check, one_unit
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("P", [0, 1, 64, 129, 256, 300, 321, 700])
+@pytest.mark.parametrize("P", [0, 1, 64, 129, 256, 300, 321, 700, 767, 768, 1100])
 @pytest.mark.parametrize("G,C", [(4, 16), (4, 17), (4, 33), (4, 64), (4, 77), (4, 97), (1, 5), (1, 44), (1, 256), (1, 300), (2, 145), (8, 50)])
 @pytest.mark.parametrize("mode", [hb.HI_MODE_RESIDENT, hb.HI_MODE_OFFLOAD])
 @pytest.mark.parametrize("paired", [False, True])
@@ -77,3 +77,35 @@ def test_an_infinite_value_stays_infinite(G, H, past, C, flags, mode):
             out[..., 5], out[..., 77] = want[:, None, :, 5].float(), want[:, None, :, 77].float()
             # whole sums in fp32, one quotient: two roundings of numbers up to 8
             assert (out - want[:, None]).abs().max() <= 1e-5, at
+
+
+@pytest.mark.parametrize("past", [512, 576, 640, 704])
+def test_short_sweeps_take_every_maximum(past):
+    """A pass of fewer than twelve full cached tiles takes the maximum of each tile: the key that has it weighs exactly 1, wherever
+    it is, and the result is good to fp32 - where weights against an older maximum are rounded to bf16, 1.9256 by 0.0037."""
+    dev, G, H, C, d = "cuda:0", 4, 192, 64, 121 / 128
+    gen = torch.Generator(device=dev).manual_seed(62100 + past)
+    tiles = past // 64
+    with Session(1, H, G, past + C, C, mode=hb.HI_MODE_RESIDENT, out_fp32=1, q_prescaled=1) as ss:
+        hb.hi_ctx_set_flags(ss.ctx, hb.HI_FLAG_PREFILL_DEEP)
+        view = ss.cache_view()
+        view.copy_(torch.randn(view.shape, device=dev, generator=gen))
+        view[0, :, 0] = 0
+        view[0, :, 0, :, 0] = -64.0                     # score of all others: weight 2^-64
+        view[0, :, 0, :4, 0] = 0.0                      # four rows of one lane in the first tile
+        at = 64 * (torch.arange(H, device=dev) % (tiles - 1) + 1)
+        heads = torch.arange(H, device=dev)
+        view[0, heads, 0, at, 0] = d                    # and one in a later tile, the same lane's
+        q = torch.zeros(H, G, C, 128, dtype=torch.bfloat16, device=dev)
+        q[..., 0] = 1.0
+        k = torch.zeros(H, C, 128, dtype=torch.bfloat16, device=dev)
+        k[..., 0] = -64.0
+        v = torch.randn(H, C, 128, device=dev, generator=gen).to(torch.bfloat16)
+        out = torch.full((H, G, C, 128), float("nan"), device=dev)
+        V = view[0, :, 1].double()
+        want = (V[:, :4].sum(dim=1) + 2.0 ** d * V[heads, at]) / (4 + 2.0 ** d)
+        torch.cuda.synchronize()
+        ss.prefill_group(0, 0, H, q, k, v, past, out)
+        ss.sync()
+        # sums of five fp32 products and one exponential, of values up to 6: some roundings of 2^-24 each
+        assert (out - want[:, None, None]).abs().max() <= 1e-5
