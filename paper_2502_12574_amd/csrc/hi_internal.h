@@ -57,7 +57,6 @@ struct PrefillLaunch {
   int img_row;         // state images of one grid row (a head, a quad of query heads)
   int xcd;             // the workgroups of a grid row are numbered so that neighbours share an XCD (pf_wg_index)
   int past_tiles;      // 4-wave kernel, split > 1: tiles of the unit's cached rows
-  int strip;           // positions of a block where they are fewer than the 8-wave kernel has room for (0: that many)
 };
 inline PrefillLaunch prefill_launch_shape(int G, int64_t chunk_len, int n_heads, int variant, int last, int has_own) {
   PrefillLaunch p;
@@ -65,7 +64,7 @@ inline PrefillLaunch prefill_launch_shape(int G, int64_t chunk_len, int n_heads,
   p.split = prefill_split(G, chunk_len, n_heads);
   p.nbk = (int)ceil_div(chunk_len, 2 * strip);
   p.deep = base == 3 || (base == 0 && (int64_t)p.nbk * gy * n_heads * p.split >= kPrefillDeepMinWorkgroups);
-  p.paired = p.merge = p.xcd = p.past_tiles = p.strip = 0;
+  p.paired = p.merge = p.xcd = p.past_tiles = 0;
   p.img_row = pf_images_per_row(p.nbk, p.split);
   if (p.deep) {
     // tiles the workgroups of the deepest block sweep beyond the average (the causal triangle), which pairing removes
@@ -78,6 +77,12 @@ inline PrefillLaunch prefill_launch_shape(int G, int64_t chunk_len, int n_heads,
     p.carry_bytes = ceil_div(chunk_len, strip) * gy * n_heads * kWgThreads * kCarryFloatsPerLane * 4;
   }
   return p;
+}
+
+// Does a launch of the 8-wave kernel over this many K/V rows run its wide form?
+inline bool prefill_is_wide(int variant, int split, int64_t rows) {
+  if (variant & 16) return false;
+  return (variant & 128) != 0 || ((variant & 64) == 0 && rows / 64 >= (int64_t)kPrefillWideMinTiles * split);
 }
 
 constexpr int kPrefillUnitMaxSplit = 64;
@@ -206,14 +211,6 @@ inline PrefillLaunch prefill_unit_shape(int G, int64_t C, int n_heads, int varia
       best.img_row = (int)images;
       best.carry_bytes = images * rows * image;
     }
-  }
-  // Blocks of one height instead of full ones and a rest: the rest's workgroups, with fewer matrix instructions per tile, would run
-  // ahead through K/V rows that the others then fetch once more.  (prefill_kernel_deep16 only; a block is a multiple of 16
-  // positions.)  300 rows of 32 heads, one query head each: 256 + 44 positions -> 160 + 140, 204 -> 199 us behind 30 thousand, 76 ->
-  // 69 behind 3000; 77 rows of 32 heads behind 3000, 64 + 13 -> 48 + 29: 73 -> 67; of 8 heads behind 100 thousand the same.
-  if (best.deep && !(variant & (16 | 128))) {
-    const int64_t even = round_up(ceil_div(C, best.nbk), 16);
-    if (even < 2 * strip && (best.nbk - 1) * even < C) best.strip = (int)even;
   }
   // neighbours in the numbering read the same K/V rows: let them share an XCD's L2 when one round of workgroups holds all
   best.xcd = best.deep && best.split > 1 && best.nbk * best.split % 8 == 0 &&

@@ -23,10 +23,6 @@ int main() {
     const int64_t na = nb == 0 ? 1 + pick(4000) : (i % 7 ? pick(4000) : 0);
     const int64_t C = nb ? nb : 1 + pick(1000);
     s.nbk = (int)((C + 64 * s.m - 1) / (64 * s.m));
-    if (pick(2)) {                                     // blocks of one height, a multiple of 16 positions
-      const int even = (int)(((C + s.nbk - 1) / s.nbk + 15) / 16 * 16);
-      if ((s.nbk - 1) * even < C) s.strip = even;
-    }
     s.ta = (int)((na + 63) / 64);
     s.tb_all = (int)((nb + 63) / 64);
     s.paired = nb > 0 && s.nbk >= 2 && pick(2);
@@ -44,7 +40,7 @@ int main() {
       return jump && at >= edge + far && at - far + rows * 256 <= na * 256;
     };
     for (int b = 0; b < s.nbk && nb; ++b) {             // a block's last row sees the chunk's rows up to itself
-      const int64_t last = std::min<int64_t>((b + 1) * (s.strip ? s.strip : 64 * s.m), C) - 1;
+      const int64_t last = std::min<int64_t>((b + 1) * 64 * s.m, C) - 1;
       CHECK(pf_own_tiles(s, b) == (int)(last / 64) + 1);
     }
     for (int j = 0; j < 6; ++j) {
@@ -67,7 +63,7 @@ int main() {
         }
         // tiles that need no maximum, searched tile by tile: groups of four in runs over the past (up to a jump, and from two
         // tiles before it on) and over the own rows, each entered where eight tiles are left of it
-        const int pos = ps.bx * (s.strip ? s.strip : 64 * s.m), ta = sw.ta;
+        const int pos = ps.bx * 64 * s.m, ta = sw.ta;
         std::vector<char> steady(sw.T, 0);
         {
           int t = 1;

@@ -109,3 +109,24 @@ def test_short_sweeps_take_every_maximum(past):
         ss.sync()
         # sums of five fp32 products and one exponential, of values up to 6: some roundings of 2^-24 each
         assert (out - want[:, None, None]).abs().max() <= 1e-5
+
+
+def test_long_sweeps_over_blocks_in_part_take_the_wide_form():
+    """1300 rows of 32 one-query heads behind 60 thousand, five full blocks of 256 positions and a rest, 957 tiles a workgroup: the
+    bits of the form that launches of 640 tiles and more run, and not those of the other one."""
+    dev, H, past, C = "cuda:0", 32, 60000, 1300
+    gen = torch.Generator(device=dev).manual_seed(62200)
+    with Session(1, H, 1, past + C, C, mode=hb.HI_MODE_RESIDENT, out_fp32=1, q_prescaled=1) as ss:
+        view = ss.cache_view()
+        for h in range(H):
+            view[0, h] = torch.randn(view.shape[2:], device=dev, generator=gen).to(torch.bfloat16)
+        q = (torch.randn(H, 1, C, 128, device=dev, generator=gen) * hb.HI_Q_PRESCALE).to(torch.bfloat16)
+        k, v = (torch.randn(H, C, 128, device=dev, generator=gen).to(torch.bfloat16) for _ in range(2))
+        outs = []
+        for flags in (0, hb.HI_FLAG_PREFILL_WIDE, hb.HI_FLAG_PREFILL_8WAVE):
+            hb.hi_ctx_set_flags(ss.ctx, flags)
+            outs.append(torch.full((H, 1, C, 128), float("nan"), device=dev))
+            torch.cuda.synchronize()
+            ss.prefill_group(0, 0, H, q, k, v, past, outs[-1])
+            ss.sync()
+    assert torch.equal(outs[0], outs[1]) and not torch.equal(outs[0], outs[2]) and torch.isfinite(outs[2]).all()

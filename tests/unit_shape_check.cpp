@@ -2,6 +2,7 @@
 // the split and pairing chosen for it are replayed on sets of tile ids, as partition_check.cpp does for the default
 // shape - every block of positions must have seen each of its tiles exactly once, no image may lie outside the
 // capacity, and the closed form of pf_contributors must agree with counting.
+#include <algorithm>
 #include <cstdio>
 #include <set>
 #include <vector>
@@ -126,7 +127,8 @@ static void run_unit(int G, int C, int nh, int variant, long past, long slice, l
       const long na = launches == 1 ? past : (past - l * slice < slice ? past - l * slice : slice);
       for (long t = 0; t < (na + 63) / 64; ++t) want.insert(1000000L * (l + 1) + t);
     }
-    for (int t = 0; t < pf_own_tiles(sh, b); ++t) want.insert(t);
+    const long end = std::min<long>((long)(b + 1) * 64 * m, C);        // the block's rows see own tiles up to that of its last row
+    for (int t = 0; t < (end + 63) / 64; ++t) want.insert(t);
     CHECK(out[b] == want, "block %d of G=%d C=%d nh=%d variant=%d past=%ld slice=%ld split=%d paired=%d", b, G, C, nh, variant, past, slice, unit.split, unit.paired);
   }
 }
@@ -147,6 +149,14 @@ int main() {
     for (long past : {0L, 100L, 1536L, 2049L, 3001L, 20000L, 131072L, 1000003L}) for (long slice : {0L, 512L, 4096L, 65536L}) for (long room : {1L, 8L, 64L})
       run_narrow(G, C, nh, variant, past, slice, prefill_carry_bound(G, C, 8) + room * (1L << 20), 8);
   CHECK(narrow > 1000 && narrow_most > 40, "%ld units of the 4-wave kernel cut, into %ld at most", narrow, narrow_most);
+  // launches whose workgroups sweep 640 tiles and more run the wide form, also where the chunk does not fill its last block
+  struct { int G, C, nh; long past; } longs[] = {{1, 1300, 32, 60000}, {1, 2100, 32, 300000}, {1, 3590, 32, 200000}, {4, 77, 8, 1000000}, {1, 200, 32, 1 << 20}};
+  for (const auto& u : longs) {
+    const PrefillLaunch pl = prefill_unit_shape(u.G, u.C, u.nh, 0, u.past, 0, 1L << 40, u.nh);
+    CHECK(pl.deep && prefill_is_wide(0, pl.split, u.past + u.C), "%d rows behind %ld: split %d", u.C, u.past, pl.split);
+    CHECK(!prefill_is_wide(0, pl.split, 640L * 64 * pl.split - 1) && !prefill_is_wide(16, 1, 1L << 30) && !prefill_is_wide(64, 1, 1L << 30) &&
+          prefill_is_wide(128, pl.split, 64), "rule");
+  }
   for (int nbk : {2, 3, 7, 10}) for (int m : {1, 2, 4}) for (int ta : {0, 1, 5, 47, 200}) for (int split : {1, 2, 3, 5, 11, 40}) for (int clip : {0, 1}) {
     PfShape s{nbk, m, ta, nbk * m - clip, split, 1, 0};
     for (int p = 0; p < nbk / 2; ++p) for (int sw = 0; sw < 2; ++sw) {
