@@ -153,7 +153,9 @@ typedef struct hi_stats {
   int64_t peak_staging_bytes;        /* largest number of staging bytes holding live K/V at once */
   double prefill_kernel_ms, decode_kernel_ms; /* HIP-event time of the attention kernels since the last
                                                  hi_reset_stats; only with HI_FLAG_TIME_KERNELS; hi_get_stats
-                                                 synchronises to read them */
+                                                 synchronises to read them.  With that flag the rows of a resident unit
+                                                 enter the cache in a launch of their own, which is not counted; without
+                                                 it a unit's merge launch takes them along */
   double h2d_copy_ms, d2h_copy_ms;   /* the same for the prefetch copies (on stream_h2d) and the write-backs (on
                                         stream_d2h): time the copy engines spent on them */
   double exposed_copy_ms;            /* time stream_compute spent between consecutive attention launches (from the same

@@ -686,12 +686,13 @@ static hi_status prefill_impl(hi_ctx* c, int32_t layer, int32_t kv_head, int32_t
   // same stream, and their partials do not outlive them
   const PrefillLaunch unit = prefill_unit_shape(G, chunk_len, nh, pf_variant(c), past_len, from_ring ? rows_of(c, nh) : 0,
                                                 c->plan.ws_writeback_offset, c->prob.n_kv_heads);
+  // append: rows that ride on the unit's merge launch; followed: the unit has another launch behind this one
   auto launch = [&](const PrefillSegment& seg, const PrefillSegment& own, int first, int last,
-                    const PrefillAppend* append = nullptr) -> hi_status {
+                    const PrefillAppend* append = nullptr, bool followed = false) -> hi_status {
     TimedSpan sp;
     if (timed) HI_TRY(span_begin(c, 0, &sp));
     HI_TRY(launch_prefill(c->sc, q_dev, G, chunk_len, seg, own, first, last, c->ws, out_dev, c->prob.out_fp32,
-                          pf_variant(c), unit, nh, c->plan.ws_writeback_offset, append, last ? unit_end(c) : nullptr));
+                          pf_variant(c), unit, nh, c->plan.ws_writeback_offset, append, last && !followed ? unit_end(c) : nullptr));
     if (timed) HI_TRY(span_end(c, sp));
     c->stats.n_prefill_kernels += 1;
     return HI_OK;
@@ -742,8 +743,11 @@ static hi_status prefill_impl(hi_ctx* c, int32_t layer, int32_t kv_head, int32_t
                            2 * c->prob.max_context * kRowBytes};
     HI_TRY(prefetch_hint(c, next));
     if (!run) return write_back(c, layer, kv_head, nh, k_new_dev, v_new_dev, past_len, chunk_len);
+    // the rows ride on the merge launch, unless the attention launches are timed: the time is theirs alone
     const PrefillAppend append = resident_append(c, layer, kv_head, nh, k_new_dev, v_new_dev, past_len, chunk_len);
-    return launch(pastseg, diag, 1, 1, &append);
+    if (unit.merge && !timed) return launch(pastseg, diag, 1, 1, &append);
+    HI_TRY(launch(pastseg, diag, 1, 1, nullptr, true));
+    return launch_kv_append(c->sc, append, unit_end(c));
   }
 
   HI_TRY(adopt_unit(c, layer, kv_head, nh, past_len));

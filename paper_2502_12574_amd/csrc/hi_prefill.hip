@@ -2206,7 +2206,8 @@ hi_status launch_prefill(void* stream, const void* q, int G, int chunk_len, cons
     set_last_error("prefill launch: carry of %lld bytes needed, %lld provided", (long long)pl.carry_bytes, (long long)carry_bytes);
     return HI_ERR_ARG;
   }
-  // the rows to append ride on the merge launch, as blocks behind its z_merge x (threads) ones, or go in a launch of their own
+  // the rows to append ride on the merge launch, as blocks behind its z_merge x (threads) ones
+  if (append && !pl.merge) { set_last_error("prefill launch: rows to append, but no merge to take them along"); return HI_ERR_ARG; }
   PrefillAppendArgs app = {};
   int64_t app_units = 0;
   if (append) {
@@ -2217,7 +2218,7 @@ hi_status launch_prefill(void* stream, const void* q, int G, int chunk_len, cons
     app.first_z = (int)z_merge;
     return dim3(x, y, z_merge + (unsigned)ceil_div(app_units, (int64_t)x * y * threads));
   };
-  void* const kernel_done = pl.merge || append ? nullptr : done;      // the attention kernel, if nothing follows it
+  void* const kernel_done = pl.merge ? nullptr : done;      // the attention kernel's, if no merge follows it
   a.split = pl.split;
   a.paired = pl.paired;
   a.nbk = pl.nbk;
@@ -2293,7 +2294,7 @@ hi_status launch_prefill(void* stream, const void* q, int G, int chunk_len, cons
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) { set_last_error("prefill launch: %s", hipGetErrorString(e)); return HI_ERR_HIP; }
-  return append && !pl.merge ? launch_kv_append(stream, *append, done) : HI_OK;
+  return HI_OK;
 }
 
 hi_status launch_prefill_window(void* stream, const void* q, int G, int chunk_len, const void* store_k,
