@@ -80,10 +80,13 @@ __device__ __forceinline__ uint16_t float_to_bf16_bits(float f) {
 // A launch, and an event (hipEvent_t, may be null) that marks its end.  The event is the launch's own completion signal: recorded
 // behind the launch it is a packet of its own, which holds the next kernel back by 2.8 us and costs the host 0.5 us more
 // (kernels of 3 us back to back: 7.8 us each with a record, 5.0 without or with the signal).  Not for streams being captured.
-template <class... P, class... A>
-inline void launch_kernel(void (*kernel)(P...), dim3 grid, dim3 block, unsigned lds, void* stream, void* done, const A&... args) {
-  if (done) hipExtLaunchKernelGGL(kernel, grid, block, lds, (hipStream_t)stream, nullptr, (hipEvent_t)done, 0, P(args)...);
-  else hipLaunchKernelGGL(kernel, grid, block, lds, (hipStream_t)stream, P(args)...);
+// The arguments convert to the kernel's parameters as in a call.
+template <class T> struct AsGiven { using type = T; };
+template <class... P>
+inline void launch_kernel(void (*kernel)(P...), dim3 grid, dim3 block, unsigned lds, void* stream, void* done,
+                          typename AsGiven<P>::type... args) {
+  if (done) hipExtLaunchKernelGGL(kernel, grid, block, lds, (hipStream_t)stream, nullptr, (hipEvent_t)done, 0, args...);
+  else hipLaunchKernelGGL(kernel, grid, block, lds, (hipStream_t)stream, args...);
 }
 
 }  // namespace hi
