@@ -72,14 +72,20 @@ _lib = None
 _native = None       # _pycall, bound to the library: the calls of a token without ctypes (csrc/hi_pycall.cpp)
 
 
+class _CtypesOnly:
+    """In _pycall's place where it was not built for this interpreter: every call goes through ctypes."""
+    prefill_group = decode_group = decode_group_ragged = qkv_rope = out_proj = staticmethod(lambda *args: None)
+
+
 def _load_native():
     """The native marshalling; it returns None for arguments out of the ordinary, which then go through ctypes."""
     global _native
     L = lib()
     try:
         from . import _pycall
-    except ImportError as e:
-        raise RuntimeError("_pycall is missing: run `python -m paper_2502_12574_amd.build` first") from e
+    except ImportError:
+        _native = _CtypesOnly
+        return _native
     _pycall.bind(*[C.cast(f, C.c_void_p).value for f in (L.hi_prefill_group, L.hi_decode_group, L.hi_decode_group_ragged,
                                                          L.hi_qkv_rope, L.hi_out_proj)], C.c_void_p)
     _native = _pycall

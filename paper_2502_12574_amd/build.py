@@ -49,20 +49,32 @@ def build(verbose: bool = False) -> str:
             raise RuntimeError(f"hipcc failed on {src}:\n{out}")
         if verbose and out.strip():
             print(out)
-    tmp = PYCALL + ".tmp"
-    cmd = ["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-I", sysconfig.get_paths()["include"], "-I", os.path.join(ROOT, "include"),
-           os.path.join(CSRC, "hi_pycall.cpp"), "-o", tmp]
-    r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
-    if r.returncode != 0:
-        raise RuntimeError("g++ failed on hi_pycall.cpp:\n" + r.stdout)
-    os.replace(tmp, PYCALL)
     tmp = LIB + ".tmp"
     cmd = [hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp, *objs]
     r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     if r.returncode != 0:
         raise RuntimeError("link failed:\n" + r.stdout)
     os.replace(tmp, LIB)
+    build_pycall()
     return LIB
+
+
+def build_pycall() -> str | None:
+    """The native marshalling for this interpreter, where a host compiler and Python's headers are there (binding.py does without)."""
+    if os.path.exists(PYCALL):
+        os.remove(PYCALL)
+    gxx, headers = shutil.which("g++") or shutil.which("c++"), sysconfig.get_paths()["include"]
+    if gxx is None or not os.path.exists(os.path.join(headers, "Python.h")):
+        print("no host compiler or no Python.h: every call from Python will go through ctypes (2 us more for each call of a token)")
+        return None
+    tmp = PYCALL + ".tmp"
+    cmd = [gxx, "-O2", "-std=c++17", "-shared", "-fPIC", "-I", headers, "-I", os.path.join(ROOT, "include"),
+           os.path.join(CSRC, "hi_pycall.cpp"), "-o", tmp]
+    r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("the host compiler failed on hi_pycall.cpp:\n" + r.stdout)
+    os.replace(tmp, PYCALL)
+    return PYCALL
 
 
 if __name__ == "__main__":

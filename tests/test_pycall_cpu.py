@@ -93,3 +93,24 @@ def test_same_errors(seen, monkeypatch, call, error):
     monkeypatch.setattr(hb, "last_error", lambda: "")
     with pytest.raises(error):
         call()
+
+
+def test_without_the_extension(seen, monkeypatch):
+    """Not built for this interpreter, the native marshalling is done without: the same calls, through ctypes."""
+    import sys
+
+    import paper_2502_12574_amd as package
+    from paper_2502_12574_amd import build
+    monkeypatch.setitem(sys.modules, package.__name__ + "._pycall", None)
+    monkeypatch.delattr(package, "_pycall", raising=False)
+    monkeypatch.setattr(hb, "_native", None)
+    for call, name in ((lambda: hb.hi_prefill_group(CTX, 0, 0, 8, T, T, T, 0, 1, T, check=False), NAMES[0]),
+                       (lambda: hb.hi_decode_group(CTX, 0, 0, 1, T, T, T, 5, T, check=False), NAMES[1]),
+                       (lambda: hb.hi_decode_group_ragged(CTX, 0, 0, 2, T, T, T, [4, 6], T, check=False), NAMES[2]),
+                       (lambda: hb.hi_qkv_rope(None, T, T, 4096, 32, 8, 1, 3, 1e4, 0, T, T, T, T, check=False), NAMES[3]),
+                       (lambda: hb.hi_out_proj(None, T, T, 32, 4096, 1, 0, T, check=False), NAMES[4])):
+        assert call() == -5 and seen.pop()[0] == name
+    # and the library is built without a host compiler
+    monkeypatch.setattr(build, "PYCALL", "/nonexistent/_pycall.so")
+    monkeypatch.setattr(build.shutil, "which", lambda name: None)
+    assert build.build_pycall() is None
