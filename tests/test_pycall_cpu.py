@@ -45,12 +45,27 @@ def seen(monkeypatch):
     hb._load_native()               # bound to the library again
 
 
-def _both(seen, monkeypatch, call):
-    """what the call hands over natively, and through ctypes"""
+class _Noting:
+    """The native module, with what its functions returned."""
+
+    def __init__(self, module):
+        self.module, self.returned = module, []
+
+    def __getattr__(self, name):
+        def call(*args):
+            self.returned.append(getattr(self.module, name)(*args))
+            return self.returned[-1]
+        return call
+
+
+def _both(seen, monkeypatch, call, ordinary):
+    """what the call hands over natively (or by itself, if it is out of the ordinary), and through ctypes"""
+    noting = _Noting(hb._native)
+    monkeypatch.setattr(hb, "_native", noting)
     assert call() == -5
+    assert noting.returned == ([-5] if ordinary else [None])         # None: left to ctypes, nothing called
     native = seen.pop()
-    refuse = type("Refuse", (), {"__getattr__": lambda self, name: lambda *a: None})()
-    monkeypatch.setattr(hb, "_native", refuse)
+    monkeypatch.setattr(hb, "_native", hb._CtypesOnly)
     assert call() == -5
     through_ctypes = seen.pop()
     assert not seen
@@ -61,7 +76,7 @@ T = torch.zeros(64, dtype=torch.bfloat16)
 CTX = C.c_void_p(0x123456789ABC)
 
 
-@pytest.mark.parametrize("call", [
+ORDINARY = [
     lambda: hb.hi_prefill_group(CTX, 1, 2, 3, T, T[8:], None, 1 << 33, 77, 0x7F00_0000_1000, 4, 5, 6, 7 << 32, check=False),
     lambda: hb.hi_prefill_group(CTX, 0, 0, 8, T, T, T, 0, 1, T, check=False),
     lambda: hb.hi_decode_group(CTX, 1, 2, 3, T, T[8:], T, 1 << 33, T, -1, 0, 1, 0, check=False),
@@ -70,14 +85,19 @@ CTX = C.c_void_p(0x123456789ABC)
     lambda: hb.hi_qkv_rope(_Stream(), T, T, 4096, 32, 8, 1, 1 << 20, 5e5, 0, T, T, T, T, q_scale=hb.HI_Q_PRESCALE, check=False),
     lambda: hb.hi_qkv_rope(0, T, T, 4096, 32, 8, 1, 3, 0.0, 1, T, T, T, None, check=False),
     lambda: hb.hi_out_proj(None, T, T, 32, 4096, 1, 0, T, check=False),
-    # out of the ordinary: other number types, a tuple of lengths, an int for the base, more than 32 bits
+]
+# other number types, a tuple of lengths, an int for the base, more than 32 bits
+OUT_OF_THE_ORDINARY = [
     lambda: hb.hi_decode_group(CTX, np.int64(1), 2, 3, T, T, T, np.int32(9), T, check=False),
     lambda: hb.hi_decode_group(CTX, (1 << 32) + 1, 2, 3, T, T, T, 9, T, check=False),
     lambda: hb.hi_decode_group_ragged(CTX, 0, 0, 2, T, T, T, (4, np.int64(6)), T, check=False),
     lambda: hb.hi_qkv_rope(_Stream(), T, T, 4096, 32, 8, 1, 3, 10000, 0, T, T, T, T, check=False),
-])
-def test_same_arguments_as_through_ctypes(seen, monkeypatch, call):
-    native, through_ctypes = _both(seen, monkeypatch, call)
+]
+
+
+@pytest.mark.parametrize("call,ordinary", [(c, True) for c in ORDINARY] + [(c, False) for c in OUT_OF_THE_ORDINARY])
+def test_same_arguments_as_through_ctypes(seen, monkeypatch, call, ordinary):
+    native, through_ctypes = _both(seen, monkeypatch, call, ordinary)
     assert native == through_ctypes
 
 
