@@ -27,22 +27,46 @@ def test_short_sweeps_and_empty_blocks(G, C, P, mode, paired):
 
 # units with a merge launch, which takes the append along: of the 8-wave kernel (few blocks, many; two grid rows a head) and of
 # the 4-wave kernel's ranges
-@pytest.mark.parametrize("G,H,first,nh,past,C", [(1, 17, 1, 16, 3000, 150), (4, 8, 0, 8, 3001, 77), (8, 9, 2, 7, 1500, 130),
-                                                 (4, 8, 0, 8, 64, 1000), (4, 3, 1, 1, 4000, 33), (1, 2, 0, 2, 2500, 1)])
-def test_rows_land_in_place_along_with_a_merge(G, H, first, nh, past, C):
+MERGED = [(1, 17, 1, 16, 3000, 150), (4, 8, 0, 8, 3001, 77), (8, 9, 2, 7, 1500, 130), (4, 3, 1, 1, 4000, 33), (1, 2, 0, 2, 2500, 1)]
+# and without one, where the append is a launch of its own
+ALONE = [(4, 8, 0, 8, 64, 1000), (1, 5, 2, 3, 100, 40)]
+
+
+def _rows_land(G, H, first, nh, past, C, flags=0):
     dev = "cuda:0"
-    with Session(1, H, G, past + C + 200, C, mode=hb.HI_MODE_RESIDENT, out_fp32=0) as ss:
+    gen = torch.Generator(device=dev).manual_seed(61500 + past)
+    with Session(1, H, G, past + C + 200, C, mode=hb.HI_MODE_RESIDENT, out_fp32=1) as ss:
+        hb.hi_ctx_set_flags(ss.ctx, flags)
         view = ss.cache_view()
-        view.copy_(torch.randn(view.shape, device=dev).to(torch.bfloat16))
-        k, v = (torch.randn(nh, C, 128, device=dev).to(torch.bfloat16) for _ in range(2))
-        q = torch.randn(nh, G, C, 128, device=dev).to(torch.bfloat16)
-        out = torch.full((nh, G, C, 128), float("nan"), dtype=torch.bfloat16, device=dev)
+        view.copy_(torch.randn(view.shape, device=dev, generator=gen).to(torch.bfloat16))
+        k, v = (torch.randn(nh, C, 128, device=dev, generator=gen).to(torch.bfloat16) for _ in range(2))
+        q = torch.randn(nh, G, C, 128, device=dev, generator=gen).to(torch.bfloat16)
+        out = torch.full((nh, G, C, 128), float("nan"), device=dev)
         want = view.clone()
         want[0, first:first + nh, 0, past:past + C], want[0, first:first + nh, 1, past:past + C] = k, v
         ss.s_compute.wait_stream(torch.cuda.current_stream())
         ss.prefill_group(0, first, nh, q, k, v, past, out)
         ss.sync()
-        assert torch.equal(view, want) and torch.isfinite(out).all()
+        assert torch.equal(view, want)
+        rows = want[0, first:first + nh, :, :past + C].cpu()
+    for h in range(nh):
+        ref = oa.attn_head(synth.to_f64(q[h].cpu()), synth.to_f64(rows[h, 0]), synth.to_f64(rows[h, 1]), past_len=past)
+        check(out[h], ref, f"head {h}")
+
+
+@pytest.mark.parametrize("G,H,first,nh,past,C", MERGED)
+def test_rows_land_in_place_along_with_a_merge(G, H, first, nh, past, C):
+    _rows_land(G, H, first, nh, past, C)
+
+
+@pytest.mark.parametrize("G,H,first,nh,past,C", ALONE)
+def test_rows_land_in_place_without_a_merge(G, H, first, nh, past, C):
+    _rows_land(G, H, first, nh, past, C)
+
+
+@pytest.mark.parametrize("G,H,first,nh,past,C", MERGED[:2])
+def test_rows_land_in_place_where_launches_are_timed(G, H, first, nh, past, C):
+    _rows_land(G, H, first, nh, past, C, hb.HI_FLAG_TIME_KERNELS)
 
 
 # ranges of the 8-wave kernel (2, 3, 5, 16 and more images of a block: below, at and beyond what the merge has in flight), its other

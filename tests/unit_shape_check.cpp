@@ -157,6 +157,11 @@ int main() {
     CHECK(!prefill_is_wide(0, pl.split, 640L * 64 * pl.split - 1) && !prefill_is_wide(16, 1, 1L << 30) && !prefill_is_wide(64, 1, 1L << 30) &&
           prefill_is_wide(128, pl.split, 64), "rule");
   }
+  // the units of test_gpu_prefill_sweep.py that have a merge launch, and those that have none, whatever room they find
+  struct { int G, H, nh; long past; int C, merge; } merged[] = {{1, 17, 16, 3000, 150, 1}, {4, 8, 8, 3001, 77, 1}, {8, 9, 7, 1500, 130, 1}, {4, 3, 1, 4000, 33, 1},
+                                                                {1, 2, 2, 2500, 1, 1}, {4, 8, 8, 64, 1000, 0}, {1, 5, 3, 100, 40, 0}};
+  for (const auto& u : merged) for (long room : {0L, 1L << 40})
+    CHECK(prefill_unit_shape(u.G, u.C, u.nh, 0, u.past, 0, prefill_carry_bound(u.G, u.C, u.H) + room, u.H).merge == u.merge, "%d rows behind %ld: merge", u.C, u.past);
   for (int nbk : {2, 3, 7, 10}) for (int m : {1, 2, 4}) for (int ta : {0, 1, 5, 47, 200}) for (int split : {1, 2, 3, 5, 11, 40}) for (int clip : {0, 1}) {
     PfShape s{nbk, m, ta, nbk * m - clip, split, 1, 0};
     for (int p = 0; p < nbk / 2; ++p) for (int sw = 0; sw < 2; ++sw) {
