@@ -132,9 +132,10 @@ inline int prefill_narrow_split(int G, int64_t C, int64_t past, int64_t capacity
 // 1.9 per tile for its first 14 tiles (ring fill, masked and alignment tiles), then 1.1 per tile while at most 190 run and
 // up to 1.45 on a full chip (power).  A paired launch makes two passes (12 more).  The merge: 5 + 0.035 per image.  The
 // 4-wave kernel: 4 + 1.3 per tile with one workgroup per compute unit, 1.9 with two.
-// (The constants are those of the 8-wave kernel before its short launches became steady ones; constants re-fitted to it, 8 to
-// start, 0.35 more for each of four tiles, 1.15 to 1.5 per tile, 8 a second pass, chose worse ones: 0.79 to 1.02 times as fast
-// over 23 shapes.)
+// (The constants were fitted to an 8-wave kernel that began 2.5 us later and took 2.6 us for a tile that takes its maximum, where
+// it takes 2.3 now.  Constants re-fitted to a faster form of it - 8 to start, 0.35 more for each of four tiles, 1.15 to 1.5 per
+// tile, 8 a second pass - chose worse splits, 0.79 to 1.02 times as fast over 23 shapes: the model has one fill for all
+// workgroups and knows nothing of rows that neighbours share in an L2, which the old constants happen to cover.)
 // What it replaces sized the split by the chunk alone, in powers of two up to 8: 77 rows of 8 heads behind 100 thousand ran
 // on 128 workgroups (302 us, now 178), 600 rows behind 3000 in two rounds of workgroups (92 -> 70), 2400 rows behind 5000
 // likewise (333 -> 277).  Chunks that the rule by the chunk alone gives to the 4-wave kernel stay there, cut into ranges.
@@ -275,7 +276,7 @@ struct PrefillSegment {
 };
 
 // Rows [heads][rows][128] of K and of V to the heads' places in an HBM cache, head_stride bytes apart: in a launch of its own, or
-// along with a unit's last prefill launch (which reads the cache only before those rows).
+// along with a unit's merge launch (the unit reads the cache only before those rows).
 struct PrefillAppend {
   const void* k_new; const void* v_new;
   void* k_dst; void* v_dst;

@@ -164,7 +164,6 @@ __device__ __forceinline__ void pf_issue_tile(const char* kt, const char* vt, in
 
 typedef __attribute__((address_space(3))) bf16x8 lds_bf16x8;
 typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
-typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 
 struct PfState {
   f32x16 o[4];
@@ -1247,11 +1246,11 @@ __device__ __forceinline__ Pf16Rows pf16_rows(const PrefillArgs& a, int bx, int 
 // Which tiles take their maxima first is pf_next_run's rule: the steady ones do not, and the largest weight of a row is then no
 // longer exactly 1.  With the maxima of the first eight tiles only, short launches were 6 us faster and 1 to 3 % further off
 // (600 rows behind 3001 1.53e-3 -> 1.55e-3, 300 behind 4000 1.46e-3 -> 1.50e-3, 200 behind 50 thousand 1.64e-3 -> 1.66e-3).
-// What a pass costs, by time stamps of 600 rows of 8 heads behind 3000 (240 workgroups of 17 tiles): 6.5 us until the first
+// What a pass costs, by time stamps of 600 rows of 8 heads behind 3000 (240 workgroups of 17 or 18 tiles): 6.5 us until the first
 // tile is done (the fill of 144 KB per workgroup), 2.3 us for a tile that takes its maximum (two in three), 1.5 for a steady
 // one, 2 to store the state.  Before, a tile of the first kind took 2.6 us, in which it chose its ring slot and its loads tile by
-// tile and added every operand's address between the MFMAs, and integer divisions took 3 us at the start: 58 us a
-// launch, now 54.
+// tile and added every operand's address between the MFMAs, and integer divisions took 3 us at the start: 57 us a
+// launch, now 53 (shortest of 33; medians 59 and 55).
 template <bool PRESCALED, int NQ>
 __device__ __forceinline__ void pd16_pass(const PrefillArgs& a, const PfPass& ps, uint32_t lds_base, int lane,
                                           int wave, int g, int pos, int i0, float* images) {
@@ -1670,9 +1669,9 @@ __device__ __forceinline__ bool pf_append_block(const PrefillAppendArgs& p) {
 // of both query rows of the lane.  Bound by the read of the images (139 KB each, up to 64 per block), and where a block has
 // few of them by its latency: CH images are in flight per lane, and behind the first CH the references of all others.  The largest
 // reference comes first, then the sums in the images' order, each image with one weight.  Shortest and median time with the
-// append: 8 heads of 2 blocks of 16 images 8.6 and 10.0 us, of 10 blocks of 3 images 9.2 and 10.3; 10.2 and 11.5, 9.4 and 10 without
-// the append where four images were in flight in two loops.  (A single pass that rescales what it has summed takes 7.6 and 8.8 for
-// the first, and other bits.)  Behind the merge's blocks others append the chunk's rows to the cache: as a launch of its own
+// append: 8 heads of 2 blocks of 16 images 9.7 and 10.7 us, of 10 blocks of 3 images 9.5 and 10.0; without the append, four images
+// in flight in two loops, 10.0 and 11.6, 9.2 and 10.0.  (A single pass that rescales what it has summed takes 1 us less for the
+// first, and gives other bits.)  Behind the merge's blocks others append the chunk's rows to the cache: as a launch of its own
 // behind this one that took 4.3 us and the gap before it.
 template <int NQ, int CH>
 __device__ __forceinline__ void pf16_merge(const PrefillArgs& a, const PfShape& sh, const Pf16Rows& rows16, int bx, int db, int n_e,

@@ -39,7 +39,7 @@ struct PfShape {
 };
 
 // x / d as one multiplication: the kernels divide by split and nbk before they can ask for their first byte, and the
-// compiler's division is about 40 dependent instructions of a lone wavefront (0.3 us each: 3 us of a 59 us launch of 600 rows
+// compiler's division is about 40 dependent instructions of a lone wavefront (0.3 us each: 3 us of a 57 us launch of 600 rows
 // behind 3000 went to this arithmetic).  With magic = floor(2^32 / d) + 1 the quotient is exact for x d < 2^32; pf_magic gives
 // 0, and pf_div divides, where x can be larger.
 HI_HD uint32_t pf_magic(uint32_t d, uint64_t x_max) {
