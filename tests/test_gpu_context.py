@@ -172,4 +172,4 @@ def test_the_attention_time_of_a_resident_unit_is_that_of_the_attention(flags):
                 times.append(ss.stats().prefill_kernel_ms)
                 hb.hi_reset_stats(ss.ctx)
             ms[mode] = sorted(times)[12]
-    assert ms[hb.HI_MODE_RESIDENT] <= 1.07 * ms[hb.HI_MODE_OFFLOAD], ms
+    assert ms[hb.HI_MODE_RESIDENT] <= 1.1 * ms[hb.HI_MODE_OFFLOAD], ms
