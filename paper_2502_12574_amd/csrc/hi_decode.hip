@@ -21,20 +21,32 @@ constexpr int kDecStageBytes = 2 * kDecTileBytes;                // K tile then 
 constexpr int kDecWaveLds = kDecStages * kDecStageBytes;         // 32 KiB per wavefront
 constexpr int kDecLdsBytes = 4 * kDecWaveLds;                    // 128 KiB per workgroup
 
-// issue the 8 loads (4 K + 4 V) of block `blk` into `stage`; rows beyond n-1 re-read row n-1 (masked later)
-__device__ __forceinline__ void dec_issue_block(const char* __restrict__ k, const char* __restrict__ v, int64_t blk,
-                                                int64_t n, lds_char* stage, int lane) {
-  const int r_in = lane >> 4;        // row within the 4-row group of one load instruction
-  const int cpos = lane & 15;        // LDS chunk position within the row
+// The 8 loads (4 K + 4 V) of a block as uniform base + lane offset: LDS chunk position p of row r holds chunk p ^ (r % 16) of a
+// K row, p ^ 2 (r % 8) of a V row.  ok / ov: the lane's offset in the first four rows; load i lies i * 1024 bytes further on with the
+// swizzle bits of its rows, which are bits of their own.  A block that ends beyond row n - 1 takes per-lane row numbers (rows past
+// the end re-read row n - 1 and are masked later).
+struct DecLane { uint32_t ok, ov; };
+__device__ __forceinline__ DecLane dec_lane(int lane) {
+  const int r = lane >> 4, p = lane & 15;       // row within the 4-row group of one load instruction, LDS chunk position
+  return {(uint32_t)(r * kRowBytes + ((p ^ r) << 4)), (uint32_t)(r * kRowBytes + ((p ^ (2 * r)) << 4))};
+}
+__device__ __forceinline__ void dec_issue_block(const char* __restrict__ k, const char* __restrict__ v, int blk, int64_t n,
+                                                uint32_t stage, int lane, const DecLane& dl) {
+  const int64_t at = (int64_t)blk * kDecTileBytes;
+  const int64_t left = n - (int64_t)blk * kDecBlockRows;
+  if (left >= kDecBlockRows) {
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int r = 4 * i + r_in;
-    int64_t row = blk * kDecBlockRows + r;
-    row = row < n ? row : n - 1;
-    const int ck = cpos ^ (r & 15);          // K swizzle
-    const int cv = cpos ^ ((r & 7) << 1);    // V swizzle
-    g2lds16_stream(k + row * kRowBytes + ck * 16, stage + i * 1024);
-    g2lds16_stream(v + row * kRowBytes + cv * 16, stage + kDecTileBytes + i * 1024);
+    for (int i = 0; i < 4; ++i) {
+      g2lds16_s_stream(k + at, dl.ok ^ (uint32_t)(i * 1024 + i * 64), stage + i * 1024);
+      g2lds16_s_stream(v + at, dl.ov ^ (uint32_t)(i * 1024 + (i & 1) * 128), stage + kDecTileBytes + i * 1024);
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int r = 4 * i + (lane >> 4), p = lane & 15, row = r < (int)left ? r : (int)left - 1;
+      g2lds16_s_stream(k + at, (uint32_t)(row * kRowBytes + ((p ^ r) << 4)), stage + i * 1024);
+      g2lds16_s_stream(v + at, (uint32_t)(row * kRowBytes + ((p ^ ((r & 7) << 1)) << 4)), stage + kDecTileBytes + i * 1024);
+    }
   }
 }
 
@@ -42,13 +54,17 @@ struct NoLens {};        // every head of the launch has the same number of rows
 template <class Lens> constexpr bool kRagged = std::is_same<Lens, DecodeLens>::value;
 
 // partials that cross workgroups inside one launch: through the point all XCDs agree on, past the L2s
-__device__ __forceinline__ void store_shared(float* p, float x) {
-  __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+__device__ __forceinline__ void store_shared2(float* p, float2 x) {   // 8-byte aligned
+  __hip_atomic_store((uint64_t*)p, (uint64_t)__float_as_uint(x.x) | ((uint64_t)__float_as_uint(x.y) << 32), __ATOMIC_RELAXED,
+                     __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ __forceinline__ float2 load_shared2(const float* p) {      // 8-byte aligned
   const uint64_t v = __hip_atomic_load((const uint64_t*)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   return make_float2(__uint_as_float((uint32_t)v), __uint_as_float((uint32_t)(v >> 32)));
 }
+
+// x of lane p (a constant)
+__device__ __forceinline__ float from_lane(float x, int p) { return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(x), p)); }
 
 // What decode_combine_kernel does, for all G query heads of one KV head, by the workgroup that finished its partial last, in
 // that kernel's order of operations (at most one partition per lane there): the same bits, so that a captured step, which
@@ -98,8 +114,7 @@ __device__ __forceinline__ void decode_tail(int kv, const uint16_t* q, int G, co
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
     score[h] = bf16_bits_to_float(q_lo[h]) * bf16_bits_to_float(k_lo) + bf16_bits_to_float(q_hi[h]) * bf16_bits_to_float(k_hi);
-    if (4 * h < G)
-      for (int off = 32; off > 0; off >>= 1) score[h] += __shfl_xor(score[h], off);
+    if (4 * h < G) score[h] = over_wave(score[h], op_add);
   }
   if (tid < n_part * G) {
     w[tid] = ml.x;
@@ -112,8 +127,7 @@ __device__ __forceinline__ void decode_tail(int kv, const uint16_t* q, int G, co
     if (g >= G) break;
     const float d = score[h];
     const float m = lane < n_part ? w[lane * G + g] : kNegBig;
-    float mx = fmaxf(d, m);
-    for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
+    const float mx = over_wave(fmaxf(d, m), op_max);
     const float wp = lane < n_part ? fast_exp2((m - mx) * c) : 0.f;
     const float lp = lane < n_part ? wp * sum[lane * G + g] : 0.f;
     const float p_new = fast_exp2((d - mx) * c);
@@ -121,7 +135,7 @@ __device__ __forceinline__ void decode_tail(int kv, const uint16_t* q, int G, co
     float total = 0.f;
 #pragma unroll
     for (int p = 0; p < kTailMaxParts; ++p) {
-      const float x = __shfl(wp, p), l = __shfl(lp, p);
+      const float x = from_lane(wp, p), l = from_lane(lp, p);
       acc.x += x * o[h][p].x;
       acc.y += x * o[h][p].y;
       total += l;
@@ -141,8 +155,14 @@ __device__ __forceinline__ void decode_tail(int kv, const uint16_t* q, int G, co
 // more KV heads), and partitions in proportion or the same number each (see decode_cut).
 // TAIL: this launch writes all partials of its heads, few enough of them (kTailMaxParts) for one workgroup to combine: the
 // workgroup of a head that finishes last does so, and no combine launch follows.
+// Over a short history this is a chain of latencies in which every instruction of a lone wavefront counts 7 cycles.  By time stamps
+// of 8 heads of 1000 rows: arguments 0.45 us, addresses and loads out 0.5, rows and queries here 1.2, the block 0.6, wavefronts merged
+// 0.5, partials out and counted 0.9, combined 1.7.  With 64-bit divisions and row addresses per lane, sums and maxima by __shfl
+// (an LDS round trip a step) and accumulators in AGPRs (64 moves a block, as the compiler has it for a kernel that may use more than 256
+// registers) it was 7.4 us instead of 6.1; a call, back to back with others of its kind: 8 heads of 60 / 1000 / 6003 / 20 thousand /
+// 130 thousand rows 8.2 / 9.3 / 13.8 / 21.2 / 86 -> 6.9 / 7.5 / 11.9 / 19.4 / 83.6 us, a million 621 -> 616.
 template <class Lens, bool TAIL>
-__global__ __launch_bounds__(256) void decode_partial_kernel(const uint16_t* __restrict__ q, int G,
+__global__ __launch_bounds__(256, 2) void decode_partial_kernel(const uint16_t* __restrict__ q, int G,
                                                              const char* __restrict__ k, const char* __restrict__ v,
                                                              int64_t n, float* partials, int part0,
                                                              float c, int64_t kv_head_stride,
@@ -178,26 +198,25 @@ __global__ __launch_bounds__(256) void decode_partial_kernel(const uint16_t* __r
   v += head_i * kv_head_stride;
   partials += head_i * part_head_stride;
   extern __shared__ __attribute__((aligned(1024))) char lds_raw[];
-  lds_char* lds = (lds_char*)lds_raw;
   const int lane = lane_id();
   const int wave = wave_id();
-  lds_char* wlds = lds + wave * kDecWaveLds;
+  const uint32_t wlds = (uint32_t)(uintptr_t)(lds_char*)lds_raw + wave * kDecWaveLds;
 
   const int head = lane & 15;
   const int g4 = lane >> 4;
 
   // 16-row blocks are dealt round-robin to the wavefronts of the grid, so at any moment the whole chip reads one
   // compact window of the K and V streams (friendlier to HBM pages and TLBs than one far-apart range per wave)
-  const int64_t n_blocks = (n + kDecBlockRows - 1) / kDecBlockRows;
-  const int64_t n_waves = (int64_t)n_part * 4;
-  const int64_t wid = (int64_t)part * 4 + wave;
-  const int64_t cnt = wid < n_blocks ? (n_blocks - wid + n_waves - 1) / n_waves : 0;   // blocks of this wave
-  const int64_t skip_blk = skip_row >= 0 ? skip_row / kDecBlockRows : -1;
+  const int n_blocks = (int)((n + kDecBlockRows - 1) / kDecBlockRows);       // (an HBM-resident head has far fewer than 2^31)
+  const int n_waves = n_part * 4;
+  const int wid = part * 4 + wave;
+  const int skip_blk = skip_row >= 0 ? (int)(skip_row / kDecBlockRows) : -1;
+  const DecLane dl = dec_lane(lane);
 
   // prologue: up to three blocks in flight, before the queries are asked for (one wait for both: over a short history
   // two memory latencies in a row were a third of the kernel)
   for (int s = 0; s < kDecStages - 1; ++s)
-    if (s < cnt) dec_issue_block(k, v, wid + s * n_waves, n, wlds + s * kDecStageBytes, lane);
+    if (wid + s * n_waves < n_blocks) dec_issue_block(k, v, wid + s * n_waves, n, wlds + s * kDecStageBytes, lane, dl);
 
   // Q^T as the B operand of S^T = K Q^T: lane holds q[head][32*kk + 8*g4 .. +7]; heads >= G are zero columns
   bf16x8 qf[4];
@@ -230,19 +249,27 @@ __global__ __launch_bounds__(256) void decode_partial_kernel(const uint16_t* __r
   const int v_row = 4 * g4 + ((lane & 15) >> 2);
   const int v_sub = lane & 3;      // which 8-byte quarter of the 32-byte column group
 
-  for (int64_t i = 0; i < cnt; ++i) {
-    const int64_t b = wid + i * n_waves;
-    const int stage = (int)(i & (kDecStages - 1));
-    if (i + (kDecStages - 1) < cnt) {
-      dec_issue_block(k, v, b + (kDecStages - 1) * n_waves, n,
-                      wlds + (int)((i + kDecStages - 1) & (kDecStages - 1)) * kDecStageBytes, lane);
+  int stage = 0;
+  for (int b = wid; b < n_blocks; b += n_waves) {
+    const int ahead = b + (kDecStages - 1) * n_waves;
+    if (ahead < n_blocks) {
+      dec_issue_block(k, v, ahead, n, wlds + ((stage + kDecStages - 1) & (kDecStages - 1)) * kDecStageBytes, lane, dl);
       wait_vmcnt<24>();   // everything but the 3 newest blocks has landed
     } else {
       wait_vmcnt<0>();
     }
-    lds_char* kt = wlds + stage * kDecStageBytes;
+    lds_char* kt = (lds_char*)(uintptr_t)(wlds + stage * kDecStageBytes);
     lds_char* vt = kt + kDecTileBytes;
+    stage = (stage + 1) & (kDecStages - 1);
 
+    // V^T operands: lane receives dim 16*db + (lane & 15) of rows 4*g4 .. 4*g4+3 (read here, so that their latency passes under the
+    // scores)
+    bf16x4 vop[8];
+#pragma unroll
+    for (int db = 0; db < 8; ++db) {
+      const int chunk = (2 * db + (v_sub >> 1)) ^ ((v_row & 7) << 1);
+      vop[db] = lds_read_tr8(vt + v_row * kRowBytes + (chunk << 4) + ((v_sub & 1) << 3));
+    }
     f32x4 s = (f32x4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) {
@@ -251,17 +278,16 @@ __global__ __launch_bounds__(256) void decode_partial_kernel(const uint16_t* __r
     }
     // register r of lane (g4, head) is the score of row 16*b + 4*g4 + r
     // hidden rows: beyond the end, or the one row a streaming head's token is about to replace
-    const bool hides = (b + 1) * kDecBlockRows > n || b == skip_blk;
+    const bool hides = (int64_t)(b + 1) * kDecBlockRows > n || b == skip_blk;
     if (hides) {
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int64_t row = b * kDecBlockRows + 4 * g4 + r;
+        const int64_t row = (int64_t)b * kDecBlockRows + 4 * g4 + r;
         if (row >= n || row == skip_row) s[r] = kNegBig;
       }
     }
     float mx = fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]));
-    mx = fmaxf(mx, __shfl_xor(mx, 16));
-    mx = fmaxf(mx, __shfl_xor(mx, 32));
+    mx = over_rows16(mx, op_max);
     const float m_new = fmaxf(m, mx);
     if (__builtin_amdgcn_ballot_w64(m_new > m) != 0) {
       const float alpha = fast_exp2((m - m_new) * c);
@@ -286,53 +312,52 @@ __global__ __launch_bounds__(256) void decode_partial_kernel(const uint16_t* __r
     const short4v pbs = __builtin_bit_cast(short4v, pb);
 #pragma unroll
     for (int db = 0; db < 8; ++db) {
-      // V^T operand: lane receives dim 16*db + (lane & 15) of rows 4*g4 .. 4*g4+3
-      const int chunk = (2 * db + (v_sub >> 1)) ^ ((v_row & 7) << 1);
-      bf16x4 a = lds_read_tr8(vt + v_row * kRowBytes + (chunk << 4) + ((v_sub & 1) << 3));
-      o[db] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(short4v, a), pbs, o[db], 0, 0, 0);
+      o[db] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(short4v, vop[db]), pbs, o[db], 0, 0, 0);
     }
     asm volatile("" ::: "memory");
   }
 
   // per-lane-group partial sums -> per-head sums
-  l += __shfl_xor(l, 16);
-  l += __shfl_xor(l, 32);
+  l = over_rows16(l, op_add);
 
   // merge the four wavefronts through LDS (the ring is idle now)
   __syncthreads();
   float* red = (float*)lds_raw;                 // [4 waves][16 heads][130]
-  float* mine = red + wave * 16 * kPartialFloats;
+  if (head < G) {
+    float* mine = red + (wave * 16 + head) * kPartialFloats;
 #pragma unroll
-  for (int db = 0; db < 8; ++db)
+    for (int db = 0; db < 8; ++db)
 #pragma unroll
-    for (int r = 0; r < 4; ++r) mine[head * kPartialFloats + 16 * db + 4 * g4 + r] = o[db][r];
-  if (g4 == 0) {
-    mine[head * kPartialFloats + kHeadDim] = m;
-    mine[head * kPartialFloats + kHeadDim + 1] = l;
+      for (int r = 0; r < 4; r += 2) *(float2*)(mine + 16 * db + 4 * g4 + r) = make_float2(o[db][r], o[db][r + 1]);
+    if (g4 == 0) *(float2*)(mine + kHeadDim) = make_float2(m, l);
   }
   __syncthreads();
+  // a thread takes two dims of a query head; every read of it is asked for at once
   float* dst = partials + (int64_t)(part0 + part) * G * kPartialFloats;
-  for (int idx = threadIdx.x; idx < G * kHeadDim; idx += blockDim.x) {
-    const int h = idx >> 7, dim = idx & 127;
-    float mw[4], M = kNegBig;
+  for (int idx = threadIdx.x; idx < G * kHeadDim / 2; idx += blockDim.x) {
+    const int h = idx >> 6, dim = 2 * (idx & 63);
+    float2 ml[4], x[4];
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
-      mw[w] = red[(w * 16 + h) * kPartialFloats + kHeadDim];
-      M = fmaxf(M, mw[w]);
+      const float* src = red + (w * 16 + h) * kPartialFloats;
+      ml[w] = *(const float2*)(src + kHeadDim);
+      x[w] = *(const float2*)(src + dim);
     }
-    float acc = 0.f, L = 0.f;
+    float M = kNegBig;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) M = fmaxf(M, ml[w].x);
+    float2 acc = make_float2(0.f, 0.f);
+    float L = 0.f;
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
-      const float wgt = fast_exp2((mw[w] - M) * c);
-      acc += wgt * red[(w * 16 + h) * kPartialFloats + dim];
-      L += wgt * red[(w * 16 + h) * kPartialFloats + kHeadDim + 1];
+      const float wgt = fast_exp2((ml[w].x - M) * c);
+      acc.x += wgt * x[w].x;
+      acc.y += wgt * x[w].y;
+      L += wgt * ml[w].y;
     }
-    auto put = [&](float* p, float x) { if (TAIL) store_shared(p, x); else *p = x; };
+    auto put = [&](float* p, float2 y) { if (TAIL) store_shared2(p, y); else *(float2*)p = y; };
     put(dst + h * kPartialFloats + dim, acc);
-    if (dim == 0) {
-      put(dst + h * kPartialFloats + kHeadDim, M);
-      put(dst + h * kPartialFloats + kHeadDim + 1, L);
-    }
+    if (dim == 0) put(dst + h * kPartialFloats + kHeadDim, make_float2(M, L));
   }
   if constexpr (TAIL) {
     // Every wavefront's partials have arrived before the count goes up; the last workgroup of the head resets it.  The
@@ -409,10 +434,10 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(const uint16_t* __r
   if (tid < 64) {
     float d = bf16_bits_to_float(q[g * kHeadDim + tid]) * bf16_bits_to_float(k_new[tid]) +
               bf16_bits_to_float(q[g * kHeadDim + 64 + tid]) * bf16_bits_to_float(k_new[64 + tid]);
-    for (int off = 32; off > 0; off >>= 1) d += __shfl_xor(d, off);
+    d = over_wave(d, op_add);
     if (tid == 0) bc = d;
   }
-  for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
+  mx = over_wave(mx, op_max);
   if ((tid & 63) == 0) red[tid >> 6] = mx;
   __syncthreads();
   const float s_new = bc;

@@ -31,17 +31,17 @@ __device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane
 // before touching a tile, which is what lets several tiles stay in flight.  M0 is written without being declared
 // (the compiler rejects it as a clobber); nothing else in these kernels uses M0: no dynamic register indexing,
 // no compiler-issued LDS-DMA.
-__device__ __forceinline__ void g2lds16_stream(const char* gsrc, lds_char* lds_uniform) {
-  const uint32_t m0v = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)lds_uniform);
-  // non-temporal: the decode kernel reads every K/V byte exactly once; keeping the stream from displacing the L2's
-  // contents measured 5.9 -> 6.6 TB/s over a million rows
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off nt"
+//
+// Addressed as (64-bit scalar base) + (32-bit per-lane byte offset): no vector ALU work per load.  Non-temporal: the decode kernel
+// reads every K/V byte exactly once; keeping the stream from displacing the L2's contents measured 5.9 -> 6.6 TB/s over a million rows.
+__device__ __forceinline__ void g2lds16_s_stream(const char* sbase, uint32_t voff, uint32_t lds_uniform_addr) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt"
                :
-               : "s"(m0v), "v"(gsrc)
+               : "s"(lds_uniform_addr), "v"(voff), "s"(sbase)
                : "memory");
 }
 
-// Same, addressed as (64-bit scalar base) + (32-bit per-lane byte offset) + immediate: no vector ALU work per load.
+// Same without the hint, and with an immediate.
 // The instruction's immediate offset is added to the global address and to the LDS address alike.
 template <int IMM>
 __device__ __forceinline__ void g2lds16_s(const char* sbase, uint32_t voff, uint32_t lds_uniform_addr) {
@@ -65,6 +65,35 @@ __device__ __forceinline__ bf16x8 lds_read16(lds_char* p) {
 __device__ __forceinline__ bf16x4 lds_read_tr8(lds_char* p) {
   return __builtin_amdgcn_ds_read_tr16_b64_v4bf16((__attribute__((address_space(3))) bf16x4*)p);
 }
+
+// Sums and maxima over lanes without a trip through LDS (over 100 cycles a step with __shfl_xor, about 10 here): halves and rows of
+// 16 lanes change places inside the register file, and within a row of 16 the other operand is a rotation.  The order is that of
+// a butterfly from lane ^ 32 down to lane ^ 1 (a rotation by OFF is lane ^ OFF where the values repeat every 2 OFF lanes).
+template <int OFF>
+__device__ __forceinline__ float row_ror(float x) {
+  const int u = __builtin_bit_cast(int, x);
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(u, u, 0x120 + OFF, 0xf, 0xf, false));
+}
+template <class Op>
+__device__ __forceinline__ float over_rows16(float x, Op op) {          // lanes ^ 16 and ^ 32
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  x = op(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return op(__uint_as_float(s[0]), __uint_as_float(s[1]));
+}
+template <class Op>
+__device__ __forceinline__ float over_wave(float x, Op op) {
+  const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  x = op(__uint_as_float(s[0]), __uint_as_float(s[1]));
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  x = op(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  x = op(x, row_ror<8>(x));
+  x = op(x, row_ror<4>(x));
+  x = op(x, row_ror<2>(x));
+  return op(x, row_ror<1>(x));
+}
+__device__ __forceinline__ float op_add(float a, float b) { return a + b; }
+__device__ __forceinline__ float op_max(float a, float b) { return fmaxf(a, b); }
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
