@@ -51,6 +51,12 @@ __device__ __forceinline__ void g2lds16_s(const char* sbase, uint32_t voff, uint
                : "memory");
 }
 
+// The same in two steps, so that an instruction in between (an MFMA) covers the wait state that the load needs behind a write of M0.
+__device__ __forceinline__ void set_m0(uint32_t lds_uniform_addr) { asm volatile("s_mov_b32 m0, %0" : : "s"(lds_uniform_addr) : "memory"); }
+__device__ __forceinline__ void g2lds16_m0(const char* sbase, uint32_t voff) {
+  asm volatile("global_load_lds_dwordx4 %0, %1" : : "v"(voff), "s"(sbase) : "memory");
+}
+
 template <int N>
 __device__ __forceinline__ void wait_vmcnt() {
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");

@@ -146,6 +146,18 @@ __global__ __launch_bounds__(256, 1) void proj_gemm_kernel(ProjArgs p) {
     }
   };
 
+  // the same in two parts, on either side of an MFMA
+  auto load_at = [&](int stage, int u) __attribute__((always_inline)) {
+    set_m0(lds_base + wave * 8192 + stage * kPjStageBytes + (u < 8 ? 0 : kPjOperandBytes) + (u & 7) * 1024);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto load_now = [&](int t, int u) __attribute__((always_inline)) {
+    __builtin_amdgcn_sched_barrier(0);
+    const int k0 = t * kPjK;
+    if (u < 8) g2lds16_m0(p.a + (int64_t)k0 * 2, ga_off[u]);
+    else g2lds16_m0(MODE == kPjOut ? p.b + (int64_t)(k0 >> 7) * p.b_head_stride + (k0 & 127) * 2 : p.b + (int64_t)k0 * 2, gb_off[u - 8]);
+  };
+
   // ---- operand reads: lane l reads row (32 * block + l), chunk (2 kk + hl), of the A and of the B slice.  The
   // addresses are kept whole in registers per (stage, sub-step), the block is an immediate: no vector ALU work in
   // the loop (with one wavefront per SIMD every such instruction between two MFMAs is matrix-pipe time lost)
@@ -177,7 +189,7 @@ __global__ __launch_bounds__(256, 1) void proj_gemm_kernel(ProjArgs p) {
 #pragma unroll
   for (int u = 0; u < 16; ++u) issue_one(0, 0, u);
 #pragma unroll
-  for (int u = 0; u < 16; ++u) issue_one(1, 1, u);
+  for (int u = 0; u < 8; ++u) issue_one(1, 1, u);
 
   for (int s = li; cur_j >= 0; s += n_li) {
     f32x16 acc[4][4];
@@ -197,10 +209,14 @@ __global__ __launch_bounds__(256, 1) void proj_gemm_kernel(ProjArgs p) {
     // The schedule.  One wavefront per SIMD keeps the matrix pipe busy on its own: operand reads run one sub-step (16
     // contraction elements, 16 MFMAs) ahead of their use, across the step boundary too.  The barrier that publishes
     // step t+1's slices sits before the LAST sub-step of step t, whose MFMAs then cover the first operand reads of
-    // step t+1 and the issue of step t+2's loads into the stage step t has just finished reading.  One barrier per
-    // step; a wavefront waiting at it still has 16 MFMAs in the pipe.
+    // step t+1 and the issue of step t+2's A loads into the stage step t has just finished reading; its B loads follow in the
+    // first sub-step of step t+1.  One barrier per step; a wavefront waiting at it still has 16 MFMAs in the pipe.
+    // The loads go out one behind every second MFMA: the texture path takes 16 cycles for each, 1024 for the 64 of a workgroup's
+    // step, and all of them behind the 16 MFMAs (528 cycles) of one sub-step made every wavefront wait for it.  The B rows are
+    // the activations, which the caches hold, so theirs are the loads with the shorter way to their barrier.  Hidden size 4096, 32 + 16
+    // heads, Q/K/V and output at 4096 / 8192 / 16384 tokens: 221 / 350 / 691 -> 206 / 326 / 654 us, 114 / 224 / 440 -> 109 / 212 / 423.
     bf16x8 cur[8], nxt[8];
-    wait_vmcnt<16>();          // step 0 has landed (at most step 1's loads and earlier stores are still in flight)
+    wait_vmcnt<8>();           // step 0 has landed (at most step 1's A loads and earlier stores are still in flight)
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < 8; ++i) cur[i] = read_op(0, 0, i);
@@ -219,7 +235,10 @@ __global__ __launch_bounds__(256, 1) void proj_gemm_kernel(ProjArgs p) {
           if (j < 8) {
             if (kk & 1) cur[j] = read_op(ST, kk + 1, j); else nxt[j] = read_op(ST, kk + 1, j);
           }
+          const bool load = MORE1 && kk == 0 && (j & 1);
+          if (load) load_at(SN, 8 + (j >> 1));
           mfma_j((kk & 1) ? nxt : cur, j);
+          if (load) load_now(t + 1, 8 + (j >> 1));
           __builtin_amdgcn_sched_barrier(0);
         }
       }
@@ -231,8 +250,10 @@ __global__ __launch_bounds__(256, 1) void proj_gemm_kernel(ProjArgs p) {
 #pragma unroll
       for (int j = 0; j < 16; ++j) {
         if (j < 8 && MORE1) cur[j] = read_op(SN, 0, j);
+        const bool load = MORE2 && (j & 1);
+        if (load) load_at(STAGE, j >> 1);
         mfma_j(nxt, j);
-        if (MORE2) issue_one(t + 2, STAGE, j);
+        if (load) load_now(t + 2, j >> 1);
         __builtin_amdgcn_sched_barrier(0);
       }
     };
@@ -309,7 +330,7 @@ __global__ __launch_bounds__(256, 1) void proj_gemm_kernel(ProjArgs p) {
 #pragma unroll
       for (int u = 0; u < 16; ++u) issue_one(0, 0, u);
 #pragma unroll
-      for (int u = 0; u < 16; ++u) issue_one(1, 1, u);
+      for (int u = 0; u < 8; ++u) issue_one(1, 1, u);
     }
 
     if (MODE == kPjQkv) { tab_load(0, 0, tab0); tab_load(0, 1, tab1); }
