@@ -424,18 +424,21 @@ __global__ __launch_bounds__(256, 1) void proj_gemm_kernel(ProjArgs p) {
 // rotary pairs still meet in one lane).  A step of 64 contraction elements moves 32 KB into LDS and 64 KB out of it, 750
 // cycles or 0.31 us at its 128 bytes a cycle (the 16 MFMAs of a wavefront take 512).  Measured over contractions of 1024 to
 // 8192 at 600 tokens, kernel time is 5 to 6 us to launch, fill the ring and write, and per step 0.53 us with weights from
-// HBM and 0.43 with weights from the caches for the 240 workgroups of Q/K/V, 0.45 and 0.35 for the 160 of the output: it
-// grows with the workgroups that load, 15 to 18 TB/s out of the L2s, so what binds is the feed of the ring, not the LDS
-// (a fifth stage changed nothing).  One workgroup per compute unit has to cover the latency of its loads itself: four stages of
-// 32 KB, loads three steps (of 64 elements) ahead, operand reads two sub-steps ahead.  The order of every sum is the large
+// HBM and 0.43 with weights from the caches for the 240 workgroups of Q/K/V, 0.45 and 0.35 for the 160 of the output.  A step's
+// MFMAs, its loads through the texture path (64 bytes a cycle) and its LDS traffic take 512 cycles each; it takes 720, at a clock
+// that falls with them (2.3 GHz with 48 workgroups at work, 1.8 with 240).  One workgroup per compute unit has to cover the
+// latency of its loads itself: five stages of 32 KB, loads three steps (of 64 elements) ahead and spread evenly over the step,
+// operand reads two sub-steps ahead with one wait for the four of a sub-step.  The order of every sum is the large
 // tile's, so the results are the same bits.  Measured (hidden size 4096, 32 + 16 heads, weights of 6 layers in turn;
 // large tile -> small): Q/K/V with its table at 64 / 600 / 1000 / 2000 tokens 90 -> 33, 97 -> 40, 102 -> 69, 110 -> 108 us,
-// output 74 -> 24, 77 -> 28, 78 -> 35, 80 -> 66 us.
+// output 74 -> 24, 77 -> 28, 78 -> 35, 80 -> 66 us.  With four stages, all loads in the half step behind the barrier and a wait for the
+// stage's last reads in front of it: 100 tokens 35.1 and 24.0 us, now 33.5 and 22.0; 600 40.0 and 32.3, now 39.1 and 31; 2000 110 and
+// 67, now 107 and 65.
 constexpr int kPsTile = 128;
 constexpr int kPsOperandBytes = kPsTile * kPjRowBytes;    // 16 KiB
 constexpr int kPsStageBytes = 2 * kPsOperandBytes;
-constexpr int kPsStages = 4;
-constexpr int kPsLdsBytes = kPsStages * kPsStageBytes;    // 128 KiB
+constexpr int kPsStages = 5;
+constexpr int kPsLdsBytes = kPsStages * kPsStageBytes;    // 160 KiB
 
 template <int MODE>
 __global__ __launch_bounds__(256, 1) void proj_gemm_small_kernel(ProjArgs p) {
@@ -466,15 +469,16 @@ __global__ __launch_bounds__(256, 1) void proj_gemm_small_kernel(ProjArgs p) {
     ga_off[u] = (uint32_t)ra * p.a_stride + (chunk << 4);
     gb_off[u] = (uint32_t)rb * p.b_stride + (chunk << 4);
   }
-  auto issue_one = [&](int t, int u) __attribute__((always_inline)) {
+  const uint32_t lds_wave = lds_base + wave * 4096;
+  // load u of the step whose slices begin at ap and bp
+  auto issue_one = [&](const char* ap, const char* bp, uint32_t stage, int u) __attribute__((always_inline)) {
+    const uint32_t dst = lds_wave + stage + (u & 3) * 1024;
+    if (u < 4) g2lds16_s<0>(ap, ga_off[u], dst);
+    else g2lds16_s<0>(bp, gb_off[u - 4], dst + kPsOperandBytes);
+  };
+  auto b_slice = [&](int t) __attribute__((always_inline)) {
     const int k0 = t * kPjK;
-    const uint32_t la = lds_base + (t & (kPsStages - 1)) * kPsStageBytes + wave * 4096;
-    if (u < 4) {
-      g2lds16_s<0>(p.a + (int64_t)k0 * 2, ga_off[u], la + u * 1024);
-    } else {
-      const char* bb = MODE == kPjOut ? p.b + (int64_t)(k0 >> 7) * p.b_head_stride + (k0 & 127) * 2 : p.b + (int64_t)k0 * 2;
-      g2lds16_s<0>(bb, gb_off[u - 4], la + kPsOperandBytes + (u - 4) * 1024);
-    }
+    return MODE == kPjOut ? p.b + (int64_t)(k0 >> 7) * p.b_head_stride + (k0 & 127) * 2 : p.b + (int64_t)k0 * 2;
   };
 
   // operand reads: lane l reads row (block + l), chunk (2 kk + hl); operands 0, 1: A blocks, 2, 3: B blocks
@@ -495,9 +499,9 @@ __global__ __launch_bounds__(256, 1) void proj_gemm_small_kernel(ProjArgs p) {
 
   const int T = p.K / kPjK;        // at least 4 (the launcher's rule)
 #pragma unroll
-  for (int t = 0; t < kPsStages; ++t)
+  for (int t = 0; t < kPsStages - 1; ++t)
 #pragma unroll
-    for (int u = 0; u < 8; ++u) issue_one(t, u);
+    for (int u = 0; u < (t < kPsStages - 2 ? 8 : 4); ++u) issue_one(p.a + t * kPjRowBytes, b_slice(t), t * kPsStageBytes, u);
 
   f32x16 acc[2][2];
 #pragma unroll
@@ -511,52 +515,85 @@ __global__ __launch_bounds__(256, 1) void proj_gemm_small_kernel(ProjArgs p) {
     acc[j & 1][j >> 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op[kk][j & 1], op[kk][2 + (j >> 1)], acc[j & 1][j >> 1], 0, 0, 0);
   };
 
-  wait_vmcnt<24>();          // step 0 has landed
+  // one wait for the four operands of a sub-step
+  auto here = [](bf16x8 (&x)[4]) __attribute__((always_inline)) { asm volatile("" : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3])); };
+
+  wait_vmcnt<20>();          // step 0 has landed
   __syncthreads();
 #pragma unroll
   for (int kk = 0; kk < 2; ++kk)
 #pragma unroll
     for (int i = 0; i < 4; ++i) op[kk][i] = read_op(0, kk, i);
 
-  // Step t: sub-steps 0 and 1 read the operands of 2 and 3; then this wavefront is done with the stage, the barrier
-  // publishes step t + 1, and sub-steps 2 and 3 cover the first reads of step t + 1 and the issue of step t + 4 into the
-  // stage just freed.  LEFT: steps after this one whose loads may still be in flight behind step t + 1's (8 per step).
-  auto step = [&](int t, auto left_tag, auto issue_tag) __attribute__((always_inline)) {
+  // Step t, in stage st: sub-steps 0 and 1 read the operands of 2 and 3; the barrier publishes step t + 1 (stage sn); sub-steps 2
+  // and 3 cover its first reads.  The loads go out evenly, one behind every second MFMA: the texture path takes 16 cycles for
+  // each, 512 for the 32 of a workgroup's step, and four wavefronts that issue all of theirs in one half of a step wait for it.
+  // In the first half these are the B rows of step t + 3 (stage sb), in the second the A rows of step t + 4, into stage sa, that of
+  // step t - 1: every wavefront has used the last of that stage's operands before it came to this barrier, so nobody has to
+  // wait for its reads there.  LEFT: steps after this one whose loads may still be in flight behind step t + 1's (8 per step).
+  auto step = [&](uint32_t st, uint32_t sn, uint32_t sb, uint32_t sa, const char* bp, const char* ap, auto left_tag, auto a_tag, auto b_tag)
+                  __attribute__((always_inline)) {
     constexpr int LEFT = decltype(left_tag)::value;          // -1: this is the last step
-    constexpr bool ISSUE = decltype(issue_tag)::value;
-    const uint32_t st = (uint32_t)(t & (kPsStages - 1)) * kPsStageBytes;
-    const uint32_t sn = (uint32_t)((t + 1) & (kPsStages - 1)) * kPsStageBytes;
+    constexpr bool A = decltype(a_tag)::value, B = decltype(b_tag)::value;
+    const uint32_t fill_a = lds_wave + sa, fill_b = lds_wave + sb + kPsOperandBytes;
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int kk = 0; kk < 2; ++kk)
+    for (int kk = 0; kk < 2; ++kk) {
+      here(op[kk]);
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
+        const int u = kk * 2 + (j >> 1);
+        if (B && (j & 1)) set_m0(fill_b + u * 1024);
         op[kk + 2][j] = read_op(st, kk + 2, j);
+        __builtin_amdgcn_sched_barrier(0);
         mfma4(kk, j);
         __builtin_amdgcn_sched_barrier(0);
+        if (B && (j & 1)) g2lds16_m0(bp, gb_off[u]);
+        __builtin_amdgcn_sched_barrier(0);
       }
+    }
     if (LEFT >= 0) {
       wait_vmcnt<LEFT < 0 ? 0 : 8 * LEFT>();                // this wave's loads of step t + 1 have landed
-      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // this wave is done reading this stage
-      __syncthreads();
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
       __builtin_amdgcn_sched_barrier(0);
     }
 #pragma unroll
-    for (int kk = 0; kk < 2; ++kk)
+    for (int kk = 0; kk < 2; ++kk) {
+      here(op[kk + 2]);
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
+        const int u = kk * 2 + (j >> 1);
+        if (A && (j & 1)) set_m0(fill_a + u * 1024);
         if (LEFT >= 0) op[kk][j] = read_op(sn, kk, j);
+        __builtin_amdgcn_sched_barrier(0);
         mfma4(kk + 2, j);
-        if (ISSUE) issue_one(t + kPsStages, kk * 4 + j);
+        __builtin_amdgcn_sched_barrier(0);
+        if (A && (j & 1)) g2lds16_m0(ap, ga_off[u]);
         __builtin_amdgcn_sched_barrier(0);
       }
+    }
   };
+  auto after = [](uint32_t stage) __attribute__((always_inline)) { return stage + kPsStageBytes < (uint32_t)kPsLdsBytes ? stage + kPsStageBytes : 0u; };
+  using Yes = std::true_type;
+  using No = std::false_type;
+  uint32_t st = 0, sb = (kPsStages - 2) * kPsStageBytes, sa = (kPsStages - 1) * kPsStageBytes;
+  const char* ap = p.a + (kPsStages - 1) * kPjRowBytes;
   int t = 0;
-  for (; t + kPsStages < T; ++t) step(t, std::integral_constant<int, 2>(), std::true_type());
-  step(t, std::integral_constant<int, 2>(), std::false_type());
-  step(t + 1, std::integral_constant<int, 1>(), std::false_type());
-  step(t + 2, std::integral_constant<int, 0>(), std::false_type());
-  step(t + 3, std::integral_constant<int, -1>(), std::false_type());
+  for (; t + kPsStages - 1 < T; ++t) {
+    const uint32_t sn = after(st);
+    step(st, sn, sb, sa, b_slice(t + kPsStages - 2), ap, std::integral_constant<int, 2>(), Yes(), Yes());
+    ap += kPjRowBytes;
+    sb = sa;
+    sa = st;
+    st = sn;
+  }
+  step(st, after(st), sb, 0, b_slice(T - 1), nullptr, std::integral_constant<int, 2>(), No(), Yes());
+  st = after(st);
+  step(st, after(st), 0, 0, nullptr, nullptr, std::integral_constant<int, 1>(), No(), No());
+  st = after(st);
+  step(st, after(st), 0, 0, nullptr, nullptr, std::integral_constant<int, 0>(), No(), No());
+  step(after(st), 0, 0, 0, nullptr, nullptr, std::integral_constant<int, -1>(), No(), No());
 
   // Register r of block (ia, ib): feature 64 ia + 32 wa + 8 (r / 4) + 4 hl + r % 4 of the tile, token 64 wb + 32 ib + l.
   char* base;
@@ -933,7 +970,7 @@ static hi_status pj_launch(void* stream, ProjArgs& p, int mode) {
   const int64_t small_tiles = ceil_div(p.a_rows, kPsTile) * ceil_div(p.b_rows, kPsTile), rest = total % 256;
   const int64_t small_us = 33 * ceil_div(small_tiles, 256);
   const int64_t large_us = 112 * (total / 256) + (rest ? 78 + 34 * rest / 256 : 0);
-  if (wide && p.K >= kPsStages * kPjK && small_us < large_us) {
+  if (wide && p.K >= (kPsStages - 1) * kPjK && small_us < large_us) {
     p.a_tiles = (int)ceil_div(p.a_rows, kPsTile);
     p.b_tiles = (int)ceil_div(p.b_rows, kPsTile);
     p.ga = p.a_tiles / 8 > 0 ? p.a_tiles / 8 : 1;
