@@ -963,13 +963,15 @@ static hi_status pj_launch(void* stream, ProjArgs& p, int mode) {
   // 16-byte stores need bf16 output, whole runs of 128 features per wavefront and an aligned row pitch
   const bool wide = !p.out_fp32 && p.a_rows % 128 == 0 && (mode == kPjQkv || (p.y_stride * 2) % 16 == 0);
   const dim3 block(kPjWaves * 64);
-  // Which tile: at a contraction of 4096 a round of 256 small tiles takes 25 to 33 us; 256 large ones take 112 us, and a
-  // last round with fewer of them 78 (a few, no power limit) to 112 us.  So the small tile wins up to about 2400 tokens of
-  // a Llama-3-8B Q/K/V projection and just above 2730, where the large one starts a second round (165 against 199 us at
-  // 3000), and the large one from there on (a 16384-token chunk: 6 full rounds against 24).
+  // Which tile: at a contraction of 4096 a round of 256 small tiles takes 31 to 36 us; 256 large ones take 106, and a last round with
+  // fewer of them 66 to 86 (a few, no power limit) to 108.  Measured with either tile forced (hidden size 4096, small / large):
+  // Q/K/V of 1200 tokens 71 / 89 us, 1400 94 / 89, 1700 99 / 93, 2000 106 / 98, 2400 130 / 108, 2600 to 3300, where the large one starts
+  // a second round, 136 / 178 to 167 / 190, 4000 199 / 198, 4600 227 / 205; output of 2000 65 / 70, 2600 89 / 84, 4000 126 / 108, 4600 153 / 179,
+  // 5200 181 / 179.  Of 108 such pairs (500 to 6000 tokens, hidden sizes 1024, 4096, 8192) the sums below pick the slower one in 3, by
+  // 1.8 % at most.
   const int64_t small_tiles = ceil_div(p.a_rows, kPsTile) * ceil_div(p.b_rows, kPsTile), rest = total % 256;
-  const int64_t small_us = 33 * ceil_div(small_tiles, 256);
-  const int64_t large_us = 112 * (total / 256) + (rest ? 78 + 34 * rest / 256 : 0);
+  const int64_t small_us = 35 * ceil_div(small_tiles, 256);
+  const int64_t large_us = 106 * (total / 256) + (rest ? 72 + 36 * rest / 256 : 0);
   if (wide && p.K >= (kPsStages - 1) * kPjK && small_us < large_us) {
     p.a_tiles = (int)ceil_div(p.a_rows, kPsTile);
     p.b_tiles = (int)ceil_div(p.b_rows, kPsTile);
