@@ -60,6 +60,8 @@ struct ProjArgs {
 };
 
 struct RopeFreqs { double inv[64]; };      // theta^(-i / 64)
+struct RopeChunk { RopeFreqs f; int64_t past; int on; };      // the rotation of a chunk that begins at position `past` (on = 0: none)
+struct NoRope {};
 
 // tile j of the grid: groups of ga A-tiles; inside a group B-major with the A-tile index fastest, so that any run of
 // consecutive j is a compact block
@@ -440,8 +442,17 @@ constexpr int kPsStageBytes = 2 * kPsOperandBytes;
 constexpr int kPsStages = 5;
 constexpr int kPsLdsBytes = kPsStages * kPsStageBytes;    // 160 KiB
 
-template <int MODE>
-__global__ __launch_bounds__(256, 1) void proj_gemm_small_kernel(ProjArgs p) {
+// The rotation needs (cos, sin) of 64 pairs at the tile's 128 tokens.  Every workgroup forms them itself, under the latency of its first
+// loads: a wavefront takes 32 tokens, a lane one pair - the first angle and one step of a position in double precision,
+// then rotations by that step, rounded to fp32 as the table of rope_table_kernel is - keeps them in 64 registers (there is one
+// wavefront per SIMD) and puts them into the ring's place in LDS for the epilogue.  As a table of its own launch they were 5 us in
+// front of this one: Q/K/V of 65 / 300 / 600 tokens at a hidden size of 4096 32.5 / 33.0 / 38.9 -> 30.2 / 30.9 / 37.1 us, of 600 tokens at 1024
+// 12.3 -> 10.6.
+constexpr int kPsTrigPitch = kPsTile * 32 + 32;      // a group of 4 pairs: [token][4] (cos, sin), and 32 bytes against bank conflicts
+static_assert(16 * kPsTrigPitch <= kPsLdsBytes, "the table takes the ring's place");
+
+template <int MODE, class Rope>
+__global__ __launch_bounds__(256, 1) void proj_gemm_small_kernel(ProjArgs p, Rope rope) {
   extern __shared__ __attribute__((aligned(1024))) char lds_dyn[];
   const uint32_t lds_base = (uint32_t)(uintptr_t)(lds_char*)lds_dyn;
   const int lane = lane_id();
@@ -502,6 +513,27 @@ __global__ __launch_bounds__(256, 1) void proj_gemm_small_kernel(ProjArgs p) {
   for (int t = 0; t < kPsStages - 1; ++t)
 #pragma unroll
     for (int u = 0; u < (t < kPsStages - 2 ? 8 : 4); ++u) issue_one(p.a + t * kPjRowBytes, b_slice(t), t * kPsStageBytes, u);
+
+  bool rotate = false;
+  float trig_c[32], trig_s[32];  // this lane's pair at tokens 32 wave .. +31 of the tile
+  if constexpr (MODE == kPjQkv) {
+    rotate = rope.on && ta < p.n_q_heads + p.n_kv_heads;
+    if (rotate) {
+      const double w = rope.f.inv[lane];
+      double s, c, s1, c1;
+      sincos((double)(rope.past + tb * kPsTile + 32 * wave) * w, &s, &c);
+      sincos(w, &s1, &c1);
+#pragma unroll
+      for (int i = 0; i < 32; ++i) {
+        trig_c[i] = (float)c;
+        trig_s[i] = (float)s;
+        asm volatile("" : "+v"(trig_c[i]), "+v"(trig_s[i]));     // here, and not in front of the epilogue
+        const double cn = c * c1 - s * s1;
+        s = s * c1 + c * s1;
+        c = cn;
+      }
+    }
+  }
 
   f32x16 acc[2][2];
 #pragma unroll
@@ -595,10 +627,17 @@ __global__ __launch_bounds__(256, 1) void proj_gemm_small_kernel(ProjArgs p) {
   step(st, after(st), 0, 0, nullptr, nullptr, std::integral_constant<int, 0>(), No(), No());
   step(after(st), 0, 0, 0, nullptr, nullptr, std::integral_constant<int, -1>(), No(), No());
 
+  if (MODE == kPjQkv && rotate) {
+    __syncthreads();             // nobody reads the ring any more
+    char* const at = lds_dyn + (lane >> 2) * kPsTrigPitch + wave * 1024 + (lane & 3) * 8;
+#pragma unroll
+    for (int i = 0; i < 32; ++i) *(float2*)(at + i * 32) = make_float2(trig_c[i], trig_s[i]);
+    __syncthreads();
+  }
+
   // Register r of block (ia, ib): feature 64 ia + 32 wa + 8 (r / 4) + 4 hl + r % 4 of the tile, token 64 wb + 32 ib + l.
   char* base;
   int64_t row_bytes;
-  bool rotate = false;
   float osc = 1.0f;
   if (MODE == kPjQkv) {
     const int head = ta;
@@ -606,7 +645,6 @@ __global__ __launch_bounds__(256, 1) void proj_gemm_small_kernel(ProjArgs p) {
     if (head < p.n_q_heads) { base = (char*)p.q_out; hh = head; osc = p.q_scale; }
     else if (head < p.n_q_heads + p.n_kv_heads) { base = (char*)p.k_out; hh = head - p.n_q_heads; }
     else { base = (char*)p.v_out; hh = head - p.n_q_heads - p.n_kv_heads; }
-    rotate = p.rope != nullptr && head < p.n_q_heads + p.n_kv_heads;
     base += (int64_t)hh * p.b_rows * kRowBytes;
     row_bytes = kRowBytes;
   } else {
@@ -622,10 +660,9 @@ __global__ __launch_bounds__(256, 1) void proj_gemm_small_kernel(ProjArgs p) {
     for (int r = 0; r < 16; ++r) { lo[r] = acc[0][ib][r]; hi[r] = acc[1][ib][r]; }
     if (MODE == kPjQkv) {
       if (rotate) {
-        const int mt = ok ? m : p.b_rows - 1;
 #pragma unroll
         for (int rq = 0; rq < 4; ++rq) {
-          const float4* cs = (const float4*)(p.rope + ((int64_t)(8 * wa + 2 * rq + hl) * p.b_rows + mt) * 4);
+          const float4* cs = (const float4*)(lds_dyn + (8 * wa + 2 * rq + hl) * kPsTrigPitch + (64 * wb + 32 * ib + l) * 32);
           const float4 c01 = cs[0], c23 = cs[1];
           const float cv[4] = {c01.x, c01.z, c23.x, c23.z}, sv[4] = {c01.y, c01.w, c23.y, c23.w};
 #pragma unroll
@@ -942,13 +979,14 @@ static hi_status gemv_launch(void* stream, const GemvArgs& g) {
   return HI_OK;
 }
 
-static hi_status pj_launch(void* stream, ProjArgs& p, int mode) {
+// table: room for the rotary table of the chunk, which the large tile reads (rope.on)
+static hi_status pj_launch(void* stream, ProjArgs& p, int mode, const RopeChunk& rope, void* table) {
   static std::once_flag attr_once;      // the projections are stateless: any host thread may get here first
   static hipError_t attr_err = hipSuccess;
   std::call_once(attr_once, [] {
     const void* kernels[6] = {(const void*)proj_gemm_kernel<kPjQkv, true>, (const void*)proj_gemm_kernel<kPjQkv, false>,
                               (const void*)proj_gemm_kernel<kPjOut, true>, (const void*)proj_gemm_kernel<kPjOut, false>,
-                              (const void*)proj_gemm_small_kernel<kPjQkv>, (const void*)proj_gemm_small_kernel<kPjOut>};
+                              (const void*)proj_gemm_small_kernel<kPjQkv, RopeChunk>, (const void*)proj_gemm_small_kernel<kPjOut, NoRope>};
     for (int i = 0; i < 6 && attr_err == hipSuccess; ++i)
       attr_err = hipFuncSetAttribute(kernels[i], hipFuncAttributeMaxDynamicSharedMemorySize, i < 4 ? kPjLdsBytes : kPsLdsBytes);
   });
@@ -977,11 +1015,18 @@ static hi_status pj_launch(void* stream, ProjArgs& p, int mode) {
     p.b_tiles = (int)ceil_div(p.b_rows, kPsTile);
     p.ga = p.a_tiles / 8 > 0 ? p.a_tiles / 8 : 1;
     const dim3 sgrid((unsigned)(8 * ceil_div(small_tiles, 8)));
-    if (mode == kPjQkv) hipLaunchKernelGGL(proj_gemm_small_kernel<kPjQkv>, sgrid, block, kPsLdsBytes, (hipStream_t)stream, p);
-    else hipLaunchKernelGGL(proj_gemm_small_kernel<kPjOut>, sgrid, block, kPsLdsBytes, (hipStream_t)stream, p);
+    if (mode == kPjQkv) hipLaunchKernelGGL((proj_gemm_small_kernel<kPjQkv, RopeChunk>), sgrid, block, kPsLdsBytes, (hipStream_t)stream, p, rope);
+    else hipLaunchKernelGGL((proj_gemm_small_kernel<kPjOut, NoRope>), sgrid, block, kPsLdsBytes, (hipStream_t)stream, p, NoRope());
     hipError_t es = hipGetLastError();
     if (es != hipSuccess) { set_last_error("projection launch: %s", hipGetErrorString(es)); return HI_ERR_HIP; }
     return HI_OK;
+  }
+  if (rope.on) {
+    hipLaunchKernelGGL(rope_table_kernel, dim3((unsigned)ceil_div((int64_t)p.b_rows * 64, 256)), dim3(256), 0, (hipStream_t)stream,
+                       (float2*)table, rope.past, p.b_rows, rope.f);
+    hipError_t er = hipGetLastError();
+    if (er != hipSuccess) { set_last_error("rope table launch: %s", hipGetErrorString(er)); return HI_ERR_HIP; }
+    p.rope = (const float2*)table;
   }
   if (mode == kPjQkv && wide) hipLaunchKernelGGL((proj_gemm_kernel<kPjQkv, true>), grid, block, kPjLdsBytes, (hipStream_t)stream, p);
   else if (mode == kPjQkv) hipLaunchKernelGGL((proj_gemm_kernel<kPjQkv, false>), grid, block, kPjLdsBytes, (hipStream_t)stream, p);
@@ -1080,18 +1125,13 @@ static hi_status qkv_rope_impl(void* stream, const void* x_dev, const void* w_qk
   p.n_q_heads = n_q_heads; p.n_kv_heads = n_kv_heads;
   p.rope = nullptr;
   p.q_scale = q_scale;
-  RopeFreqs f = {};
-  if (rope_theta > 0)
-    for (int i = 0; i < 64; ++i) f.inv[i] = pow(rope_theta, -(double)i / 64.0);
-  if (chunk_len <= kPfwMaxTokens) return pj_few_launch<kPjQkv>(stream, p, past_len, f, rope_theta > 0 ? n_q_heads + n_kv_heads : 0);
-  if (rope_theta > 0) {
-    hipLaunchKernelGGL(rope_table_kernel, dim3((unsigned)ceil_div((int64_t)chunk_len * 64, 256)), dim3(256), 0,
-                       (hipStream_t)stream, (float2*)workspace_dev, past_len, chunk_len, f);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) { set_last_error("rope table launch: %s", hipGetErrorString(e)); return HI_ERR_HIP; }
-    p.rope = (const float2*)workspace_dev;
-  }
-  return pj_launch(stream, p, kPjQkv);
+  RopeChunk rope = {};
+  rope.past = past_len;
+  rope.on = rope_theta > 0;
+  if (rope.on)
+    for (int i = 0; i < 64; ++i) rope.f.inv[i] = pow(rope_theta, -(double)i / 64.0);
+  if (chunk_len <= kPfwMaxTokens) return pj_few_launch<kPjQkv>(stream, p, past_len, rope.f, rope.on ? n_q_heads + n_kv_heads : 0);
+  return pj_launch(stream, p, kPjQkv, rope, workspace_dev);
 }
 
 extern "C" hi_status hi_qkv_rope(void* stream, const void* x_dev, const void* w_qkv_dev, int32_t d_model,
@@ -1177,5 +1217,5 @@ extern "C" hi_status hi_out_proj(void* stream, const void* attn_dev, const void*
   p.out_fp32 = out_fp32;
   p.y = y_out_dev; p.y_stride = d_model;
   if (chunk_len <= kPfwMaxTokens) return pj_few_launch<kPjOut>(stream, p, 0, RopeFreqs(), 0);
-  return pj_launch(stream, p, kPjOut);
+  return pj_launch(stream, p, kPjOut, RopeChunk(), nullptr);
 }
