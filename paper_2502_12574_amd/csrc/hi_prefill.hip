@@ -1672,16 +1672,18 @@ __device__ __forceinline__ bool pf_append_block(const PrefillAppendArgs& p) {
 }
 
 // Merge of the states of prefill_kernel_deep16 (its own image layout): grid (blocks, grid rows, 8): z is one dim block
-// of both query rows of the lane.  Bound by the read of the images (139 KB each, up to 64 per block), and where a block has
+// of both query rows of the lane; where that is no workgroup for every compute unit, z = 16: one dim block of one query row.
+// Bound by the read of the images (139 KB each, up to 64 per block), and where a block has
 // few of them by its latency: CH images are in flight per lane, and behind the first CH the references of all others.  The largest
 // reference comes first, then the sums in the images' order, each image with one weight.  Shortest and median time with the
-// append: 8 heads of 2 blocks of 16 images 9.7 and 10.7 us, of 10 blocks of 3 images 9.5 and 10.0; without the append, four images
+// append: 8 heads of 2 blocks of 16 images 7.4 and 8.4 us (128 workgroups, both rows in each: 9.7 and 10.7), of 10 blocks of 3 images 9.5 and
+// 10.0 (1280 workgroups of one row each: 10.4 and 10.8); without the append, four images
 // in flight in two loops, 10.0 and 11.6, 9.2 and 10.0.  (A single pass that rescales what it has summed takes 1 us less for the
 // first, and gives other bits.)  Behind the merge's blocks others append the chunk's rows to the cache: as a launch of its own
 // behind this one that took 4.3 us and the gap before it.
 template <int NQ, int CH>
-__device__ __forceinline__ void pf16_merge(const PrefillArgs& a, const PfShape& sh, const Pf16Rows& rows16, int bx, int db, int n_e,
-                                           int n, int g, int g16, int c16) {
+__device__ __forceinline__ void pf16_merge(const PrefillArgs& a, const PfShape& sh, const Pf16Rows& rows16, int bx, int db, int qb0,
+                                           int n_e, int n, int g, int g16, int c16) {
   constexpr int kLanes = kPdWaves * 64;
   constexpr int kImageFloats = kCarryFloatsPerLane * kLanes;
   const float* images = a.carry + (int64_t)blockIdx.y * a.img_row * kImageFloats + threadIdx.x;
@@ -1705,10 +1707,10 @@ __device__ __forceinline__ void pf16_merge(const PrefillArgs& a, const PfShape& 
       const float* im = image_of(i0 + j);
 #pragma unroll
       for (int qb = 0; qb < NQ; ++qb) {
-        mi[j][qb] = im[(64 + qb) * kLanes];
-        li[j][qb] = im[(66 + qb) * kLanes];
+        mi[j][qb] = im[(64 + qb0 + qb) * kLanes];
+        li[j][qb] = im[(66 + qb0 + qb) * kLanes];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) oi[j][qb][r] = im[((db * 2 + qb) * 4 + r) * kLanes];
+        for (int r = 0; r < 4; ++r) oi[j][qb][r] = im[((db * 2 + qb0 + qb) * 4 + r) * kLanes];
       }
     }
     if (i0 == 0) {
@@ -1719,7 +1721,7 @@ __device__ __forceinline__ void pf16_merge(const PrefillArgs& a, const PfShape& 
         for (int j = 0; j < 6; ++j) {
           const float* im = image_of(k0 + j);
 #pragma unroll
-          for (int qb = 0; qb < NQ; ++qb) x[j][qb] = im[(64 + qb) * kLanes];
+          for (int qb = 0; qb < NQ; ++qb) x[j][qb] = im[(64 + qb0 + qb) * kLanes];
         }
 #pragma unroll
         for (int j = 0; j < 6; ++j)
@@ -1750,7 +1752,7 @@ __device__ __forceinline__ void pf16_merge(const PrefillArgs& a, const PfShape& 
 #pragma unroll
   for (int qb = 0; qb < NQ; ++qb) {
     const f32x4 rows[1] = {o[qb]};
-    pf16_write_row<1>(a.out, a.out_fp32, a.C, g, rows16.i0 + rows16.step * qb + c16, g16, db, rows, l[qb]);
+    pf16_write_row<1>(a.out, a.out_fp32, a.C, g, rows16.i0 + rows16.step * (qb0 + qb) + c16, g16, db, rows, l[qb]);
   }
 }
 
@@ -1760,18 +1762,20 @@ __global__ __launch_bounds__(512, 4) void prefill_merge16_kernel(PrefillArgs a, 
   const int wave = wave_id();
   const int gl = a.G < 4 ? a.G : 4;
   const int bx = blockIdx.x;
-  const int db = blockIdx.z;
+  const bool apart = append.first_z == 16;
+  const int db = blockIdx.z & 7, qb = blockIdx.z >> 3;
   const int g = pf_select_head(a) * 4 + (wave % gl);
   const Pf16Rows rows16 = pf16_rows(a, bx, gl, wave);
-  if (rows16.nq == 0) return;               // rows past the end
+  if (qb >= rows16.nq) return;              // rows past the end
   const PfShape sh = pf_shape_of(a, a.strip);
   int n_e, n_x;
   pf_block_images(sh, bx, n_e, n_x);
   const int n = n_e + n_x;
   if (n == 1 && a.split == 1) return;
-  if (rows16.nq == 1) pf16_merge<1, 8>(a, sh, rows16, bx, db, n_e, n, g, lane >> 4, lane & 15);
-  else if (n <= 4) pf16_merge<2, 4>(a, sh, rows16, bx, db, n_e, n, g, lane >> 4, lane & 15);
-  else pf16_merge<2, 8>(a, sh, rows16, bx, db, n_e, n, g, lane >> 4, lane & 15);
+  if (apart && n > 8) pf16_merge<1, 16>(a, sh, rows16, bx, db, qb, n_e, n, g, lane >> 4, lane & 15);
+  else if (apart || rows16.nq == 1) pf16_merge<1, 8>(a, sh, rows16, bx, db, qb, n_e, n, g, lane >> 4, lane & 15);
+  else if (n <= 4) pf16_merge<2, 4>(a, sh, rows16, bx, db, 0, n_e, n, g, lane >> 4, lane & 15);
+  else pf16_merge<2, 8>(a, sh, rows16, bx, db, 0, n_e, n, g, lane >> 4, lane & 15);
 }
 
 #include "hi_prefill_wide.inc"
@@ -2285,7 +2289,7 @@ hi_status launch_prefill(void* stream, const void* q, int G, int chunk_len, cons
       hipError_t e1 = hipGetLastError();
       if (e1 != hipSuccess) { set_last_error("prefill launch: %s", hipGetErrorString(e1)); return HI_ERR_HIP; }
       if (mfma32) launch_kernel(prefill_merge_kernel, merge_grid((unsigned)pl.nbk, grid.y, 4, kPdWaves * 64), dim3(kPdWaves * 64), 0, stream, done, a, app);
-      else launch_kernel(prefill_merge16_kernel, merge_grid((unsigned)pl.nbk, grid.y, 8, kPdWaves * 64), dim3(kPdWaves * 64), 0, stream, done, a, app);
+      else launch_kernel(prefill_merge16_kernel, merge_grid((unsigned)pl.nbk, grid.y, 8u * pl.nbk * grid.y < kPrefillCus ? 16 : 8, kPdWaves * 64), dim3(kPdWaves * 64), 0, stream, done, a, app);
     }
   } else {
     const dim3 blocks((unsigned)ceil_div(chunk_len, strip), (unsigned)(gy * n_heads));
