@@ -105,6 +105,12 @@ struct PfLaneConst {
                      // pair, +4096 second 16-row group, +8192 second sub-block)
 };
 
+// x, formed anew where this stands: what the compiler derives from it is not kept in registers across the loop around it
+__device__ __forceinline__ int formed_here(int x) {
+  asm volatile("" : "+v"(x));
+  return x;
+}
+
 // One tile's K loads (or V loads) by the whole workgroup of NW wavefronts: 16 / NW instructions per wavefront.
 // Full tiles need no vector ALU work at all; the last tile of a segment clamps its row indices (rows past the
 // end re-read the last row and are masked by the caller).  lds_tile is the LDS byte address of the 16 KiB tile.
@@ -121,6 +127,7 @@ __device__ __forceinline__ void pf_issue_k(const char* kt, int rows, uint32_t ld
       g2lds16_s<0>(kt, lc.gk[3], ldk + 3072);
     }
   } else {
+    lane = formed_here(lane);
     const int r_in = lane >> 4;
     const int cpos = lane & 15;
 #pragma unroll
@@ -145,6 +152,7 @@ __device__ __forceinline__ void pf_issue_v(const char* vt, int rows, uint32_t ld
       g2lds16_s<3072>(vt, lc.gv, ldv);
     }
   } else {
+    lane = formed_here(lane);
     const int r_in = lane >> 4;
     const int cpos = lane & 15;
 #pragma unroll
@@ -189,10 +197,7 @@ __device__ __forceinline__ void pf_write_row(void* out, int out_fp32, int C, int
       if (out_fp32) {
         *(float4*)((float*)out + base + dim) = make_float4(x0, x1, x2, x3);
       } else {
-        uint2 pk;
-        pk.x = (uint32_t)float_to_bf16_bits(x0) | ((uint32_t)float_to_bf16_bits(x1) << 16);
-        pk.y = (uint32_t)float_to_bf16_bits(x2) | ((uint32_t)float_to_bf16_bits(x3) << 16);
-        *(uint2*)((uint16_t*)out + base + dim) = pk;
+        *(uint2*)((uint16_t*)out + base + dim) = make_uint2(pack_bf16(x0, x1), pack_bf16(x2, x3));
       }
     }
 }
@@ -354,6 +359,114 @@ __device__ __forceinline__ void pf_pv(lds_char* vt, const PfLaneConst& lc, const
     st.o[i & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op[i % (A + 1)], pb[i >> 3][(i >> 2) & 1], st.o[i & 3], 0, 0, 0);
     __builtin_amdgcn_sched_barrier(0);
   }
+}
+
+// One tile of a 4-wave kernel, the next tile's scores one step ahead: the wavefront's vector ALU works on the softmax of the tile
+// whose scores are in s0 (rows 0..31) and s1 while its matrix pipe forms those of the tile behind it (K tile at kt; NEXT = false:
+// there is none), and the second half of the exponentials goes between the first MFMAs of O^T += V^T P^T (V tile at vt).  The next
+// tile's rows 32..63 come first, into next1; its rows 0..31 then take the place of those that have become weights, in s0.
+// What bounds such a tile is the number of instructions of any kind: a wavefront issues one per 6 to 7 cycles, and two share a SIMD.
+// So the operands of four MFMAs are read together and waited for once, the tile loads (load(i), eight of them, M0 set one MFMA
+// before by load_at(i)) go between MFMAs instead of stalling in a row, and whatever the caller can keep out of the tile loop
+// (addresses, the choice of masks) it keeps out.
+// mask(s0, s1) hides scores, and is called where `masked` says so.  A lane that has seen nothing yet (m == kNegBig) adds
+// weights of zero.
+template <bool NEXT, class Mask, class At, class Load>
+__device__ __forceinline__ void pf_tile4(lds_char* kt, lds_char* vt, const PfLaneConst& lc, const bf16x8 (&qf)[8],
+                                         f32x16& s0, f32x16& s1, f32x16& next1, PfState& st, float c, bool masked, Mask mask,
+                                         At load_at, Load load) {
+  constexpr int F = NEXT ? 0 : 16, kMax = 2;
+  bf16x8 op[2][4];
+  u32x4 pw[2][2];                // the weights, two to a word: B operands of the second product
+  // operand i: K fragment of (sub-block, contraction step) = (1 - i / 8, i % 8), from 16 on V^T of (keys, dim block) = ((i - 16) / 4, i % 4)
+  auto read = [&](int i) __attribute__((always_inline)) {
+    bf16x8& x = op[(i >> 2) & 1][i & 3];
+    if (i < 16) { x = *(lds_bf16x8*)(kt + lc.koff[i & 7] + (i < 8 ? 8192 : 0)); return; }
+    lds_char* p = vt + lc.voff[i & 3] + ((i - 16) >> 2) * 4096;
+    const bf16x4 v0 = lds_read_tr8(p), v1 = lds_read_tr8(p + 2048);
+    x = (bf16x8)__builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7);
+  };
+  auto mfma = [&](int i) __attribute__((always_inline)) {
+    if (i < 16 && !NEXT) return;
+    bf16x8 (&o4)[4] = op[(i >> 2) & 1];
+    if ((i & 3) == 0) asm volatile("" : "+v"(o4[0]), "+v"(o4[1]), "+v"(o4[2]), "+v"(o4[3]));     // one wait for the four
+    const bf16x8 x = o4[i & 3];
+    f32x16 z;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) z[r] = 0.f;
+    if (NEXT && i < 16 && (i & 1) == 0) {
+      load_at(i >> 1);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    if (i < 8) next1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, qf[i], i == 0 ? z : next1, 0, 0, 0);
+    else if (i < 16) s0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, qf[i - 8], i == 8 ? z : s0, 0, 0, 0);
+    else st.o[i & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, __builtin_bit_cast(bf16x8, pw[(i - 16) >> 3][(i >> 2) & 1]), st.o[i & 3], 0, 0, 0);
+    if (NEXT && i < 16 && (i & 1) == 0) {
+      __builtin_amdgcn_sched_barrier(0);
+      load(i >> 1);
+    }
+    if ((i & 3) < 2 && (i | 3) + 4 < 32) {                         // the next four operands
+      read((i | 3) + 1 + 2 * (i & 3));
+      read((i | 3) + 2 + 2 * (i & 3));
+    }
+  };
+  if (masked) mask(s0, s1);
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) read(F + i);
+  float mx = s0[0];
+#pragma unroll
+  for (int i = 0; i < kMax; ++i) {
+    mfma(i);
+#pragma unroll
+    for (int r = 32 / kMax * i; r < 32 / kMax * (i + 1); ++r) mx = fmaxf(mx, r < 16 ? s0[r] : s1[r & 15]);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  const float m_new = fmaxf(st.m, max_halves(mx));
+  if (__builtin_amdgcn_ballot_w64(m_new > st.m) != 0) {
+    const float alpha = fast_exp2((st.m - m_new) * c);
+    st.l *= alpha;
+#pragma unroll
+    for (int db = 0; db < 4; ++db)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) st.o[db][r] *= alpha;
+    st.m = m_new;
+  }
+  const float mc = st.m > kNegBig ? st.m * c : 0.f;
+  float lq[4];
+  // weights 2 p, 2 p + 1 of the tile: registers 8 (p / 4 % 2) + 2 (p % 4) .. of sub-block p / 8
+  auto pair = [&](int p) __attribute__((always_inline)) {
+    const int sb = p >> 3, u = (p >> 2) & 1, j = 2 * (p & 3);
+    float w[2], &sum = lq[2 * sb + u];
+#pragma unroll
+    for (int e = 0; e < 2; ++e) w[e] = fast_exp2(__builtin_fmaf(sb == 0 ? s0[8 * u + j + e] : s1[8 * u + j + e], c, -mc));
+    sum = (j == 0 ? w[0] : sum + w[0]) + w[1];
+    typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+    uint32_t word = __builtin_bit_cast(uint32_t, (bf16x2){(__bf16)w[0], (__bf16)w[1]});
+    asm volatile("" : "+v"(sum), "+v"(word));          // here, and not where the sums and the operand are next used
+    pw[sb][u][j >> 1] = word;
+  };
+#pragma unroll
+  for (int i = kMax; i < 8; ++i) {
+    mfma(i);
+#pragma unroll
+    for (int p = (i - kMax) * 8 / (8 - kMax); p < (i - kMax + 1) * 8 / (8 - kMax); ++p) pair(p);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+#pragma unroll
+  for (int i = 8; i < 16; ++i) {
+    mfma(i);
+    if (NEXT && (i & 1)) pair(8 + ((i - 8) >> 1));
+    __builtin_amdgcn_sched_barrier(0);
+  }
+#pragma unroll
+  for (int i = 16; i < 32; ++i) {
+    mfma(i);
+    if (!NEXT && i < 20) pair(8 + i - 16);
+    if (i < 28 && i % 3 == 0) pair(12 + (i - 18) / 3);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  st.l += (lq[0] + lq[1]) + (lq[2] + lq[3]);
 }
 
 // ---- helpers of the 8-wave kernel.  Its LDS holds a ring of K tiles at [0, 64 KiB) and a ring of V tiles at
@@ -1921,70 +2034,13 @@ struct PrefillWindowArgs {
 // Rows [0, n) of a tile as a bit mask.
 __device__ __forceinline__ uint64_t pf_rows_below(int n) { return n <= 0 ? 0 : n >= 64 ? ~0ull : (1ull << n) - 1; }
 
-// pf_softmax for a tile in which lane-dependent sets of rows are hidden: bit 8 (r / 4) + r % 4 of seen[sb] says whether the
-// lane's row r of sub-block sb is visible.  A lane may see nothing of the tile (and nothing so far): hidden entries
-// contribute exactly zero whatever the running maximum is.  The bits are applied as bit operations: as comparisons and
-// selects per element the compiler made branches of them, for tiles that need no mask too (83 -> 77 us a launch over 4 heads
-// x 8192 rows, sink 128 + recent 512).
-__device__ __forceinline__ void pf_softmax_window(f32x16 (&s)[2], PfState& st, float c, bool masked,
-                                                  const uint32_t (&seen)[2], bf16x8 (&pb)[2][2]) {
-  auto bit = [&](int sb, int r) __attribute__((always_inline)) {       // all ones if visible, else 0
-    return (uint32_t)__builtin_amdgcn_sbfe((int)seen[sb], 8 * (r >> 2) + (r & 3), 1);
-  };
-  if (masked) {
-#pragma unroll
-    for (int sb = 0; sb < 2; ++sb)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const uint32_t t = bit(sb, r);
-        s[sb][r] = __uint_as_float((__float_as_uint(s[sb][r]) & t) | (__float_as_uint(kNegBig) & ~t));
-      }
-  }
-  float mx = s[0][0];
-#pragma unroll
-  for (int sb = 0; sb < 2; ++sb)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[sb][r]);
-  mx = max_halves(mx);
-  const float m_new = fmaxf(st.m, mx);
-  if (__builtin_amdgcn_ballot_w64(m_new > st.m) != 0) {
-    const float alpha = fast_exp2((st.m - m_new) * c);
-    st.l *= alpha;
-#pragma unroll
-    for (int db = 0; db < 4; ++db)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) st.o[db][r] *= alpha;
-    st.m = m_new;
-  }
-  const float mc = st.m * c;
-#pragma unroll
-  for (int sb = 0; sb < 2; ++sb)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) s[sb][r] = fast_exp2(__builtin_fmaf(s[sb][r], c, -mc));
-  if (masked) {
-#pragma unroll
-    for (int sb = 0; sb < 2; ++sb)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) s[sb][r] = __uint_as_float(__float_as_uint(s[sb][r]) & bit(sb, r));
-  }
-  float lq[4];
-#pragma unroll
-  for (int sb = 0; sb < 2; ++sb)
-#pragma unroll
-    for (int u = 0; u < 2; ++u)
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const float p = s[sb][8 * u + j];
-        lq[2 * sb + u] = j == 0 ? p : lq[2 * sb + u] + p;
-        pb[sb][u][j] = (__bf16)p;
-      }
-  st.l += (lq[0] + lq[1]) + (lq[2] + lq[3]);
-}
-
-// Where the time of a launch over 4 heads x 8192 rows (1024 workgroups, two rounds of two per compute unit) goes: 1.85 us per
-// tile and round, near the 4-wave kernel's rate, and about 9 us a round to fetch queries and first tiles and to write the
-// rows, which two resident workgroups hide only in part.  Asking for the first tile before the queries and keeping
-// neighbouring blocks on one XCD took it from 72 to 66 us; a ring of four stages with one workgroup of 8 wavefronts, or of
+// A launch over 4 heads x 8192 rows (1024 workgroups, two rounds of two per compute unit, 11 tiles each) keeps one of a SIMD's two
+// pipes at work nearly all the time: 56 % of the cycles the vector ALU, 41 % the matrix pipe.  The scores of a visit are formed
+// under the softmax of the one before it (pf_tile4), two K and two V tiles have places in LDS, and the loads are streams that
+// cost a pointer's increment: 53 thousand cycles a workgroup, of which 14 thousand to fetch queries and first tiles and to write the
+// rows, instead of 59 - at a clock that falls for it (2.1 GHz over many launches); 155.6 -> 152.6 us for two chunks in a row, perf ab
+// 165.4 -> 162.9.  Before: asking for the first tile before the queries and keeping
+// neighbouring blocks on one XCD took a launch from 72 to 66 us; a ring of four stages with one workgroup of 8 wavefronts, or of
 // three K and two V tiles with two of 4, was no faster (87, 84 against 83 us), and starting the scores from minus the
 // running reference spilled registers (89).
 __global__ __launch_bounds__(256, 2) void prefill_window_kernel(PrefillWindowArgs a) {
@@ -2053,87 +2109,143 @@ __global__ __launch_bounds__(256, 2) void prefill_window_kernel(PrefillWindowArg
     return w < b1 ? w : b2 + (w - b1);
   };
 
-  auto issue = [&](int v) __attribute__((always_inline)) {
-    const uint32_t stage = lds_base + (uint32_t)(v & (kPfStages - 1)) * kPfStageBytes;
+  // The loads of K tiles, and of V tiles, as two streams: the next visit's rows lie at `base`, off[] are the lane's byte offsets
+  // behind it (those of 64 rows in a row if `usual`), and up to visit `until` the next tile is the next 16 KiB with the same offsets.
+  struct Stream { const char* base; int v, until, usual; uint32_t off[4]; };
+  auto meet = [&](Stream& w, auto v_tag) __attribute__((always_inline)) {       // the stream has come to visit w.v: what is there?
+    constexpr bool VP = decltype(v_tag)::value;
+    const int here = formed_here(lane), r_in = here >> 4, cpos = here & 15;
     bool in_b;
-    const int tile = locate(v, in_b);
-    if (in_b) {
-      const int row0 = tile * kPfTileRows;
-      const int left = a.C - row0;
-      pf_issue_tile<4>(a.kb + (int64_t)row0 * kRowBytes, a.vb + (int64_t)row0 * kRowBytes,
-                       left < kPfTileRows ? left : kPfTileRows, stage, wave, lane, lc);
-    } else {
-      // rows of A come through the ring mapping: per-lane addresses
-      const int r_in = lane >> 4, cpos = lane & 15;
-      const uint32_t ld = stage + wave * 4096;
+    const int tile = locate(w.v < T ? w.v : T - 1, in_b);      // behind the last visit: its rows again, which nobody reads
+    const int row0 = tile * kPfTileRows;
+    const int whole = (in_b ? a.C : a.ns) / kPfTileRows, end = in_b && tile >= b1 ? tb : in_b ? b1 : whole;
+    const bool usual = tile < whole;              // full tiles of the chunk, and of sink rows; else the chunk's last rows, or rows of the ring
+    w.until = w.v + (usual ? (end < whole ? end : whole) - tile : 1);
+    w.base = in_b ? (VP ? a.vb : a.kb) : (VP ? a.vs : a.ks);
+    if (usual || in_b) w.base += (int64_t)row0 * kRowBytes;
+    if (usual && w.usual) return;
+    w.usual = usual;
+    const int rows = usual ? kPfTileRows : a.C - row0;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int r = (wave * 4 + i) * 4 + r_in;
-        int u = tile * kPfTileRows + r;
+    for (int i = 0; i < 4; ++i) {
+      const int r = (wave * 4 + i) * 4 + r_in;
+      int at = r < rows ? r : rows - 1;
+      if (!usual && !in_b) {                      // rows of A come through the ring mapping
+        int u = row0 + r;
         if (u > nA - 1) u = nA - 1;
-        int phys = u;
+        at = u;
         if (u >= a.ns) {
-          int w = a.ring0 + (u - a.ns);
-          if (w >= a.n_recent) w -= a.n_recent;
-          phys = a.n_sink + w;
+          int x = a.ring0 + (u - a.ns);
+          if (x >= a.n_recent) x -= a.n_recent;
+          at = a.n_sink + x;
         }
-        g2lds16_s<0>(a.ks, (uint32_t)phys * kRowBytes + ((cpos ^ swz_k(r)) << 4), ld + i * 1024);
-        g2lds16_s<0>(a.vs, (uint32_t)phys * kRowBytes + ((cpos ^ swz_v(r)) << 4), ld + kPfTileBytes + i * 1024);
       }
+      w.off[i] = (uint32_t)at * kRowBytes + ((cpos ^ (VP ? swz_v(r) : swz_k(r))) << 4);
     }
   };
+  using KPlane = std::false_type;
+  using VPlane = std::true_type;
+  auto go_on = [&](Stream& w, auto v_tag) __attribute__((always_inline)) {
+    w.base += kPfTileBytes;
+    if (++w.v == w.until) meet(w, v_tag);
+  };
+  const uint32_t lds_wave = lds_base + wave * 4096;
+  auto issue = [&](const Stream& w, uint32_t slot) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) g2lds16_s<0>(w.base, w.off[i], lds_wave + slot + i * 1024);
+  };
 
-  issue(0);                    // before the queries: one wait for both
+  Stream sk, sv;
+  sk.v = sv.v = sk.usual = sv.usual = 0;
+  meet(sk, KPlane());
+  meet(sv, VPlane());
+  issue(sk, 0);                // before the queries: one wait for all
+  issue(sv, kPfStageBytes);
+  go_on(sk, KPlane());
+  go_on(sv, VPlane());
+  issue(sk, kPfTileBytes);
   bf16x8 qf[8];
   {
     const uint16_t* qrow = a.q + ((int64_t)g * a.C + qi) * kHeadDim + 8 * hl;
 #pragma unroll
     for (int kk = 0; kk < 8; ++kk) qf[kk] = __builtin_bit_cast(bf16x8, *(const uint4*)(qrow + 16 * kk));
   }
+  go_on(sk, KPlane());
 #pragma unroll
   for (int kk = 0; kk < 8; ++kk) asm volatile("" : "+v"(qf[kk]));
   const float c = a.c;
-  auto step = [&](int v, auto stage_tag) __attribute__((always_inline)) {
-    constexpr int STAGE = decltype(stage_tag)::value;
+  f32x16 s0, s1a, s1b;         // scores of a visit's rows 0..31, and of its rows 32..63 (even and odd visits)
+  wait_vmcnt<0>();
+  __syncthreads();
+  {
+    f32x16 s[2];
+    pf_scores(lds, lc, qf, s);
+    s0 = s[0];
+    s1a = s[1];
+  }
+  // visits [seen0, seen0 + n_seen) of the recent rows of B are visible in full to every query row of this wave
+  int seen0, n_seen;
+  {
+    const int from = i0 + 31 - a.n_recent + 1, last = i0 < a.C - 1 ? i0 : a.C - 1;
+    int t0 = from <= 0 ? 0 : (from + kPfTileRows - 1) / kPfTileRows;
+    if (t0 < b2) t0 = b2;
+    const int t1 = (last + 1) / kPfTileRows;
+    seen0 = nAv + b1 + t0 - b2;
+    n_seen = t1 > t0 ? t1 - t0 : 0;
+  }
+  // Visit v: its weights and sums, and the scores of visit v + 1.  On entry both of v + 1's K rows and v's V rows are on their way;
+  // behind the barrier everybody is done with the K tile of v and the V tile of v - 1, whose places take the next ones.
+  // parity: v % 2, a constant where every LDS address shall be an immediate.
+  auto step = [&](int v, auto parity, auto more, f32x16& cur, f32x16& nxt) __attribute__((always_inline)) {
+    const int odd = parity;
+    constexpr bool NEXT = decltype(more)::value;
     wait_vmcnt<0>();
     __syncthreads();
-    if (v + 1 < T) issue(v + 1);
-    bool in_b;
-    const int j0 = locate(v, in_b) * kPfTileRows;
-    // per lane: row visible iff row <= hi and (row < sk or row >= lo), rows relative to the tile
-    int hi, sk, lo;
-    bool full;          // wave-uniform: every row of the tile is visible to every query row of this wave
-    if (in_b) {
-      hi = (my_i < a.C - 1 ? my_i : a.C - 1) - j0;
-      sk = a.sink_b - j0;
-      lo = my_i - a.n_recent + 1 - j0;
-      full = j0 + kPfTileRows - 1 <= (i0 < a.C - 1 ? i0 : a.C - 1) &&
-             (j0 + kPfTileRows - 1 < a.sink_b || j0 >= i0 + 31 - a.n_recent + 1);
-    } else {
-      hi = nA - 1 - j0;
-      sk = a.ns - j0;
-      lo = a.lo0 + my_i - j0;
-      full = j0 + kPfTileRows - 1 <= nA - 1 && (j0 + kPfTileRows - 1 < a.ns || j0 >= a.lo0 + i0 + 31);
+    bool full = (uint32_t)(v - seen0) < (uint32_t)n_seen, in_b = false;
+    int j0 = 0;
+    if (!full) {
+      j0 = locate(v, in_b) * kPfTileRows;
+      full = in_b ? j0 + kPfTileRows - 1 <= (i0 < a.C - 1 ? i0 : a.C - 1) && j0 + kPfTileRows - 1 < a.sink_b
+                  : j0 + kPfTileRows - 1 <= nA - 1 && (j0 + kPfTileRows - 1 < a.ns || j0 >= a.lo0 + i0 + 31);
     }
-    lds_char* kt = lds + STAGE * kPfStageBytes;
-    f32x16 s[2];
-    bf16x8 pb[2][2];
-    pf_scores(kt, lc, qf, s);
-    uint32_t seen[2];
-    {
+    // per lane: row visible iff row <= hi and (row < sk or row >= lo), rows relative to the tile; hidden scores become kNegBig as
+    // bit operations (comparisons and selects per element became branches, 83 -> 77 us a launch)
+    auto mask = [&](f32x16& s0, f32x16& s1) __attribute__((always_inline)) {
+      const int my_i = i0 + (formed_here(lane) & 31), hl = formed_here(lane) >> 5;
+      const int hi = (in_b ? (my_i < a.C - 1 ? my_i : a.C - 1) : nA - 1) - j0;
+      const int sk = (in_b ? a.sink_b : a.ns) - j0;
+      const int lo = (in_b ? my_i - a.n_recent + 1 : a.lo0 + my_i) - j0;
       const uint64_t rows = (pf_rows_below(hi + 1) & (pf_rows_below(sk) | ~pf_rows_below(lo))) >> (4 * hl);
-      seen[0] = (uint32_t)rows;
-      seen[1] = (uint32_t)(rows >> 32);
+      const uint32_t seen[2] = {(uint32_t)rows, (uint32_t)(rows >> 32)};
+#pragma unroll
+      for (int sb = 0; sb < 2; ++sb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          f32x16& s = sb == 0 ? s0 : s1;
+          const uint32_t t = (uint32_t)__builtin_amdgcn_sbfe((int)seen[sb], 8 * (r >> 2) + (r & 3), 1);
+          s[r] = __uint_as_float((__float_as_uint(s[r]) & t) | (__float_as_uint(kNegBig) & ~t));
+        }
+    };
+    // K of visit v + 2 into the place of v's, V of v + 1 into that of v - 1's
+    auto at = [&](int i) __attribute__((always_inline)) {
+      set_m0(lds_wave + (i < 4 ? odd * kPfTileBytes : kPfStageBytes + (1 - odd) * kPfTileBytes) + (i & 3) * 1024);
+    };
+    auto load = [&](int i) __attribute__((always_inline)) { g2lds16_m0(i < 4 ? sk.base : sv.base, i < 4 ? sk.off[i] : sv.off[i & 3]); };
+    pf_tile4<NEXT>(lds + (1 - odd) * kPfTileBytes, lds + kPfStageBytes + odd * kPfTileBytes, lc, qf, s0, cur, nxt, st, c, !full, mask,
+                   at, load);
+    if (NEXT) {
+      go_on(sk, KPlane());
+      go_on(sv, VPlane());
     }
-    pf_softmax_window(s, st, c, !full, seen, pb);
-    pf_pv(kt + kPfTileBytes, lc, pb, st);
   };
   int v = 0;
-  for (; v + 1 < T; v += 2) {
-    step(v, std::integral_constant<int, 0>());
-    step(v + 1, std::integral_constant<int, 1>());
+  for (;;) {
+    if (v + 1 >= T) break;
+    step(v++, std::integral_constant<int, 0>(), std::true_type(), s1a, s1b);
+    if (v + 1 >= T) { s1a = s1b; break; }
+    step(v++, std::integral_constant<int, 1>(), std::true_type(), s1b, s1a);
   }
-  if (v < T) step(v, std::integral_constant<int, 0>());
+  step(v, v & 1, std::false_type(), s1a, s1b);
 
   pf_write_row(a.out, a.out_fp32, a.C, g, my_i, hl, st.o, st.l);
 }

@@ -894,7 +894,6 @@ struct GemvArgs {
   void* y;                                                            // kPjOut
 };
 
-typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 __device__ __forceinline__ uint4 gemv_load_stream(const uint16_t* p) {
   const u32x4 v = __builtin_nontemporal_load((const u32x4*)p);
   return make_uint4(v[0], v[1], v[2], v[3]);
