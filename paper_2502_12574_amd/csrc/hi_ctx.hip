@@ -727,13 +727,21 @@ static hi_status prefill_impl(hi_ctx* c, int32_t layer, int32_t kv_head, int32_t
     char* sv = stream_plane(c, layer, kv_head, 1);
     HI_TRY(prefetch_hint(c, next));
     if (run) {
+      // the rows ride on the attention launch, unless that is timed (the time is its alone) or would make its end wait for them
+      PrefillWindowUpdate update;
+      bool ride = !timed && window_update(G, chunk_len, past_len, c->prob.sink_tokens, c->prob.recent_tokens, &update);
+      if (ride && update.readers > 0) {
+        ride = can_tail(c, 1, nh);
+        update.counters = c->counters;
+      }
       TimedSpan sp;
       if (timed) HI_TRY(span_begin(c, 0, &sp));
       HI_TRY(launch_prefill_window(c->sc, q_dev, G, chunk_len, sk, sv, stream_head_stride(c), k_new_dev, v_new_dev,
                                    past_len, c->prob.sink_tokens, c->prob.recent_tokens, out_dev, c->prob.out_fp32, nh,
-                                   q_pre(c)));
+                                   q_pre(c), ride ? &update : nullptr, ride ? unit_end(c) : nullptr));
       if (timed) HI_TRY(span_end(c, sp));
       c->stats.n_prefill_kernels += 1;
+      if (ride) return HI_OK;
     }
     return launch_stream_store_update(c->sc, k_new_dev, v_new_dev, chunk_len, past_len, c->prob.sink_tokens,
                                       c->prob.recent_tokens, sk, sv, stream_head_stride(c), nh, unit_end(c));

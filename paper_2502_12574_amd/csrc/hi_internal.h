@@ -410,10 +410,14 @@ constexpr int64_t kStreamMaxRows = 1 << 22;
 // One chunk of such a head (a group of n_heads, their stores store_head_stride bytes apart): row past_len + i
 // sees key j iff j <= past_len + i and (j < n_sink or past_len + i - j < n_recent); the past comes from the
 // store, the chunk's own rows from k_new / v_new.  Layouts of q, k_new, v_new, out as in launch_prefill.
+// update: the launch takes the chunk's rows into the store itself (window_update says which, and whether it should: where the last
+// of a head's workgroups that read what the rows replace comes early; counters: one int per head if there are any).
+struct PrefillWindowUpdate { int cs, u0, cr, readers; int* counters; };
+bool window_update(int G, int chunk_len, int64_t past_len, int n_sink, int n_recent, PrefillWindowUpdate* w);
 hi_status launch_prefill_window(void* stream, const void* q, int G, int chunk_len, const void* store_k,
                                 const void* store_v, int64_t store_head_stride, const void* k_new, const void* v_new,
                                 int64_t past_len, int n_sink, int n_recent, void* out, int out_fp32, int n_heads,
-                                bool q_prescaled);
+                                bool q_prescaled, const PrefillWindowUpdate* update = nullptr, void* done = nullptr);
 // The chunk's rows enter the store (run it after the chunk's attention, on the same stream).
 hi_status launch_stream_store_update(void* stream, const void* k_new, const void* v_new, int chunk_len,
                                      int64_t past_len, int n_sink, int n_recent, void* store_k, void* store_v,

@@ -2029,7 +2029,25 @@ struct PrefillWindowArgs {
   int lo0;                // index in A of the first recent row visible to chunk row 0 (row i: lo0 + i); may be < ns
   int sink_b;             // chunk rows that are sink tokens: clamp(n_sink - P, 0, C)
   int64_t s_head_stride;  // bytes between the heads' stores
+  // The chunk's rows on their way into the store (update = 0: in a launch of their own, 4.2 us behind this one of 61): chunk rows [0, cs) to rows s0 .., rows u0 + i
+  // (i < cr) to ring slots (slot0 + i) mod n_recent.  The workgroups of a head's first `readers` strips read rows that these
+  // replace: the last of them to finish writes all the head's rows.  Without readers every workgroup writes its own.
+  int update, cs, s0, u0, cr, slot0, readers;
+  int* counters;          // one per head, zero between launches (readers > 0)
 };
+
+// Row u of the chunk, its 16-byte part `part` of K and of V, to its place in the store.
+__device__ __forceinline__ void pf_store_row(const PrefillWindowArgs& a, int u, int part) {
+  int dst = a.s0 + u;
+  if (u >= a.cs) {
+    dst = a.slot0 + (u - a.u0);
+    dst = a.n_sink + (dst >= a.n_recent ? dst - a.n_recent : dst);
+  }
+  const int64_t src = (int64_t)u * kRowBytes + part * 16, at = (int64_t)dst * kRowBytes + part * 16;
+  const uint4 k = *(const uint4*)(a.kb + src), v = *(const uint4*)(a.vb + src);
+  *(uint4*)((char*)a.ks + at) = k;
+  *(uint4*)((char*)a.vs + at) = v;
+}
 
 // Rows [0, n) of a tile as a bit mask.
 __device__ __forceinline__ uint64_t pf_rows_below(int n) { return n <= 0 ? 0 : n >= 64 ? ~0ull : (1ull << n) - 1; }
@@ -2054,9 +2072,12 @@ __global__ __launch_bounds__(256, 2) void prefill_window_kernel(PrefillWindowArg
 
   const int gl = a.G < 4 ? a.G : 4;
   const int strip = 32 * (4 / gl);
-  // neighbouring blocks of positions read the same rows: let them share an XCD's L2
-  const int bx = pf_wg_index(blockIdx.x, gridDim.x, gridDim.x % 8 == 0);
-  const int head = blockIdx.y / a.gy;
+  // neighbouring blocks of positions read the same rows: let them share an XCD's L2 (the numbering runs over all heads, so that
+  // the strips that read the store, a head's first ones, come early everywhere)
+  const int n_wgs = gridDim.x * gridDim.y;
+  const int wg = pf_wg_index(blockIdx.y * gridDim.x + blockIdx.x, n_wgs, n_wgs % 8 == 0);
+  const int by = wg / (int)gridDim.x, bx = wg - by * (int)gridDim.x;
+  const int head = by / a.gy;
   {  // group launches: this workgroup's head
     const int64_t rows = (int64_t)head * a.C;
     a.q += rows * a.G * kHeadDim;
@@ -2066,7 +2087,7 @@ __global__ __launch_bounds__(256, 2) void prefill_window_kernel(PrefillWindowArg
     a.kb += rows * kRowBytes;
     a.vb += rows * kRowBytes;
   }
-  const int g = (blockIdx.y - head * a.gy) * 4 + (wave % gl);
+  const int g = (by - head * a.gy) * 4 + (wave % gl);
   const int i_lo = bx * strip;                      // first and last query position of the workgroup
   const int i_hi = i_lo + strip - 1;
   const int i0 = i_lo + 32 * (wave / gl);           // first query position of this wave
@@ -2248,6 +2269,30 @@ __global__ __launch_bounds__(256, 2) void prefill_window_kernel(PrefillWindowArg
   step(v, v & 1, std::false_type(), s1a, s1b);
 
   pf_write_row(a.out, a.out_fp32, a.C, g, my_i, hl, st.o, st.l);
+  if (!a.update) return;
+  if (a.readers == 0) {                             // nobody reads what the rows replace
+    if (by != head * a.gy) return;
+    for (int j = threadIdx.x; j < strip * 16; j += 256) {
+      const int u = i_lo + (j >> 4);
+      if (u < a.cs || (u >= a.u0 && u < a.u0 + a.cr)) pf_store_row(a, u, j & 15);
+    }
+    return;
+  }
+  if (bx >= a.readers) return;
+  // every wavefront's last loads have landed (it waited for them in its last step); the counter orders nothing else
+  int* const flag = (int*)lds_raw;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    const int before = __hip_atomic_fetch_add(a.counters + head, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const int last = before == a.readers * a.gy - 1;
+    if (last) __hip_atomic_store(a.counters + head, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    *flag = last;
+  }
+  __syncthreads();
+  if (*flag == 0) return;
+  const int rows = a.cs + a.cr;
+#pragma unroll 4
+  for (int j = threadIdx.x; j < rows * 16; j += 256) pf_store_row(a, (j >> 4) < a.cs ? j >> 4 : a.u0 + (j >> 4) - a.cs, j & 15);
 }
 
 // The chunk's rows enter a streaming head's store (after the chunk's attention has read it): chunk rows that are
@@ -2421,10 +2466,26 @@ hi_status launch_prefill(void* stream, const void* q, int G, int chunk_len, cons
   return HI_OK;
 }
 
+// Which rows of a chunk enter a streaming head's store, and how many of the head's first strips of positions read rows that they
+// replace: ring rows, in the tiles of A behind the sink rows (or in the last sink rows' tile, which every strip visits).
+bool window_update(int G, int chunk_len, int64_t past_len, int n_sink, int n_recent, PrefillWindowUpdate* w) {
+  const int64_t P = past_len, t0 = P - n_recent + 1 > n_sink ? P - n_recent + 1 : n_sink;
+  const int64_t ns = P < n_sink ? P : n_sink, m = P > t0 ? P - t0 : 0, lo0 = P - n_recent - t0 + 1 + ns;
+  w->cs = (int)(n_sink > P ? (n_sink - P < chunk_len ? n_sink - P : chunk_len) : 0);
+  w->u0 = chunk_len - n_recent > w->cs ? chunk_len - n_recent : w->cs;
+  w->cr = chunk_len - w->u0;
+  w->counters = nullptr;
+  const int64_t strip = prefill_strip(G), strips = ceil_div(chunk_len, strip);
+  int64_t readers = m == 0 ? 0 : ns % kPfTileRows != 0 ? strips : ceil_div(kPfTileRows * ceil_div(ns + m, kPfTileRows) - lo0, strip);
+  if (readers < 0) readers = 0;
+  w->readers = (int)(readers < strips ? readers : strips);
+  return 2 * w->readers <= strips;
+}
+
 hi_status launch_prefill_window(void* stream, const void* q, int G, int chunk_len, const void* store_k,
                                 const void* store_v, int64_t store_head_stride, const void* k_new, const void* v_new,
                                 int64_t past_len, int n_sink, int n_recent, void* out, int out_fp32, int n_heads,
-                                bool q_prescaled) {
+                                bool q_prescaled, const PrefillWindowUpdate* update, void* done) {
   if (n_heads < 1 || chunk_len < 1 || !(G == 1 || G == 2 || G == 4 || G == 8) || past_len < 0 || n_sink < 0 ||
       n_recent < 1 || (int64_t)n_sink + n_recent > kStreamMaxRows) {
     set_last_error("windowed prefill launch: bad shape");
@@ -2447,8 +2508,15 @@ hi_status launch_prefill_window(void* stream, const void* q, int G, int chunk_le
   a.lo0 = (int)(P - n_recent - t0 + 1) + a.ns;       // token P - n_recent + 1 as an index into A
   a.sink_b = (int)(n_sink > P ? (n_sink - P < chunk_len ? n_sink - P : chunk_len) : 0);
   a.s_head_stride = store_head_stride;
+  a.update = update != nullptr;
+  if (update) {
+    a.cs = update->cs; a.s0 = (int)P; a.u0 = update->u0; a.cr = update->cr; a.readers = update->readers;
+    a.slot0 = a.cr > 0 ? (int)((P + a.u0 - n_sink) % n_recent) : 0;
+    a.counters = update->counters;
+    if (a.readers > 0 && !a.counters) { set_last_error("windowed prefill launch: no counters"); return HI_ERR_ARG; }
+  }
   dim3 grid((unsigned)ceil_div(chunk_len, prefill_strip(G)), (unsigned)(a.gy * n_heads));
-  hipLaunchKernelGGL(prefill_window_kernel, grid, dim3(kWgThreads), 0, (hipStream_t)stream, a);
+  launch_kernel(prefill_window_kernel, grid, dim3(kWgThreads), 0, stream, done, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) { set_last_error("windowed prefill launch: %s", hipGetErrorString(e)); return HI_ERR_HIP; }
   return HI_OK;
