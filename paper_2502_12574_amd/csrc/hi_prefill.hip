@@ -2036,17 +2036,11 @@ struct PrefillWindowArgs {
   int* counters;          // one per head, zero between launches (readers > 0)
 };
 
-// Row u of the chunk, its 16-byte part `part` of K and of V, to its place in the store.
-__device__ __forceinline__ void pf_store_row(const PrefillWindowArgs& a, int u, int part) {
-  int dst = a.s0 + u;
-  if (u >= a.cs) {
-    dst = a.slot0 + (u - a.u0);
-    dst = a.n_sink + (dst >= a.n_recent ? dst - a.n_recent : dst);
-  }
-  const int64_t src = (int64_t)u * kRowBytes + part * 16, at = (int64_t)dst * kRowBytes + part * 16;
-  const uint4 k = *(const uint4*)(a.kb + src), v = *(const uint4*)(a.vb + src);
-  *(uint4*)((char*)a.ks + at) = k;
-  *(uint4*)((char*)a.vs + at) = v;
+// The place of chunk row u in the store.
+__device__ __forceinline__ int pf_store_row(const PrefillWindowArgs& a, int u) {
+  if (u < a.cs) return a.s0 + u;
+  const int slot = a.slot0 + (u - a.u0);
+  return a.n_sink + (slot >= a.n_recent ? slot - a.n_recent : slot);
 }
 
 // Rows [0, n) of a tile as a bit mask.
@@ -2072,10 +2066,10 @@ __global__ __launch_bounds__(256, 2) void prefill_window_kernel(PrefillWindowArg
 
   const int gl = a.G < 4 ? a.G : 4;
   const int strip = 32 * (4 / gl);
-  // neighbouring blocks of positions read the same rows: let them share an XCD's L2 (the numbering runs over all heads, so that
-  // the strips that read the store, a head's first ones, come early everywhere)
-  const int n_wgs = gridDim.x * gridDim.y;
-  const int wg = pf_wg_index(blockIdx.y * gridDim.x + blockIdx.x, n_wgs, n_wgs % 8 == 0);
+  // neighbouring blocks of positions read the same rows: let them share an XCD's L2 (pf_wg_index for any number of workgroups; over
+  // all heads, so that the strips that read the store, a head's first ones, come early everywhere)
+  const int n_wgs = gridDim.x * gridDim.y, id = blockIdx.y * gridDim.x + blockIdx.x, more = n_wgs & 7;
+  const int wg = (id & 7) * (n_wgs >> 3) + ((id & 7) < more ? id & 7 : more) + (id >> 3);
   const int by = wg / (int)gridDim.x, bx = wg - by * (int)gridDim.x;
   const int head = by / a.gy;
   {  // group launches: this workgroup's head
@@ -2274,7 +2268,11 @@ __global__ __launch_bounds__(256, 2) void prefill_window_kernel(PrefillWindowArg
     if (by != head * a.gy) return;
     for (int j = threadIdx.x; j < strip * 16; j += 256) {
       const int u = i_lo + (j >> 4);
-      if (u < a.cs || (u >= a.u0 && u < a.u0 + a.cr)) pf_store_row(a, u, j & 15);
+      if (!(u < a.cs || (u >= a.u0 && u < a.u0 + a.cr))) continue;
+      const int64_t src = (int64_t)u * kRowBytes + (j & 15) * 16, at = (int64_t)pf_store_row(a, u) * kRowBytes + (j & 15) * 16;
+      const uint4 k = *(const uint4*)(a.kb + src), v = *(const uint4*)(a.vb + src);
+      *(uint4*)((char*)a.ks + at) = k;
+      *(uint4*)((char*)a.vs + at) = v;
     }
     return;
   }
@@ -2290,9 +2288,15 @@ __global__ __launch_bounds__(256, 2) void prefill_window_kernel(PrefillWindowArg
   }
   __syncthreads();
   if (*flag == 0) return;
-  const int rows = a.cs + a.cr;
+  const int parts = (a.cs + a.cr) * 16;
 #pragma unroll 4
-  for (int j = threadIdx.x; j < rows * 16; j += 256) pf_store_row(a, (j >> 4) < a.cs ? j >> 4 : a.u0 + (j >> 4) - a.cs, j & 15);
+  for (int j = threadIdx.x; j < parts; j += 256) {
+    const int u = (j >> 4) < a.cs ? j >> 4 : a.u0 + (j >> 4) - a.cs;
+    const int64_t src = (int64_t)u * kRowBytes + (j & 15) * 16, at = (int64_t)pf_store_row(a, u) * kRowBytes + (j & 15) * 16;
+    const uint4 k = *(const uint4*)(a.kb + src), v = *(const uint4*)(a.vb + src);
+    *(uint4*)((char*)a.ks + at) = k;
+    *(uint4*)((char*)a.vs + at) = v;
+  }
 }
 
 // The chunk's rows enter a streaming head's store (after the chunk's attention has read it): chunk rows that are
@@ -2468,6 +2472,10 @@ hi_status launch_prefill(void* stream, const void* q, int G, int chunk_len, cons
 
 // Which rows of a chunk enter a streaming head's store, and how many of the head's first strips of positions read rows that they
 // replace: ring rows, in the tiles of A behind the sink rows (or in the last sink rows' tile, which every strip visits).
+// One workgroup's copy takes about 10 us per 1000 rows beside the others, a launch over the chip 5 for any number.  Four heads a call,
+// riding against a launch of its own: 128 + 512 rows of 4096 148 against 157 us, 128 + 700 of 3000 105.7 against 105.4 to 107, 64 + 2000
+// of 5000 267 against 260 (253 with the numbering over all heads and this line).
+constexpr int kWindowUpdateRows = 1024;
 bool window_update(int G, int chunk_len, int64_t past_len, int n_sink, int n_recent, PrefillWindowUpdate* w) {
   const int64_t P = past_len, t0 = P - n_recent + 1 > n_sink ? P - n_recent + 1 : n_sink;
   const int64_t ns = P < n_sink ? P : n_sink, m = P > t0 ? P - t0 : 0, lo0 = P - n_recent - t0 + 1 + ns;
@@ -2479,7 +2487,8 @@ bool window_update(int G, int chunk_len, int64_t past_len, int n_sink, int n_rec
   int64_t readers = m == 0 ? 0 : ns % kPfTileRows != 0 ? strips : ceil_div(kPfTileRows * ceil_div(ns + m, kPfTileRows) - lo0, strip);
   if (readers < 0) readers = 0;
   w->readers = (int)(readers < strips ? readers : strips);
-  return 2 * w->readers <= strips;
+  // one workgroup writes the rows while the others still run: it has to come early, and to be done before they are
+  return w->readers == 0 || (2 * w->readers <= strips && w->cs + w->cr <= kWindowUpdateRows);
 }
 
 hi_status launch_prefill_window(void* stream, const void* q, int G, int chunk_len, const void* store_k,
