@@ -339,28 +339,6 @@ __device__ __forceinline__ void pf_softmax_fast(f32x16 (&s)[2], PfState& st, flo
     for (int u = 0; u < 2; ++u) asm volatile("" : "+v"(pb[sb][u]));
 }
 
-// O^T += V^T P^T for one 64-row V tile at vt: contraction index 8*hl + j of MFMA (sb,u) is tile row
-// 32*sb + 16*u + 8*(j/4) + 4*hl + j%4.
-__device__ __forceinline__ void pf_pv(lds_char* vt, const PfLaneConst& lc, const bf16x8 (&pb)[2][2], PfState& st) {
-  constexpr int A = kPf4AheadV;
-  bf16x8 op[A + 1];
-  auto read = [&](int i) __attribute__((always_inline)) {           // MFMA i: dim block i % 4, contraction group i / 4
-    lds_char* p = vt + lc.voff[i & 3] + (i >> 2) * 4096;
-    const bf16x4 v0 = lds_read_tr8(p), v1 = lds_read_tr8(p + 2048);
-    return (bf16x8)__builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7);
-  };
-  __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-  for (int i = 0; i < A; ++i) op[i] = read(i);
-  __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    if (i + A < 16) op[(i + A) % (A + 1)] = read(i + A);
-    st.o[i & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op[i % (A + 1)], pb[i >> 3][(i >> 2) & 1], st.o[i & 3], 0, 0, 0);
-    __builtin_amdgcn_sched_barrier(0);
-  }
-}
-
 // One tile of a 4-wave kernel, the next tile's scores one step ahead: the wavefront's vector ALU works on the softmax of the tile
 // whose scores are in s0 (rows 0..31) and s1 while its matrix pipe forms those of the tile behind it (K tile at kt; NEXT = false:
 // there is none), and the second half of the exponentials goes between the first MFMAs of O^T += V^T P^T (V tile at vt).  The next
@@ -587,16 +565,14 @@ __device__ __forceinline__ PfLaneConst pf_lane_const_4w(int wave, int lane) {
   return lc;
 }
 
-// One 64-row tile out of the LDS stage starting at kt, straight through.
-__device__ __forceinline__ void pf_compute_tile(lds_char* kt, const PfLaneConst& lc, const bf16x8 (&qf)[8],
-                                                PfState& st, float c, bool masked, int mask_rel, int hl) {
-  f32x16 s[2];
-  bf16x8 pb[2][2];
-  pf_scores(kt, lc, qf, s);
-  pf_softmax(s, st, c, masked, mask_rel, hl, pb);
-  pf_pv(kt + kPfTileBytes, lc, pb, st);
-}
+// Rows [0, n) of a tile as a bit mask.
+__device__ __forceinline__ uint64_t pf_rows_below(int n) { return n <= 0 ? 0 : n >= 64 ? ~0ull : (1ull << n) - 1; }
 
+// The 4-wave kernel: short chunks, and units of few workgroups.  One wavefront or two on a SIMD, so what bounds it is a wavefront's own
+// chain: matrix phase, softmax, matrix phase of one tile after the other.  The scores are formed one visit ahead (pf_tile4; K and V
+// tiles have two places each in LDS, the loads are streams), straight through before: 1239 rows of 6 heads of 4 queries 31 -> 27 us,
+// 1500 of one head of 2 behind 395 42.1 -> 35.3, 1000 of 8 heads of 4 27.2 -> 24.2, 204 of one 9.0 -> 8.5; ranges of 5 to 7 tiles
+// (276 rows of 2 heads behind 3111) the same 13.5, two workgroups on every compute unit (2 rows behind 88778) the same 68.6.
 // SPLIT: a.split workgroups per block of positions, each on its range of the unit's tiles (pf_narrow_range) with a state
 // image of its own, merged after the last launch (prefill_merge4_kernel).
 template <bool SPLIT>
@@ -625,11 +601,12 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(PrefillArgs a) {
     if (r.lo >= r.hi) return;
     fresh = r.fresh != 0;
     image = (int64_t)blockIdx.y * a.img_row + k * blocks + bx;
-    a0 = r.lo - a.tile0;
-    b0 = r.lo > a.past_tiles ? r.lo - a.past_tiles : 0;
-    ta_range = (r.hi < a.past_tiles ? r.hi : a.past_tiles) - r.lo;
+    const int lo = __builtin_amdgcn_readfirstlane(r.lo), hi = __builtin_amdgcn_readfirstlane(r.hi);
+    a0 = lo - a.tile0;
+    b0 = lo > a.past_tiles ? lo - a.past_tiles : 0;
+    ta_range = (hi < a.past_tiles ? hi : a.past_tiles) - lo;
     if (ta_range < 0) ta_range = 0;
-    t_range = r.hi - r.lo;
+    t_range = hi - lo;
   }
   const int g = pf_select_head(a) * 4 + (wave % gl);
   const int i0 = bx * strip + 32 * (wave / gl);     // first query position of this wave
@@ -647,6 +624,63 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(PrefillArgs a) {
 #pragma unroll
     for (int kk = 0; kk < 8; ++kk) qf[kk] = __builtin_bit_cast(bf16x8, *(const uint4*)(qrow + 16 * kk));
   }
+
+  // tiles: segment A (all of it), then the part of segment B at or below the workgroup's causal boundary
+  const int na = (int)a.na, nb = (int)a.nb;         // (a 64-bit comparison would put all that follows from it into vector registers)
+  const int nb_vis = nb < i_hi + 1 ? nb : i_hi + 1;
+  const int ta = SPLIT ? ta_range : na / kPfTileRows + (na % kPfTileRows != 0);
+  const int T = SPLIT ? t_range : ta + (nb_vis + kPfTileRows - 1) / kPfTileRows;     // >= 1
+  const int wholeA = na / kPfTileRows, wholeB = nb / kPfTileRows;                    // full tiles of the segments
+
+  // The loads of K tiles, and of V tiles, as two streams (as in prefill_window_kernel): visit v's rows lie at `base`, off[] are the
+  // lane's byte offsets behind it (those of 64 rows if `usual`), up to visit `until` the next tile is the next 16 KiB.
+  struct Stream { const char* base; int v, until, usual; uint32_t off[4]; };
+  auto meet = [&](Stream& w, auto v_tag) __attribute__((always_inline)) {
+    constexpr bool VP = decltype(v_tag)::value;
+    const int here = formed_here(lane), r_in = here >> 4, cpos = here & 15;
+    const bool in_b = w.v >= ta;
+    const int tile = in_b ? b0 + w.v - ta : a0 + w.v, whole = in_b ? wholeB : wholeA;
+    const bool jumped = SPLIT && !in_b && a.a_jump_tile > 0 && tile >= a.a_jump_tile;
+    const bool usual = tile < whole;
+    int end = whole;                              // the run of tiles that follow each other
+    if (SPLIT && !in_b && a.a_jump_tile > 0 && !jumped && a.a_jump_tile < end) end = a.a_jump_tile;
+    w.until = w.v + (usual ? end - tile : 1);
+    if (!in_b && w.until > ta) w.until = ta;
+    w.base = (in_b ? (VP ? a.vb : a.kb) : (VP ? a.va : a.ka)) + (int64_t)tile * kPfTileBytes;
+    if (jumped) w.base += a.a_jump_bytes;
+    if (usual && w.usual) return;
+    w.usual = usual;
+    const int rows = usual ? kPfTileRows : (in_b ? nb : na) - tile * kPfTileRows;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int r = (wave * 4 + i) * 4 + r_in;
+      w.off[i] = (uint32_t)(r < rows ? r : rows - 1) * kRowBytes + ((cpos ^ (VP ? swz_v(r) : swz_k(r))) << 4);
+    }
+  };
+  using KPlane = std::false_type;
+  using VPlane = std::true_type;
+  auto go_on = [&](Stream& w, auto v_tag) __attribute__((always_inline)) {
+    w.base += kPfTileBytes;
+    if (++w.v != w.until) return;
+    if (w.v < T) { meet(w, v_tag); return; }
+    w.base -= kPfTileBytes;      // behind the last visit: its rows again, which nobody reads
+    w.until = w.v + 1;
+  };
+  const uint32_t lds_wave = lds_base + wave * 4096;
+  auto issue = [&](const Stream& w, uint32_t slot) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) g2lds16_s<0>(w.base, w.off[i], lds_wave + slot + i * 1024);
+  };
+  Stream sk, sv;
+  sk.v = sv.v = sk.usual = sv.usual = 0;
+  meet(sk, KPlane());
+  meet(sv, VPlane());
+  issue(sk, 0);
+  issue(sv, kPfStageBytes);
+  go_on(sk, KPlane());
+  go_on(sv, VPlane());
+  issue(sk, kPfTileBytes);
+  go_on(sk, KPlane());
 
   PfState st;
   float* carry = a.carry + image * (kCarryFloatsPerLane * kWgThreads) + threadIdx.x;
@@ -672,57 +706,65 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(PrefillArgs a) {
 #pragma unroll
   for (int db = 0; db < 4; ++db) asm volatile("" : "+v"(st.o[db]));
 
-  // tiles: segment A (all of it), then the part of segment B at or below the workgroup's causal boundary
-  const int64_t nb_vis = a.nb < (int64_t)i_hi + 1 ? a.nb : (int64_t)i_hi + 1;
-  const int ta = SPLIT ? ta_range : (int)((a.na + kPfTileRows - 1) / kPfTileRows);
-  const int T = SPLIT ? t_range : ta + (int)((nb_vis + kPfTileRows - 1) / kPfTileRows);
-
-  auto issue = [&](int t) {
-    const uint32_t stage = lds_base + (uint32_t)(t & (kPfStages - 1)) * kPfStageBytes;
-    if (t < ta) {
-      const int64_t row0 = (int64_t)(a0 + t) * kPfTileRows;
-      const int64_t left = a.na - row0;
-      const int64_t at = row0 * kRowBytes + (SPLIT && a.a_jump_tile > 0 && a0 + t >= a.a_jump_tile ? a.a_jump_bytes : 0);
-      pf_issue_tile<4>(a.ka + at, a.va + at, left < kPfTileRows ? (int)left : kPfTileRows, stage, wave, lane, lc);
-    } else {
-      const int64_t row0 = (int64_t)(b0 + t - ta) * kPfTileRows;
-      const int64_t left = a.nb - row0;
-      pf_issue_tile<4>(a.kb + row0 * kRowBytes, a.vb + row0 * kRowBytes, left < kPfTileRows ? (int)left : kPfTileRows,
-                       stage, wave, lane, lc);
-    }
-  };
-
-  if (T > 0) issue(0);
-
   const float c = a.c;
-  // one tile: wait for it, let everybody see it (and be done with the previous one), refill the freed stage,
-  // compute.  The loop is unrolled by the two LDS stages so every LDS address is an immediate and the
-  // accumulators never meet at a control-flow join inside the loop.
-  auto step = [&](int t, auto stage_tag) {
-    constexpr int STAGE = decltype(stage_tag)::value;
+  f32x16 s0, s1a, s1b;         // scores of a visit's rows 0..31, and of its rows 32..63 (even and odd visits)
+  wait_vmcnt<0>();
+  __syncthreads();
+  {
+    f32x16 s[2];
+    pf_scores(lds, lc, qf, s);
+    s0 = s[0];
+    s1a = s[1];
+  }
+  // visits [0, openA) and [ta, openB) show all their rows to every query row of this wave: the others are a segment's last rows, or
+  // own rows behind a query's position
+  const int openA = wholeA - a0 < ta ? wholeA - a0 : ta;
+  const int openB = ta + ((i0 + 1) / kPfTileRows < wholeB ? (i0 + 1) / kPfTileRows : wholeB) - b0;
+  // Visit v: its weights and sums, and the scores of visit v + 1.  On entry both of v + 1's K rows and v's V rows are on their way;
+  // behind the barrier everybody is done with the K tile of v and the V tile of v - 1, whose places take the next ones.
+  auto step = [&](int v, auto parity, auto more, f32x16& cur, f32x16& nxt) __attribute__((always_inline)) {
+    const int odd = parity;
+    constexpr bool NEXT = decltype(more)::value;
     wait_vmcnt<0>();
     __syncthreads();
-    if (t + 1 < T) issue(t + 1);
-    // masks: rows past the end of the segment, and (chunk's own rows) rows after the query's position
-    const bool in_b = t >= ta;
-    const int64_t j0 = (int64_t)(in_b ? (b0 + t - ta) : a0 + t) * kPfTileRows;
-    const int64_t n_seg = in_b ? a.nb : a.na;
-    const bool masked = (j0 + kPfTileRows > n_seg) || (in_b && (j0 + kPfTileRows - 1 > i0));
-    int rel = kPfTileRows;
-    if (masked) {
-      int64_t lim = n_seg - 1;                       // last visible row index
-      if (in_b && (int64_t)my_i < lim) lim = my_i;
-      const int64_t d = lim - j0;
-      rel = d < -1 ? -1 : (d > kPfTileRows ? kPfTileRows : (int)d);
+    const bool masked = !(v < openA || (v >= ta && v < openB));
+    // hidden scores become kNegBig as bit operations (see prefill_window_kernel)
+    auto mask = [&](f32x16& s0, f32x16& s1) __attribute__((always_inline)) {
+      const int my_i = i0 + (formed_here(lane) & 31), hl = formed_here(lane) >> 5;
+      const bool in_b = v >= ta;
+      const int j0 = (in_b ? b0 + v - ta : a0 + v) * kPfTileRows;
+      const int end = (in_b ? nb : na) - j0, own = in_b ? my_i + 1 - j0 : kPfTileRows;
+      const uint64_t rows = pf_rows_below(end < own ? end : own) >> (4 * hl);
+      const uint32_t seen[2] = {(uint32_t)rows, (uint32_t)(rows >> 32)};
+#pragma unroll
+      for (int sb = 0; sb < 2; ++sb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          f32x16& s = sb == 0 ? s0 : s1;
+          const uint32_t t = (uint32_t)__builtin_amdgcn_sbfe((int)seen[sb], 8 * (r >> 2) + (r & 3), 1);
+          s[r] = __uint_as_float((__float_as_uint(s[r]) & t) | (__float_as_uint(kNegBig) & ~t));
+        }
+    };
+    // K of visit v + 2 into the place of v's, V of v + 1 into that of v - 1's
+    auto at = [&](int i) __attribute__((always_inline)) {
+      set_m0(lds_wave + (i < 4 ? odd * kPfTileBytes : kPfStageBytes + (1 - odd) * kPfTileBytes) + (i & 3) * 1024);
+    };
+    auto load = [&](int i) __attribute__((always_inline)) { g2lds16_m0(i < 4 ? sk.base : sv.base, i < 4 ? sk.off[i] : sv.off[i & 3]); };
+    pf_tile4<NEXT>(lds + (1 - odd) * kPfTileBytes, lds + kPfStageBytes + odd * kPfTileBytes, lc, qf, s0, cur, nxt, st, c, masked, mask,
+                   at, load);
+    if (NEXT) {
+      go_on(sk, KPlane());
+      go_on(sv, VPlane());
     }
-    pf_compute_tile(lds + STAGE * kPfStageBytes, lc, qf, st, c, masked, rel, hl);
   };
-  int t = 0;
-  for (; t + 1 < T; t += 2) {
-    step(t, std::integral_constant<int, 0>());
-    step(t + 1, std::integral_constant<int, 1>());
+  int v = 0;
+  for (;;) {
+    if (v + 1 >= T) break;
+    step(v++, std::integral_constant<int, 0>(), std::true_type(), s1a, s1b);
+    if (v + 1 >= T) { s1a = s1b; break; }
+    step(v++, std::integral_constant<int, 1>(), std::true_type(), s1b, s1a);
   }
-  if (t < T) step(t, std::integral_constant<int, 0>());
+  step(v, v & 1, std::false_type(), s1a, s1b);
 
   if (SPLIT || !a.last) {
 #pragma unroll
@@ -2043,9 +2085,6 @@ __device__ __forceinline__ int pf_store_row(const PrefillWindowArgs& a, int u) {
   return a.n_sink + (slot >= a.n_recent ? slot - a.n_recent : slot);
 }
 
-// Rows [0, n) of a tile as a bit mask.
-__device__ __forceinline__ uint64_t pf_rows_below(int n) { return n <= 0 ? 0 : n >= 64 ? ~0ull : (1ull << n) - 1; }
-
 // A launch over 4 heads x 8192 rows (1024 workgroups, two rounds of two per compute unit, 11 tiles each) keeps one of a SIMD's two
 // pipes at work nearly all the time: 56 % of the cycles the vector ALU, 41 % the matrix pipe.  The scores of a visit are formed
 // under the softmax of the one before it (pf_tile4), two K and two V tiles have places in LDS, and the loads are streams that
@@ -2470,12 +2509,13 @@ hi_status launch_prefill(void* stream, const void* q, int G, int chunk_len, cons
   return HI_OK;
 }
 
-// Which rows of a chunk enter a streaming head's store, and how many of the head's first strips of positions read rows that they
-// replace: ring rows, in the tiles of A behind the sink rows (or in the last sink rows' tile, which every strip visits).
 // One workgroup's copy takes about 10 us per 1000 rows beside the others, a launch over the chip 5 for any number.  Four heads a call,
 // riding against a launch of its own: 128 + 512 rows of 4096 148 against 157 us, 128 + 700 of 3000 105.7 against 105.4 to 107, 64 + 2000
 // of 5000 267 against 260 (253 with the numbering over all heads and this line).
 constexpr int kWindowUpdateRows = 1024;
+
+// Which rows of a chunk enter a streaming head's store, and how many of the head's first strips of positions read rows that they
+// replace: ring rows, in the tiles of A behind the sink rows (or in the last sink rows' tile, which every strip visits).
 bool window_update(int G, int chunk_len, int64_t past_len, int n_sink, int n_recent, PrefillWindowUpdate* w) {
   const int64_t P = past_len, t0 = P - n_recent + 1 > n_sink ? P - n_recent + 1 : n_sink;
   const int64_t ns = P < n_sink ? P : n_sink, m = P > t0 ? P - t0 : 0, lo0 = P - n_recent - t0 + 1 + ns;
