@@ -312,7 +312,7 @@ int pf_variant(const hi_ctx* c) {
 // context has counters for it.  What that saves is the second launch, 2.5 us of host time, which is what bounds a token at
 // short contexts (32 layers of 8 heads at 1K: 13.6 us a layer against 16.6); on the GPU it is 8.4 us against 5.6 + 3.9.
 // With 32 partitions the last workgroup alone takes 6.4 us where the combine kernel, spread over the chip, takes 4; between
-// 16 and 32 one launch was not timed (a call over 8 heads of 1024 rows takes 11.8 us, of 1025 with its second launch 14.0).
+// 16 and 32 one launch was not timed.
 // A captured step keeps the second launch: a graph may outlive the context, and then its launches must hold no memory but
 // the caller's.
 bool can_tail(hi_ctx* c, int np, int nh) {
