@@ -1500,12 +1500,11 @@ __device__ __forceinline__ void pd16_pass(const PrefillArgs& a, const PfPass& ps
   }
 
   // Q^T operands: lane holds q[g][qi[qb]][32*kk + 8*g16 .. +7]
-  int my_i[NS];
+  const int my_i = i0 + c16;           // of the first query row; the second one is `step` behind
   bf16x8 qf[4][NS];
 #pragma unroll
   for (int qb = 0; qb < NQ; ++qb) {
-    my_i[qb] = i0 + step * qb + c16;
-    const int qi = my_i[qb] > a.C - 1 ? a.C - 1 : my_i[qb];
+    const int qi = my_i + step * qb > a.C - 1 ? a.C - 1 : my_i + step * qb;
     const uint16_t* qrow = a.q + ((int64_t)g * a.C + qi) * kHeadDim + 8 * g16;
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) qf[kk][qb] = __builtin_bit_cast(bf16x8, *(const uint4*)(qrow + 32 * kk));
@@ -1561,7 +1560,7 @@ __device__ __forceinline__ void pd16_pass(const PrefillArgs& a, const PfPass& ps
     for (int qb = 0; qb < NQ; ++qb) {
       int lim = pf_tile_rows(sw, t) - 1;
       if (t >= sw.ta) {
-        const int d = my_i[qb] - (t + sw.own0) * kPfTileRows;
+        const int d = my_i + (step * qb - (t + sw.own0) * kPfTileRows);
         lim = d < lim ? d : lim;
       }
       rel[qb] = lim;
@@ -1747,7 +1746,7 @@ __device__ __forceinline__ void pd16_pass(const PrefillArgs& a, const PfPass& ps
       f32x4 rows[8];
 #pragma unroll
       for (int db = 0; db < 8; ++db) rows[db] = q4_get(st.o[(NQ * db + qb) >> 2], (NQ * db + qb) & 3);
-      pf16_write_row<8>(a.out, a.out_fp32, a.C, g, my_i[qb], g16, 0, rows, st.l[qb]);
+      pf16_write_row<8>(a.out, a.out_fp32, a.C, g, my_i + step * qb, g16, 0, rows, st.l[qb]);
     }
   }
 }
