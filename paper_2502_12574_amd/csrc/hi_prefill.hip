@@ -49,7 +49,6 @@ struct PrefillArgs {
   int64_t a_head_stride;  // bytes between the heads' rows in the past segment
   int paired;             // 8-wave kernel: deep and shallow blocks of the causal triangle share their tiles
   int nbk;                // 8-wave kernel: blocks of positions per head
-  int strip;              // prefill_kernel_deep16: positions of a block
   int img_row;            // state images per grid row (8-wave kernel; 4-wave kernel with split > 1)
   int xcd;                // see pf_wg_index
   int tile0, past_tiles;  // 4-wave kernel with split > 1: first tile of the past segment in the unit, past tiles of the unit
@@ -75,7 +74,6 @@ __device__ __forceinline__ int pf_select_head(PrefillArgs& a) {
 __host__ __device__ __forceinline__ PfShape pf_shape_of(const PrefillArgs& a, int strip) {
   PfShape sh;
   sh.nbk = a.nbk; sh.m = strip / kPfTileRows;
-  sh.strip = strip;
   sh.ta = (int)((a.na + kPfTileRows - 1) / kPfTileRows);
   sh.tb_all = (int)((a.nb + kPfTileRows - 1) / kPfTileRows);
   sh.split = a.split; sh.paired = a.paired; sh.carried = !a.first;
@@ -1386,18 +1384,13 @@ __device__ __forceinline__ void pf16_write_row(void* out, int out_fp32, int C, i
   }
 }
 
-// Where the wavefront's two blocks of 16 query rows lie in a block of a.strip positions: next to each other where the block is
-// full (the layout prefill_kernel_wide shares); with fewer positions every wavefront's first block comes before any second one,
-// so that both groups have work.  NQ of them are there (before the end of the block and of the chunk).
-struct Pf16Rows { int i0, step, nq; };
+// The wavefront's two blocks of 16 query rows in block bx of positions: the first position, and how many of the two hold rows
+// before the chunk's end.
+struct Pf16Rows { int i0, nq; };
 __device__ __forceinline__ Pf16Rows pf16_rows(const PrefillArgs& a, int bx, int gl, int wave) {
-  const int subs = kPdWaves / gl, sub = wave / gl;
-  const bool full = a.strip == 32 * subs;
   Pf16Rows r;
-  r.step = full ? 16 : 16 * subs;
-  r.i0 = bx * a.strip + (full ? 32 : 16) * sub;
-  const int end = (bx + 1) * a.strip < a.C ? (bx + 1) * a.strip : a.C;
-  r.nq = end - r.i0 > r.step ? 2 : end > r.i0 ? 1 : 0;
+  r.i0 = 32 * (bx * (kPdWaves / gl) + wave / gl);
+  r.nq = a.C - r.i0 > 16 ? 2 : a.C > r.i0 ? 1 : 0;
   return r;
 }
 
@@ -1415,7 +1408,7 @@ __device__ __forceinline__ Pf16Rows pf16_rows(const PrefillArgs& a, int bx, int 
 // launch, now 53 (shortest of 33; medians 59 and 55).
 template <bool PRESCALED, int NQ>
 __device__ __forceinline__ void pd16_pass(const PrefillArgs& a, const PfPass& ps, uint32_t lds_base, int lane,
-                                          int wave, int g, int pos, int i0, int step, float* images) {
+                                          int wave, int g, int pos, int i0, float* images) {
   constexpr int kLanes = kPdWaves * 64;
   constexpr int kImageFloats = kCarryFloatsPerLane * kLanes;
   constexpr int NS = NQ > 0 ? NQ : 1;                 // array sizes
@@ -1500,11 +1493,12 @@ __device__ __forceinline__ void pd16_pass(const PrefillArgs& a, const PfPass& ps
   }
 
   // Q^T operands: lane holds q[g][qi[qb]][32*kk + 8*g16 .. +7]
-  const int my_i = i0 + c16;           // of the first query row; the second one is `step` behind
+  int my_i[NS];
   bf16x8 qf[4][NS];
 #pragma unroll
   for (int qb = 0; qb < NQ; ++qb) {
-    const int qi = my_i + step * qb > a.C - 1 ? a.C - 1 : my_i + step * qb;
+    my_i[qb] = i0 + 16 * qb + c16;
+    const int qi = my_i[qb] > a.C - 1 ? a.C - 1 : my_i[qb];
     const uint16_t* qrow = a.q + ((int64_t)g * a.C + qi) * kHeadDim + 8 * g16;
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) qf[kk][qb] = __builtin_bit_cast(bf16x8, *(const uint4*)(qrow + 32 * kk));
@@ -1560,7 +1554,7 @@ __device__ __forceinline__ void pd16_pass(const PrefillArgs& a, const PfPass& ps
     for (int qb = 0; qb < NQ; ++qb) {
       int lim = pf_tile_rows(sw, t) - 1;
       if (t >= sw.ta) {
-        const int d = my_i + (step * qb - (t + sw.own0) * kPfTileRows);
+        const int d = my_i[qb] - (t + sw.own0) * kPfTileRows;
         lim = d < lim ? d : lim;
       }
       rel[qb] = lim;
@@ -1746,7 +1740,7 @@ __device__ __forceinline__ void pd16_pass(const PrefillArgs& a, const PfPass& ps
       f32x4 rows[8];
 #pragma unroll
       for (int db = 0; db < 8; ++db) rows[db] = q4_get(st.o[(NQ * db + qb) >> 2], (NQ * db + qb) & 3);
-      pf16_write_row<8>(a.out, a.out_fp32, a.C, g, my_i + step * qb, g16, 0, rows, st.l[qb]);
+      pf16_write_row<8>(a.out, a.out_fp32, a.C, g, my_i[qb], g16, 0, rows, st.l[qb]);
     }
   }
 }
@@ -1761,7 +1755,8 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel_deep16(PrefillArgs a) {
   const int gl = a.G < 4 ? a.G : 4;
   const int g = pf_select_head(a) * 4 + (wave % gl);
 
-  const PfShape sh = pf_shape_of(a, a.strip);
+  const int strip = 32 * (kPdWaves / gl);
+  const PfShape sh = pf_shape_of(a, strip);
   constexpr int kLanes = kPdWaves * 64;
   constexpr int kImageFloats = kCarryFloatsPerLane * kLanes;
   float* const images = a.carry + (int64_t)blockIdx.y * a.img_row * kImageFloats + threadIdx.x;
@@ -1791,9 +1786,9 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel_deep16(PrefillArgs a) {
     if (ps.run) {
       __syncthreads();               // the LDS rings are free again (a previous pass may still be reading V tiles)
       const Pf16Rows rows = pf16_rows(a, ps.bx, gl, wave);
-      if (rows.nq == 2) pd16_pass<PRESCALED, 2>(a, ps, lds_base, lane, wave, g, ps.bx * a.strip, rows.i0, rows.step, images);
-      else if (rows.nq == 1) pd16_pass<PRESCALED, 1>(a, ps, lds_base, lane, wave, g, ps.bx * a.strip, rows.i0, rows.step, images);
-      else pd16_pass<PRESCALED, 0>(a, ps, lds_base, lane, wave, g, ps.bx * a.strip, rows.i0, rows.step, images);
+      if (rows.nq == 2) pd16_pass<PRESCALED, 2>(a, ps, lds_base, lane, wave, g, ps.bx * strip, rows.i0, images);
+      else if (rows.nq == 1) pd16_pass<PRESCALED, 1>(a, ps, lds_base, lane, wave, g, ps.bx * strip, rows.i0, images);
+      else pd16_pass<PRESCALED, 0>(a, ps, lds_base, lane, wave, g, ps.bx * strip, rows.i0, images);
     }
     ps = other;
     other.run = other.init = 0;
@@ -1906,7 +1901,7 @@ __device__ __forceinline__ void pf16_merge(const PrefillArgs& a, const PfShape& 
 #pragma unroll
   for (int qb = 0; qb < NQ; ++qb) {
     const f32x4 rows[1] = {o[qb]};
-    pf16_write_row<1>(a.out, a.out_fp32, a.C, g, rows16.i0 + rows16.step * (qb0 + qb) + c16, g16, db, rows, l[qb]);
+    pf16_write_row<1>(a.out, a.out_fp32, a.C, g, rows16.i0 + 16 * (qb0 + qb) + c16, g16, db, rows, l[qb]);
   }
 }
 
@@ -1921,7 +1916,7 @@ __global__ __launch_bounds__(512, 4) void prefill_merge16_kernel(PrefillArgs a, 
   const int g = pf_select_head(a) * 4 + (wave % gl);
   const Pf16Rows rows16 = pf16_rows(a, bx, gl, wave);
   if (qb >= rows16.nq) return;              // rows past the end
-  const PfShape sh = pf_shape_of(a, a.strip);
+  const PfShape sh = pf_shape_of(a, 32 * (kPdWaves / gl));
   int n_e, n_x;
   pf_block_images(sh, bx, n_e, n_x);
   const int n = n_e + n_x;
@@ -2430,12 +2425,11 @@ hi_status launch_prefill(void* stream, const void* q, int G, int chunk_len, cons
   a.split = pl.split;
   a.paired = pl.paired;
   a.nbk = pl.nbk;
-  a.strip = pl.strip > 0 ? pl.strip : 2 * strip;
   a.img_row = pl.img_row;
   a.xcd = pl.xcd;
   a.by_split = a.by_nbk = 0;
   if (pl.deep) {
-    const PfShape sh = pf_shape_of(a, a.strip);
+    const PfShape sh = pf_shape_of(a, 2 * strip);
     a.by_split = pf_magic((uint32_t)pl.split, pf_largest_cut(sh));
     a.by_nbk = pf_magic((uint32_t)pl.nbk, (uint64_t)pl.nbk * (uint64_t)pl.split);
   }
@@ -2475,9 +2469,7 @@ hi_status launch_prefill(void* stream, const void* q, int G, int chunk_len, cons
     const bool mfma32 = (variant & 16) != 0;        // the 32x32x16 form of the kernel (its state images differ)
     // the 4-wave, 64-rows-per-wavefront form of the 16x16x32 kernel: for workgroups that sweep enough tiles to pay for its
     // slow straight-line ones (it gains about 3 % per steady-state tile and loses about 20 tiles' worth at the ends)
-    if (pl.strip > 0 && mfma32) { set_last_error("prefill launch: this kernel takes full blocks of positions"); return HI_ERR_UNSUPPORTED; }
     const bool wide = prefill_is_wide(variant, pl.split, sa.n + sb.n);
-    if (pl.strip > 0 && wide) { set_last_error("prefill launch: the wide form takes full blocks of positions"); return HI_ERR_UNSUPPORTED; }
     auto attend = [&](auto kernel, int waves) { launch_kernel(kernel, grid, dim3(waves * 64), kPdLdsBytes, stream, kernel_done, a); };
     if (mfma32) attend(prefill_kernel_deep, kPdWaves);
     else if (wide && q_prescaled) attend(prefill_kernel_wide<true>, kPwWaves);

@@ -36,7 +36,6 @@ struct PfShape {
   int paired;   // balanced partition over (deep, shallow) pairs of blocks
   int carried;  // the images E hold states of earlier launches of the unit
   uint32_t by_split = 0, by_nbk = 0;    // pf_magic of split and nbk (0: divide)
-  int strip = 0;                        // positions of a block (0: 64 m)
 };
 
 // x / d as one multiplication: the kernels divide by split and nbk before they can ask for their first byte, and the
@@ -76,7 +75,7 @@ HI_HD int pf_cut(int L, int k, int nr) { return (int)((uint32_t)L * (uint32_t)k 
 HI_HD int pf_wg_index(int x, int n, int xcd) { return xcd ? (x & 7) * (n >> 3) + (x >> 3) : x; }
 
 HI_HD int pf_own_tiles(const PfShape& s, int b) {
-  const int o = s.strip > 0 ? ((b + 1) * s.strip + 63) >> 6 : (b + 1) * s.m;
+  const int o = (b + 1) * s.m;
   return o < s.tb_all ? o : s.tb_all;
 }
 
