@@ -1821,7 +1821,8 @@ __device__ __forceinline__ bool pf_append_block(const PrefillAppendArgs& p) {
 }
 
 // Merge of the states of prefill_kernel_deep16 (its own image layout): grid (blocks, grid rows, 8): z is one dim block
-// of both query rows of the lane; where that is no workgroup for every compute unit, z = 16: one dim block of one query row.
+// of both query rows of the lane; where that is no workgroup for every compute unit, z = 16: one dim block of one query row (APART;
+// a kernel of its own: with all four bodies in one, chosen at run time, it had 3604 instructions instead of 2498).
 // Bound by the read of the images (139 KB each, up to 64 per block), and where a block has
 // few of them by its latency: CH images are in flight per lane, and behind the first CH the references of all others.  The largest
 // reference comes first, then the sums in the images' order, each image with one weight.  Shortest and median time with the
@@ -1905,14 +1906,14 @@ __device__ __forceinline__ void pf16_merge(const PrefillArgs& a, const PfShape& 
   }
 }
 
+template <bool APART>
 __global__ __launch_bounds__(512, 4) void prefill_merge16_kernel(PrefillArgs a, PrefillAppendArgs append) {
   if (pf_append_block(append)) return;
   const int lane = lane_id();
   const int wave = wave_id();
   const int gl = a.G < 4 ? a.G : 4;
   const int bx = blockIdx.x;
-  const bool apart = append.first_z == 16;
-  const int db = blockIdx.z & 7, qb = blockIdx.z >> 3;
+  const int db = APART ? blockIdx.z & 7 : blockIdx.z, qb = APART ? blockIdx.z >> 3 : 0;
   const int g = pf_select_head(a) * 4 + (wave % gl);
   const Pf16Rows rows16 = pf16_rows(a, bx, gl, wave);
   if (qb >= rows16.nq) return;              // rows past the end
@@ -1921,10 +1922,14 @@ __global__ __launch_bounds__(512, 4) void prefill_merge16_kernel(PrefillArgs a, 
   pf_block_images(sh, bx, n_e, n_x);
   const int n = n_e + n_x;
   if (n == 1 && a.split == 1) return;
-  if (apart && n > 8) pf16_merge<1, 16>(a, sh, rows16, bx, db, qb, n_e, n, g, lane >> 4, lane & 15);
-  else if (apart || rows16.nq == 1) pf16_merge<1, 8>(a, sh, rows16, bx, db, qb, n_e, n, g, lane >> 4, lane & 15);
-  else if (n <= 4) pf16_merge<2, 4>(a, sh, rows16, bx, db, 0, n_e, n, g, lane >> 4, lane & 15);
-  else pf16_merge<2, 8>(a, sh, rows16, bx, db, 0, n_e, n, g, lane >> 4, lane & 15);
+  if constexpr (APART) {
+    if (n > 8) pf16_merge<1, 16>(a, sh, rows16, bx, db, qb, n_e, n, g, lane >> 4, lane & 15);
+    else pf16_merge<1, 8>(a, sh, rows16, bx, db, qb, n_e, n, g, lane >> 4, lane & 15);
+  } else {
+    if (rows16.nq == 1) pf16_merge<1, 8>(a, sh, rows16, bx, db, 0, n_e, n, g, lane >> 4, lane & 15);
+    else if (n <= 4) pf16_merge<2, 4>(a, sh, rows16, bx, db, 0, n_e, n, g, lane >> 4, lane & 15);
+    else pf16_merge<2, 8>(a, sh, rows16, bx, db, 0, n_e, n, g, lane >> 4, lane & 15);
+  }
 }
 
 #include "hi_prefill_wide.inc"
@@ -2480,7 +2485,8 @@ hi_status launch_prefill(void* stream, const void* q, int G, int chunk_len, cons
       hipError_t e1 = hipGetLastError();
       if (e1 != hipSuccess) { set_last_error("prefill launch: %s", hipGetErrorString(e1)); return HI_ERR_HIP; }
       if (mfma32) launch_kernel(prefill_merge_kernel, merge_grid((unsigned)pl.nbk, grid.y, 4, kPdWaves * 64), dim3(kPdWaves * 64), 0, stream, done, a, app);
-      else launch_kernel(prefill_merge16_kernel, merge_grid((unsigned)pl.nbk, grid.y, 8u * pl.nbk * grid.y < kPrefillCus ? 16 : 8, kPdWaves * 64), dim3(kPdWaves * 64), 0, stream, done, a, app);
+      else if (8u * pl.nbk * grid.y < kPrefillCus) launch_kernel(prefill_merge16_kernel<true>, merge_grid((unsigned)pl.nbk, grid.y, 16, kPdWaves * 64), dim3(kPdWaves * 64), 0, stream, done, a, app);
+      else launch_kernel(prefill_merge16_kernel<false>, merge_grid((unsigned)pl.nbk, grid.y, 8, kPdWaves * 64), dim3(kPdWaves * 64), 0, stream, done, a, app);
     }
   } else {
     const dim3 blocks((unsigned)ceil_div(chunk_len, strip), (unsigned)(gy * n_heads));
