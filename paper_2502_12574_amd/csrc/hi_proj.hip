@@ -26,6 +26,7 @@
 #include <type_traits>
 #include "hi_device.h"
 #include "hi_internal.h"
+#include "hi_rope.h"
 
 namespace hi {
 
@@ -443,11 +444,12 @@ constexpr int kPsStages = 5;
 constexpr int kPsLdsBytes = kPsStages * kPsStageBytes;    // 160 KiB
 
 // The rotation needs (cos, sin) of 64 pairs at the tile's 128 tokens.  Every workgroup forms them itself, under the latency of its first
-// loads: a wavefront takes 32 tokens, a lane one pair - the first angle and one step of a position in double precision,
-// then rotations by that step, rounded to fp32 as the table of rope_table_kernel is - keeps them in 64 registers (there is one
-// wavefront per SIMD) and puts them into the ring's place in LDS for the epilogue.  As a table of its own launch they were 5 us in
-// front of this one: Q/K/V of 65 / 300 / 600 tokens at a hidden size of 4096 32.5 / 33.0 / 38.9 -> 30.2 / 30.9 / 37.1 us, of 600 tokens at 1024
-// 12.3 -> 10.6.
+// loads: a wavefront takes 32 tokens, a lane one pair (RopeRun, as the table of the 256-row tile does: the same bits), keeps them in
+// 64 registers (there is one wavefront per SIMD) and puts them into the ring's place in LDS for the epilogue.  As a table of its own launch
+// they were 5 us in front of this one: Q/K/V of 65 / 300 / 600 tokens at a hidden size of 4096 32.5 / 33.0 / 38.9 -> 30.2 / 30.9 / 37.1 us,
+// of 600 tokens at 1024 12.3 -> 10.6.  The lane's frequency is in its register before the first load goes out: with a wait for it (and
+// so for all loads) behind them, and 190 instructions less for the angles, 65 / 100 / 300 / 600 tokens take 33.7 / 37.1 / 32.7 / 38.9 us where
+// this takes 33.4 / 36.7 / 32.4 / 38.6 (other weights and clocks than above; at a hidden size of 1024 10.28 and 10.33).
 constexpr int kPsTrigPitch = kPsTile * 32 + 32;      // a group of 4 pairs: [token][4] (cos, sin), and 32 bytes against bank conflicts
 static_assert(16 * kPsTrigPitch <= kPsLdsBytes, "the table takes the ring's place");
 
@@ -465,6 +467,10 @@ __global__ __launch_bounds__(256, 1) void proj_gemm_small_kernel(ProjArgs p, Rop
   const int per = (total + 7) >> 3;
   const int slot = (int)(blockIdx.x >> 3), tile = (int)(blockIdx.x & 7) * per + slot;
   if (slot >= per || tile >= total) return;
+  // this lane's frequency, asked for and waited for in front of the ring's first loads: the compiler does not count those, and a wait
+  // behind them would be for all of them
+  double freq = 0.0;
+  if constexpr (MODE == kPjQkv) freq = rope.f.inv[lane];
   int ta, tb;
   pj_tile_of(p, tile, ta, tb);
 
@@ -509,28 +515,22 @@ __global__ __launch_bounds__(256, 1) void proj_gemm_small_kernel(ProjArgs p, Rop
   };
 
   const int T = p.K / kPjK;        // at least 4 (the launcher's rule)
+  if constexpr (MODE == kPjQkv) asm volatile("" : "+v"(freq) : : "memory");
 #pragma unroll
   for (int t = 0; t < kPsStages - 1; ++t)
 #pragma unroll
     for (int u = 0; u < (t < kPsStages - 2 ? 8 : 4); ++u) issue_one(p.a + t * kPjRowBytes, b_slice(t), t * kPsStageBytes, u);
 
   bool rotate = false;
-  float trig_c[32], trig_s[32];  // this lane's pair at tokens 32 wave .. +31 of the tile
+  float trig_c[kRopeRun], trig_s[kRopeRun];  // this lane's pair at tokens 32 wave .. +31 of the tile
   if constexpr (MODE == kPjQkv) {
     rotate = rope.on && ta < p.n_q_heads + p.n_kv_heads;
     if (rotate) {
-      const double w = rope.f.inv[lane];
-      double s, c, s1, c1;
-      sincos((double)(rope.past + tb * kPsTile + 32 * wave) * w, &s, &c);
-      sincos(w, &s1, &c1);
+      RopeRun run(rope.past + tb * kPsTile + kRopeRun * wave, freq);
 #pragma unroll
-      for (int i = 0; i < 32; ++i) {
-        trig_c[i] = (float)c;
-        trig_s[i] = (float)s;
+      for (int i = 0; i < kRopeRun; ++i) {
+        run.next(trig_c[i], trig_s[i]);
         asm volatile("" : "+v"(trig_c[i]), "+v"(trig_s[i]));     // here, and not in front of the epilogue
-        const double cn = c * c1 - s * s1;
-        s = s * c1 + c * s1;
-        c = cn;
       }
     }
   }
@@ -689,15 +689,17 @@ __global__ __launch_bounds__(256, 1) void proj_gemm_small_kernel(ProjArgs p, Rop
   }
 }
 
-// (cos, sin) of position (past + t) times theta^(-i / 64) for i < 64, in double precision: at a million tokens the
-// angle of the fastest pair is a million radians, beyond what fp32 can reduce
-__global__ __launch_bounds__(256) void rope_table_kernel(float2* __restrict__ out, int64_t past, int n, RopeFreqs f) {
-  const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= n * 64) return;
-  const int t = idx >> 6, i = idx & 63;
-  double s, c;
-  sincos((double)(past + t) * f.inv[i], &s, &c);
-  out[((int64_t)(i >> 2) * n + t) * 4 + (i & 3)] = make_float2((float)c, (float)s);   // [i / 4][token][i % 4]
+// (cos, sin) of position (past + t) times theta^(-i / 64) for i < 64: a thread takes a pair at 32 tokens, the runs of the 128-row tile
+__global__ __launch_bounds__(64) void rope_table_kernel(float2* __restrict__ out, int64_t past, int n, RopeFreqs f) {
+  const int i = threadIdx.x, t0 = blockIdx.x * kRopeRun;
+  RopeRun run(past + t0, f.inv[i]);
+  float2* const at = out + ((int64_t)(i >> 2) * n + t0) * 4 + (i & 3);   // [i / 4][token][i % 4]
+  const int left = n - t0 < kRopeRun ? n - t0 : kRopeRun;
+  for (int k = 0; k < left; ++k) {
+    float c, s;
+    run.next(c, s);
+    at[4 * k] = make_float2(c, s);
+  }
 }
 
 // ---- 2 to 64 tokens: the read of the weights is the bound (50 MB of Q/K/V at a hidden size of 4096), and the 128-row tiles
@@ -1021,7 +1023,7 @@ static hi_status pj_launch(void* stream, ProjArgs& p, int mode, const RopeChunk&
     return HI_OK;
   }
   if (rope.on) {
-    hipLaunchKernelGGL(rope_table_kernel, dim3((unsigned)ceil_div((int64_t)p.b_rows * 64, 256)), dim3(256), 0, (hipStream_t)stream,
+    hipLaunchKernelGGL(rope_table_kernel, dim3((unsigned)ceil_div(p.b_rows, kRopeRun)), dim3(64), 0, (hipStream_t)stream,
                        (float2*)table, rope.past, p.b_rows, rope.f);
     hipError_t er = hipGetLastError();
     if (er != hipSuccess) { set_last_error("rope table launch: %s", hipGetErrorString(er)); return HI_ERR_HIP; }

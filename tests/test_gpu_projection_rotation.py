@@ -31,3 +31,23 @@ def test_rotation(D, Hq, Hkv, C, past, theta):
         rel = float(np.sqrt(((got - ref) ** 2).sum() / (ref ** 2).sum()))
         # one rounding to bf16 (2^-9 at most, 1.7e-3 in the mean square) on fp32 sums
         assert rel <= 2.0e-3 and float((np.abs(got - ref) / (np.abs(ref) + 1.0)).max()) <= 2.0 ** -8 + 1e-5, (name, rel)
+
+
+# The 256-row tile (fp32 output) reads its rotation from a table, the 128-row tile (bf16) forms its own: the same angles, so that bf16 output
+# is the fp32 output rounded, to the bit.  A last bit of the angle shows in one of a million outputs, at long positions.
+@pytest.mark.parametrize("past", [131072, 4000000, 100000000])
+def test_bf16_output_is_fp32_output_rounded(past):
+    D, Hq, Hkv, C = 256, 126, 1, 128
+    gen = torch.Generator(device=DEV).manual_seed(past)
+    ws = torch.empty(hb.hi_proj_workspace_bytes(C), dtype=torch.uint8, device=DEV)
+    for r in range(16):
+        x = torch.randn(C, D, device=DEV, generator=gen).to(torch.bfloat16)
+        w = (torch.randn((Hq + 2 * Hkv) * 128, D, device=DEV, generator=gen) / 16).to(torch.bfloat16)
+        out = []
+        for dtype in (torch.bfloat16, torch.float32):
+            q, k, v = (torch.empty(h, C, 128, dtype=dtype, device=DEV) for h in (Hq, Hkv, Hkv))
+            hb.hi_qkv_rope(torch.cuda.current_stream(), x, w, D, Hq, Hkv, C, past + 1000 * r, 500000.0, int(dtype == torch.float32),
+                           q, k, v, ws)
+            out.append((q, k, v))
+        for a, b in zip(*out):
+            assert torch.equal(a, b.to(torch.bfloat16)), r
