@@ -96,8 +96,8 @@ __device__ __forceinline__ float sum_halves(float x) {
 
 // Per-lane constants of the tile traffic, computed once per kernel.
 struct PfLaneConst {
-  uint32_t gk[4];    // global byte offset inside a 64-row K tile of this lane's 4 load instructions
-  uint32_t gv;       // same for V (instruction i adds i * 1024)
+  uint32_t gk[2];    // 8-wave kernel: global byte offset inside a 64-row K tile of this lane's 2 load instructions
+  uint32_t gv;       // same for V (the second instruction adds 1024)
   uint32_t koff[8];  // LDS byte offset of the K operand read for contraction step kk (sub-block 1 adds 8192)
   uint32_t voff[4];  // LDS byte offset of the V^T transpose read for dim block db (+2048 next 4 rows of the
                      // pair, +4096 second 16-row group, +8192 second sub-block)
@@ -109,65 +109,45 @@ __device__ __forceinline__ int formed_here(int x) {
   return x;
 }
 
-// One tile's K loads (or V loads) by the whole workgroup of NW wavefronts: 16 / NW instructions per wavefront.
+// One tile's K loads (or V loads) by the whole workgroup of 8 wavefronts, two instructions each.
 // Full tiles need no vector ALU work at all; the last tile of a segment clamps its row indices (rows past the
 // end re-read the last row and are masked by the caller).  lds_tile is the LDS byte address of the 16 KiB tile.
-template <int NW>
 __device__ __forceinline__ void pf_issue_k(const char* kt, int rows, uint32_t lds_tile, int wave, int lane,
                                            const PfLaneConst& lc) {
-  constexpr int NI = 16 / NW;
-  const uint32_t ldk = lds_tile + wave * (NI * 1024);
+  const uint32_t ldk = lds_tile + wave * 2048;
   if (rows >= kPfTileRows) {
     g2lds16_s<0>(kt, lc.gk[0], ldk);
     g2lds16_s<0>(kt, lc.gk[1], ldk + 1024);
-    if (NI > 2) {
-      g2lds16_s<0>(kt, lc.gk[2], ldk + 2048);
-      g2lds16_s<0>(kt, lc.gk[3], ldk + 3072);
-    }
   } else {
     lane = formed_here(lane);
     const int r_in = lane >> 4;
     const int cpos = lane & 15;
 #pragma unroll
-    for (int i = 0; i < NI; ++i) {
-      const int r = (wave * NI + i) * 4 + r_in;
+    for (int i = 0; i < 2; ++i) {
+      const int r = (wave * 2 + i) * 4 + r_in;
       const int rc = r < rows ? r : rows - 1;
       g2lds16_s<0>(kt, (uint32_t)(rc * kRowBytes + ((cpos ^ swz_k(r)) << 4)), ldk + i * 1024);
     }
   }
 }
 
-template <int NW>
 __device__ __forceinline__ void pf_issue_v(const char* vt, int rows, uint32_t lds_tile, int wave, int lane,
                                            const PfLaneConst& lc) {
-  constexpr int NI = 16 / NW;
-  const uint32_t ldv = lds_tile + wave * (NI * 1024);
+  const uint32_t ldv = lds_tile + wave * 2048;
   if (rows >= kPfTileRows) {
     g2lds16_s<0>(vt, lc.gv, ldv);
     g2lds16_s<1024>(vt, lc.gv, ldv);     // the immediate advances the global AND the LDS address
-    if (NI > 2) {
-      g2lds16_s<2048>(vt, lc.gv, ldv);
-      g2lds16_s<3072>(vt, lc.gv, ldv);
-    }
   } else {
     lane = formed_here(lane);
     const int r_in = lane >> 4;
     const int cpos = lane & 15;
 #pragma unroll
-    for (int i = 0; i < NI; ++i) {
-      const int r = (wave * NI + i) * 4 + r_in;
+    for (int i = 0; i < 2; ++i) {
+      const int r = (wave * 2 + i) * 4 + r_in;
       const int rc = r < rows ? r : rows - 1;
       g2lds16_s<0>(vt, (uint32_t)(rc * kRowBytes + ((cpos ^ swz_v(r)) << 4)), ldv + i * 1024);
     }
   }
-}
-
-// One stage's tile loads (K tile, then V tile).
-template <int NW>
-__device__ __forceinline__ void pf_issue_tile(const char* kt, const char* vt, int rows, uint32_t lds_stage,
-                                              int wave, int lane, const PfLaneConst& lc) {
-  pf_issue_k<NW>(kt, rows, lds_stage, wave, lane, lc);
-  pf_issue_v<NW>(vt, rows, lds_stage + kPfTileBytes, wave, lane, lc);
 }
 
 typedef __attribute__((address_space(3))) bf16x8 lds_bf16x8;
@@ -200,17 +180,12 @@ __device__ __forceinline__ void pf_write_row(void* out, int out_fp32, int C, int
     }
 }
 
-
-// Operands that the 4-wave kernels read ahead of their MFMAs (scores, weighted V): left to itself the compiler keeps two
-// in flight and the MFMAs wait for LDS.  1000 rows of 8 heads behind 1000: 60.0 -> 55.7 us; 6 or 8 ahead are no faster.
-constexpr int kPf4AheadK = 4, kPf4AheadV = 4;
-
 // S^T = K Q^T for one 64-row K tile at kt: register r of sub-block sb is tile row 32*sb + 8*(r/4) + 4*hl + r%4
 // (query row = lane % 32).  The two sub-blocks' accumulation chains alternate, so consecutive MFMAs never
-// depend on each other.
+// depend on each other.  The first tile of a 4-wave kernel; those behind it come out of pf_tile4.
 __device__ __forceinline__ void pf_scores(lds_char* kt, const PfLaneConst& lc, const bf16x8 (&qf)[8],
                                           f32x16 (&s)[2]) {
-  constexpr int A = kPf4AheadK;
+  constexpr int A = 4;           // operands read ahead: left to itself the compiler keeps two in flight and the MFMAs wait for LDS
   bf16x8 op[A + 1];
   auto read = [&](int i) __attribute__((always_inline)) { return *(lds_bf16x8*)(kt + lc.koff[i >> 1] + (i & 1) * 8192); };
 #pragma unroll
@@ -540,17 +515,9 @@ __device__ __forceinline__ void pd_matrix_phase(uint32_t v_off, uint32_t k_off, 
 
 // Lane constants of a 4-wavefront workgroup whose LDS stage is a K tile followed by a V tile (offsets relative
 // to the tile).
-__device__ __forceinline__ PfLaneConst pf_lane_const_4w(int wave, int lane) {
+__device__ __forceinline__ PfLaneConst pf_lane_const_4w(int lane) {      // (gk and gv stay unused: its loads are streams)
   PfLaneConst lc;
   const int hl = lane >> 5, col = lane & 31;
-  const int r_in = lane >> 4, cpos = lane & 15;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int r = (wave * 4 + i) * 4 + r_in;
-    lc.gk[i] = (uint32_t)(r * kRowBytes + ((cpos ^ swz_k(r)) << 4));
-  }
-  const int r0 = wave * 16 + r_in;                // swz_v depends on r & 3 only, so +4 rows = +1024 bytes
-  lc.gv = (uint32_t)(r0 * kRowBytes + ((cpos ^ swz_v(r0)) << 4));
 #pragma unroll
   for (int kk = 0; kk < 8; ++kk) lc.koff[kk] = (uint32_t)(col * kRowBytes + (((2 * kk + hl) ^ swz_k(col)) << 4));
   const int s16 = lane & 15, q16 = col >> 4;
@@ -613,7 +580,7 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(PrefillArgs a) {
   const int my_i = qi;
   if (qi > a.C - 1) qi = a.C - 1;
 
-  const PfLaneConst lc = pf_lane_const_4w(wave, lane);
+  const PfLaneConst lc = pf_lane_const_4w(lane);
 
   // Q^T operand: lane holds q[g][qi][16*kk + 8*hl .. +7]
   bf16x8 qf[8];
@@ -803,7 +770,6 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel_deep(PrefillArgs a) {
       const int r = (wave * 2 + i) * 4 + r_in;
       lc.gk[i] = (uint32_t)(r * kRowBytes + ((cpos ^ swz_k(r)) << 4));
     }
-    lc.gk[2] = lc.gk[3] = 0;
     const int r0 = wave * 8 + r_in;
     lc.gv = (uint32_t)(r0 * kRowBytes + ((cpos ^ swz_v(r0)) << 4));
 #pragma unroll
@@ -904,8 +870,8 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel_deep(PrefillArgs a) {
       const int64_t left = (in_b ? a.nb : na_p) - row0;
       const int rows = left < kPfTileRows ? (int)left : kPfTileRows;
       const uint32_t slot = lds_base + (uint32_t)(t & (kPdStages - 1)) * kPfTileBytes;
-      if (which == 0) pf_issue_k<kPdWaves>((in_b ? a.kb : ka_p) + row0 * kRowBytes, rows, slot, wave, lane, lc);
-      else pf_issue_v<kPdWaves>((in_b ? a.vb : va_p) + row0 * kRowBytes, rows, slot + kPdVRing, wave, lane, lc);
+      if (which == 0) pf_issue_k((in_b ? a.kb : ka_p) + row0 * kRowBytes, rows, slot, wave, lane, lc);
+      else pf_issue_v((in_b ? a.vb : va_p) + row0 * kRowBytes, rows, slot + kPdVRing, wave, lane, lc);
     };
     // Every wave issues, in this order: K0 | K1 V0 | K2 V1 | then, in the matrix phase of tile t, K(t+3) V(t+2)
     // (2 instructions each).  The one wait per tile is at the end of the softmax phase of tile t: everything up to
@@ -2126,7 +2092,7 @@ __global__ __launch_bounds__(256, 2) void prefill_window_kernel(PrefillWindowArg
   const int my_i = i0 + col;
   const int qi = my_i > a.C - 1 ? a.C - 1 : my_i;
 
-  const PfLaneConst lc = pf_lane_const_4w(wave, lane);
+  const PfLaneConst lc = pf_lane_const_4w(lane);
 
   PfState st;
   st.m = kNegBig;
