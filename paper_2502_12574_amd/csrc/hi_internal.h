@@ -4,6 +4,7 @@
 #include <cstddef>
 #include "headinfer.h"
 #include "hi_prefill_part.h"
+#include "hi_prefill_visits.h"
 
 namespace hi {
 
@@ -398,10 +399,15 @@ constexpr int64_t kStreamMaxRows = 1 << 22;
 // One chunk of such a head (a group of n_heads, their stores store_head_stride bytes apart): row past_len + i
 // sees key j iff j <= past_len + i and (j < n_sink or past_len + i - j < n_recent); the past comes from the
 // store, the chunk's own rows from k_new / v_new.  Layouts of q, k_new, v_new, out as in launch_prefill.
-// update: the launch takes the chunk's rows into the store itself (window_update says which, and whether it should: where the last
-// of a head's workgroups that read what the rows replace comes early; counters: one int per head if there are any).
-struct PrefillWindowUpdate { int cs, u0, cr, readers; int* counters; };
-bool window_update(int G, int chunk_len, int64_t past_len, int n_sink, int n_recent, PrefillWindowUpdate* w);
+// update: the launch takes the chunk's rows into the store itself (window_update says which, and whether it should: pf_store_rides;
+// counters: one int per head if there are readers).
+struct PrefillWindowUpdate { PfStoreRows rows; int* counters; };
+inline bool window_update(int G, int chunk_len, int64_t past_len, int n_sink, int n_recent, PrefillWindowUpdate* w) {
+  const int strip = prefill_strip(G);
+  w->rows = pf_store_rows(pf_window_of(past_len, chunk_len, n_sink, n_recent), past_len, strip);
+  w->counters = nullptr;
+  return pf_store_rides(w->rows, chunk_len, strip);
+}
 hi_status launch_prefill_window(void* stream, const void* q, int G, int chunk_len, const void* store_k,
                                 const void* store_v, int64_t store_head_stride, const void* k_new, const void* v_new,
                                 int64_t past_len, int n_sink, int n_recent, void* out, int out_fp32, int n_heads,

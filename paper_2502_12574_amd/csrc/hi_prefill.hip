@@ -27,6 +27,7 @@
 #include "hi_device.h"
 #include "hi_internal.h"
 #include "hi_prefill_part.h"
+#include "hi_prefill_visits.h"
 
 namespace hi {
 
@@ -530,8 +531,82 @@ __device__ __forceinline__ PfLaneConst pf_lane_const_4w(int lane) {      // (gk 
   return lc;
 }
 
-// Rows [0, n) of a tile as a bit mask.
-__device__ __forceinline__ uint64_t pf_rows_below(int n) { return n <= 0 ? 0 : n >= 64 ? ~0ull : (1ull << n) - 1; }
+// A 4-wave kernel's load stream, with the lane's byte offsets of its four instructions.
+struct PfStream4 : PfLoads { uint32_t off[4]; };
+// V = false: K tiles, true: V tiles; row_of(r): where row r of the tile lies, in rows behind the stream's base
+template <bool V, class RowOf>
+__device__ __forceinline__ void pf_stream4_offsets(PfStream4& w, int wave, int lane, RowOf row_of) {
+  const int r_in = lane >> 4, cpos = lane & 15;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int r = (wave * 4 + i) * 4 + r_in;
+    w.off[i] = (uint32_t)row_of(r) * kRowBytes + ((cpos ^ (V ? swz_v(r) : swz_k(r))) << 4);
+  }
+}
+__device__ __forceinline__ void pf_stream4_issue(const PfStream4& w, uint32_t lds) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) g2lds16_s<0>(w.base, w.off[i], lds + i * 1024);
+}
+
+// All visits of a workgroup.  LDS: two places for K tiles, then two for V tiles; on entry the first two K tiles and the first V tile are
+// on their way, sk stands at visit 2 and sv at visit 1.  masked(v): visit v hides rows of some query row of the wavefront; seen(): rows of
+// that visit that the lane's query row sees.  Hidden scores become kNegBig as bit operations (comparisons and selects per
+// element became branches, 83 -> 77 us a launch of prefill_window_kernel).
+template <class GoOnK, class GoOnV, class Masked, class Seen>
+__device__ __forceinline__ void pf_sweep4(lds_char* lds, uint32_t lds_wave, const PfLaneConst& lc, const bf16x8 (&qf)[8], PfState& st,
+                                          float c, int T, int lane, PfStream4& sk, PfStream4& sv, GoOnK go_on_k, GoOnV go_on_v,
+                                          Masked masked, Seen seen) {
+  f32x16 s0, s1a, s1b;         // scores of a visit's rows 0..31, and of its rows 32..63 (even and odd visits)
+  wait_vmcnt<0>();
+  __syncthreads();
+  {
+    f32x16 s[2];
+    pf_scores(lds, lc, qf, s);
+    s0 = s[0];
+    s1a = s[1];
+  }
+  // Visit v: its weights and sums, and the scores of visit v + 1.  On entry both of v + 1's K rows and v's V rows are on their way;
+  // behind the barrier everybody is done with the K tile of v and the V tile of v - 1, whose places take the next ones.
+  // parity: v % 2, a constant where every LDS address shall be an immediate.
+  auto step = [&](int v, auto parity, auto more, f32x16& cur, f32x16& nxt) __attribute__((always_inline)) {
+    const int odd = parity;
+    constexpr bool NEXT = decltype(more)::value;
+    wait_vmcnt<0>();
+    __syncthreads();
+    const bool hides = masked(v);
+    auto mask = [&](f32x16& s0, f32x16& s1) __attribute__((always_inline)) {
+      const uint64_t rows = seen(v) >> (4 * (formed_here(lane) >> 5));
+      const uint32_t bits[2] = {(uint32_t)rows, (uint32_t)(rows >> 32)};
+#pragma unroll
+      for (int sb = 0; sb < 2; ++sb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          f32x16& s = sb == 0 ? s0 : s1;
+          const uint32_t t = (uint32_t)__builtin_amdgcn_sbfe((int)bits[sb], 8 * (r >> 2) + (r & 3), 1);
+          s[r] = __uint_as_float((__float_as_uint(s[r]) & t) | (__float_as_uint(kNegBig) & ~t));
+        }
+    };
+    // K of visit v + 2 into the place of v's, V of v + 1 into that of v - 1's
+    auto at = [&](int i) __attribute__((always_inline)) {
+      set_m0(lds_wave + (i < 4 ? odd * kPfTileBytes : kPfStageBytes + (1 - odd) * kPfTileBytes) + (i & 3) * 1024);
+    };
+    auto load = [&](int i) __attribute__((always_inline)) { g2lds16_m0(i < 4 ? sk.base : sv.base, i < 4 ? sk.off[i] : sv.off[i & 3]); };
+    pf_tile4<NEXT>(lds + (1 - odd) * kPfTileBytes, lds + kPfStageBytes + odd * kPfTileBytes, lc, qf, s0, cur, nxt, st, c, hides, mask,
+                   at, load);
+    if (NEXT) {
+      go_on_k();
+      go_on_v();
+    }
+  };
+  int v = 0;
+  for (;;) {
+    if (v + 1 >= T) break;
+    step(v++, std::integral_constant<int, 0>(), std::true_type(), s1a, s1b);
+    if (v + 1 >= T) { s1a = s1b; break; }
+    step(v++, std::integral_constant<int, 1>(), std::true_type(), s1b, s1a);
+  }
+  step(v, v & 1, std::false_type(), s1a, s1b);
+}
 
 // The 4-wave kernel: short chunks, and units of few workgroups.  One wavefront or two on a SIMD, so what bounds it is a wavefront's own
 // chain: matrix phase, softmax, matrix phase of one tile after the other.  The scores are formed one visit ahead (pf_tile4; K and V
@@ -591,61 +666,36 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(PrefillArgs a) {
   }
 
   // tiles: segment A (all of it), then the part of segment B at or below the workgroup's causal boundary
-  const int na = (int)a.na, nb = (int)a.nb;         // (a 64-bit comparison would put all that follows from it into vector registers)
-  const int nb_vis = nb < i_hi + 1 ? nb : i_hi + 1;
-  const int ta = SPLIT ? ta_range : na / kPfTileRows + (na % kPfTileRows != 0);
-  const int T = SPLIT ? t_range : ta + (nb_vis + kPfTileRows - 1) / kPfTileRows;     // >= 1
-  const int wholeA = na / kPfTileRows, wholeB = nb / kPfTileRows;                    // full tiles of the segments
+  PfNarrow n;
+  n.na = (int)a.na; n.nb = (int)a.nb;               // (a 64-bit comparison would put all that follows from it into vector registers)
+  n.a0 = a0; n.b0 = b0;
+  n.jump_tile = SPLIT ? a.a_jump_tile : 0;
+  n.jump_bytes = a.a_jump_bytes;
+  const int nb_vis = n.nb < i_hi + 1 ? n.nb : i_hi + 1;
+  n.ta = SPLIT ? ta_range : n.na / kPfTileRows + (n.na % kPfTileRows != 0);
+  n.T = SPLIT ? t_range : n.ta + (nb_vis + kPfTileRows - 1) / kPfTileRows;           // >= 1
 
-  // The loads of K tiles, and of V tiles, as two streams (as in prefill_window_kernel): visit v's rows lie at `base`, off[] are the
-  // lane's byte offsets behind it (those of 64 rows if `usual`), up to visit `until` the next tile is the next 16 KiB.
-  struct Stream { const char* base; int v, until, usual; uint32_t off[4]; };
-  auto meet = [&](Stream& w, auto v_tag) __attribute__((always_inline)) {
-    constexpr bool VP = decltype(v_tag)::value;
-    const int here = formed_here(lane), r_in = here >> 4, cpos = here & 15;
-    const bool in_b = w.v >= ta;
-    const int tile = in_b ? b0 + w.v - ta : a0 + w.v, whole = in_b ? wholeB : wholeA;
-    const bool jumped = SPLIT && !in_b && a.a_jump_tile > 0 && tile >= a.a_jump_tile;
-    const bool usual = tile < whole;
-    int end = whole;                              // the run of tiles that follow each other
-    if (SPLIT && !in_b && a.a_jump_tile > 0 && !jumped && a.a_jump_tile < end) end = a.a_jump_tile;
-    w.until = w.v + (usual ? end - tile : 1);
-    if (!in_b && w.until > ta) w.until = ta;
-    w.base = (in_b ? (VP ? a.vb : a.kb) : (VP ? a.va : a.ka)) + (int64_t)tile * kPfTileBytes;
-    if (jumped) w.base += a.a_jump_bytes;
-    if (usual && w.usual) return;
-    w.usual = usual;
-    const int rows = usual ? kPfTileRows : (in_b ? nb : na) - tile * kPfTileRows;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int r = (wave * 4 + i) * 4 + r_in;
-      w.off[i] = (uint32_t)(r < rows ? r : rows - 1) * kRowBytes + ((cpos ^ (VP ? swz_v(r) : swz_k(r))) << 4);
-    }
+  PfStream4 sk, sv;
+  sk.v = sv.v = sk.usual = sv.usual = 0;
+  auto meet = [&](PfStream4& w, auto v_tag) __attribute__((always_inline)) {
+    constexpr bool V = decltype(v_tag)::value;
+    int rows;
+    if (pf_narrow_meet(w, n, V ? a.va : a.ka, V ? a.vb : a.kb, rows))
+      pf_stream4_offsets<V>(w, wave, formed_here(lane), [&](int r) { return r < rows ? r : rows - 1; });
   };
   using KPlane = std::false_type;
   using VPlane = std::true_type;
-  auto go_on = [&](Stream& w, auto v_tag) __attribute__((always_inline)) {
-    w.base += kPfTileBytes;
-    if (++w.v != w.until) return;
-    if (w.v < T) { meet(w, v_tag); return; }
-    w.base -= kPfTileBytes;      // behind the last visit: its rows again, which nobody reads
-    w.until = w.v + 1;
-  };
+  auto go_on_k = [&]() __attribute__((always_inline)) { if (pf_loads_next(sk, n.T)) meet(sk, KPlane()); };
+  auto go_on_v = [&]() __attribute__((always_inline)) { if (pf_loads_next(sv, n.T)) meet(sv, VPlane()); };
   const uint32_t lds_wave = lds_base + wave * 4096;
-  auto issue = [&](const Stream& w, uint32_t slot) __attribute__((always_inline)) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) g2lds16_s<0>(w.base, w.off[i], lds_wave + slot + i * 1024);
-  };
-  Stream sk, sv;
-  sk.v = sv.v = sk.usual = sv.usual = 0;
   meet(sk, KPlane());
   meet(sv, VPlane());
-  issue(sk, 0);
-  issue(sv, kPfStageBytes);
-  go_on(sk, KPlane());
-  go_on(sv, VPlane());
-  issue(sk, kPfTileBytes);
-  go_on(sk, KPlane());
+  pf_stream4_issue(sk, lds_wave);
+  pf_stream4_issue(sv, lds_wave + kPfStageBytes);
+  go_on_k();
+  go_on_v();
+  pf_stream4_issue(sk, lds_wave + kPfTileBytes);
+  go_on_k();
 
   PfState st;
   float* carry = a.carry + image * (kCarryFloatsPerLane * kWgThreads) + threadIdx.x;
@@ -671,65 +721,10 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(PrefillArgs a) {
 #pragma unroll
   for (int db = 0; db < 4; ++db) asm volatile("" : "+v"(st.o[db]));
 
-  const float c = a.c;
-  f32x16 s0, s1a, s1b;         // scores of a visit's rows 0..31, and of its rows 32..63 (even and odd visits)
-  wait_vmcnt<0>();
-  __syncthreads();
-  {
-    f32x16 s[2];
-    pf_scores(lds, lc, qf, s);
-    s0 = s[0];
-    s1a = s[1];
-  }
-  // visits [0, openA) and [ta, openB) show all their rows to every query row of this wave: the others are a segment's last rows, or
-  // own rows behind a query's position
-  const int openA = wholeA - a0 < ta ? wholeA - a0 : ta;
-  const int openB = ta + ((i0 + 1) / kPfTileRows < wholeB ? (i0 + 1) / kPfTileRows : wholeB) - b0;
-  // Visit v: its weights and sums, and the scores of visit v + 1.  On entry both of v + 1's K rows and v's V rows are on their way;
-  // behind the barrier everybody is done with the K tile of v and the V tile of v - 1, whose places take the next ones.
-  auto step = [&](int v, auto parity, auto more, f32x16& cur, f32x16& nxt) __attribute__((always_inline)) {
-    const int odd = parity;
-    constexpr bool NEXT = decltype(more)::value;
-    wait_vmcnt<0>();
-    __syncthreads();
-    const bool masked = !(v < openA || (v >= ta && v < openB));
-    // hidden scores become kNegBig as bit operations (see prefill_window_kernel)
-    auto mask = [&](f32x16& s0, f32x16& s1) __attribute__((always_inline)) {
-      const int my_i = i0 + (formed_here(lane) & 31), hl = formed_here(lane) >> 5;
-      const bool in_b = v >= ta;
-      const int j0 = (in_b ? b0 + v - ta : a0 + v) * kPfTileRows;
-      const int end = (in_b ? nb : na) - j0, own = in_b ? my_i + 1 - j0 : kPfTileRows;
-      const uint64_t rows = pf_rows_below(end < own ? end : own) >> (4 * hl);
-      const uint32_t seen[2] = {(uint32_t)rows, (uint32_t)(rows >> 32)};
-#pragma unroll
-      for (int sb = 0; sb < 2; ++sb)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          f32x16& s = sb == 0 ? s0 : s1;
-          const uint32_t t = (uint32_t)__builtin_amdgcn_sbfe((int)seen[sb], 8 * (r >> 2) + (r & 3), 1);
-          s[r] = __uint_as_float((__float_as_uint(s[r]) & t) | (__float_as_uint(kNegBig) & ~t));
-        }
-    };
-    // K of visit v + 2 into the place of v's, V of v + 1 into that of v - 1's
-    auto at = [&](int i) __attribute__((always_inline)) {
-      set_m0(lds_wave + (i < 4 ? odd * kPfTileBytes : kPfStageBytes + (1 - odd) * kPfTileBytes) + (i & 3) * 1024);
-    };
-    auto load = [&](int i) __attribute__((always_inline)) { g2lds16_m0(i < 4 ? sk.base : sv.base, i < 4 ? sk.off[i] : sv.off[i & 3]); };
-    pf_tile4<NEXT>(lds + (1 - odd) * kPfTileBytes, lds + kPfStageBytes + odd * kPfTileBytes, lc, qf, s0, cur, nxt, st, c, masked, mask,
-                   at, load);
-    if (NEXT) {
-      go_on(sk, KPlane());
-      go_on(sv, VPlane());
-    }
-  };
-  int v = 0;
-  for (;;) {
-    if (v + 1 >= T) break;
-    step(v++, std::integral_constant<int, 0>(), std::true_type(), s1a, s1b);
-    if (v + 1 >= T) { s1a = s1b; break; }
-    step(v++, std::integral_constant<int, 1>(), std::true_type(), s1b, s1a);
-  }
-  step(v, v & 1, std::false_type(), s1a, s1b);
+  const PfOpen open = pf_narrow_open(n, i0);
+  pf_sweep4(lds, lds_wave, lc, qf, st, a.c, n.T, lane, sk, sv, go_on_k, go_on_v,
+            [&](int v) __attribute__((always_inline)) { return !(v < open.a || (v >= n.ta && v < open.b)); },
+            [&](int v) __attribute__((always_inline)) { return pf_narrow_seen(n, v, i0 + (formed_here(lane) & 31)); });
 
   if (SPLIT || !a.last) {
 #pragma unroll
@@ -2022,33 +2017,20 @@ __global__ __launch_bounds__(256) void prefill_merge4_kernel(PrefillArgs a, Pref
 // rows, then the m most recent past rows in token order, read through the ring mapping), and B, the chunk's own
 // rows.  A workgroup visits only the 64-row tiles some of its rows can see: the sink tiles and the tiles from its
 // first row's window start on, in each sequence.
-struct PrefillWindowArgs {
+struct PrefillWindowArgs : PfWindow {
   const uint16_t* q;      // [G][C][128]
   const char* ks; const char* vs;   // the store's K and V planes
   const char* kb; const char* vb;   // the chunk's own rows
   void* out;
-  int G, C, out_fp32, gy;
+  int G, out_fp32, gy;
   float c;
-  int n_sink, n_recent;
-  int ns;                 // sink rows of the past: min(P, n_sink)
-  int m;                  // recent rows of the past held by the ring: tokens t0 .. P-1, t0 = max(n_sink, P-n_recent+1)
-  int ring0;              // ring slot of token t0
-  int lo0;                // index in A of the first recent row visible to chunk row 0 (row i: lo0 + i); may be < ns
-  int sink_b;             // chunk rows that are sink tokens: clamp(n_sink - P, 0, C)
   int64_t s_head_stride;  // bytes between the heads' stores
-  // The chunk's rows on their way into the store (update = 0: in a launch of their own, 4.2 us behind this one of 61): chunk rows [0, cs) to rows s0 .., rows u0 + i
-  // (i < cr) to ring slots (slot0 + i) mod n_recent.  The workgroups of a head's first `readers` strips read rows that these
-  // replace: the last of them to finish writes all the head's rows.  Without readers every workgroup writes its own.
-  int update, cs, s0, u0, cr, slot0, readers;
-  int* counters;          // one per head, zero between launches (readers > 0)
+  // The chunk's rows on their way into the store (update = 0: in a launch of their own, 4.2 us behind this one of 61).  The last of the
+  // workgroups that read what they replace writes all the head's rows; without such readers every workgroup writes its own.
+  int update;
+  PfStoreRows rows;
+  int* counters;          // one per head, zero between launches (rows.readers > 0)
 };
-
-// The place of chunk row u in the store.
-__device__ __forceinline__ int pf_store_row(const PrefillWindowArgs& a, int u) {
-  if (u < a.cs) return a.s0 + u;
-  const int slot = a.slot0 + (u - a.u0);
-  return a.n_sink + (slot >= a.n_recent ? slot - a.n_recent : slot);
-}
 
 // A launch over 4 heads x 8192 rows (1024 workgroups, two rounds of two per compute unit, 11 tiles each) keeps one of a SIMD's two
 // pipes at work nearly all the time: 56 % of the cycles the vector ALU, 41 % the matrix pipe.  The scores of a visit are formed
@@ -2102,201 +2084,82 @@ __global__ __launch_bounds__(256, 2) void prefill_window_kernel(PrefillWindowArg
 #pragma unroll
     for (int r = 0; r < 16; ++r) st.o[db][r] = 0.f;
 
-  // tiles this workgroup visits: A [0, a1) and [a2, ta), then B [0, b1) and [b2, tb)
-  const int nA = a.ns + a.m;
-  const int ta = (nA + kPfTileRows - 1) / kPfTileRows;
-  const int nb_vis = a.C < i_hi + 1 ? a.C : i_hi + 1;
-  const int tb = (nb_vis + kPfTileRows - 1) / kPfTileRows;
-  int a1 = (a.ns + kPfTileRows - 1) / kPfTileRows;
-  if (a1 > ta) a1 = ta;
-  const int loA = a.lo0 + i_lo;
-  int a2 = loA <= 0 ? 0 : loA / kPfTileRows;
-  a2 = a2 < a1 ? a1 : (a2 > ta ? ta : a2);
-  int b1 = (a.sink_b + kPfTileRows - 1) / kPfTileRows;
-  if (b1 > tb) b1 = tb;
-  const int loB = i_lo - a.n_recent + 1;
-  int b2 = loB <= 0 ? 0 : loB / kPfTileRows;
-  b2 = b2 < b1 ? b1 : (b2 > tb ? tb : b2);
-  const int nAv = a1 + (ta - a2);
-  const int T = nAv + b1 + (tb - b2);            // >= 1: the tile holding the workgroup's first row
+  const PfWindowTiles t = pf_window_tiles(a, i_lo, i_hi);
 
-  // visit v -> (sequence, tile)
-  auto locate = [&](int v, bool& in_b) __attribute__((always_inline)) {
-    in_b = v >= nAv;
-    if (!in_b) return v < a1 ? v : a2 + (v - a1);
-    const int w = v - nAv;
-    return w < b1 ? w : b2 + (w - b1);
-  };
-
-  // The loads of K tiles, and of V tiles, as two streams: the next visit's rows lie at `base`, off[] are the lane's byte offsets
-  // behind it (those of 64 rows in a row if `usual`), and up to visit `until` the next tile is the next 16 KiB with the same offsets.
-  struct Stream { const char* base; int v, until, usual; uint32_t off[4]; };
-  auto meet = [&](Stream& w, auto v_tag) __attribute__((always_inline)) {       // the stream has come to visit w.v: what is there?
-    constexpr bool VP = decltype(v_tag)::value;
-    const int here = formed_here(lane), r_in = here >> 4, cpos = here & 15;
-    bool in_b;
-    const int tile = locate(w.v < T ? w.v : T - 1, in_b);      // behind the last visit: its rows again, which nobody reads
-    const int row0 = tile * kPfTileRows;
-    const int whole = (in_b ? a.C : a.ns) / kPfTileRows, end = in_b && tile >= b1 ? tb : in_b ? b1 : whole;
-    const bool usual = tile < whole;              // full tiles of the chunk, and of sink rows; else the chunk's last rows, or rows of the ring
-    w.until = w.v + (usual ? (end < whole ? end : whole) - tile : 1);
-    w.base = in_b ? (VP ? a.vb : a.kb) : (VP ? a.vs : a.ks);
-    if (usual || in_b) w.base += (int64_t)row0 * kRowBytes;
-    if (usual && w.usual) return;
-    w.usual = usual;
-    const int rows = usual ? kPfTileRows : a.C - row0;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int r = (wave * 4 + i) * 4 + r_in;
-      int at = r < rows ? r : rows - 1;
-      if (!usual && !in_b) {                      // rows of A come through the ring mapping
-        int u = row0 + r;
-        if (u > nA - 1) u = nA - 1;
-        at = u;
-        if (u >= a.ns) {
-          int x = a.ring0 + (u - a.ns);
-          if (x >= a.n_recent) x -= a.n_recent;
-          at = a.n_sink + x;
-        }
-      }
-      w.off[i] = (uint32_t)at * kRowBytes + ((cpos ^ (VP ? swz_v(r) : swz_k(r))) << 4);
-    }
+  PfStream4 sk, sv;
+  sk.v = sv.v = sk.usual = sv.usual = 0;
+  auto meet = [&](PfStream4& w, auto v_tag) __attribute__((always_inline)) {
+    constexpr bool V = decltype(v_tag)::value;
+    int rows, row0;
+    if (!pf_window_meet(w, a, t, V ? a.vs : a.ks, V ? a.vb : a.kb, rows, row0)) return;
+    const int nA = a.ns + a.m;
+    pf_stream4_offsets<V>(w, wave, formed_here(lane), [&](int r) __attribute__((always_inline)) {
+      return rows ? (r < rows ? r : rows - 1) : pf_window_row(a, row0 + r < nA ? row0 + r : nA - 1);
+    });
   };
   using KPlane = std::false_type;
   using VPlane = std::true_type;
-  auto go_on = [&](Stream& w, auto v_tag) __attribute__((always_inline)) {
-    w.base += kPfTileBytes;
-    if (++w.v == w.until) meet(w, v_tag);
-  };
+  auto go_on_k = [&]() __attribute__((always_inline)) { if (pf_loads_next(sk, t.T)) meet(sk, KPlane()); };
+  auto go_on_v = [&]() __attribute__((always_inline)) { if (pf_loads_next(sv, t.T)) meet(sv, VPlane()); };
   const uint32_t lds_wave = lds_base + wave * 4096;
-  auto issue = [&](const Stream& w, uint32_t slot) __attribute__((always_inline)) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) g2lds16_s<0>(w.base, w.off[i], lds_wave + slot + i * 1024);
-  };
-
-  Stream sk, sv;
-  sk.v = sv.v = sk.usual = sv.usual = 0;
   meet(sk, KPlane());
   meet(sv, VPlane());
-  issue(sk, 0);                // before the queries: one wait for all
-  issue(sv, kPfStageBytes);
-  go_on(sk, KPlane());
-  go_on(sv, VPlane());
-  issue(sk, kPfTileBytes);
+  pf_stream4_issue(sk, lds_wave);                // before the queries: one wait for all
+  pf_stream4_issue(sv, lds_wave + kPfStageBytes);
+  go_on_k();
+  go_on_v();
+  pf_stream4_issue(sk, lds_wave + kPfTileBytes);
   bf16x8 qf[8];
   {
     const uint16_t* qrow = a.q + ((int64_t)g * a.C + qi) * kHeadDim + 8 * hl;
 #pragma unroll
     for (int kk = 0; kk < 8; ++kk) qf[kk] = __builtin_bit_cast(bf16x8, *(const uint4*)(qrow + 16 * kk));
   }
-  go_on(sk, KPlane());
+  go_on_k();
 #pragma unroll
   for (int kk = 0; kk < 8; ++kk) asm volatile("" : "+v"(qf[kk]));
-  const float c = a.c;
-  f32x16 s0, s1a, s1b;         // scores of a visit's rows 0..31, and of its rows 32..63 (even and odd visits)
-  wait_vmcnt<0>();
-  __syncthreads();
-  {
-    f32x16 s[2];
-    pf_scores(lds, lc, qf, s);
-    s0 = s[0];
-    s1a = s[1];
-  }
-  // visits [seen0, seen0 + n_seen) of the recent rows of B are visible in full to every query row of this wave
-  int seen0, n_seen;
-  {
-    const int from = i0 + 31 - a.n_recent + 1, last = i0 < a.C - 1 ? i0 : a.C - 1;
-    int t0 = from <= 0 ? 0 : (from + kPfTileRows - 1) / kPfTileRows;
-    if (t0 < b2) t0 = b2;
-    const int t1 = (last + 1) / kPfTileRows;
-    seen0 = nAv + b1 + t0 - b2;
-    n_seen = t1 > t0 ? t1 - t0 : 0;
-  }
-  // Visit v: its weights and sums, and the scores of visit v + 1.  On entry both of v + 1's K rows and v's V rows are on their way;
-  // behind the barrier everybody is done with the K tile of v and the V tile of v - 1, whose places take the next ones.
-  // parity: v % 2, a constant where every LDS address shall be an immediate.
-  auto step = [&](int v, auto parity, auto more, f32x16& cur, f32x16& nxt) __attribute__((always_inline)) {
-    const int odd = parity;
-    constexpr bool NEXT = decltype(more)::value;
-    wait_vmcnt<0>();
-    __syncthreads();
-    bool full = (uint32_t)(v - seen0) < (uint32_t)n_seen, in_b = false;
-    int j0 = 0;
-    if (!full) {
-      j0 = locate(v, in_b) * kPfTileRows;
-      full = in_b ? j0 + kPfTileRows - 1 <= (i0 < a.C - 1 ? i0 : a.C - 1) && j0 + kPfTileRows - 1 < a.sink_b
-                  : j0 + kPfTileRows - 1 <= nA - 1 && (j0 + kPfTileRows - 1 < a.ns || j0 >= a.lo0 + i0 + 31);
-    }
-    // per lane: row visible iff row <= hi and (row < sk or row >= lo), rows relative to the tile; hidden scores become kNegBig as
-    // bit operations (comparisons and selects per element became branches, 83 -> 77 us a launch)
-    auto mask = [&](f32x16& s0, f32x16& s1) __attribute__((always_inline)) {
-      const int my_i = i0 + (formed_here(lane) & 31), hl = formed_here(lane) >> 5;
-      const int hi = (in_b ? (my_i < a.C - 1 ? my_i : a.C - 1) : nA - 1) - j0;
-      const int sk = (in_b ? a.sink_b : a.ns) - j0;
-      const int lo = (in_b ? my_i - a.n_recent + 1 : a.lo0 + my_i) - j0;
-      const uint64_t rows = (pf_rows_below(hi + 1) & (pf_rows_below(sk) | ~pf_rows_below(lo))) >> (4 * hl);
-      const uint32_t seen[2] = {(uint32_t)rows, (uint32_t)(rows >> 32)};
-#pragma unroll
-      for (int sb = 0; sb < 2; ++sb)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          f32x16& s = sb == 0 ? s0 : s1;
-          const uint32_t t = (uint32_t)__builtin_amdgcn_sbfe((int)seen[sb], 8 * (r >> 2) + (r & 3), 1);
-          s[r] = __uint_as_float((__float_as_uint(s[r]) & t) | (__float_as_uint(kNegBig) & ~t));
-        }
-    };
-    // K of visit v + 2 into the place of v's, V of v + 1 into that of v - 1's
-    auto at = [&](int i) __attribute__((always_inline)) {
-      set_m0(lds_wave + (i < 4 ? odd * kPfTileBytes : kPfStageBytes + (1 - odd) * kPfTileBytes) + (i & 3) * 1024);
-    };
-    auto load = [&](int i) __attribute__((always_inline)) { g2lds16_m0(i < 4 ? sk.base : sv.base, i < 4 ? sk.off[i] : sv.off[i & 3]); };
-    pf_tile4<NEXT>(lds + (1 - odd) * kPfTileBytes, lds + kPfStageBytes + odd * kPfTileBytes, lc, qf, s0, cur, nxt, st, c, !full, mask,
-                   at, load);
-    if (NEXT) {
-      go_on(sk, KPlane());
-      go_on(sv, VPlane());
-    }
-  };
-  int v = 0;
-  for (;;) {
-    if (v + 1 >= T) break;
-    step(v++, std::integral_constant<int, 0>(), std::true_type(), s1a, s1b);
-    if (v + 1 >= T) { s1a = s1b; break; }
-    step(v++, std::integral_constant<int, 1>(), std::true_type(), s1b, s1a);
-  }
-  step(v, v & 1, std::false_type(), s1a, s1b);
+  const PfSeenVisits open = pf_window_open(a, t, i0);
+  bool in_b = false;
+  int j0 = 0;
+  pf_sweep4(lds, lds_wave, lc, qf, st, a.c, t.T, lane, sk, sv, go_on_k, go_on_v,
+            [&](int v) __attribute__((always_inline)) {
+              if ((uint32_t)(v - open.first) < (uint32_t)open.n) return false;
+              j0 = pf_window_locate(t, v, in_b) * kPfTileRows;
+              return !pf_window_full(a, in_b, j0, i0);
+            },
+            [&](int) __attribute__((always_inline)) { return pf_window_seen(a, in_b, j0, i0 + (formed_here(lane) & 31)); });
 
   pf_write_row(a.out, a.out_fp32, a.C, g, my_i, hl, st.o, st.l);
   if (!a.update) return;
-  if (a.readers == 0) {                             // nobody reads what the rows replace
+  if (a.rows.readers == 0) {                             // nobody reads what the rows replace
     if (by != head * a.gy) return;
     for (int j = threadIdx.x; j < strip * 16; j += 256) {
       const int u = i_lo + (j >> 4);
-      if (!(u < a.cs || (u >= a.u0 && u < a.u0 + a.cr))) continue;
-      const int64_t src = (int64_t)u * kRowBytes + (j & 15) * 16, at = (int64_t)pf_store_row(a, u) * kRowBytes + (j & 15) * 16;
+      if (!(u < a.rows.cs || (u >= a.rows.u0 && u < a.rows.u0 + a.rows.cr))) continue;
+      const int64_t src = (int64_t)u * kRowBytes + (j & 15) * 16, at = (int64_t)pf_store_row(a.rows, a.n_sink, a.n_recent, u) * kRowBytes + (j & 15) * 16;
       const uint4 k = *(const uint4*)(a.kb + src), v = *(const uint4*)(a.vb + src);
       *(uint4*)((char*)a.ks + at) = k;
       *(uint4*)((char*)a.vs + at) = v;
     }
     return;
   }
-  if (bx >= a.readers) return;
+  if (bx >= a.rows.readers) return;
   // every wavefront's last loads have landed (it waited for them in its last step); the counter orders nothing else
   int* const flag = (int*)lds_raw;
   __syncthreads();
   if (threadIdx.x == 0) {
     const int before = __hip_atomic_fetch_add(a.counters + head, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const int last = before == a.readers * a.gy - 1;
+    const int last = before == a.rows.readers * a.gy - 1;
     if (last) __hip_atomic_store(a.counters + head, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     *flag = last;
   }
   __syncthreads();
   if (*flag == 0) return;
-  const int parts = (a.cs + a.cr) * 16;
+  const int parts = (a.rows.cs + a.rows.cr) * 16;
 #pragma unroll 4
   for (int j = threadIdx.x; j < parts; j += 256) {
-    const int u = (j >> 4) < a.cs ? j >> 4 : a.u0 + (j >> 4) - a.cs;
-    const int64_t src = (int64_t)u * kRowBytes + (j & 15) * 16, at = (int64_t)pf_store_row(a, u) * kRowBytes + (j & 15) * 16;
+    const int u = (j >> 4) < a.rows.cs ? j >> 4 : a.rows.u0 + (j >> 4) - a.rows.cs;
+    const int64_t src = (int64_t)u * kRowBytes + (j & 15) * 16, at = (int64_t)pf_store_row(a.rows, a.n_sink, a.n_recent, u) * kRowBytes + (j & 15) * 16;
     const uint4 k = *(const uint4*)(a.kb + src), v = *(const uint4*)(a.vb + src);
     *(uint4*)((char*)a.ks + at) = k;
     *(uint4*)((char*)a.vs + at) = v;
@@ -2472,28 +2335,6 @@ hi_status launch_prefill(void* stream, const void* q, int G, int chunk_len, cons
   return HI_OK;
 }
 
-// One workgroup's copy takes about 10 us per 1000 rows beside the others, a launch over the chip 5 for any number.  Four heads a call,
-// riding against a launch of its own: 128 + 512 rows of 4096 148 against 157 us, 128 + 700 of 3000 105.7 against 105.4 to 107, 64 + 2000
-// of 5000 267 against 260 (253 with the numbering over all heads and this line).
-constexpr int kWindowUpdateRows = 1024;
-
-// Which rows of a chunk enter a streaming head's store, and how many of the head's first strips of positions read rows that they
-// replace: ring rows, in the tiles of A behind the sink rows (or in the last sink rows' tile, which every strip visits).
-bool window_update(int G, int chunk_len, int64_t past_len, int n_sink, int n_recent, PrefillWindowUpdate* w) {
-  const int64_t P = past_len, t0 = P - n_recent + 1 > n_sink ? P - n_recent + 1 : n_sink;
-  const int64_t ns = P < n_sink ? P : n_sink, m = P > t0 ? P - t0 : 0, lo0 = P - n_recent - t0 + 1 + ns;
-  w->cs = (int)(n_sink > P ? (n_sink - P < chunk_len ? n_sink - P : chunk_len) : 0);
-  w->u0 = chunk_len - n_recent > w->cs ? chunk_len - n_recent : w->cs;
-  w->cr = chunk_len - w->u0;
-  w->counters = nullptr;
-  const int64_t strip = prefill_strip(G), strips = ceil_div(chunk_len, strip);
-  int64_t readers = m == 0 ? 0 : ns % kPfTileRows != 0 ? strips : ceil_div(kPfTileRows * ceil_div(ns + m, kPfTileRows) - lo0, strip);
-  if (readers < 0) readers = 0;
-  w->readers = (int)(readers < strips ? readers : strips);
-  // one workgroup writes the rows while the others still run: it has to come early, and to be done before they are
-  return w->readers == 0 || (2 * w->readers <= strips && w->cs + w->cr <= kWindowUpdateRows);
-}
-
 hi_status launch_prefill_window(void* stream, const void* q, int G, int chunk_len, const void* store_k,
                                 const void* store_v, int64_t store_head_stride, const void* k_new, const void* v_new,
                                 int64_t past_len, int n_sink, int n_recent, void* out, int out_fp32, int n_heads,
@@ -2504,28 +2345,20 @@ hi_status launch_prefill_window(void* stream, const void* q, int G, int chunk_le
     return HI_ERR_ARG;
   }
   PrefillWindowArgs a;
+  (PfWindow&)a = pf_window_of(past_len, chunk_len, n_sink, n_recent);
   a.q = (const uint16_t*)q;
   a.ks = (const char*)store_k; a.vs = (const char*)store_v;
   a.kb = (const char*)k_new; a.vb = (const char*)v_new;
   a.out = out;
-  a.G = G; a.C = chunk_len; a.out_fp32 = out_fp32;
+  a.G = G; a.out_fp32 = out_fp32;
   a.gy = prefill_grid_y(G);
   a.c = softmax_scale_log2(q_prescaled);
-  a.n_sink = n_sink; a.n_recent = n_recent;
-  const int64_t P = past_len;
-  const int64_t t0 = P - n_recent + 1 > n_sink ? P - n_recent + 1 : n_sink;
-  a.ns = (int)(P < n_sink ? P : n_sink);
-  a.m = (int)(P > t0 ? P - t0 : 0);
-  a.ring0 = a.m > 0 ? (int)((t0 - n_sink) % n_recent) : 0;
-  a.lo0 = (int)(P - n_recent - t0 + 1) + a.ns;       // token P - n_recent + 1 as an index into A
-  a.sink_b = (int)(n_sink > P ? (n_sink - P < chunk_len ? n_sink - P : chunk_len) : 0);
   a.s_head_stride = store_head_stride;
   a.update = update != nullptr;
   if (update) {
-    a.cs = update->cs; a.s0 = (int)P; a.u0 = update->u0; a.cr = update->cr; a.readers = update->readers;
-    a.slot0 = a.cr > 0 ? (int)((P + a.u0 - n_sink) % n_recent) : 0;
+    a.rows = update->rows;
     a.counters = update->counters;
-    if (a.readers > 0 && !a.counters) { set_last_error("windowed prefill launch: no counters"); return HI_ERR_ARG; }
+    if (a.rows.readers > 0 && !a.counters) { set_last_error("windowed prefill launch: no counters"); return HI_ERR_ARG; }
   }
   dim3 grid((unsigned)ceil_div(chunk_len, prefill_strip(G)), (unsigned)(a.gy * n_heads));
   launch_kernel(prefill_window_kernel, grid, dim3(kWgThreads), 0, stream, done, a);

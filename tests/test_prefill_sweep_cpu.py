@@ -1,4 +1,5 @@
-"""The work partition's division by multiplication against the compiler's, and the tile loads of a pass (csrc/hi_prefill_part.h), on the host."""
+"""The work partition's division by multiplication against the compiler's, the tile loads of a pass (csrc/hi_prefill_part.h) and the visits of
+the 4-wave kernels (csrc/hi_prefill_visits.h), on the host."""
 import os
 import shutil
 import subprocess
@@ -8,13 +9,13 @@ import pytest
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
-@pytest.mark.parametrize("name", ["partition_magic_check", "prefill_sweep_check"])
+@pytest.mark.parametrize("name", ["partition_magic_check", "prefill_sweep_check", "prefill_visits_check"])
 def test_on_the_host(tmp_path, name):
     gxx = shutil.which("g++")
     if gxx is None:
         pytest.skip("no host C++ compiler")
     exe = str(tmp_path / name)
-    subprocess.run([gxx, "-O2", "-std=c++17", "-I", os.path.join(ROOT, "paper_2502_12574_amd", "csrc"),
+    subprocess.run([gxx, "-O2", "-std=c++17", "-I", os.path.join(ROOT, "include"), "-I", os.path.join(ROOT, "paper_2502_12574_amd", "csrc"),
                     os.path.join(ROOT, "tests", name + ".cpp"), "-o", exe], check=True)
     r = subprocess.run([exe], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=300)
     assert r.returncode == 0 and " 0 failures" in r.stdout, r.stdout[-2000:]
