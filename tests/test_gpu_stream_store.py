@@ -51,3 +51,82 @@ def test_store_and_outputs(G, H, sink, recent, chunks, flags):
                 store = ss.stream_view().view(H, 2, sink + recent, 128)
                 assert torch.equal(store[:, 0, at], k[:, tokens]) and torch.equal(store[:, 1, at], v[:, tokens]), past
                 past = e
+
+
+def _rows(seed, H, G, S):
+    gen = torch.Generator(device=DEV).manual_seed(seed)
+    return tuple(torch.randn(*s, dtype=torch.bfloat16, device=DEV, generator=gen) for s in ((H, G, S, 128), (H, S, 128), (H, S, 128)))
+
+
+# a chunk whose rows would ride with a counter (its first strips read the store), one without readers, one that reads everywhere
+@pytest.mark.parametrize("sink,recent,past,C", [(128, 512, 2048, 2100), (128, 512, 0, 900), (4, 200, 700, 800)])
+def test_captured_chunk(sink, recent, past, C):
+    """A captured chunk holds no counters: replayed from a graph, with eager chunks of another context in between, it leaves the same store
+    and the same outputs, bit for bit, as the eager call."""
+    G, H = 4, 2
+    q, k, v = _rows(past + C, H, G, past + C)
+    make = lambda: Session(1, 2 * H, G, past + C, max(past, C), mode=hb.HI_MODE_RESIDENT, out_fp32=1, streaming_heads=H,  # noqa: E731
+                           sink_tokens=sink, recent_tokens=recent)
+    part = lambda a, b: (q[:, :, a:b].contiguous(), k[:, a:b].contiguous(), v[:, a:b].contiguous())                      # noqa: E731
+    with make() as ss, make() as other:
+        out, out2 = (torch.full((H, G, C, 128), float("nan"), device=DEV) for _ in range(2))
+        head, tail = part(0, past), part(past, past + C)
+        torch.cuda.synchronize()
+
+        def begin(ctx):
+            ctx.staging.zero_()
+            torch.cuda.synchronize()
+            if past:
+                ctx.prefill_group(0, H, H, *head, 0, torch.empty(H, G, past, 128, device=DEV))
+            ctx.sync()
+
+        hb.hi_ctx_set_run_ahead(ss.ctx, 0)
+        begin(ss)
+        ss.prefill_group(0, H, H, *tail, past, out)
+        ss.sync()
+        want, store = out.clone(), ss.stream_view().clone()
+        assert torch.isfinite(want).all()
+        begin(ss)
+        graph = torch.cuda.CUDAGraph()
+        torch.cuda.synchronize()
+        with torch.cuda.graph(graph, stream=ss.s_compute):
+            ss.prefill_group(0, H, H, *tail, past, out)
+        for _ in range(3):
+            begin(ss)
+            begin(other)
+            out.zero_()
+            torch.cuda.synchronize()
+            graph.replay()
+            other.prefill_group(0, H, H, *tail, past, out2)      # (on its own stream and counters)
+            torch.cuda.synchronize()
+            assert torch.equal(out, want) and torch.equal(ss.stream_view(), store)
+            assert torch.equal(out2, want) and torch.equal(other.stream_view(), store)
+
+
+def test_contexts_without_counters():
+    """More contexts than there are counters: those that got none write the chunk's rows in a launch of their own - the same rows, the
+    same outputs, whoever has one."""
+    G, H, sink, recent, past, C = 4, 1, 64, 100, 700, 900
+    q, k, v = _rows(7, H, G, past + C)
+    part = lambda a, b: (q[:, :, a:b].contiguous(), k[:, a:b].contiguous(), v[:, a:b].contiguous())                      # noqa: E731
+    one_launch, first = [], None
+    open_ = [Session(1, 2, G, past + C, C, mode=hb.HI_MODE_RESIDENT, out_fp32=1, streaming_heads=H, sink_tokens=sink, recent_tokens=recent)
+             for _ in range(68)]
+    for ss in open_:
+        out = torch.full((H, G, C, 128), float("nan"), device=DEV)
+        ss.staging.zero_()
+        ss.cache_view()[:] = 0
+        torch.cuda.synchronize()
+        for a, b, o in ((0, past, torch.empty(H, G, past, 128, device=DEV)), (past, past + C, out)):
+            ss.prefill_group(0, 1, H, *part(a, b), a, o)
+            ss.sync()
+        # whether this one has counters: a token over a short resident history takes one launch with them, two without
+        ss.decode_group(0, 0, 1, q[:, :, 0].contiguous(), k[:, 0].contiguous(), v[:, 0].contiguous(), 130, torch.empty(1, G, 128, device=DEV))
+        ss.sync()
+        one_launch.append(ss.stats().n_combine_kernels == 0)
+        got = (out, ss.stream_view().clone())
+        first = first or got
+        assert torch.isfinite(out).all() and torch.equal(got[0], first[0]) and torch.equal(got[1], first[1])
+    for ss in open_:
+        ss.close()
+    assert one_launch == [True] * 64 + [False] * 4
