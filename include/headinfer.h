@@ -194,9 +194,10 @@ hi_status hi_offload_plan(const hi_problem* problem, hi_plan* plan);
  * With hi_problem.link_kv_bits = 4 the cache layout is [layer][kv_head][K|V][S_max][plan.link_row_bytes] bytes.
  * A context is used by one host thread at a time (its calls mutate the ring's bookkeeping without locks); different
  * contexts are independent.  The only device memory the library has of its own (besides hi_qkv_rope_static's table) are
- * counters for 64 contexts per process, which decode steps over short HBM-resident histories use instead of a second
- * launch; a 65th context, and a step that is being captured into a graph, take the second launch.  A captured step of
- * HBM-resident heads so holds no memory but the caller's, and its graph may be replayed after hi_ctx_destroy.
+ * counters for 64 contexts per process, which decode steps over short HBM-resident histories, and chunks of streaming heads
+ * (whose rows then enter the store in the attention launch), use instead of a second launch; a 65th context, and a call that is
+ * being captured into a graph, take the second launch.  A captured call of HBM-resident or streaming heads so holds no memory
+ * but the caller's, and its graph may be replayed after hi_ctx_destroy.
  * Errors: HI_ERR_ARG, HI_ERR_NOT_PINNED, HI_ERR_UNSUPPORTED, HI_ERR_HIP.
  * kv_cache may be null when every layer's rows are given by hi_ctx_set_layer_cache before the layer is first used.
  */
@@ -330,7 +331,8 @@ hi_status hi_decode_group_ragged(hi_ctx* ctx, int32_t layer, int32_t kv_head, in
  * d_model must be a multiple of 128; every operand must be smaller than 4 GiB; all pointers 16-byte aligned.
  * Both enqueue on `stream` (a hipStream_t) and return.  Errors: HI_ERR_ARG, HI_ERR_UNSUPPORTED, HI_ERR_HIP.
  * chunk_len = 1 (decode) takes a matrix-vector kernel, 2 to 64 one that streams the weights through the whole chip: both are
- * bound by the read of the weights, and neither uses the workspace (which 2 to 64 rotated rows still have to pass).
+ * bound by the read of the weights.  Neither uses the workspace, nor do the chunks that are cheaper in 128 x 128 tiles, which
+ * form their rotation themselves; 2 and more rotated rows still have to pass one.
  */
 hi_status hi_proj_workspace_bytes(int32_t chunk_len, int64_t* bytes);
 hi_status hi_qkv_rope(void* stream, const void* x_dev, const void* w_qkv_dev, int32_t d_model, int32_t n_q_heads,
@@ -346,8 +348,8 @@ hi_status hi_out_proj(void* stream, const void* attn_dev, const void* w_o_dev, i
  * held until the process ends) instead of workspace_dev.  chunk_len may be at most 16384 (HI_ERR_RANGE beyond, nothing
  * enqueued).  The call allocates nothing and frees nothing.  All calls on one GPU share that GPU's array: calls that
  * may overlap in time on one GPU (different streams, different host threads) race on it and must be ordered by the
- * caller; calls on one stream are ordered by the stream.  Nothing needs clearing between calls: a call rewrites the
- * table for every token it rotates.  Otherwise as hi_qkv_rope (arguments, layouts, errors).
+ * caller; calls on one stream are ordered by the stream.  Nothing needs clearing between calls: a call that reads the
+ * table has written it for every token it rotates.  Otherwise as hi_qkv_rope (arguments, layouts, errors).
  */
 hi_status hi_qkv_rope_static(void* stream, const void* x_dev, const void* w_qkv_dev, int32_t d_model, int32_t n_q_heads,
                              int32_t n_kv_heads, int32_t chunk_len, int64_t past_len, double rope_theta,

@@ -50,7 +50,8 @@ struct hi_ctx {
   bool enqueuing = false;    // the running call has passed its checks and started to enqueue
   char* staging = nullptr;
   char* ws = nullptr;
-  int* counters = nullptr;   // device, for decode launches that combine their own partials; taken by the first of them
+  int* counters = nullptr;   // device, for decode launches that combine their own partials and for streaming chunks whose rows enter
+                             // the store in the attention launch; taken by the first of them
   int counter_slot = -1;
   bool counters_refused = false;     // (none were left)
   bool capturing = false;    // the running call's compute stream is being captured into a graph
@@ -310,7 +311,7 @@ int pf_variant(const hi_ctx* c) {
 
 // A decode launch of np partitions per head combines them itself where it has few of them (a short history) and the
 // context has counters for it.  What that saves is the second launch, 2.5 us of host time, which is what bounds a token at
-// short contexts (32 layers of 8 heads at 1K: 13.6 us a layer against 16.6); on the GPU it is 8.4 us against 5.6 + 3.9.
+// short contexts (32 layers of 8 heads at 1K: 13.6 us a layer against 16.6); on the GPU it was 8.4 us against 5.6 + 3.9 (7 now).
 // With 32 partitions the last workgroup alone takes 6.4 us where the combine kernel, spread over the chip, takes 4; between
 // 16 and 32 one launch was not timed.
 // A captured step keeps the second launch: a graph may outlive the context, and then its launches must hold no memory but

@@ -1959,7 +1959,7 @@ __global__ __launch_bounds__(512) void prefill_merge_kernel(PrefillArgs a, Prefi
 
 // Merge of the ranges of the 4-wave kernel: grid (blocks, grid rows, 16), z = 4 (dim block) + quarter: four of its
 // registers, dims 32 db + 8 rq + 4 hl ..; that kernel's own lane layout.  A lane whose query sees none of a range's keys (own
-// rows only, all behind it) left its image's sums at what masked scores add up to; it takes no part.
+// rows only, all behind it) left its image's reference at kNegBig and its sums at zero; it takes no part.
 // Bound by the latency of its reads (70 KB per image, up to 64 images of a block, and few blocks where there are many), so
 // the grid splits an image finely and many images are in flight per lane: 63 images of 8 blocks take 18 us, 16 images
 // of 16 blocks 6.4 (30 and 9.3 with whole dim blocks and four images in flight).
@@ -2036,8 +2036,8 @@ struct PrefillWindowArgs : PfWindow {
 // pipes at work nearly all the time: 56 % of the cycles the vector ALU, 41 % the matrix pipe.  The scores of a visit are formed
 // under the softmax of the one before it (pf_tile4), two K and two V tiles have places in LDS, and the loads are streams that
 // cost a pointer's increment: 53 thousand cycles a workgroup, of which 14 thousand to fetch queries and first tiles and to write the
-// rows, instead of 59 - at a clock that falls for it (2.1 GHz over many launches); 155.6 -> 152.6 us for two chunks in a row, perf ab
-// 165.4 -> 162.9.  Before: asking for the first tile before the queries and keeping
+// rows, instead of 59 - at a clock that falls for it (2.1 GHz over many launches); 155.6 -> 152.6 us for two chunks in a row, a
+// pass with its hand-over to the caller's stream 165.4 -> 162.9.  Before: asking for the first tile before the queries and keeping
 // neighbouring blocks on one XCD took a launch from 72 to 66 us; a ring of four stages with one workgroup of 8 wavefronts, or of
 // three K and two V tiles with two of 4, was no faster (87, 84 against 83 us), and starting the scores from minus the
 // running reference spilled registers (89).

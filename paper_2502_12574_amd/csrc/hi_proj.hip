@@ -424,11 +424,10 @@ __global__ __launch_bounds__(256, 1) void proj_gemm_kernel(ProjArgs p) {
 // ---- chunks too short to fill the chip with 256 x 256 tiles: the same contraction in 128 x 128 tiles, one per workgroup.
 // 600 tokens of Llama-3-8B are 72 (Q/K/V) and 48 (output) of the large tiles on 256 compute units, 240 and 160 of these.
 // A wavefront owns 64 x 64 (2 x 2 blocks of the 32x32x16 MFMA; its A rows are 32 wa .. +31 and 64 + 32 wa .. +31, so that
-// rotary pairs still meet in one lane).  A step of 64 contraction elements moves 32 KB into LDS and 64 KB out of it, 750
-// cycles or 0.31 us at its 128 bytes a cycle (the 16 MFMAs of a wavefront take 512).  Measured over contractions of 1024 to
+// rotary pairs still meet in one lane).  A step of 64 contraction elements moves 32 KB into LDS and 64 KB out of it.  Measured over contractions of 1024 to
 // 8192 at 600 tokens, kernel time is 5 to 6 us to launch, fill the ring and write, and per step 0.53 us with weights from
 // HBM and 0.43 with weights from the caches for the 240 workgroups of Q/K/V, 0.45 and 0.35 for the 160 of the output.  A step's
-// MFMAs, its loads through the texture path (64 bytes a cycle) and its LDS traffic take 512 cycles each; it takes 720, at a clock
+// MFMAs, its loads through the texture path (64 bytes a cycle) and its operand reads (128 bytes a cycle) take 512 cycles each; it takes 720, at a clock
 // that falls with them (2.3 GHz with 48 workgroups at work, 1.8 with 240).  One workgroup per compute unit has to cover the
 // latency of its loads itself: five stages of 32 KB, loads three steps (of 64 elements) ahead and spread evenly over the step,
 // operand reads two sub-steps ahead with one wait for the four of a sub-step.  The order of every sum is the large
