@@ -121,16 +121,28 @@ HI_HD int pf_window_row(const PfWindow& a, int u) {
   return a.n_sink + x;
 }
 // The stream has come to visit w.v.  True: it takes offsets of its own, row min(r, rows - 1) for r; rows = 0: rows of A from `row0` on,
-// through the ring, behind the store's first row.
+// through the ring, behind the store's first row.  Tiles follow each other inside the chunk, among the sink rows, and in the ring up to
+// where it wraps.  With offsets formed for every tile of the ring, twice now that K and V are streams of their own, four one-query heads of
+// 4000 rows behind 4000 took 58.4 us at a window of 64 + 1500 where one set for both planes had taken 51.2; in runs they take 43.9.
 HI_HD bool pf_window_meet(PfLoads& w, const PfWindow& a, const PfWindowTiles& t, const char* store, const char* own, int& rows, int& row0) {
   bool in_b;
   const int tile = pf_window_locate(t, w.v, in_b);
-  const int whole = (in_b ? a.C : a.ns) / kPfSweepRows, end = in_b && tile >= t.b1 ? t.tb : in_b ? t.b1 : whole;
-  const bool usual = tile < whole;              // full tiles of the chunk, and of sink rows; else the chunk's last rows, or rows of the ring
   row0 = tile * kPfSweepRows;
-  w.until = w.v + (usual ? (end < whole ? end : whole) - tile : 1);
+  int run, at = row0;                           // tiles that follow each other, and the first one's row
+  if (in_b) {
+    const int whole = a.C / kPfSweepRows, end = tile >= t.b1 ? t.tb : t.b1;
+    run = (end < whole ? end : whole) - tile;
+  } else if (row0 < a.ns) {
+    run = a.ns / kPfSweepRows - tile;
+  } else {
+    at = pf_window_row(a, row0);
+    const int wraps = a.n_sink + a.n_recent - at, left = a.ns + a.m - row0;
+    run = (wraps < left ? wraps : left) / kPfSweepRows;
+  }
+  const bool usual = run > 0;                   // else the chunk's last rows, rows on both sides of an edge of the ring or of the sink rows
+  w.until = w.v + (usual ? run : 1);
   w.base = in_b ? own : store;
-  if (usual || in_b) w.base += (int64_t)row0 * (kPfSweepBytes / kPfSweepRows);
+  if (usual || in_b) w.base += (int64_t)at * (kPfSweepBytes / kPfSweepRows);
   rows = usual ? kPfSweepRows : in_b ? a.C - row0 : 0;
   const bool anew = !(usual && w.usual);
   w.usual = usual;
