@@ -730,7 +730,7 @@ static hi_status prefill_impl(hi_ctx* c, int32_t layer, int32_t kv_head, int32_t
     if (run) {
       // the rows ride on the attention launch, unless that is timed (the time is its alone) or would make its end wait for them
       PrefillWindowUpdate update;
-      bool ride = !timed && window_update(G, chunk_len, past_len, c->prob.sink_tokens, c->prob.recent_tokens, &update);
+      bool ride = !timed && window_update(G, chunk_len, past_len, c->prob.sink_tokens, c->prob.recent_tokens, nh, &update);
       if (ride && update.rows.readers > 0) {
         ride = can_tail(c, 1, nh);
         update.counters = c->counters;

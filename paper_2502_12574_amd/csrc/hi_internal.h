@@ -402,11 +402,12 @@ constexpr int64_t kStreamMaxRows = 1 << 22;
 // update: the launch takes the chunk's rows into the store itself (window_update says which, and whether it should: pf_store_rides;
 // counters: one int per head if there are readers).
 struct PrefillWindowUpdate { PfStoreRows rows; int* counters; };
-inline bool window_update(int G, int chunk_len, int64_t past_len, int n_sink, int n_recent, PrefillWindowUpdate* w) {
+inline bool window_update(int G, int chunk_len, int64_t past_len, int n_sink, int n_recent, int n_heads, PrefillWindowUpdate* w) {
   const int strip = prefill_strip(G);
   w->rows = pf_store_rows(pf_window_of(past_len, chunk_len, n_sink, n_recent), past_len, strip);
   w->counters = nullptr;
-  return pf_store_rides(w->rows, chunk_len, strip);
+  const int64_t strips = ceil_div(chunk_len, strip);
+  return pf_store_rides(w->rows, strips, strips * prefill_grid_y(G) * n_heads);
 }
 hi_status launch_prefill_window(void* stream, const void* q, int G, int chunk_len, const void* store_k,
                                 const void* store_v, int64_t store_head_stride, const void* k_new, const void* v_new,

@@ -193,14 +193,16 @@ HI_HD int pf_store_row(const PfStoreRows& r, int n_sink, int n_recent, int u) {
   const int slot = r.slot0 + (u - r.u0);
   return n_sink + (slot >= n_recent ? slot - n_recent : slot);
 }
-// One workgroup's copy takes about 10 us per 1000 rows beside the others, a launch over the chip 5 for any number.  Four heads a call,
-// riding against a launch of its own: 128 + 512 rows of 4096 148 against 157 us, 128 + 700 of 3000 105.7 against 105.4 to 107, 64 + 2000
-// of 5000 267 against 260 (253 with the numbering over all heads and this line).
-constexpr int kStoreRideRows = 1024;
-// Whether the attention launch should write them: by the last of its readers while the others still run, so it has to come early, and
-// to be done before they are; without readers by every workgroup.
-HI_HD bool pf_store_rides(const PfStoreRows& r, int C, int strip) {
-  return r.readers == 0 || (2ll * r.readers <= ((int64_t)C + strip - 1) / strip && r.cs + r.cr <= kStoreRideRows);
+// Whether the attention launch should write them: without readers by every workgroup; else by the last reader while the others still run,
+// so it has to come early, and what it writes has to take no longer than the launch of its own that it saves.  That launch costs 2.4 us
+// for any number of rows (calls back to back), one workgroup's copy 1 us per 100 - and where all workgroups run at once, two on
+// each of 256 compute units, nobody is left to hide it.  Gain of riding, microseconds of a call behind 3000 rows, for 64 / 128 / 256 / 384 /
+// 512 / 900 rows: 60 to 376 workgroups 2.4 / 1.6 / 0.2 / -1.3 / -2.8 / -8 (240, two heads to an XCD: -12 at 900); 480, of 8 heads, 4.0 / 3.4 /
+// 2.7 / 1.1 / 0.1 / -1.5; 564 2.0 / 0.6 / -1.5 / -4.7 / -6.6 / -13; 1024 3.8 / 2.3 / 0.7 / -0.3 / -2.1 / -4.2; more than two rounds, 1128 4.1 /
+// 4.0 / 4.2 / 3.4 / 3.7 / 2.5, 2048 3.6 / 3.0 / 2.0 / 1.3 / 0.3 / -2.  Of 328 shapes this line picks the slower way in
+// 28: by 1.5 us at most where it rides, by 5.9 of 159 where it does not.
+HI_HD bool pf_store_rides(const PfStoreRows& r, int64_t strips, int64_t workgroups) {
+  return r.readers == 0 || (2 * r.readers <= strips && r.cs + r.cr <= (workgroups > 1024 ? 512 : 256));
 }
 
 }  // namespace hi

@@ -117,7 +117,8 @@ static void window(std::mt19937_64& rng, int i) {
     if (t < sink || t >= P - recent) store[place(t)] = t;
   const PfWindow a = pf_window_of(P, C, sink, recent);
   PrefillWindowUpdate u;
-  const bool ride = window_update(G, C, P, sink, recent, &u);
+  const int heads = 1 + (int)pick(40);
+  const bool ride = window_update(G, C, P, sink, recent, heads, &u);
   const PfStoreRows& rows = u.rows;
   const int strips = (C + strip - 1) / strip;
   // the rows the chunk puts into the store, and what the store then holds
@@ -188,7 +189,8 @@ static void window(std::mt19937_64& rng, int i) {
     }
   }
   CHECK(last_reader < rows.readers);             // nobody reads a row behind the workgroups that are counted
-  CHECK(ride == (rows.readers == 0 || (2 * rows.readers <= strips && rows.cs + rows.cr <= 1024)));
+  const long workgroups = (long)strips * (G == 8 ? 2 : 1) * heads;
+  CHECK(ride == (rows.readers == 0 || (2 * rows.readers <= strips && rows.cs + rows.cr <= (workgroups > 1024 ? 512 : 256))));
   if (ride && rows.readers > 0) ++rides;
   if (!ride) ++waits;
 }
@@ -198,11 +200,13 @@ int main() {
   for (int i = 0; i < 12000; ++i) narrow(rng, i);
   for (int i = 0; i < 1500; ++i) window(rng, i);
   CHECK(rides > 200 && waits > 200);
-  // the rule's edges: exactly half of the strips, one row more than 1024
+  // the rule's edges: half of the strips, one row more than 256 and 512, one strip more than 1024 workgroups
   PrefillWindowUpdate u;
-  CHECK(window_update(4, 200, 4000, 64, 101, &u) == (2 * u.rows.readers <= 7) && u.rows.readers > 0);
-  CHECK(window_update(4, 5000, 9000, 0, 1024, &u) && u.rows.readers > 0 && !window_update(4, 5000, 9000, 0, 1025, &u));
-  CHECK(window_update(4, 5000, 0, 0, 4000, &u) && u.rows.readers == 0);
+  CHECK(window_update(4, 192, 4000, 64, 65, 1, &u) && u.rows.readers == 2 && window_update(4, 160, 4000, 64, 65, 1, &u));
+  CHECK(!window_update(4, 96, 4000, 64, 65, 1, &u) && u.rows.readers == 2);
+  CHECK(window_update(4, 5000, 9000, 0, 256, 1, &u) && u.rows.readers > 0 && !window_update(4, 5000, 9000, 0, 257, 1, &u));
+  CHECK(!window_update(4, 8192, 9000, 0, 512, 4, &u) && window_update(4, 8193, 9000, 0, 512, 4, &u) && !window_update(4, 8193, 9000, 0, 513, 4, &u));
+  CHECK(window_update(4, 5000, 0, 0, 4000, 1, &u) && u.rows.readers == 0);
   std::printf("%ld checks, %ld rides, %ld launches of their own, %ld failures\n", checks, rides, waits, bad);
   return bad != 0;
 }

@@ -59,7 +59,7 @@ def _rows(seed, H, G, S):
 
 
 # a chunk whose rows would ride with a counter (its first strips read the store), one without readers, one that reads everywhere
-@pytest.mark.parametrize("sink,recent,past,C", [(128, 512, 2048, 2100), (128, 512, 0, 900), (4, 200, 700, 800)])
+@pytest.mark.parametrize("sink,recent,past,C", [(128, 200, 2048, 2100), (128, 512, 0, 900), (4, 200, 700, 800)])
 def test_captured_chunk(sink, recent, past, C):
     """A captured chunk holds no counters: replayed from a graph, with eager chunks of another context in between, it leaves the same store
     and the same outputs, bit for bit, as the eager call."""
