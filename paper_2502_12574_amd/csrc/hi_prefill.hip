@@ -549,13 +549,51 @@ __device__ __forceinline__ void pf_stream4_issue(const PfStream4& w, uint32_t ld
 }
 
 // All visits of a workgroup.  LDS: two places for K tiles, then two for V tiles; on entry the first two K tiles and the first V tile are
-// on their way, sk stands at visit 2 and sv at visit 1.  masked(v): visit v hides rows of some query row of the wavefront; seen(): rows of
+// on their way, sk stands at visit 2 and sv at visit 1 (STRAIGHT: the first K tile only, and both stand at visit 1).  masked(v): visit v hides rows of some query row of the wavefront; seen(): rows of
 // that visit that the lane's query row sees.  Hidden scores become kNegBig as bit operations (comparisons and selects per
 // element became branches, 83 -> 77 us a launch of prefill_window_kernel).
-template <class GoOnK, class GoOnV, class Masked, class Seen>
+template <bool STRAIGHT, class GoOnK, class GoOnV, class Masked, class Seen>
 __device__ __forceinline__ void pf_sweep4(lds_char* lds, uint32_t lds_wave, const PfLaneConst& lc, const bf16x8 (&qf)[8], PfState& st,
                                           float c, int T, int lane, PfStream4& sk, PfStream4& sv, GoOnK go_on_k, GoOnV go_on_v,
                                           Masked masked, Seen seen) {
+  auto hide = [&](int v, f32x16& s0, f32x16& s1) __attribute__((always_inline)) {
+    const uint64_t rows = seen(v) >> (4 * (formed_here(lane) >> 5));
+    const uint32_t bits[2] = {(uint32_t)rows, (uint32_t)(rows >> 32)};
+#pragma unroll
+    for (int sb = 0; sb < 2; ++sb)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        f32x16& s = sb == 0 ? s0 : s1;
+        const uint32_t t = (uint32_t)__builtin_amdgcn_sbfe((int)bits[sb], 8 * (r >> 2) + (r & 3), 1);
+        s[r] = __uint_as_float((__float_as_uint(s[r]) & t) | (__float_as_uint(kNegBig) & ~t));
+      }
+  };
+  if constexpr (STRAIGHT) {
+    auto step = [&](int v, auto parity) __attribute__((always_inline)) {
+      constexpr int odd = decltype(parity)::value;
+      wait_vmcnt<0>();
+      __syncthreads();
+      if (v + 1 < T) {
+        pf_stream4_issue(sk, lds_wave + (1 - odd) * kPfTileBytes);
+        pf_stream4_issue(sv, lds_wave + kPfStageBytes + (1 - odd) * kPfTileBytes);
+        go_on_k();
+        go_on_v();
+      }
+      f32x16 s[2], none;
+      pf_scores(lds + odd * kPfTileBytes, lc, qf, s);
+      const bool hides = masked(v);
+      auto mask = [&](f32x16& s0, f32x16& s1) __attribute__((always_inline)) { hide(v, s0, s1); };
+      auto nothing = [](int) __attribute__((always_inline)) {};
+      pf_tile4<false>(lds, lds + kPfStageBytes + odd * kPfTileBytes, lc, qf, s[0], s[1], none, st, c, hides, mask, nothing, nothing);
+    };
+    int v = 0;
+    for (; v + 1 < T; v += 2) {
+      step(v, std::integral_constant<int, 0>());
+      step(v + 1, std::integral_constant<int, 1>());
+    }
+    if (v < T) step(v, std::integral_constant<int, 0>());
+    return;
+  }
   f32x16 s0, s1a, s1b;         // scores of a visit's rows 0..31, and of its rows 32..63 (even and odd visits)
   wait_vmcnt<0>();
   __syncthreads();
@@ -574,18 +612,7 @@ __device__ __forceinline__ void pf_sweep4(lds_char* lds, uint32_t lds_wave, cons
     wait_vmcnt<0>();
     __syncthreads();
     const bool hides = masked(v);
-    auto mask = [&](f32x16& s0, f32x16& s1) __attribute__((always_inline)) {
-      const uint64_t rows = seen(v) >> (4 * (formed_here(lane) >> 5));
-      const uint32_t bits[2] = {(uint32_t)rows, (uint32_t)(rows >> 32)};
-#pragma unroll
-      for (int sb = 0; sb < 2; ++sb)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          f32x16& s = sb == 0 ? s0 : s1;
-          const uint32_t t = (uint32_t)__builtin_amdgcn_sbfe((int)bits[sb], 8 * (r >> 2) + (r & 3), 1);
-          s[r] = __uint_as_float((__float_as_uint(s[r]) & t) | (__float_as_uint(kNegBig) & ~t));
-        }
-    };
+    auto mask = [&](f32x16& s0, f32x16& s1) __attribute__((always_inline)) { hide(v, s0, s1); };
     // K of visit v + 2 into the place of v's, V of v + 1 into that of v - 1's
     auto at = [&](int i) __attribute__((always_inline)) {
       set_m0(lds_wave + (i < 4 ? odd * kPfTileBytes : kPfStageBytes + (1 - odd) * kPfTileBytes) + (i & 3) * 1024);
@@ -612,10 +639,17 @@ __device__ __forceinline__ void pf_sweep4(lds_char* lds, uint32_t lds_wave, cons
 // chain: matrix phase, softmax, matrix phase of one tile after the other.  The scores are formed one visit ahead (pf_tile4; K and V
 // tiles have two places each in LDS, the loads are streams), straight through before: 1239 rows of 6 heads of 4 queries 31 -> 27 us,
 // 1500 of one head of 2 behind 395 42.1 -> 35.3, 1000 of 8 heads of 4 27.2 -> 24.2, 204 of one 9.0 -> 8.5; ranges of 5 to 7 tiles
-// (276 rows of 2 heads behind 3111) the same 13.5, two workgroups on every compute unit (2 rows behind 88778) the same 68.6.
+// (276 rows of 2 heads behind 3111) the same 13.5.
+// STRAIGHT: scores, softmax and product of a tile one after the other, its loads a tile ahead in a row behind the barrier; the same bits.  For
+// launches of more workgroups than compute units: two wavefronts share each SIMD and hide each other's softmax, so that a visit ahead gains
+// nothing there, and what it costs is the clock of the kernels around it.  A prompt of 12288 rows of 8 heads, two a call, in chunks of
+// 5955, whose last chunk is cut into 504 workgroups: 1885 us a pass with this kernel a visit ahead (at 2.11 GHz; every other kernel
+// of the pass 3 % slower too), 1815 straight (2.18 GHz); 16 two-query heads one by one in chunks of 5266 2675 and 2650; 2 rows of 8 heads
+// behind 88778 86.2 and 85.0, 20 behind 67854 91.2 and 87.3.  With 256 workgroups and fewer it is the other way round: calls of 209 rows of a
+// one-query head behind 32701 (116 workgroups) 1530 us for 32 of them against 1640, 459 behind 459 (30) 18.6 against 20.2.
 // SPLIT: a.split workgroups per block of positions, each on its range of the unit's tiles (pf_narrow_range) with a state
 // image of its own, merged after the last launch (prefill_merge4_kernel).
-template <bool SPLIT>
+template <bool SPLIT, bool STRAIGHT>
 __global__ __launch_bounds__(256, 2) void prefill_kernel(PrefillArgs a) {
   __shared__ __attribute__((aligned(1024))) char lds_raw[kPfLdsBytes];
   lds_char* lds = (lds_char*)lds_raw;
@@ -694,8 +728,10 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(PrefillArgs a) {
   pf_stream4_issue(sv, lds_wave + kPfStageBytes);
   go_on_k();
   go_on_v();
-  pf_stream4_issue(sk, lds_wave + kPfTileBytes);
-  go_on_k();
+  if (!STRAIGHT) {
+    pf_stream4_issue(sk, lds_wave + kPfTileBytes);
+    go_on_k();
+  }
 
   PfState st;
   float* carry = a.carry + image * (kCarryFloatsPerLane * kWgThreads) + threadIdx.x;
@@ -722,7 +758,7 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(PrefillArgs a) {
   for (int db = 0; db < 4; ++db) asm volatile("" : "+v"(st.o[db]));
 
   const PfOpen open = pf_narrow_open(n, i0);
-  pf_sweep4(lds, lds_wave, lc, qf, st, a.c, n.T, lane, sk, sv, go_on_k, go_on_v,
+  pf_sweep4<STRAIGHT>(lds, lds_wave, lc, qf, st, a.c, n.T, lane, sk, sv, go_on_k, go_on_v,
             [&](int v) __attribute__((always_inline)) { return !(v < open.a || (v >= n.ta && v < open.b)); },
             [&](int v) __attribute__((always_inline)) { return pf_narrow_seen(n, v, i0 + (formed_here(lane) & 31)); });
 
@@ -2121,7 +2157,7 @@ __global__ __launch_bounds__(256, 2) void prefill_window_kernel(PrefillWindowArg
   const PfSeenVisits open = pf_window_open(a, t, i0);
   bool in_b = false;
   int j0 = 0;
-  pf_sweep4(lds, lds_wave, lc, qf, st, a.c, t.T, lane, sk, sv, go_on_k, go_on_v,
+  pf_sweep4<false>(lds, lds_wave, lc, qf, st, a.c, t.T, lane, sk, sv, go_on_k, go_on_v,
             [&](int v) __attribute__((always_inline)) {
               if ((uint32_t)(v - open.first) < (uint32_t)open.n) return false;
               j0 = pf_window_locate(t, v, in_b) * kPfTileRows;
@@ -2320,14 +2356,17 @@ hi_status launch_prefill(void* stream, const void* q, int G, int chunk_len, cons
   } else {
     const dim3 blocks((unsigned)ceil_div(chunk_len, strip), (unsigned)(gy * n_heads));
     if (pl.split > 1) {
-      launch_kernel(prefill_kernel<true>, dim3(blocks.x * (unsigned)pl.split, blocks.y), dim3(kWgThreads), 0, stream, kernel_done, a);
+      const dim3 cut(blocks.x * (unsigned)pl.split, blocks.y);
+      // more than one wavefront on a SIMD: straight (see prefill_kernel, with both sides' times)
+      if ((int64_t)cut.x * cut.y > kPrefillCus) launch_kernel(prefill_kernel<true, true>, cut, dim3(kWgThreads), 0, stream, kernel_done, a);
+      else launch_kernel(prefill_kernel<true, false>, cut, dim3(kWgThreads), 0, stream, kernel_done, a);
       if (pl.merge) {
         hipError_t e1 = hipGetLastError();
         if (e1 != hipSuccess) { set_last_error("prefill launch: %s", hipGetErrorString(e1)); return HI_ERR_HIP; }
         launch_kernel(prefill_merge4_kernel, merge_grid(blocks.x, blocks.y, 16, kWgThreads), dim3(kWgThreads), 0, stream, done, a, app);
       }
     } else {
-      launch_kernel(prefill_kernel<false>, blocks, dim3(kWgThreads), 0, stream, kernel_done, a);
+      launch_kernel(prefill_kernel<false, false>, blocks, dim3(kWgThreads), 0, stream, kernel_done, a);
     }
   }
   hipError_t e = hipGetLastError();
